@@ -385,48 +385,146 @@ __global__ __launch_bounds__(kWideNT) __attribute__((amdgpu_waves_per_eu(1, 1)))
 }
 
 // The same 128 x 128 tiles on the fp4 form of the scaled MFMA
-// (V_MFMA_F32_32X32X64_F8F6F4, both operands e2m1): a bit becomes the nibble
-// 0b0010 (1.0) or 0, so one 64-bit word is one K = 64 step (32 bits per lane
-// group) and a table of 256 dwords turns 8 bits into 8 nibbles.  The lanes'
-// k order is the same for both operands, so the dot product is the popcount
-// of the AND.  Products are 0 or 1 and the float32 sums stay below 2^24
+// (V_MFMA_F32_32X32X64_F8F6F4, both operands e2m1): one 64-bit word is one
+// K = 64 step, 32 bits per lane group (lanes 32g..32g+31 read half g of the
+// word).  The lanes' k order is the same for both operands, so the dot
+// product is the popcount of the AND.  Products are 0 or 1 and the float32 sums stay below 2^24
 // (at most kFp4MaxK word rows per block), so every count is exact.
 constexpr uint64_t kFp4MaxK = (1u << 24) / 64 - 1;
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// The table is held in COPIES copies, entry x of copy c at word COPIES x + c.
-// With 32 copies lane l reads copy l % 32, so the lanes of one read fall in
-// distinct banks whatever bytes they look up (with one copy, data-dependent
-// indices collide in the banks on dense words, but the extra address
-// arithmetic costs more than it saves on sparse words and in the 256 x 256
-// kernel, so both forms are tile variants).
-template <uint32_t COPIES>
-__device__ __forceinline__ void fill_nibble_lut(uint32_t *lut) {
-    for (uint32_t e = threadIdx.x; e < 256 * COPIES; e += blockDim.x) {
-        const uint32_t i = e / COPIES;
-        uint32_t d = 0;
-        for (int b = 0; b < 8; ++b) d |= ((i >> b) & 1u) << (4 * b + 1);
-        lut[e] = d;
-    }
-}
-
-// lutc: the table copy of this lane (lut + lane % 32 with 32 copies, else lut)
-template <uint32_t COPIES>
-__device__ __forceinline__ v8i bits32_fp4(const uint32_t *lutc, uint32_t x) {
+// A lane expands its 32 bits by masks alone, in registers: nibble i of operand
+// dword r holds bit 4i + r, so each dword is one AND (after a shift where the
+// bit has to move).  A bit that stays where it is in its nibble stands for
+// 0.5, 1.0 or 2.0 (e2m1 0b0001, 0b0010, 0b0100), so the A form takes 0.5, 1,
+// 2, 2 for r = 0..3 and the B form the inverses 2, 1, 0.5, 0.5: every product
+// of two set bits is exactly 1.  5 and 7 VALU operations per 32 bits; looking
+// 8 bits at a time up in an LDS table took 4 reads and as many address
+// operations and left the matrix units waiting.
+__device__ __forceinline__ v8i expand_a(uint32_t x) {
     v8i r = {0, 0, 0, 0, 0, 0, 0, 0};
-    r[0] = (int)lutc[(x & 255u) * COPIES];
-    r[1] = (int)lutc[((x >> 8) & 255u) * COPIES];
-    r[2] = (int)lutc[((x >> 16) & 255u) * COPIES];
-    r[3] = (int)lutc[(x >> 24) * COPIES];
+    r[0] = (int)(x & 0x11111111u);
+    r[1] = (int)(x & 0x22222222u);
+    r[2] = (int)(x & 0x44444444u);
+    r[3] = (int)((x >> 1) & 0x44444444u);
+    return r;
+}
+__device__ __forceinline__ v8i expand_b(uint32_t x) {
+    v8i r = {0, 0, 0, 0, 0, 0, 0, 0};
+    r[0] = (int)((x << 2) & 0x44444444u);
+    r[1] = (int)(x & 0x22222222u);
+    r[2] = (int)((x >> 2) & 0x11111111u);
+    r[3] = (int)((x >> 3) & 0x11111111u);
     return r;
 }
 
-template <int WPE, int STEP, uint32_t COPIES>
-__global__ __launch_bounds__(kMfmaNT) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void k_gram_fp4(
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+// A wave's TA x TB MFMA tiles (TA, TB even) over word rows [k0, k1) of W.
+// Lane group g takes row g of each pair of rows: a lane loads 16 bytes, the
+// words of two adjacent columns, which serve two tiles and two MFMA steps
+// (the low, then the high halves), so a pair of rows takes (TA + TB) / 2
+// loads.  Tile x's row m is column 64 (x / 2) + 2 m + x % 2 of the wave's
+// block (fp4_add undoes it).  A pair is read through a buffer descriptor of
+// its own: the address is wave-uniform, a lane adds a 32-bit offset (oa, ob:
+// its columns' bytes, plus one row for group 1), and the descriptor ends with
+// row k1, so rows past it read as zeros and add nothing.  D pairs are in
+// flight; a step's operands are expanded while the step before it is in the
+// matrix unit.
+template <int TA, int TB, int D>
+__device__ __forceinline__ void fp4_block(const uint64_t *__restrict__ W, uint64_t ldw, uint64_t k0, uint64_t k1,
+                                          const uint32_t (&oa)[TA / 2], const uint32_t (&ob)[TB / 2],
+                                          v16f (&acc)[TA][TB]) {
+#pragma unroll
+    for (int x = 0; x < TA; ++x)
+#pragma unroll
+        for (int y = 0; y < TB; ++y)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
+    const uint32_t rows = (uint32_t)(k1 - k0), bytes = (uint32_t)(ldw * 8);
+    const uint64_t *p = W + k0 * ldw;
+    v4u ra[D][TA / 2], rb[D][TB / 2];
+    const auto load = [&](uint32_t q, v4u (&a)[TA / 2], v4u (&b)[TB / 2]) {
+        const uint32_t left = 2 * q < rows ? rows - 2 * q : 0;  // rows from this pair on
+        const auto pair = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(p + (uint64_t)(2 * q) * ldw), 0,
+                                                            min(left, 2u) * bytes, 0x00020000);
+#pragma unroll
+        for (int x = 0; x < TA / 2; ++x) a[x] = __builtin_amdgcn_raw_buffer_load_b128(pair, oa[x], 0, 0);
+#pragma unroll
+        for (int y = 0; y < TB / 2; ++y) b[y] = __builtin_amdgcn_raw_buffer_load_b128(pair, ob[y], 0, 0);
+    };
+    v8i va[TA], vb[TB];  // operands of the step about to be multiplied
+    const auto step = [&](const v4u (&a)[TA / 2], const v4u (&b)[TB / 2], int h) {
+        v8i wa[TA], wb[TB];  // operands of the step after it: half h of a pair's words
+#pragma unroll
+        for (int x = 0; x < TA; ++x) wa[x] = expand_a(a[x / 2][2 * (x & 1) + h]);
+#pragma unroll
+        for (int y = 0; y < TB; ++y) wb[y] = expand_b(b[y / 2][2 * (y & 1) + h]);
+#pragma unroll
+        for (int x = 0; x < TA; ++x)
+#pragma unroll
+            for (int y = 0; y < TB; ++y)
+                acc[x][y] =
+                    __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va[x], vb[y], acc[x][y], 4, 4, 0, 0, 0, 0);
+        // issue order: an MFMA, then its share of the masks
+#pragma unroll
+        for (int m = 0; m < TA * TB; ++m) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, (5 * TA + 7 * TB + TA * TB - 1) / (TA * TB), 0);
+        }
+#pragma unroll
+        for (int x = 0; x < TA; ++x) va[x] = wa[x];
+#pragma unroll
+        for (int y = 0; y < TB; ++y) vb[y] = wb[y];
+    };
+#pragma unroll
+    for (int s = 0; s < D; ++s) load(s, ra[s], rb[s]);
+#pragma unroll
+    for (int x = 0; x < TA; ++x) va[x] = expand_a(ra[0][x / 2][2 * (x & 1)]);
+#pragma unroll
+    for (int y = 0; y < TB; ++y) vb[y] = expand_b(rb[0][y / 2][2 * (y & 1)]);
+    for (uint32_t q = 0; 2 * q < rows; q += D) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+            step(ra[s], rb[s], 1);  // multiplies the low halves of pair q + s
+            load(q + s + D, ra[s], rb[s]);
+            step(ra[(s + 1) % D], rb[(s + 1) % D], 0);  // its high halves
+        }
+    }
+}
+
+// Adds a wave's tiles at (I0, J0) into the strict upper part of B:
+// accumulator r of lane (lg, lm) holds row 8*(r/4) + 4*lg + r%4, column lm of
+// each 32 x 32 tile.
+template <int TA, int TB>
+__device__ __forceinline__ void fp4_add(const v16f (&acc)[TA][TB], uint32_t I0, uint32_t J0, uint32_t lm, uint32_t lg,
+                                        uint32_t n, int32_t *__restrict__ B, int upper) {
+#pragma unroll
+    for (int x = 0; x < TA; ++x)
+#pragma unroll
+        for (int y = 0; y < TB; ++y)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const uint32_t m = 8 * (r >> 2) + 4 * lg + (r & 3);
+                const uint32_t i = I0 + 64 * (x >> 1) + 2 * m + (x & 1);
+                const uint32_t j = J0 + 64 * (y >> 1) + 2 * lm + (y & 1);
+                const int32_t v = (int32_t)acc[x][y][r];  // an exact integer below 2^24
+                if (v && i < j && j < n) atomicAdd(B + out_index(i, j, n, upper), v);
+            }
+}
+
+// 128 x 128 tiles, two waves of 128 x 64 each, two waves per SIMD (232 VGPRs),
+// so one wave's loads and masks run beside the other's MFMAs.  On a diagonal
+// tile the first wave's lower half lies below the diagonal and is not
+// computed.  Bound by the matrix unit: 7.3 to 7.9 PF/s of 10.1 (n = 1024,
+// 1.25 M word rows: 20.9 -> 12.0 ms against the LDS-table form; n = 4096, 65 K:
+// 16.9 -> 9.9; n = 10000, 65 K: 96 -> 57).  256 x 256 tiles of four 128 x 128
+// waves, one per SIMD, reach 6.5: nothing runs beside a wave that waits.
+constexpr int kFp4Pairs = 4;  // row pairs in flight (3, 4 and 6 measured alike)
+__global__ __launch_bounds__(kMfmaNT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gram_fp4(
     const uint64_t *__restrict__ W, uint64_t ldw, uint64_t H, uint64_t kper, uint32_t nt, uint32_t n,
     int32_t *__restrict__ B, int upper) {
-    __shared__ uint32_t lut[256 * COPIES];
     uint32_t p, I = 0, rowlen = nt;
     uint64_t split;
     xcd_pair_split(p, split);
@@ -439,171 +537,21 @@ __global__ __launch_bounds__(kMfmaNT) __attribute__((amdgpu_waves_per_eu(WPE, WP
     const uint64_t k0 = split * kper;
     const uint64_t k1 = min(H, k0 + kper);
     if (k0 >= k1) return;
-    fill_nibble_lut<COPIES>(lut);
-    __syncthreads();
-    const uint32_t lane = threadIdx.x & 63, wc = threadIdx.x >> 6;
+    const uint32_t lane = threadIdx.x & 63, wc = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lm = lane & 31, lg = lane >> 5;
-    const uint32_t *lutc = lut + (COPIES > 1 ? lm : 0);
     const uint32_t I0 = I * kT, J0 = Jt * kT + 64 * wc;
+    const uint32_t row = lg * (uint32_t)ldw * 8;
+    const uint32_t oa[2] = {row + 8 * (I0 + 2 * lm), row + 8 * (I0 + 64 + 2 * lm)}, ob[1] = {row + 8 * (J0 + 2 * lm)};
+    if (J0 == I0) {
+        const uint32_t oh[1] = {oa[0]};
+        v16f acc[2][2];
+        fp4_block<2, 2, kFp4Pairs>(W, ldw, k0, k1, oh, ob, acc);
+        fp4_add<2, 2>(acc, I0, J0, lm, lg, n, B, upper);
+        return;
+    }
     v16f acc[4][2];
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
-    const uint64_t *pa = W + I0 + lm;
-    const uint64_t *pb = W + J0 + lm;
-    uint64_t a[STEP][4], b[STEP][2];
-#pragma unroll
-    for (int u = 0; u < STEP; ++u) {
-        const uint64_t ku = min(k0 + u, k1 - 1);
-#pragma unroll
-        for (int x = 0; x < 4; ++x) a[u][x] = pa[ku * ldw + 32 * x];
-#pragma unroll
-        for (int y = 0; y < 2; ++y) b[u][y] = pb[ku * ldw + 32 * y];
-    }
-    const uint32_t sh = 32 * lg;  // this lane group's half of the word
-    for (uint64_t k = k0; k < k1; k += STEP) {
-        uint64_t na[STEP][4], nb[STEP][2];
-#pragma unroll
-        for (int u = 0; u < STEP; ++u) {
-            const uint64_t kn = min(k + STEP + u, k1 - 1);
-#pragma unroll
-            for (int x = 0; x < 4; ++x) na[u][x] = pa[kn * ldw + 32 * x];
-#pragma unroll
-            for (int y = 0; y < 2; ++y) nb[u][y] = pb[kn * ldw + 32 * y];
-        }
-#pragma unroll
-        for (int u = 0; u < STEP; ++u) {
-            if (k + u >= k1) break;  // wave-uniform: the tail of the range
-            v8i va[4], vb[2];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) va[x] = bits32_fp4<COPIES>(lutc, (uint32_t)(a[u][x] >> sh));
-#pragma unroll
-            for (int y = 0; y < 2; ++y) vb[y] = bits32_fp4<COPIES>(lutc, (uint32_t)(b[u][y] >> sh));
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va[x], vb[y], acc[x][y], 4, 4, 0, 0,
-                                                                              0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < STEP; ++u) {
-#pragma unroll
-            for (int x = 0; x < 4; ++x) a[u][x] = na[u][x];
-#pragma unroll
-            for (int y = 0; y < 2; ++y) b[u][y] = nb[u][y];
-        }
-    }
-    // accumulator r of lane (lg, lm) holds row 8*(r/4) + 4*lg + r%4, column lm of each 32 x 32 tile
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t i = I0 + 32 * x + 8 * (r >> 2) + 4 * lg + (r & 3);
-                const uint32_t j = J0 + 32 * y + lm;
-                const int32_t v = (int32_t)acc[x][y][r];  // an exact integer below 2^24
-                if (v && i < j && j < n) atomicAdd(B + out_index(i, j, n, upper), v);
-            }
-}
-
-// fp4 on 256 x 256 tiles: the four waves of k_gram_mfma_wide, each 128 x
-// 128, with the fp4 step of k_gram_fp4 (one word per MFMA).
-template <int STEP>
-__global__ __launch_bounds__(kWideNT) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gram_fp4_wide(
-    const uint64_t *__restrict__ W, uint64_t ldw, uint64_t H, uint64_t kper, uint32_t nt, uint32_t n,
-    int32_t *__restrict__ B, int upper) {
-    __shared__ uint32_t lut[256];
-    const uint64_t split = blockIdx.y;
-    uint32_t p = blockIdx.x, I = 0, rowlen = nt;
-    while (p >= rowlen) {
-        p -= rowlen;
-        ++I;
-        --rowlen;
-    }
-    const uint32_t Jt = I + p;
-    const uint64_t k0 = split * kper;
-    const uint64_t k1 = min(H, k0 + kper);
-    if (k0 >= k1) return;
-    fill_nibble_lut<1>(lut);
-    __syncthreads();
-    const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const uint32_t lm = lane & 31, lg = lane >> 5;
-    const uint32_t I0 = I * kWideT + 128 * (wv >> 1), J0 = Jt * kWideT + 128 * (wv & 1);
-    if (I0 >= J0 + 128) return;  // the wave's block lies below the diagonal (no syncs follow)
-    v16f acc[4][4];
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
-    uint64_t ca[4], cb[4];  // this lane's columns, clamped below ldw
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        ca[x] = min<uint64_t>(I0 + lm + 32 * x, ldw - 1);
-        cb[x] = min<uint64_t>(J0 + lm + 32 * x, ldw - 1);
-    }
-    uint64_t a[STEP][4], b[STEP][4];
-#pragma unroll
-    for (int u = 0; u < STEP; ++u) {
-        const uint64_t ku = min(k0 + u, k1 - 1);
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            a[u][x] = W[ku * ldw + ca[x]];
-            b[u][x] = W[ku * ldw + cb[x]];
-        }
-    }
-    const uint32_t sh = 32 * lg;
-    for (uint64_t k = k0; k < k1; k += STEP) {
-        uint64_t na[STEP][4], nb[STEP][4];
-#pragma unroll
-        for (int u = 0; u < STEP; ++u) {
-            const uint64_t kn = min(k + STEP + u, k1 - 1);
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                na[u][x] = W[kn * ldw + ca[x]];
-                nb[u][x] = W[kn * ldw + cb[x]];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < STEP; ++u) {
-            if (k + u >= k1) break;  // wave-uniform: the tail of the range
-            v8i va[4], vb[4];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) va[x] = bits32_fp4<1>(lut, (uint32_t)(a[u][x] >> sh));
-#pragma unroll
-            for (int y = 0; y < 4; ++y) vb[y] = bits32_fp4<1>(lut, (uint32_t)(b[u][y] >> sh));
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int y = 0; y < 4; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(va[x], vb[y], acc[x][y], 4, 4, 0, 0,
-                                                                              0, 0);
-        }
-#pragma unroll
-        for (int u = 0; u < STEP; ++u)
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                a[u][x] = na[u][x];
-                b[u][x] = nb[u][x];
-            }
-    }
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t i = I0 + 32 * x + 8 * (r >> 2) + 4 * lg + (r & 3);
-                const uint32_t j = J0 + 32 * y + lm;
-                const int32_t v = (int32_t)acc[x][y][r];  // an exact integer below 2^24
-                if (v && i < j && j < n) atomicAdd(B + out_index(i, j, n, upper), v);
-            }
+    fp4_block<4, 2, kFp4Pairs>(W, ldw, k0, k1, oa, ob, acc);
+    fp4_add<4, 2>(acc, I0, J0, lm, lg, n, B, upper);
 }
 
 // Row lists: one thread per row, every pair of its (ascending) samples.
@@ -796,33 +744,26 @@ __global__ void k_finalize_upper(int32_t *__restrict__ B, const int64_t *__restr
     if (J) J[pos] = c == 0 ? 1.0 : (double)b / (double)c;
 }
 
-// Tile variants of the MFMA Gram: word rows per step of the K loop, and how
-// many blocks the K split aims for.  The autotuner (JAS_TUNE) times each on the
-// caller's db and keeps the fastest for dbs of the same shape.
-enum GramKind { kInt8 = 0, kInt8Wide = 1, kFp4 = 2, kFp4Wide = 3, kFp4Rep = 4 };
+// Tile variants of the MFMA Gram: word rows per step of the int8 K loops, and
+// how many blocks the K split aims for (int8: at least that many; fp4: at most,
+// or 0: the split fp4_split chooses).  The autotuner (JAS_TUNE) times each on
+// the caller's db and keeps the fastest for dbs of the same shape.
+enum GramKind { kInt8 = 0, kInt8Wide = 1, kFp4 = 2 };
 struct GramVariant {
     int step;
     uint64_t want_blocks;
-    int kind;  // kInt8: k_gram_mfma; kInt8Wide: 256 x 256 tiles (k_gram_mfma_wide); kFp4: k_gram_fp4;
-               // kFp4Wide: k_gram_fp4_wide; kFp4Rep: k_gram_fp4 with 32 copies of the nibble table
+    int kind;  // kInt8: k_gram_mfma; kInt8Wide: 256 x 256 tiles (k_gram_mfma_wide); kFp4: k_gram_fp4
 };
-// (wide variants with 2 word rows per step or at most 2048 blocks measured
-// slower on both dense workloads and are not listed)
 // (int8 variants aimed at 1024 blocks, or with 2 rows per step at 2048, measured
 // slower everywhere and are not listed)
-constexpr GramVariant kVariants[] = {{4, 2048, kInt8},     {4, 4096, kInt8},     {2, 4096, kInt8},
-                                     {4, 4096, kInt8Wide}, {4, 8192, kInt8Wide}, {4, 2048, kFp4},
-                                     {2, 2048, kFp4},      {4, 4096, kFp4},      {2, 4096, kFp4},
-                                     {4, 8192, kFp4},      {2, 8192, kFp4},      {4, 4096, kFp4Wide},
-                                     {4, 8192, kFp4Wide},  {4, 16384, kFp4Wide}, {4, 4096, kFp4Rep},
-                                     {4, 8192, kFp4Rep},   {2, 8192, kFp4Rep}};
+constexpr GramVariant kVariants[] = {{4, 2048, kInt8},     {4, 4096, kInt8}, {2, 4096, kInt8},  {4, 4096, kInt8Wide},
+                                     {4, 8192, kInt8Wide}, {2, 0, kFp4},     {2, 512, kFp4},    {2, 1024, kFp4},
+                                     {2, 2048, kFp4},      {2, 3072, kFp4},  {2, 4096, kFp4},   {2, 6144, kFp4},
+                                     {2, 8192, kFp4},      {2, 12288, kFp4}, {2, 16384, kFp4},  {2, 24576, kFp4},
+                                     {2, 32768, kFp4}};
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
-// Untuned choice, from the tuner's timings on MI355X: 128 x 128 fp4 tiles
-// below n = 2048 (n = 1024: 6.5 ms against 10.6 for int8 tiles), 256 x 256 fp4
-// tiles from there on (n = 4096: 16.7 against 26.9 ms; n = 10000: 0.75 against
-// 1.09 s), each aimed at 8192 blocks.
-constexpr int kDefaultNarrow = 9, kDefaultWide = 12;
-static_assert(kVariants[kDefaultNarrow].kind == kFp4 && kVariants[kDefaultWide].kind == kFp4Wide, "defaults");
+constexpr int kDefaultVariant = 5;  // untuned
+static_assert(kVariants[kDefaultVariant].kind == kFp4 && kVariants[kDefaultVariant].want_blocks == 0, "default");
 
 std::mutex g_tune_mu;
 std::map<std::tuple<int, uint32_t, uint32_t>, int> g_tuned;  // (device, n, ceil(log2 H)) -> variant
@@ -840,23 +781,48 @@ void k_split(uint64_t H, uint64_t np, uint64_t want, uint64_t &kper, uint64_t &s
     }
 }
 
+// The K split of the fp4 kernel over np tile pairs and H word rows: word rows
+// per block (a multiple of kKC) and blocks per tile pair.  kFp4Slots blocks run
+// at once, so the grid takes ceil(blocks / kFp4Slots) rounds of (rows per block
+// + kFp4Add) word rows' time, where kFp4Add is what a block's start and its
+// atomics cost, and the blocks drift apart by up to one block's time.  Fewer
+// rounds save additions, but a last round that is nearly empty costs a whole
+// one (n = 1024: 36 x 114 = 4104 blocks take 13.6 ms, 36 x 113 12.8), and long
+// blocks drift out of step and share less of their XCD's L2 (1 round 13.4 ms,
+// 8 rounds 12.4, 24 rounds 11.4; n = 300, 65 K rows: 1 round 0.177 ms, 2 rounds
+// 0.224, 8 rounds 0.51).  The split with the least such time is taken.
+constexpr uint64_t kFp4Slots = 256 * 4;  // blocks resident: two waves of 232 VGPRs each, eight waves per CU
+constexpr uint64_t kFp4Add = 96;
+constexpr uint64_t kFp4Rounds = 64;  // most rounds considered
+
+void fp4_split(uint64_t H, uint64_t np, uint64_t want, uint64_t &kper, uint64_t &splits) {
+    const auto rows = [&](uint64_t sp) { return std::min(div_up(div_up(H, sp), kKC) * kKC, kFp4MaxK / kKC * kKC); };
+    uint64_t best = 1;
+    if (want) {
+        best = std::max<uint64_t>(1, want / np);
+    } else {
+        uint64_t best_t = ~0ull;
+        for (uint64_t r = 1; r <= kFp4Rounds; ++r) {
+            const uint64_t sp = std::max<uint64_t>(1, std::min(r * kFp4Slots / np, div_up(H, kKC)));
+            const uint64_t k = rows(sp), drift = std::min(k, H * np / kFp4Slots / 8);
+            const uint64_t t = div_up(div_up(H, k) * np, kFp4Slots) * (k + kFp4Add) + drift;
+            if (t < best_t) {
+                best_t = t;
+                best = sp;
+            }
+        }
+    }
+    kper = rows(best);
+    splits = div_up(H, kper);
+}
+
 void launch_mfma(const jas_db *db, int v, hipStream_t s, int32_t *B, bool upper) {
     const uint32_t n = (uint32_t)db->n;
-    if (kVariants[v].kind == kInt8Wide || kVariants[v].kind == kFp4Wide) {
+    const uint64_t ldw = div_up(n, 128) * 128;
+    uint64_t kper, splits;
+    if (kVariants[v].kind == kInt8Wide) {
         const uint32_t nt = (uint32_t)div_up(n, kWideT);
         const uint64_t np = (uint64_t)nt * (nt + 1) / 2;
-        uint64_t kper, splits;
-        k_split(db->H, np, kVariants[v].want_blocks, kper, splits);
-        const uint64_t ldw = div_up(n, 128) * 128;
-        if (kVariants[v].kind == kFp4Wide && kper > kFp4MaxK) {  // keep every block's float sums below 2^24
-            kper = kFp4MaxK / kKC * kKC;
-            splits = div_up(db->H, kper);
-        }
-        if (kVariants[v].kind == kFp4Wide && splits <= 65535) {
-            dim3 grid((uint32_t)np, (uint32_t)splits);
-            k_gram_fp4_wide<4><<<grid, kWideNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);
-            return;
-        }
         k_split(db->H, np, kVariants[v].want_blocks, kper, splits);
         dim3 grid((uint32_t)np, (uint32_t)splits);
         k_gram_mfma_wide<4><<<grid, kWideNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);  // 4 rows per step
@@ -864,29 +830,17 @@ void launch_mfma(const jas_db *db, int v, hipStream_t s, int32_t *B, bool upper)
     }
     const uint32_t nt = (uint32_t)div_up(n, kT);
     const uint64_t np = (uint64_t)nt * (nt + 1) / 2;
-    uint64_t kper, splits;
-    k_split(db->H, np, kVariants[v].want_blocks, kper, splits);
-    const uint64_t ldw = div_up(n, 128) * 128;
-    if (kVariants[v].kind == kFp4 || kVariants[v].kind == kFp4Rep) {
-        const bool rep = kVariants[v].kind == kFp4Rep;
-        if (kper > kFp4MaxK) {  // keep every block's float sums below 2^24
-            kper = kFp4MaxK / kKC * kKC;
-            splits = div_up(db->H, kper);
-        }
+    // a pair of rows has to be within the 32-bit offsets of a buffer descriptor
+    if (kVariants[v].kind == kFp4 && ldw <= 0xFFFFFFFFull / 16) {
+        fp4_split(db->H, np, kVariants[v].want_blocks, kper, splits);
         if (splits <= 65535) {
             dim3 grid((uint32_t)np, (uint32_t)splits);
-            if (kVariants[v].step == 4 && rep)
-                k_gram_fp4<2, 4, 32><<<grid, kMfmaNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);
-            else if (kVariants[v].step == 4)
-                k_gram_fp4<2, 4, 1><<<grid, kMfmaNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);
-            else if (rep)
-                k_gram_fp4<2, 2, 32><<<grid, kMfmaNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);
-            else
-                k_gram_fp4<2, 2, 1><<<grid, kMfmaNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);
+            k_gram_fp4<<<grid, kMfmaNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);
             return;
         }
-        k_split(db->H, np, kVariants[v].want_blocks, kper, splits);  // too many blocks: the int8 kernel
     }
+    // (fp4: a grid too large, the int8 kernel)
+    k_split(db->H, np, std::max<uint64_t>(kVariants[v].want_blocks, 2048), kper, splits);
     dim3 grid((uint32_t)np, (uint32_t)splits);
     if (kVariants[v].step == 4)
         k_gram_mfma<2, 4><<<grid, kMfmaNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);
@@ -959,7 +913,7 @@ void gram(const jas_db *db, uint32_t flags, hipStream_t s, int32_t *B, int64_t *
             k_gram_popc<<<grid, kNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);
         } else {
             const auto key = std::make_tuple(db->device, n, ceil_log2_u64(db->H));
-            int v = n >= 2048 ? kDefaultWide : kDefaultNarrow;
+            int v = kDefaultVariant;
             const uint32_t forced = (flags >> 16) & 0xFFu;  // JAS_GRAM_VARIANT(v): v + 1
             if (forced) {
                 v = (int)forced - 1;
@@ -996,7 +950,7 @@ void gram(const jas_db *db, uint32_t flags, hipStream_t s, int32_t *B, int64_t *
                 const auto it = g_tuned.find(key);
                 if (it != g_tuned.end()) v = it->second;
             }
-            JAS_TIMED(kVariants[v].kind >= kFp4 ? "gram_fp4" : "gram_mfma", s);  // kFp4, kFp4Wide, kFp4Rep
+            JAS_TIMED(kVariants[v].kind == kFp4 ? "gram_fp4" : "gram_mfma", s);
             launch_mfma(db, v, s, B, upper);
         }
         check_launch("gram");

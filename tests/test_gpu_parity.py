@@ -602,6 +602,26 @@ def test_every_mfma_tile_variant_is_exact(n):
     db.close()
 
 
+@pytest.mark.parametrize("n,rows", [(2, 1), (63, 64), (65, 65), (128, 129), (129, 1000), (192, 1025), (257, 2100)])
+def test_fp4_row_pairs_and_diagonal_tiles(n, rows):
+    """The fp4 kernel reads word rows in pairs, several pairs ahead, and skips
+    the half of a diagonal tile below the diagonal: word row counts of 1, 2,
+    3, odd and one past a block's 16, columns around 64, 128 and 256."""
+    rng = np.random.default_rng(100 * n + rows)
+    every = rng.choice(1 << 20, rows, replace=False).astype(np.uint64)
+    A = rng.random((rows, n)) < 0.4
+    A[:, :2] = True  # every row is shared, so the word rows are ceil(rows / 64)
+    ids, off = csr([every[A[:, j]] for j in range(n)])
+    ref = oracle.all_pairs(ids, off)
+    db, st = jas.encode(dev(ids), dev(off), universe_bits=20, dense_min_degree=2)
+    assert st["n_word_rows"] == -(-rows // 64)
+    for upper in (False, True):
+        out = jas.gram(db, upper=upper, flags=cabi.JAS_FORCE_MFMA)
+        torch.cuda.synchronize()
+        assert_matches({k: x.cpu().numpy() for k, x in out.items()}, ref, upper=upper)
+    db.close()
+
+
 def test_repeat_runs_are_identical():
     spec = synth.scaled(synth.workload("precision"), n=300, size_scale=0.01, pool_scale=0.01)
     ids, off = synth.generate(spec)
