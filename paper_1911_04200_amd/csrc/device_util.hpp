@@ -16,6 +16,29 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
+// The lanes of the wave whose value agrees with this lane's in its low NB bits
+// (all 64 lanes must call it).  Per bit one ballot and, for each half of the
+// mask, one three-input operation: m & ~(vote ^ own bit), the own bit spread
+// over the word.
+template <int NB>
+__device__ __forceinline__ uint64_t wave_match(uint32_t v) {
+    uint32_t lo = ~0u, hi = ~0u;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        int32_t own = __builtin_amdgcn_sbfe((int32_t)v, b, 1);
+        asm("" : "+v"(own));  // compared as it is (else the bit is shifted out a second time)
+        const uint64_t vote = __ballot(own < 0);
+        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)vote, (uint32_t)own, 0x90);
+        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(vote >> 32), (uint32_t)own, 0x90);
+    }
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// Set lanes of m below this lane.
+__device__ __forceinline__ uint32_t lanes_before(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+}
+
 // Inclusive scan across the 64 lanes of a wave.
 __device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v) {
     const uint32_t l = lane_id();

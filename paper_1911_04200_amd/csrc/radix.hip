@@ -11,6 +11,7 @@
 //      rounds go in order), the tile is reordered in LDS, and each digit run
 //      is written out contiguously (coalesced).
 #include <algorithm>
+#include <type_traits>
 
 #include "device_util.hpp"
 #include "jas_internal.hpp"
@@ -185,7 +186,15 @@ constexpr int kOsWaves = kOsNT / kWave;
 // the tile's first and last entries (k_tile_samples), and an entry's sample is
 // the first one plus the sample starts inside the tile at or before it (a
 // uniform loop of scalar loads, run only by tiles that span several samples).
-template <class K, int R, bool kTable, bool kFromIds = false>
+//
+// A pass moves 16 bytes per 64-bit key; each tile's chain of latencies (loads,
+// ranks, look-back, stores) bounds it more than memory does.  Ranks by
+// unrolled ballots for a fixed number of digit bits, with the counter
+// operations in flight together, against a ballot loop whose rounds waited for
+// each other's counters (64-bit keys) and against LDS match tables (32-bit):
+// 1.78 G keys, three passes 25.3 -> 23.3 ms; 1.85 G pair words, two passes
+// 12.2 -> 11.0 ms.
+template <class K, int R, int NB, bool kFromIds = false>
 __global__ __launch_bounds__(kOsNT) __attribute__((amdgpu_waves_per_eu(4))) void k_radix_onesweep(
     const K *__restrict__ in, K *__restrict__ out, uint64_t N, uint32_t shift, uint32_t nbits,
     const uint64_t *__restrict__ gstart, uint32_t *__restrict__ status, uint32_t *__restrict__ ticket,
@@ -204,20 +213,11 @@ __global__ __launch_bounds__(kOsNT) __attribute__((amdgpu_waves_per_eu(4))) void
     const bool digit = tid < kRadix;  // this thread owns digit tid
     const uint32_t mask = (1u << nbits) - 1u;
     const uint32_t dshift = kFromIds ? shift - src.sbits : shift;  // digit position in a loaded value
-    const uint64_t lt = lanemask_lt();
     const uint64_t gs = digit ? gstart[tid] : 0;
-    // while ranking, the first kOsWaves*256 words of stage are per-wave tables
-    // of the lanes of the current round that have digit d
-    static_assert(!kTable || kOsWaves * kRadix * sizeof(uint64_t) <= (kOsNT * R) * sizeof(K),
-                  "match tables fit the stage");
-    uint64_t *T = reinterpret_cast<uint64_t *>(stage) + w * kRadix;
     // persistent: take tiles in ticket order until none is left
     for (;;) {
         if (tid == 0) tile_sh = atomicAdd(ticket, 1u);
-        for (uint32_t i = tid; i < kOsWaves * kRadix; i += kOsNT) {
-            (&wcnt[0][0])[i] = 0;
-            if constexpr (kTable) reinterpret_cast<uint64_t *>(stage)[i] = 0;
-        }
+        for (uint32_t i = tid; i < kOsWaves * kRadix; i += kOsNT) (&wcnt[0][0])[i] = 0;
         __syncthreads();
         const uint32_t tile = __builtin_amdgcn_readfirstlane(tile_sh);  // uniform: every thread reads the same ticket
         if (tile >= ntiles) break;  // uniform: every thread read the same ticket
@@ -229,72 +229,44 @@ __global__ __launch_bounds__(kOsNT) __attribute__((amdgpu_waves_per_eu(4))) void
         static_assert(!kFromIds || sizeof(K) == 8, "keys formed from IDs are 64-bit");
         uint64_t tsmp = 0;  // samples of the tile's first and last entries (low, high half), loaded ahead
         if constexpr (kFromIds) tsmp = const_load(reinterpret_cast<const uint64_t *>(src.tinfo) + tile);
+        const uint32_t cnt_tile = (uint32_t)(c1 - t0);
+        // Rank within the wave: the lanes of a round with the same digit take
+        // consecutive slots after the digit's count so far, and the lowest of
+        // them adds the group to the count.  One wave's LDS operations run in
+        // order, so the rounds' reads and additions are issued back to back
+        // without waiting for one another, each as its keys arrive.  In the
+        // last tile entries past its end take the largest digit; they come
+        // last in it, so they land past the tile's keys and only that digit's
+        // count has to be corrected.
+        const auto load_and_rank = [&](auto whole) {
 #pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const uint64_t t = wb + (uint64_t)j * kWave + lane;
-            key[j] = t < c1 ? in[t] : 0;
-        }
-        if constexpr (kTable) {
-            // Rank within the wave: lanes of a round with the same digit find each
-            // other through T[d] (each ORs in its lane bit, reads the set back and
-            // clears it; one wave's LDS operations run in order), take consecutive
-            // slots after the digit's count so far, and the lowest of them adds the
-            // group to the count with an LDS atomic whose return its peers fetch
-            // afterwards (in two halves, which keeps fewer registers live).
-    #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t info[R / 2];
-    #pragma unroll
-                for (int j = h * (R / 2); j < (h + 1) * (R / 2); ++j) {
-                    const uint64_t t = wb + (uint64_t)j * kWave + lane;
-                    const bool valid = t < c1;
-                    const uint32_t d = (uint32_t)(key[j] >> dshift) & mask;
-                    uint64_t peers = 0;
-                    if (valid) {
-                        atomicOr((unsigned long long *)&T[d], 1ull << lane);
-                        peers = __hip_atomic_load(&T[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        __hip_atomic_store(&T[d], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
-                    const uint32_t before = __popcll(peers & lt);
-                    const uint32_t leader = peers ? (uint32_t)__builtin_ctzll(peers) : lane;
-                    uint32_t old = 0;
-                    if (valid && before == 0) old = atomicAdd(&wcnt[w][d], (uint32_t)__popcll(peers));
-                    rank[j] = old;
-                    info[j - h * (R / 2)] = (leader << 8) | before;
-                }
-    #pragma unroll
-                for (int j = h * (R / 2); j < (h + 1) * (R / 2); ++j) {
-                    const uint32_t f = info[j - h * (R / 2)];
-                    rank[j] = (uint32_t)__shfl((int)rank[j], (int)(f >> 8), kWave) + (f & 255u);
-                }
-            }
-        } else {
-            // 64-bit keys: rank by one ballot per digit bit (fewer registers
-            // than the table form, which spills with 64-bit keys)
-    #pragma unroll
             for (int j = 0; j < R; ++j) {
                 const uint64_t t = wb + (uint64_t)j * kWave + lane;
-                const bool valid = t < c1;
-                const uint32_t d = (uint32_t)(key[j] >> dshift) & mask;
-                uint64_t peers = __ballot(valid);
-                for (uint32_t b = 0; b < nbits; ++b) {
-                    const bool bit = (d >> b) & 1u;
-                    const uint64_t vote = __ballot(valid && bit);
-                    peers &= bit ? vote : ~vote;
-                }
-                const uint32_t before = __popcll(peers & lt);
-                const uint32_t cnt = __popcll(peers);
-                uint32_t b0 = 0;
-                if (valid) b0 = wcnt[w][d];
-                if (valid && before == 0) wcnt[w][d] = b0 + cnt;
-                rank[j] = b0 + before;
+                if constexpr (decltype(whole)::value) key[j] = in[t];
+                else key[j] = t < c1 ? in[t] : ~(K)0;
             }
-        }
+            uint32_t before[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const uint32_t d = (uint32_t)(key[j] >> dshift) & mask;
+                const uint64_t peers = wave_match<NB>(d);
+                before[j] = lanes_before(peers);
+                rank[j] = __hip_atomic_load(&wcnt[w][d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (before[j] == 0)
+                    __hip_atomic_fetch_add(&wcnt[w][d], (uint32_t)__popcll(peers), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+#pragma unroll
+            for (int j = 0; j < R; ++j) rank[j] += before[j];
+        };
+        if (cnt_tile == kOsNT * R) load_and_rank(std::true_type{});  // uniform
+        else load_and_rank(std::false_type{});
         __syncthreads();
         uint32_t tc = 0;
         if (digit) {
 #pragma unroll
             for (int k = 0; k < kOsWaves; ++k) tc += wcnt[k][tid];
+            if (tid == mask) tc -= kOsNT * R - cnt_tile;  // the entries past the last tile's end
             // publish the tile's count of digit tid at once
             status_store(status + onesweep::status_index(tile, tid), (tile == 0 ? kFlagP : kFlagA) | tc);
         }
@@ -316,25 +288,20 @@ __global__ __launch_bounds__(kOsNT) __attribute__((amdgpu_waves_per_eu(4))) void
             // the sample starts inside the tile lie in (t0, c1), so tile-relative
             // positions compare in 32 bits
             const uint32_t s0 = (uint32_t)tsmp, s1 = (uint32_t)(tsmp >> 32);
-            const uint32_t cnt = (uint32_t)(c1 - t0), wl = (uint32_t)(wb - t0) + lane;
+            const uint32_t wl = (uint32_t)(wb - t0) + lane;
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 const uint32_t li = wl + j * kWave;  // position in the tile
-                if (li < cnt) {
-                    const uint32_t d = (uint32_t)(key[j] >> dshift) & mask;
-                    uint32_t smp = s0;
-                    for (uint32_t k = s0 + 1; k <= s1; ++k) smp += li >= (uint32_t)(const_load(src.off + k) - t0);
-                    stage[wcnt[w][d] + rank[j]] = (key[j] << src.sbits) | smp;
-                }
+                const uint32_t d = (uint32_t)(key[j] >> dshift) & mask;
+                uint32_t smp = s0;
+                for (uint32_t k = s0 + 1; k <= s1; ++k) smp += li >= (uint32_t)(const_load(src.off + k) - t0);
+                stage[wcnt[w][d] + rank[j]] = (key[j] << src.sbits) | smp;
             }
         } else {
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                const uint64_t t = wb + (uint64_t)j * kWave + lane;
-                if (t < c1) {
-                    const uint32_t d = (uint32_t)(key[j] >> shift) & mask;
-                    stage[wcnt[w][d] + rank[j]] = key[j];
-                }
+                const uint32_t d = (uint32_t)(key[j] >> shift) & mask;
+                stage[wcnt[w][d] + rank[j]] = key[j];
             }
         }
         // then look back for the digit's global offset: kLookWindow
@@ -372,7 +339,6 @@ __global__ __launch_bounds__(kOsNT) __attribute__((amdgpu_waves_per_eu(4))) void
             base[tid] = gs + excl;
         }
         __syncthreads();
-        const uint32_t cnt_tile = (uint32_t)(c1 - t0);
         for (uint32_t i = tid; i < cnt_tile; i += kOsNT) {
             const K k = stage[i];
             const uint32_t d = (uint32_t)(k >> shift) & mask;
@@ -497,28 +463,40 @@ void tile_samples(const KeySource &src, uint64_t Ncap, uint32_t tile_keys, const
     check_launch("tile samples");
 }
 
-// Launches one pass; the first reads src.ids when the keys are formed from IDs.
-template <class K, int Rounds, bool Table>
-void onesweep_pass(bool from_ids, const K *in, K *out, uint64_t N, uint32_t bit, uint32_t nbits,
-                   const uint64_t *gstart, uint32_t *status, uint32_t *ticket, uint32_t ntiles, uint32_t *err,
-                   const uint64_t *dN, const KeySource *src, uint32_t grid, hipStream_t s) {
-    if (from_ids && bit < src->sbits) fail(JAS_EDEVICE, "sort from IDs: a digit below the ID bits");
+// Launches one pass; the first reads src.ids when the keys are formed from
+// IDs.  Passes of at most 7 bits take a kernel that matches 7.
+template <class K, int Rounds, int NB>
+void onesweep_launch(bool from_ids, const K *in, K *out, uint64_t N, uint32_t bit, uint32_t nbits,
+                     const uint64_t *gstart, uint32_t *status, uint32_t *ticket, uint32_t ntiles, uint32_t *err,
+                     const uint64_t *dN, const KeySource *src, uint32_t grid, hipStream_t s) {
     if constexpr (sizeof(K) == 8) {
         if (from_ids) {
-            k_radix_onesweep<K, Rounds, Table, true><<<grid, kOsNT, 0, s>>>(
+            k_radix_onesweep<K, Rounds, NB, true><<<grid, kOsNT, 0, s>>>(
                 reinterpret_cast<const K *>(src->ids), out, N, bit, nbits, gstart, status, ticket, ntiles, err, dN,
                 *src);
             return;
         }
     }
     if (from_ids) fail(JAS_EDEVICE, "sort from IDs: 64-bit keys only");
-    k_radix_onesweep<K, Rounds, Table><<<grid, kOsNT, 0, s>>>(in, out, N, bit, nbits, gstart, status, ticket, ntiles,
-                                                             err, dN, KeySource{});
+    k_radix_onesweep<K, Rounds, NB><<<grid, kOsNT, 0, s>>>(in, out, N, bit, nbits, gstart, status, ticket, ntiles, err,
+                                                          dN, KeySource{});
+}
+template <class K, int Rounds>
+void onesweep_pass(bool from_ids, const K *in, K *out, uint64_t N, uint32_t bit, uint32_t nbits,
+                   const uint64_t *gstart, uint32_t *status, uint32_t *ticket, uint32_t ntiles, uint32_t *err,
+                   const uint64_t *dN, const KeySource *src, uint32_t grid, hipStream_t s) {
+    if (from_ids && bit < src->sbits) fail(JAS_EDEVICE, "sort from IDs: a digit below the ID bits");
+    if (nbits <= 7)
+        onesweep_launch<K, Rounds, 7>(from_ids, in, out, N, bit, nbits, gstart, status, ticket, ntiles, err, dN, src,
+                                      grid, s);
+    else
+        onesweep_launch<K, Rounds, 8>(from_ids, in, out, N, bit, nbits, gstart, status, ticket, ntiles, err, dN, src,
+                                      grid, s);
 }
 
 // With src the keys are formed from CSR sets by the first pass (keys.p is
 // not read); otherwise keys holds them.
-template <class K, int Rounds, bool Table>
+template <class K, int Rounds>
 bool onesweep_sort(DevBuf<K> &keys, DevBuf<K> &alt, uint64_t N, uint32_t lo_bit, uint32_t hi_bit, uint32_t width,
                    const unsigned long long *ghist, uint32_t *err, hipStream_t s, Budget *b, Arena *ar,
                    const char *name, const KeySource *src = nullptr) {
@@ -579,7 +557,7 @@ bool onesweep_sort(DevBuf<K> &keys, DevBuf<K> &alt, uint64_t N, uint32_t lo_bit,
         check_launch("look-back reset");
         {
             JAS_TIMED(name, s);
-            onesweep_pass<K, Rounds, Table>(src && q == 0, keys.p, alt.p, N, bit, nbits, gstart.p + q * kRadix,
+            onesweep_pass<K, Rounds>(src && q == 0, keys.p, alt.p, N, bit, nbits, gstart.p + q * kRadix,
                                             status.p, ticket.p, (uint32_t)ntiles, err, nullptr, src, grid, s);
         }
         check_launch("radix scatter (look-back)");
@@ -592,7 +570,7 @@ bool onesweep_sort(DevBuf<K> &keys, DevBuf<K> &alt, uint64_t N, uint32_t lo_bit,
 // given, nothing is read back and nothing allocated.  A digit total too large
 // for the 30-bit status counts sets bit 2 of err[0] (the result is then
 // invalid; the caller reports it after the stream completes).
-template <class K, int Rounds, bool Table>
+template <class K, int Rounds>
 void onesweep_sort_planned(K *&keys, K *&alt, const uint64_t *dN, uint64_t Ncap, uint32_t lo_bit, uint32_t hi_bit,
                            uint32_t width, const unsigned long long *ghist, uint32_t *err, const OnesweepBufs &b,
                            hipStream_t s, const char *name, const KeySource *src = nullptr) {
@@ -621,7 +599,7 @@ void onesweep_sort_planned(K *&keys, K *&alt, const uint64_t *dN, uint64_t Ncap,
         check_launch("look-back reset");
         {
             JAS_TIMED(name, s);
-            onesweep_pass<K, Rounds, Table>(src && q == 0, keys, alt, Ncap, bit, nbits, b.gstart + q * kRadix,
+            onesweep_pass<K, Rounds>(src && q == 0, keys, alt, Ncap, bit, nbits, b.gstart + q * kRadix,
                                             b.status, b.ticket, (uint32_t)ntiles, err, dN, src, grid, s);
         }
         check_launch("radix scatter (planned)");
@@ -639,7 +617,7 @@ uint64_t onesweep_status_words(uint64_t N, bool u32) {
 void radix_sort_onesweep_planned(uint64_t *&keys, uint64_t *&alt, const uint64_t *dN, uint64_t Ncap,
                                  uint32_t lo_bit, uint32_t hi_bit, uint32_t width, const unsigned long long *ghist,
                                  uint32_t *err, const OnesweepBufs &b, hipStream_t s, const KeySource *src) {
-    onesweep_sort_planned<uint64_t, 16, false>(keys, alt, dN, Ncap, lo_bit, hi_bit, width, ghist, err, b, s,
+    onesweep_sort_planned<uint64_t, 16>(keys, alt, dN, Ncap, lo_bit, hi_bit, width, ghist, err, b, s,
                                                "radix_onesweep", src);
 }
 
@@ -647,28 +625,25 @@ void radix_sort_onesweep_u32_planned(uint32_t *&keys, uint32_t *&alt, const uint
                                      uint32_t lo_bit, uint32_t hi_bit, uint32_t width,
                                      const unsigned long long *ghist, uint32_t *err, const OnesweepBufs &b,
                                      hipStream_t s) {
-    onesweep_sort_planned<uint32_t, 16, true>(keys, alt, dN, Ncap, lo_bit, hi_bit, width, ghist, err, b, s,
+    onesweep_sort_planned<uint32_t, 16>(keys, alt, dN, Ncap, lo_bit, hi_bit, width, ghist, err, b, s,
                                               "pair_sort");
 }
 
-// 64-bit keys: 16 keys per lane, ballot ranking (the table form is no faster
-// for them and needs more registers); 32-bit pair words: table ranking.
-constexpr int kU64Rounds = 16;
-constexpr bool kU64Table = false;
+constexpr int kU64Rounds = 16;  // keys per lane
 
 uint64_t onesweep_tile_keys_u64() { return (uint64_t)kOsNT * kU64Rounds; }
 
 bool radix_sort_onesweep(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, uint32_t lo_bit,
                          uint32_t hi_bit, uint32_t width, const unsigned long long *ghist, uint32_t *err,
                          hipStream_t s, Budget *b, Arena *ar, const KeySource *src) {
-    return onesweep_sort<uint64_t, kU64Rounds, kU64Table>(keys, alt, N, lo_bit, hi_bit, width, ghist, err, s, b, ar,
+    return onesweep_sort<uint64_t, kU64Rounds>(keys, alt, N, lo_bit, hi_bit, width, ghist, err, s, b, ar,
                                                           "radix_onesweep", src);
 }
 
 bool radix_sort_onesweep_u32(DevBuf<uint32_t> &keys, DevBuf<uint32_t> &alt, uint64_t N, uint32_t lo_bit,
                              uint32_t hi_bit, uint32_t width, const unsigned long long *ghist, uint32_t *err,
                              hipStream_t s, Budget *b, Arena *ar) {
-    return onesweep_sort<uint32_t, 16, true>(keys, alt, N, lo_bit, hi_bit, width, ghist, err, s, b, ar, "pair_sort");
+    return onesweep_sort<uint32_t, 16>(keys, alt, N, lo_bit, hi_bit, width, ghist, err, s, b, ar, "pair_sort");
 }
 
 }  // namespace jas
