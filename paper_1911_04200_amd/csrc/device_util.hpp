@@ -50,6 +50,16 @@ __device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v) {
     return v;
 }
 
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
+    const uint32_t l = lane_id();
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t t = __shfl_up(v, d, kWave);
+        if (l >= (uint32_t)d) v += t;
+    }
+    return v;
+}
+
 // Exclusive scan of one value per thread across a block of NT threads.
 // sh needs NT/64 entries.  Every thread of the block must call it.
 template <int NT>
@@ -67,6 +77,20 @@ __device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t *sh, ui
     }
     __syncthreads();
     *total = tot;
+    return before + inc - v;
+}
+
+// The same for 32-bit values, without the total.
+template <int NT>
+__device__ __forceinline__ uint32_t block_excl_scan_u32(uint32_t v, uint32_t *sh) {
+    const uint32_t l = lane_id(), w = threadIdx.x / kWave;
+    const uint32_t inc = wave_incl_scan_u32(v);
+    if (l == kWave - 1) sh[w] = inc;
+    __syncthreads();
+    uint32_t before = 0;
+#pragma unroll
+    for (int k = 0; k < NT / kWave; ++k) before += (k < (int)w) ? sh[k] : 0;
+    __syncthreads();
     return before + inc - v;
 }
 

@@ -29,6 +29,7 @@
 
 #include "device_util.hpp"
 #include "jas_internal.hpp"
+#include "onesweep_index.hpp"
 
 namespace jas {
 namespace {
@@ -55,9 +56,9 @@ static_assert(kStatReplicas == kStatReplicasPub, "counter replicas");
 
 // ---------------------------------------------------------------------------
 // Keys of one chunk (kChunk entries) per block, and the totals of every digit
-// of every global sort pass (ghist, kGhistReplicas copies summed later), which
-// the single-pass scatter needs.  Pass q's digit is ID bits
-// [idlo + width*q, idlo + width*(q+1)).  k_count_digits only counts (and
+// of every global sort pass (ghist, kGhistReplicas copies summed later, a row
+// of 256 digits per pass, or 512 for 9-bit passes), which the single-pass
+// scatter needs.  Pass q's digit is ID bits [idlo + width*q, idlo + width*(q+1)).  k_count_digits only counts (and
 // checks the IDs): the sort's first pass then forms the keys itself.
 template <bool kWrite>
 __device__ __forceinline__ void build_keys_chunk(const uint64_t *__restrict__ ids, const uint64_t *__restrict__ off,
@@ -67,16 +68,16 @@ __device__ __forceinline__ void build_keys_chunk(const uint64_t *__restrict__ id
                                                  unsigned long long *__restrict__ ghist,
                                                  const uint64_t *__restrict__ dsz) {
     __shared__ int32_t s_lo, s_hi;
-    __shared__ uint32_t gh[kMaxPasses][256];
+    __shared__ uint32_t gh[kMaxPasses * 256];
     const uint32_t tid = threadIdx.x;
+    const uint32_t radix = onesweep::radix_of(width);  // npass * radix <= kMaxPasses * 256
     if (plan_aborted(dsz)) return;
     if (dsz) N = dsz[PZ_N];
     const uint64_t b0 = (uint64_t)blockIdx.x * kChunk;
     if (b0 >= N) return;  // a planned launch covers the largest N
     const uint64_t b1 = min(N, b0 + kChunk);
     const uint32_t dmask = (1u << width) - 1u;
-#pragma unroll
-    for (int k = 0; k < kMaxPasses; ++k) gh[k][tid] = 0;
+    for (uint32_t i = tid; i < npass * radix; i += kNT) gh[i] = 0;
     if (kWrite && tid == 0) {
         s_lo = find_sample(off, 0, n - 1, b0);
         s_hi = find_sample(off, s_lo, n - 1, b1 - 1);
@@ -107,21 +108,21 @@ __device__ __forceinline__ void build_keys_chunk(const uint64_t *__restrict__ id
                 const uint32_t d = (uint32_t)(id >> (idlo + width * q)) & dmask;
                 if (q > 0 && __ballot(d == (uint32_t)__builtin_amdgcn_readfirstlane(d)) == active) {
                     if (lane_id() == (uint32_t)__builtin_ctzll(active))
-                        atomicAdd(&gh[q][d], (uint32_t)__popcll(active));
+                        atomicAdd(&gh[q * radix + d], (uint32_t)__popcll(active));
                 } else {
-                    atomicAdd(&gh[q][d], 1u);
+                    atomicAdd(&gh[q * radix + d], 1u);
                 }
             }
         } else {
             for (uint32_t q = 0; q < npass; ++q)
-                atomicAdd(&gh[q][(uint32_t)(id >> (idlo + width * q)) & dmask], 1u);
+                atomicAdd(&gh[q * radix + ((uint32_t)(id >> (idlo + width * q)) & dmask)], 1u);
         }
     }
     if (__ballot(bad) && lane_id() == 0) atomicOr(err, 1u);
     __syncthreads();
     unsigned long long *g = ghist + (uint64_t)(blockIdx.x % kGhistReplicas) * kMaxPasses * 256;
-    for (uint32_t q = 0; q < npass; ++q)
-        if (gh[q][tid]) atomicAdd(&g[q * 256 + tid], (unsigned long long)gh[q][tid]);
+    for (uint32_t i = tid; i < npass * radix; i += kNT)
+        if (gh[i]) atomicAdd(&g[i], (unsigned long long)gh[i]);
 }
 
 __global__ __launch_bounds__(kNT) void k_build_keys(const uint64_t *__restrict__ ids,
@@ -1973,7 +1974,6 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
         ob.gstart = p.os_gstart.p;
         ob.maxima = p.os_maxima.p;
         ob.status = p.os_status.p;
-        ob.ticket = p.os_ticket.p;
         ob.status_words = p.os_status.n;
         KeySource src;
         src.ids = ids;
@@ -2105,7 +2105,6 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
         ob.gstart = p.os2_gstart.p;
         ob.maxima = p.os2_maxima.p;
         ob.status = p.os2_status.p;
-        ob.ticket = p.os2_ticket.p;
         ob.status_words = p.os2_status.n;
         uint32_t *a = p.pk.p, *b = p.palt.p;
         radix_sort_onesweep_u32_planned(a, b, dsz + PZ_P, p.Pcap, 16, 16 + p.pair_bits, p.pair_width, p.gh.p, err,

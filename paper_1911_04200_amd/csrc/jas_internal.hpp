@@ -282,16 +282,16 @@ void radix_sort_u64(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, u
                     RadixWork &w, hipStream_t s, Budget *b, Arena *ar = nullptr);
 
 // Single-pass-per-digit sort (decoupled look-back) of keys whose digit totals
-// are known: ghist = kGhistReplicas copies of [kMaxPasses][256] totals; pass q
-// sorts on bits [lo_bit + width*q, min(lo_bit + width*(q+1), hi_bit)),
-// width <= 8.  Returns false (and does nothing) when a digit total reaches
+// are known: ghist = kGhistReplicas copies of kMaxPasses * 256 totals, a row of
+// 256 per pass (512 when width is 9); pass q sorts on bits
+// [lo_bit + width*q, min(lo_bit + width*(q+1), hi_bit)), width <= 9.  Returns false (and does nothing) when a digit total reaches
 // 2^30, where the caller uses radix_sort_u64.  A look-back that waits too long
 // sets bit 1 of err[0] (the result is then invalid).
 constexpr uint32_t kMaxPasses = 8;
 constexpr uint32_t kGhistReplicas = 32;
 // Where a sort's first pass takes its keys from when it forms them from CSR
 // sets itself (key = id << sbits | sample): the IDs and offsets of the n >= 1
-// sets, and a device buffer of 2 words per 8192-key tile (the samples holding
+// sets, and a device buffer of 2 words per tile (the samples holding
 // the tile's first and last entries), which the sort fills first.  The eager
 // sort allocates tinfo itself.
 struct KeySource {
@@ -301,7 +301,7 @@ struct KeySource {
     uint32_t *tinfo = nullptr;
     uint64_t tinfo_words = 0;
 };
-uint64_t onesweep_tile_keys_u64();  // entries per tile of the 64-bit sort
+uint64_t onesweep_tile_keys_from_ids(uint64_t N);  // entries per tile of the pass that forms N keys
 // With src, keys.p is not read: the first pass forms the keys from src.
 bool radix_sort_onesweep(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, uint32_t lo_bit,
                          uint32_t hi_bit, uint32_t width, const unsigned long long *ghist, uint32_t *err,
@@ -310,13 +310,14 @@ bool radix_sort_onesweep_u32(DevBuf<uint32_t> &keys, DevBuf<uint32_t> &alt, uint
                              uint32_t hi_bit, uint32_t width, const unsigned long long *ghist, uint32_t *err,
                              hipStream_t s, Budget *b, Arena *ar = nullptr);
 // Buffers of a planned single-pass sort (see plan.hip): digit starts
-// [kMaxPasses][256], maxima [kMaxPasses], look-back status, ticket.
+// [kMaxPasses][256], maxima [kMaxPasses], tickets and look-back status
+// (onesweep_look_back_words).
 struct OnesweepBufs {
     uint64_t *gstart = nullptr, *maxima = nullptr;
-    uint32_t *status = nullptr, *ticket = nullptr;
+    uint32_t *status = nullptr;
     uint64_t status_words = 0;
 };
-uint64_t onesweep_status_words(uint64_t N, bool u32);
+uint64_t onesweep_look_back_words(uint64_t N, uint32_t width);
 // Planned sorts: the key count is *dN (at most Ncap); keys/alt are swapped
 // as the passes go; no readback, no allocation.  err |= 4 when a digit total
 // is too large, err |= 2 when a look-back gave up.
@@ -387,7 +388,7 @@ struct PlanState {
     DevBuf<uint32_t> err, cnt, rdeg, tcnt, bs, pk, palt;
     DevBuf<unsigned long long> ghist, gh, dupc, lprep, st;
     DevBuf<uint64_t> os_gstart, os_maxima, os2_gstart, os2_maxima;
-    DevBuf<uint32_t> os_status, os_ticket, os2_status, os2_ticket, os_tinfo;
+    DevBuf<uint32_t> os_status, os2_status, os_tinfo;
     DevBuf<int64_t> card;
     DevBuf<uint64_t> W;
     uint32_t *pairs_final = nullptr;  // the buffer holding the sorted pair words after the pair sort

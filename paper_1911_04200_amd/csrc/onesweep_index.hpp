@@ -17,7 +17,9 @@
 namespace jas {
 namespace onesweep {
 
-constexpr uint32_t kRadix = 256;
+constexpr uint32_t kRadix = 256;      // digits of a pass of up to 8 bits
+constexpr uint32_t kWideRadix = 512;  // digits of a 9-bit pass
+JAS_HD inline uint32_t radix_of(uint32_t width) { return width > 8 ? kWideRadix : kRadix; }
 // status word: flag in the top two bits, a 30-bit count below
 constexpr uint32_t kFlagA = 1u << 30;  // the tile's own count is available
 constexpr uint32_t kFlagP = 2u << 30;  // the inclusive prefix over tiles 0..t is available
@@ -33,13 +35,17 @@ JAS_HD inline uint64_t tile_end(uint64_t tile, uint32_t tile_keys, uint64_t N) {
 JAS_HD inline uint64_t num_tiles(uint64_t N, uint32_t tile_keys) { return (N + tile_keys - 1) / tile_keys; }
 
 // Status words: one per (tile, digit), plus one spare.
-JAS_HD inline uint64_t status_words(uint64_t ntiles) { return ntiles * kRadix + 1; }
-JAS_HD inline uint64_t status_index(uint64_t tile, uint32_t digit) { return tile * kRadix + digit; }
+JAS_HD inline uint64_t status_words(uint64_t ntiles, uint32_t radix = kRadix) { return ntiles * radix + 1; }
+JAS_HD inline uint64_t status_index(uint64_t tile, uint32_t digit, uint32_t radix = kRadix) {
+    return tile * radix + digit;
+}
 
 // Output position of the key at position i of the tile reordered by digit,
 // whose digit d starts at tdp_d in the tile and at base_d in the output
-// (base_d = the digit's global start + the counts of d in earlier tiles).
-JAS_HD inline uint64_t out_index(uint64_t base_d, uint32_t i, uint32_t tdp_d) { return base_d + (i - tdp_d); }
+// (base_d = the digit's global start + the counts of d in earlier tiles):
+// i plus the digit's offset.
+JAS_HD inline uint64_t out_offset(uint64_t base_d, uint32_t tdp_d) { return base_d - tdp_d; }
+JAS_HD inline uint64_t out_index(uint64_t base_d, uint32_t i, uint32_t tdp_d) { return out_offset(base_d, tdp_d) + i; }
 
 }  // namespace onesweep
 }  // namespace jas

@@ -164,10 +164,9 @@ jas_status jas_plan_create(const uint64_t *ids, const uint64_t *offsets, int32_t
         plan_buf(p.ghist, (uint64_t)kGhistReplicas * kMaxPasses * 256, s, &bud, "plan digit totals");
         plan_buf(p.os_gstart, (uint64_t)kMaxPasses * 256, s, &bud, "plan digit starts");
         plan_buf(p.os_maxima, kMaxPasses, s, &bud, "plan digit maxima");
-        plan_buf(p.os_status, onesweep_status_words(p.Ncap, false), s, &bud, "plan look-back status");
-        plan_buf(p.os_ticket, 1, s, &bud, "plan tile ticket");
+        plan_buf(p.os_status, onesweep_look_back_words(p.Ncap, p.sort.width), s, &bud, "plan look-back status");
         if (p.sort.top_bits > 0)
-            plan_buf(p.os_tinfo, 2 * div_up(p.Ncap, onesweep_tile_keys_u64()), s, &bud, "plan tile samples");
+            plan_buf(p.os_tinfo, 2 * div_up(p.Ncap, onesweep_tile_keys_from_ids(p.Ncap)), s, &bud, "plan tile samples");
         plan_buf(p.rs, p.nlc_cap + 1, s, &bud, "plan range starts");
         plan_buf(p.dupc, (uint64_t)n + kStatReplicasPub, s, &bud, "plan repeat counts");
         plan_buf(p.cnt, 3 * p.nlc_cap, s, &bud, "plan range counts");
@@ -204,8 +203,7 @@ jas_status jas_plan_create(const uint64_t *ids, const uint64_t *offsets, int32_t
             plan_buf(p.gh, (uint64_t)kGhistReplicas * kMaxPasses * 256, s, &bud, "plan pair digit totals");
             plan_buf(p.os2_gstart, (uint64_t)kMaxPasses * 256, s, &bud, "plan pair digit starts");
             plan_buf(p.os2_maxima, kMaxPasses, s, &bud, "plan pair digit maxima");
-            plan_buf(p.os2_status, onesweep_status_words(p.Pcap, true), s, &bud, "plan pair look-back status");
-            plan_buf(p.os2_ticket, 1, s, &bud, "plan pair tile ticket");
+            plan_buf(p.os2_status, onesweep_look_back_words(p.Pcap, p.pair_width), s, &bud, "plan pair look-back status");
             p.pairs_final = (p.pair_npass % 2) ? p.palt.p : p.pk.p;
         }
         // the plan's db: views of the plan's buffers

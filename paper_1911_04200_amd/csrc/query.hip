@@ -148,9 +148,9 @@ __global__ void k_qfinalize(const int32_t *__restrict__ B, const unsigned long l
 uint64_t query_workspace_bytes(const jas_db *db, int32_t nq, uint64_t n_q_ids) {
     (void)db;
     // keys and second buffer, the per-pass fallback's counts, look-back status
-    // (1 KiB per 8192 keys), digit totals and starts, per-query blocks
+    // (two of 1 KiB per 8192 keys), digit totals and starts, per-query blocks
     const uint64_t nk = std::max<uint64_t>(n_q_ids, 1);
-    return 2 * 8 * nk + radix_work_bytes(n_q_ids) + (nk / 8192 + 1) * 1024 + 4 + 2 * (uint64_t)kGhistReplicas * 8 * 256 * 8 +
+    return 2 * 8 * nk + radix_work_bytes(n_q_ids) + 2 * (nk / 8192 + 1) * 1024 + 512 + 2 * (uint64_t)kGhistReplicas * 8 * 256 * 8 +
            8 * (uint64_t)(nq + 1) * 4 + scan_tmp_elems(nq) * 8 + 4096;
 }
 

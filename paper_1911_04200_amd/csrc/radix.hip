@@ -175,135 +175,184 @@ __device__ __forceinline__ uint32_t status_load(const uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One tile = kOsNT threads x R keys; threads tid < kRadix also own digit tid.
-constexpr int kOsNT = 512;  // 512 x 16 keys measured best of 512 x 8/12/16 and 1024 x 16 (one block per CU)
+// One tile = kOsNT threads x R keys; a thread also owns a digit.
+constexpr int kOsNT = 512;
 constexpr int kOsWaves = kOsNT / kWave;
+constexpr uint32_t kOsStageBytes = 65536;  // LDS the tile is reordered in (two blocks per CU fit)
+typedef uint16_t __attribute__((may_alias)) u16_alias;
+
+template <class K, class Rsrc>
+__device__ __forceinline__ K buffer_key(Rsrc r, uint32_t off) {
+    if constexpr (sizeof(K) == 8) {
+        typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+        const v2u v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+        return (uint64_t)v[1] << 32 | v[0];
+    } else {
+        return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+    }
+}
 
 // With kFromIds the pass reads CSR IDs and forms each key id << src.sbits |
 // sample itself.  Its digit is ID bits only (shift >= src.sbits), so the IDs
 // are ranked as loaded (each rank starts as soon as its load arrives) and the
-// sample joins a key when it is placed in LDS: src.tinfo holds the samples of
+// sample joins a key before it is placed in LDS: src.tinfo holds the samples of
 // the tile's first and last entries (k_tile_samples), and an entry's sample is
 // the first one plus the sample starts inside the tile at or before it (a
 // uniform loop of scalar loads, run only by tiles that span several samples).
 //
 // A pass moves 16 bytes per 64-bit key; each tile's chain of latencies (loads,
-// ranks, look-back, stores) bounds it more than memory does.  Ranks by
-// unrolled ballots for a fixed number of digit bits, with the counter
-// operations in flight together, against a ballot loop whose rounds waited for
-// each other's counters (64-bit keys) and against LDS match tables (32-bit):
-// 1.78 G keys, three passes 25.3 -> 23.3 ms; 1.85 G pair words, two passes
-// 12.2 -> 11.0 ms.
+// ranks, look-back, stores) bounds it more than memory does, so a tile is as
+// large as the registers hold (R = 32 keys per thread) and is reordered in LDS
+// a half at a time (64-bit keys), except where that leaves too few tiles.
+// Ranks come from unrolled ballots for a fixed number of digit bits, with the
+// counter operations in flight together.  Spilled registers cost more than
+// their bytes: a reload waits for the status stores before it.
+//
+// 1.78 G keys, three passes (8, 8 and 6 bits): 25.3 ms with a ballot loop whose
+// rounds waited for each other's counters and 16 keys per thread, 23.3 with
+// unrolled ballots, 20.7 with 32 (24) keys per thread: 4.1 TB/s of the 6.2 a
+// copy through such tiles reaches.  1.85 G pair words, two passes: 12.2, 11.0,
+// 8.8.  A tile's time (paperlike, 16384 keys): loads and ranks 37 %, look-back
+// 23 %, writes 16 %, counts and scan 12 %, placing 8 %.
 template <class K, int R, int NB, bool kFromIds = false>
 __global__ __launch_bounds__(kOsNT) __attribute__((amdgpu_waves_per_eu(4))) void k_radix_onesweep(
     const K *__restrict__ in, K *__restrict__ out, uint64_t N, uint32_t shift, uint32_t nbits,
-    const uint64_t *__restrict__ gstart, uint32_t *__restrict__ status, uint32_t *__restrict__ ticket,
-    uint32_t ntiles, uint32_t *__restrict__ err, const uint64_t *__restrict__ dN, KeySource src) {
-    __shared__ K stage[kOsNT * R];
-    __shared__ uint32_t wcnt[kOsWaves][kRadix];
-    __shared__ uint32_t tdp[kRadix];
-    __shared__ uint64_t base[kRadix];
-    __shared__ uint64_t sh[kOsWaves];
+    const uint64_t *__restrict__ gstart, uint32_t *__restrict__ status, uint32_t *__restrict__ next_status,
+    uint32_t *__restrict__ ticket, uint32_t ntiles, uint32_t *__restrict__ err, const uint64_t *__restrict__ dN,
+    KeySource src) {
+    constexpr uint32_t kDigits = NB > 8 ? onesweep::kWideRadix : onesweep::kRadix;
+    constexpr uint32_t kTileKeys = kOsNT * R;
+    constexpr uint32_t kParts = (kTileKeys * sizeof(K) + kOsStageBytes - 1) / kOsStageBytes;
+    constexpr uint32_t kStage = kTileKeys / kParts;  // the tile is reordered in LDS in kParts parts
+    static_assert(kTileKeys % kStage == 0 && kDigits <= kOsNT && R % 8 == 0 && kTileKeys <= 65536, "tile");
+    static_assert(!kFromIds || sizeof(K) == 8, "keys formed from IDs are 64-bit");
+    __shared__ K stage[kStage];
+    // per wave and digit d: a 16-bit count (then the first position of the wave's
+    // keys of digit d in the tile) in half d & 1 of word d >> 1
+    __shared__ uint32_t wcnt[kOsWaves][kDigits / 2];
+    __shared__ uint64_t offs[kDigits];  // output position of a key minus its position in the tile
+    __shared__ uint32_t sh[kOsWaves];
     __shared__ uint32_t tile_sh;
-    const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
     if (dN) {  // key count from device memory (planned encode): at most the buffers' N
         N = min(N, *dN);
-        ntiles = (uint32_t)onesweep::num_tiles(N, kOsNT * R);
+        ntiles = (uint32_t)onesweep::num_tiles(N, kTileKeys);
     }
-    const bool digit = tid < kRadix;  // this thread owns digit tid
     const uint32_t mask = (1u << nbits) - 1u;
     const uint32_t dshift = kFromIds ? shift - src.sbits : shift;  // digit position in a loaded value
-    const uint64_t gs = digit ? gstart[tid] : 0;
+    const uint64_t gs = threadIdx.x < kDigits ? gstart[threadIdx.x] : 0;
     // persistent: take tiles in ticket order until none is left
     for (;;) {
+        // opaque, so that nothing derived from it is held in registers from tile to tile
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const uint32_t lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
+        const u16_alias *wpos = reinterpret_cast<const u16_alias *>(wcnt[w]);
+        const bool digit = tid < kDigits;  // this thread owns digit tid
         if (tid == 0) tile_sh = atomicAdd(ticket, 1u);
-        for (uint32_t i = tid; i < kOsWaves * kRadix; i += kOsNT) (&wcnt[0][0])[i] = 0;
+        for (uint32_t i = tid; i < kOsWaves * kDigits / 2; i += kOsNT) (&wcnt[0][0])[i] = 0;
         __syncthreads();
         const uint32_t tile = __builtin_amdgcn_readfirstlane(tile_sh);  // uniform: every thread reads the same ticket
         if (tile >= ntiles) break;  // uniform: every thread read the same ticket
-        const uint64_t t0 = onesweep::tile_first(tile, kOsNT * R);
-        const uint64_t c1 = onesweep::tile_end(tile, kOsNT * R, N);
-        const uint64_t wb = t0 + (uint64_t)w * ((kOsNT * R) / kOsWaves);
-        K key[R];
-        uint32_t rank[R];
-        static_assert(!kFromIds || sizeof(K) == 8, "keys formed from IDs are 64-bit");
-        uint64_t tsmp = 0;  // samples of the tile's first and last entries (low, high half), loaded ahead
-        if constexpr (kFromIds) tsmp = const_load(reinterpret_cast<const uint64_t *>(src.tinfo) + tile);
+        const uint64_t t0 = onesweep::tile_first(tile, kTileKeys);
+        const uint64_t c1 = onesweep::tile_end(tile, kTileKeys, N);
         const uint32_t cnt_tile = (uint32_t)(c1 - t0);
-        // Rank within the wave: the lanes of a round with the same digit take
-        // consecutive slots after the digit's count so far, and the lowest of
-        // them adds the group to the count.  One wave's LDS operations run in
-        // order, so the rounds' reads and additions are issued back to back
-        // without waiting for one another, each as its keys arrive.  In the
-        // last tile entries past its end take the largest digit; they come
-        // last in it, so they land past the tile's keys and only that digit's
-        // count has to be corrected.
-        const auto load_and_rank = [&](auto whole) {
+        K key[R];
+        uint32_t pos[R / 2];  // 16 bits per key: rank within the wave and digit, then position in the tile
+        // The tile's keys, read through a buffer descriptor that ends with them
+        // (entries past the end read as 0).  Rank within the wave: the lanes of
+        // a round with the same digit take consecutive slots after the digit's
+        // count so far, and the lowest of them adds the group to the count.  One
+        // wave's LDS operations run in order, so the rounds' reads and additions
+        // are issued back to back without waiting for one another, each as its
+        // keys arrive.  Entries past the end are given the largest digit; they
+        // come last in it, so they land past the tile's keys and only that
+        // digit's count has to be corrected.
+        const auto tile_in = __builtin_amdgcn_make_buffer_rsrc(const_cast<K *>(in + t0), 0,
+                                                               cnt_tile * (uint32_t)sizeof(K), 0x00020000);
+        const uint32_t wl = w * (kTileKeys / kOsWaves) + lane;  // this lane's first entry in the tile
 #pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const uint64_t t = wb + (uint64_t)j * kWave + lane;
-                if constexpr (decltype(whole)::value) key[j] = in[t];
-                else key[j] = t < c1 ? in[t] : ~(K)0;
-            }
-            uint32_t before[R];
+        for (int j = 0; j < R; ++j) key[j] = buffer_key<K>(tile_in, (wl + j * kWave) * (uint32_t)sizeof(K));
 #pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const uint32_t d = (uint32_t)(key[j] >> dshift) & mask;
+        for (int g = 0; g < R; g += 8) {
+            uint32_t rank[8], before[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const uint32_t past = wl + (g + j) * kWave < cnt_tile ? 0u : ~0u;
+                key[g + j] |= sizeof(K) == 8 ? (K)((uint64_t)past << 32 | past) : (K)past;
+                const uint32_t d = (uint32_t)(key[g + j] >> dshift) & mask;
                 const uint64_t peers = wave_match<NB>(d);
                 before[j] = lanes_before(peers);
-                rank[j] = __hip_atomic_load(&wcnt[w][d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                rank[j] = __hip_atomic_load(&wcnt[w][d >> 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >>
+                          (16 * (d & 1));
                 if (before[j] == 0)
-                    __hip_atomic_fetch_add(&wcnt[w][d], (uint32_t)__popcll(peers), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                    __hip_atomic_fetch_add(&wcnt[w][d >> 1], (uint32_t)__popcll(peers) << (16 * (d & 1)),
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                // a round's temporaries end with it (interleaved rounds would not fit the registers)
+                if (R > 16) __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
-            for (int j = 0; j < R; ++j) rank[j] += before[j];
-        };
-        if (cnt_tile == kOsNT * R) load_and_rank(std::true_type{});  // uniform
-        else load_and_rank(std::false_type{});
+            for (int j = 0; j < 8; j += 2) {
+                pos[(g + j) / 2] = ((rank[j] & 0xFFFFu) + before[j]) | ((rank[j + 1] + before[j + 1]) << 16);
+                asm volatile("" : "+v"(pos[(g + j) / 2]));  // packed here, not where it is used
+            }
+        }
         __syncthreads();
         uint32_t tc = 0;
         if (digit) {
 #pragma unroll
-            for (int k = 0; k < kOsWaves; ++k) tc += wcnt[k][tid];
-            if (tid == mask) tc -= kOsNT * R - cnt_tile;  // the entries past the last tile's end
-            // publish the tile's count of digit tid at once
-            status_store(status + onesweep::status_index(tile, tid), (tile == 0 ? kFlagP : kFlagA) | tc);
+            for (int k = 0; k < kOsWaves; ++k) tc += reinterpret_cast<const u16_alias *>(wcnt[k])[tid];
+            if (tid == mask) tc -= kTileKeys - cnt_tile;  // the entries past the last tile's end
+            // publish the tile's count of digit tid at once, and clear its word for the next pass
+            status_store(status + onesweep::status_index(tile, tid, kDigits), (tile == 0 ? kFlagP : kFlagA) | tc);
+            next_status[onesweep::status_index(tile, tid, kDigits)] = 0;
         }
-        // reorder the tile in LDS by digit (local offsets only)
-        uint64_t tot;
-        const uint32_t ex = (uint32_t)block_excl_scan<kOsNT>(tc, sh, &tot);
-        if (digit) {  // wcnt[w][d] becomes where wave w's keys of digit d start in the tile
-            tdp[tid] = ex;
+        const uint32_t ex = block_excl_scan_u32<kOsNT>(tc, sh);  // digit tid's first position in the tile
+        if (digit) {  // the counts become where wave k's keys of digit tid start in the tile
             uint32_t run = ex;
 #pragma unroll
             for (int k = 0; k < kOsWaves; ++k) {
-                const uint32_t v = wcnt[k][tid];
-                wcnt[k][tid] = run;
+                u16_alias *p = reinterpret_cast<u16_alias *>(wcnt[k]) + tid;
+                const uint32_t v = *p;
+                *p = (uint16_t)run;
                 run += v;
             }
         }
         __syncthreads();
+        if constexpr (R > 16) {
+            // the digits are taken from the keys again: kept from the ranking, they would not fit the registers
+#pragma unroll
+            for (int j = 0; j < R; ++j) asm volatile("" : "+v"(key[j]));
+        }
+#pragma unroll
+        for (int j = 0; j < R; j += 2) {
+            pos[j / 2] += (uint32_t)wpos[(uint32_t)(key[j] >> dshift) & mask] |
+                          (uint32_t)wpos[(uint32_t)(key[j + 1] >> dshift) & mask] << 16;
+            if (R > 16) asm volatile("" : "+v"(pos[j / 2]));
+        }
         if constexpr (kFromIds) {
             // the sample starts inside the tile lie in (t0, c1), so tile-relative
             // positions compare in 32 bits
-            const uint32_t s0 = (uint32_t)tsmp, s1 = (uint32_t)(tsmp >> 32);
-            const uint32_t wl = (uint32_t)(wb - t0) + lane;
+            const uint64_t tsmp = const_load(reinterpret_cast<const uint64_t *>(src.tinfo) + tile);
+            const uint32_t s0 = (uint32_t)tsmp, s1 = (uint32_t)(tsmp >> 32);  // samples of the first and last entries
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                const uint32_t li = wl + j * kWave;  // position in the tile
-                const uint32_t d = (uint32_t)(key[j] >> dshift) & mask;
                 uint32_t smp = s0;
-                for (uint32_t k = s0 + 1; k <= s1; ++k) smp += li >= (uint32_t)(const_load(src.off + k) - t0);
-                stage[wcnt[w][d] + rank[j]] = (key[j] << src.sbits) | smp;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const uint32_t d = (uint32_t)(key[j] >> shift) & mask;
-                stage[wcnt[w][d] + rank[j]] = key[j];
+                for (uint32_t k = s0 + 1; k <= s1; ++k)
+                    smp += wl + j * kWave >= (uint32_t)(const_load(src.off + k) - t0);
+                key[j] = (key[j] << src.sbits) | smp;
             }
         }
+        // reorder the tile (its first part) in LDS by digit
+        const auto place = [&](uint32_t part) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (kParts > 1 && j % 2 == 0) asm volatile("" : "+v"(pos[j / 2]));
+                const uint32_t p = (pos[j / 2] >> (16 * (j & 1))) & 0xFFFFu;
+                if (kParts == 1) stage[p] = key[j];
+                else if (p - part * kStage < kStage) stage[p - part * kStage] = key[j];
+            }
+        };
+        place(0);
         // then look back for the digit's global offset: kLookWindow
         // predecessor tiles per step, loaded together (one memory round trip)
         // and taken nearest first
@@ -315,7 +364,7 @@ __global__ __launch_bounds__(kOsNT) __attribute__((amdgpu_waves_per_eu(4))) void
                     uint32_t v[kLookWindow];
 #pragma unroll
                     for (int k = 0; k < kLookWindow; ++k)
-                        v[k] = j0 - k >= 0 ? status_load(status + onesweep::status_index(j0 - k, tid)) : kFlagP;
+                        v[k] = j0 - k >= 0 ? status_load(status + onesweep::status_index(j0 - k, tid, kDigits)) : kFlagP;
 #pragma unroll
                     for (int k = 0; k < kLookWindow; ++k) {
                         if (found) break;
@@ -328,47 +377,70 @@ __global__ __launch_bounds__(kOsNT) __attribute__((amdgpu_waves_per_eu(4))) void
                                 break;
                             }
                             __builtin_amdgcn_s_sleep(1);
-                            v[k] = status_load(status + onesweep::status_index(j0 - k, tid));
+                            v[k] = status_load(status + onesweep::status_index(j0 - k, tid, kDigits));
                         }
                         excl += v[k] & kValMask;
                         found = (v[k] & ~kValMask) == kFlagP;
                     }
                 }
-                status_store(status + onesweep::status_index(tile, tid), kFlagP | ((excl + tc) & kValMask));
+                status_store(status + onesweep::status_index(tile, tid, kDigits), kFlagP | ((excl + tc) & kValMask));
             }
-            base[tid] = gs + excl;
+            offs[tid] = onesweep::out_offset(gs + excl, ex);
         }
         __syncthreads();
-        for (uint32_t i = tid; i < cnt_tile; i += kOsNT) {
-            const K k = stage[i];
-            const uint32_t d = (uint32_t)(k >> shift) & mask;
-            out[onesweep::out_index(base[d], i, tdp[d])] = k;
+        for (uint32_t part = 0; part < kParts; ++part) {
+            const uint32_t p0 = part * kStage;
+            if (part > 0) {
+                if (p0 >= cnt_tile) break;  // uniform
+                place(part);
+                __syncthreads();
+            }
+            const uint32_t len = min(kStage, cnt_tile - p0);
+            // a few keys per thread at a time, their LDS reads in flight together
+            constexpr uint32_t kAhead = kParts > 1 ? 4 : 8;
+            for (uint32_t i = tid; i < len; i += kAhead * kOsNT) {
+                K k[kAhead];
+                uint64_t o[kAhead];
+#pragma unroll
+                for (uint32_t u = 0; u < kAhead; ++u) k[u] = stage[(i + u * kOsNT) % kStage];
+#pragma unroll
+                for (uint32_t u = 0; u < kAhead; ++u)
+                    o[u] = offs[(uint32_t)(k[u] >> shift) & mask] + (p0 + i + u * kOsNT);
+#pragma unroll
+                for (uint32_t u = 0; u < kAhead; ++u)
+                    if (i + u * kOsNT < len) out[o[u]] = k[u];
+            }
+            __syncthreads();  // stage, offs and tile_sh are rewritten
         }
-        __syncthreads();  // stage, tdp, base and tile_sh are reused by the next tile
     }
 }
 
-// gstart[q][d] = exclusive scan over digits of the summed replicas; maxima[q] = largest digit total.
-__global__ __launch_bounds__(kNT) void k_digit_starts(const unsigned long long *__restrict__ ghist, uint32_t npass,
-                                                       uint64_t *__restrict__ gstart, uint64_t *__restrict__ maxima,
-                                                       uint32_t *__restrict__ err) {
-    __shared__ uint64_t sh[kWaves];
-    __shared__ uint64_t tot_sh[kRadix];
-    const uint32_t tid = threadIdx.x;
-    for (uint32_t q = 0; q < npass; ++q) {
-        uint64_t t = 0;
-        for (uint32_t r = 0; r < kGhistReplicas; ++r) t += ghist[((uint64_t)r * kMaxPasses + q) * kRadix + tid];
-        uint64_t all;
-        gstart[q * kRadix + tid] = block_excl_scan<kNT>(t, sh, &all);
-        tot_sh[tid] = t;
-        __syncthreads();
-        if (tid == 0) {
-            uint64_t m = 0;
-            for (int d = 0; d < kRadix; ++d) m = m > tot_sh[d] ? m : tot_sh[d];
-            maxima[q] = m;
-            if (err && m >= kValMask) atomicOr(err, 4u);  // planned sort: cannot run single-pass
-        }
-        __syncthreads();
+// Block q: gstart[q][d] = exclusive scan over pass q's digits of the summed
+// replicas; maxima[q] = largest digit total.  ghist and gstart have rows of
+// `radix` digits per pass (256, or 512 for 9-bit passes).
+__global__ __launch_bounds__(kOsNT) void k_digit_starts(const unsigned long long *__restrict__ ghist, uint32_t radix,
+                                                         uint64_t *__restrict__ gstart, uint64_t *__restrict__ maxima,
+                                                         uint32_t *__restrict__ err) {
+    __shared__ uint64_t sh[kOsWaves];
+    const uint32_t tid = threadIdx.x, q = blockIdx.x;
+    uint64_t t = 0;
+    if (tid < radix) {
+#pragma unroll
+        for (uint32_t r = 0; r < kGhistReplicas; ++r)
+            t += ghist[(uint64_t)r * kMaxPasses * kRadix + q * radix + tid];
+    }
+    uint64_t all;
+    const uint64_t ex = block_excl_scan<kOsNT>(t, sh, &all);
+    if (tid < radix) gstart[q * radix + tid] = ex;
+    uint64_t m = t;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) m = max(m, (uint64_t)__shfl_xor((unsigned long long)m, d, kWave));
+    if (lane_id() == 0) sh[tid / kWave] = m;
+    __syncthreads();
+    if (tid == 0) {
+        for (int k = 1; k < kOsWaves; ++k) m = max(m, sh[k]);
+        maxima[q] = m;
+        if (err && m >= kValMask) atomicOr(err, 4u);  // planned sort: cannot run single-pass
     }
 }
 
@@ -463,78 +535,134 @@ void tile_samples(const KeySource &src, uint64_t Ncap, uint32_t tile_keys, const
     check_launch("tile samples");
 }
 
-// Launches one pass; the first reads src.ids when the keys are formed from
-// IDs.  Passes of at most 7 bits take a kernel that matches 7.
+// Keys per thread of a tile: 32, or 24 in the pass that forms the keys (it
+// holds more, and 32 would spill), except where that leaves fewer than two
+// tiles for each resident block (then 16: more, shorter tiles).
+int tile_rounds(uint64_t N, bool from_ids) {
+    return N < (uint64_t)4 * 256 * kOsNT * 32 ? 16 : from_ids ? 24 : 32;
+}
+// Most tiles of any pass of a sort of N keys.
+uint64_t most_tiles(uint64_t N) { return onesweep::num_tiles(N, (uint32_t)kOsNT * tile_rounds(N, true)); }
+
+// The look-back words of a sort: a ticket per pass, then the status words of
+// two passes (a pass clears the other's while it runs, so only the first
+// pass's and the tickets are cleared beforehand).
+constexpr uint64_t kTicketWords = 64;
+static_assert(kTicketWords >= kMaxPasses, "tickets");
+uint64_t look_back_words(uint64_t ntiles, uint32_t radix) {
+    return kTicketWords + 2 * onesweep::status_words(ntiles, radix);
+}
+
+// What every pass of one sort is launched with.
+struct PassArgs {
+    uint64_t N = 0;
+    uint32_t *look_back = nullptr, *err = nullptr, radix = 256;
+    const uint64_t *dN = nullptr, *gstart = nullptr;
+    const KeySource *src = nullptr;  // null: the keys are in memory
+    hipStream_t s = nullptr;
+};
+
+// Launches pass q on nbits bits from `bit` on; the first reads src.ids when
+// the keys are formed from IDs.  Passes of at most 7 bits take a kernel that
+// matches 7.
 template <class K, int Rounds, int NB>
-void onesweep_launch(bool from_ids, const K *in, K *out, uint64_t N, uint32_t bit, uint32_t nbits,
-                     const uint64_t *gstart, uint32_t *status, uint32_t *ticket, uint32_t ntiles, uint32_t *err,
-                     const uint64_t *dN, const KeySource *src, uint32_t grid, hipStream_t s) {
-    if constexpr (sizeof(K) == 8) {
-        if (from_ids) {
-            k_radix_onesweep<K, Rounds, NB, true><<<grid, kOsNT, 0, s>>>(
-                reinterpret_cast<const K *>(src->ids), out, N, bit, nbits, gstart, status, ticket, ntiles, err, dN,
-                *src);
+void onesweep_launch(const PassArgs &a, uint32_t q, const K *in, K *out, uint32_t bit, uint32_t nbits) {
+    const uint32_t ntiles = (uint32_t)onesweep::num_tiles(a.N, (uint32_t)kOsNT * Rounds);
+    // persistent blocks: two per CU (256 CUs) fit, never more than there are tiles
+    const uint32_t grid = std::min<uint32_t>(ntiles, 256 * 2);
+    uint32_t *st0 = a.look_back + kTicketWords, *st1 = st0 + onesweep::status_words(most_tiles(a.N), a.radix);
+    uint32_t *st = q & 1 ? st1 : st0, *next = q & 1 ? st0 : st1, *ticket = a.look_back + q;
+    const uint64_t *gs = a.gstart + (uint64_t)q * a.radix;
+    if constexpr (sizeof(K) == 8 && Rounds != 32) {
+        if (a.src && q == 0) {
+            k_radix_onesweep<K, Rounds, NB, true><<<grid, kOsNT, 0, a.s>>>(
+                reinterpret_cast<const K *>(a.src->ids), out, a.N, bit, nbits, gs, st, next, ticket, ntiles, a.err,
+                a.dN, *a.src);
             return;
         }
     }
-    if (from_ids) fail(JAS_EDEVICE, "sort from IDs: 64-bit keys only");
-    k_radix_onesweep<K, Rounds, NB><<<grid, kOsNT, 0, s>>>(in, out, N, bit, nbits, gstart, status, ticket, ntiles, err,
-                                                          dN, KeySource{});
+    if constexpr (Rounds != 24)
+        k_radix_onesweep<K, Rounds, NB><<<grid, kOsNT, 0, a.s>>>(in, out, a.N, bit, nbits, gs, st, next, ticket, ntiles,
+                                                                a.err, a.dN, KeySource{});
 }
 template <class K, int Rounds>
-void onesweep_pass(bool from_ids, const K *in, K *out, uint64_t N, uint32_t bit, uint32_t nbits,
-                   const uint64_t *gstart, uint32_t *status, uint32_t *ticket, uint32_t ntiles, uint32_t *err,
-                   const uint64_t *dN, const KeySource *src, uint32_t grid, hipStream_t s) {
-    if (from_ids && bit < src->sbits) fail(JAS_EDEVICE, "sort from IDs: a digit below the ID bits");
-    if (nbits <= 7)
-        onesweep_launch<K, Rounds, 7>(from_ids, in, out, N, bit, nbits, gstart, status, ticket, ntiles, err, dN, src,
-                                      grid, s);
-    else
-        onesweep_launch<K, Rounds, 8>(from_ids, in, out, N, bit, nbits, gstart, status, ticket, ntiles, err, dN, src,
-                                      grid, s);
+void onesweep_digits(const PassArgs &a, uint32_t q, const K *in, K *out, uint32_t bit, uint32_t nbits) {
+    if (nbits > 8) onesweep_launch<K, Rounds, 9>(a, q, in, out, bit, nbits);
+    else if (nbits == 8) onesweep_launch<K, Rounds, 8>(a, q, in, out, bit, nbits);
+    else onesweep_launch<K, Rounds, 7>(a, q, in, out, bit, nbits);
+}
+// Every pass; keys and alt are swapped as they go.
+template <class K, class Swap>
+void onesweep_passes(const PassArgs &a, uint32_t lo_bit, uint32_t hi_bit, uint32_t width, const char *name, K *keys,
+                     K *alt, Swap swap) {
+    if (a.src && (sizeof(K) != 8 || lo_bit < a.src->sbits)) fail(JAS_EDEVICE, "sort from IDs: bad digits or keys");
+    {
+        JAS_TIMED("fill_status", a.s);
+        const uint64_t len = kTicketWords + onesweep::status_words(most_tiles(a.N), a.radix);
+        k_fill32<<<(uint32_t)std::min<uint64_t>(div_up(len, 256), 65536), 256, 0, a.s>>>(a.look_back, len);
+    }
+    check_launch("look-back reset");
+    for (uint32_t q = 0; lo_bit + width * q < hi_bit; ++q) {
+        const uint32_t bit = lo_bit + width * q, nbits = std::min(width, hi_bit - bit);
+        {
+            JAS_TIMED(name, a.s);
+            const int rounds = tile_rounds(a.N, a.src && q == 0);
+            if (rounds == 32) onesweep_digits<K, 32>(a, q, keys, alt, bit, nbits);
+            else if (rounds == 24) onesweep_digits<K, 24>(a, q, keys, alt, bit, nbits);
+            else onesweep_digits<K, 16>(a, q, keys, alt, bit, nbits);
+        }
+        check_launch("radix scatter (look-back)");
+        std::swap(keys, alt);
+        swap();
+    }
 }
 
 // With src the keys are formed from CSR sets by the first pass (keys.p is
 // not read); otherwise keys holds them.
-template <class K, int Rounds>
+template <class K>
 bool onesweep_sort(DevBuf<K> &keys, DevBuf<K> &alt, uint64_t N, uint32_t lo_bit, uint32_t hi_bit, uint32_t width,
                    const unsigned long long *ghist, uint32_t *err, hipStream_t s, Budget *b, Arena *ar,
                    const char *name, const KeySource *src = nullptr) {
     if (N <= 1 || hi_bit <= lo_bit) return true;
-    if (width < 1 || width > 8) return false;
-    const uint32_t npass = (hi_bit - lo_bit + width - 1) / width;
-    if (npass > kMaxPasses) return false;
+    if (width < 1 || width > 9) return false;
+    const uint32_t npass = (hi_bit - lo_bit + width - 1) / width, radix = onesweep::radix_of(width);
+    if (npass * radix > kMaxPasses * kRadix) return false;
     DevBuf<uint64_t> gstart, maxima;
     temp_buf(gstart, (uint64_t)kMaxPasses * kRadix, s, b, ar, "digit starts");
     temp_buf(maxima, kMaxPasses, s, b, ar, "digit maxima");
     {
         JAS_TIMED("digit_starts", s);
-        k_digit_starts<<<1, kNT, 0, s>>>(ghist, npass, gstart.p, maxima.p, nullptr);
+        k_digit_starts<<<npass, kOsNT, 0, s>>>(ghist, radix, gstart.p, maxima.p, nullptr);
     }
     check_launch("digit starts");
-    uint64_t hm[kMaxPasses];
-    JAS_HIP(hipMemcpyAsync(hm, maxima.p, sizeof(uint64_t) * npass, hipMemcpyDeviceToHost, s));
-    JAS_HIP(hipStreamSynchronize(s));
-    for (uint32_t q = 0; q < npass; ++q)
-        if (hm[q] >= std::min<uint64_t>(kValMask, scatter_count_limit())) return false;
-    const uint64_t ntiles = onesweep::num_tiles(N, (uint32_t)kOsNT * Rounds);
-    if (ntiles > 0xFFFFFFFFull) return false;
-    // persistent blocks: two per CU (256 CUs) fit, never more than there are tiles
-    const uint32_t grid = (uint32_t)std::min<uint64_t>(ntiles, 256 * 2);
-    DevBuf<uint32_t> status, ticket;
-    temp_buf(status, onesweep::status_words(ntiles), s, b, ar, "look-back status");
-    temp_buf(ticket, 1, s, b, ar, "tile ticket");
+    // no digit total is as large as the look-back counts' limit unless N is: only then they are read back
+    const uint64_t limit = std::min<uint64_t>(kValMask, scatter_count_limit());
+    if (N >= limit) {
+        uint64_t hm[kMaxPasses];
+        JAS_HIP(hipMemcpyAsync(hm, maxima.p, sizeof(uint64_t) * npass, hipMemcpyDeviceToHost, s));
+        JAS_HIP(hipStreamSynchronize(s));
+        for (uint32_t q = 0; q < npass; ++q)
+            if (hm[q] >= limit) return false;
+    }
     // What the kernel's indexing relies on (see onesweep_index.hpp): the key
-    // buffers hold N keys, the tiles cover exactly [0, N), the status array
-    // has a word for every (tile, digit), every pass has a row of digit
-    // starts, and no 30-bit status count can wrap.
-    if (keys.n < N || alt.n < N || ntiles * (uint64_t)kOsNT * Rounds < N ||
-        onesweep::tile_first(ntiles - 1, kOsNT * Rounds) >= N ||
-        status.n < onesweep::status_words(ntiles) || gstart.n < (uint64_t)npass * kRadix || grid > ntiles ||
-        N > 0xFFFFFFFFull * (uint64_t)kOsNT * Rounds)
+    // buffers hold N keys, tiles are numbered in 32 bits and cover exactly
+    // [0, N), the status array has a word for every (tile, digit) of two passes,
+    // every pass has a row of digit starts, and no 30-bit status count can wrap
+    // (checked above).
+    const uint64_t ntiles = most_tiles(N);
+    if (ntiles > 0xFFFFFFFFull) return false;
+    DevBuf<uint32_t> look_back;
+    temp_buf(look_back, look_back_words(ntiles, radix), s, b, ar, "look-back status");
+    if (keys.n < N || alt.n < N || look_back.n < look_back_words(ntiles, radix) ||
+        gstart.n < (uint64_t)npass * radix)
         fail(JAS_EDEVICE, "single-pass scatter: buffer sizes do not cover its indexing");
-    for (uint32_t q = 0; q < npass; ++q)
-        if (hm[q] > kValMask) fail(JAS_EDEVICE, "single-pass scatter: a digit total exceeds the status count");
+    PassArgs a;
+    a.N = N;
+    a.look_back = look_back.p;
+    a.err = err;
+    a.radix = radix;
+    a.gstart = gstart.p;
+    a.s = s;
     KeySource ks;
     DevBuf<uint32_t> tinfo;
     if (src) {
@@ -542,27 +670,10 @@ bool onesweep_sort(DevBuf<K> &keys, DevBuf<K> &alt, uint64_t N, uint32_t lo_bit,
         temp_buf(tinfo, 2 * ntiles, s, b, ar, "tile samples");
         ks.tinfo = tinfo.p;
         ks.tinfo_words = tinfo.n;
-        tile_samples(ks, N, (uint32_t)kOsNT * Rounds, nullptr, s);
-        src = &ks;
+        tile_samples(ks, N, (uint32_t)kOsNT * tile_rounds(N, true), nullptr, s);
+        a.src = &ks;
     }
-    for (uint32_t q = 0; q < npass; ++q) {
-        const uint32_t bit = lo_bit + width * q;
-        const uint32_t nbits = min(width, hi_bit - bit);
-        {
-            JAS_TIMED("fill_status", s);
-            k_fill32<<<(uint32_t)std::min<uint64_t>(div_up(ntiles * kRadix + 1, 256), 65536), 256, 0, s>>>(
-                status.p, ntiles * kRadix + 1);
-            k_fill32<<<1, 64, 0, s>>>(ticket.p, 1);
-        }
-        check_launch("look-back reset");
-        {
-            JAS_TIMED(name, s);
-            onesweep_pass<K, Rounds>(src && q == 0, keys.p, alt.p, N, bit, nbits, gstart.p + q * kRadix,
-                                            status.p, ticket.p, (uint32_t)ntiles, err, nullptr, src, grid, s);
-        }
-        check_launch("radix scatter (look-back)");
-        swap_bufs(keys, alt);
-    }
+    onesweep_passes<K>(a, lo_bit, hi_bit, width, name, keys.p, alt.p, [&] { swap_bufs(keys, alt); });
     return true;
 }
 // The same passes for a planned encode: the key count is read from *dN
@@ -570,80 +681,67 @@ bool onesweep_sort(DevBuf<K> &keys, DevBuf<K> &alt, uint64_t N, uint32_t lo_bit,
 // given, nothing is read back and nothing allocated.  A digit total too large
 // for the 30-bit status counts sets bit 2 of err[0] (the result is then
 // invalid; the caller reports it after the stream completes).
-template <class K, int Rounds>
+template <class K>
 void onesweep_sort_planned(K *&keys, K *&alt, const uint64_t *dN, uint64_t Ncap, uint32_t lo_bit, uint32_t hi_bit,
                            uint32_t width, const unsigned long long *ghist, uint32_t *err, const OnesweepBufs &b,
                            hipStream_t s, const char *name, const KeySource *src = nullptr) {
     if (Ncap <= 1 || hi_bit <= lo_bit) return;
-    const uint32_t npass = (hi_bit - lo_bit + width - 1) / width;
-    if (npass > kMaxPasses || width < 1 || width > 8) fail(JAS_EUNSUPPORTED, "planned sort: bad digit plan");
-    const uint64_t ntiles = onesweep::num_tiles(Ncap, (uint32_t)kOsNT * Rounds);
-    if (b.status_words < onesweep::status_words(ntiles) || ntiles > 0xFFFFFFFFull)
+    const uint32_t npass = (hi_bit - lo_bit + width - 1) / width, radix = onesweep::radix_of(width);
+    if (npass * radix > kMaxPasses * kRadix || width < 1 || width > 9)
+        fail(JAS_EUNSUPPORTED, "planned sort: bad digit plan");
+    const uint64_t ntiles = most_tiles(Ncap);
+    if (b.status_words < look_back_words(ntiles, radix) || ntiles > 0xFFFFFFFFull)
         fail(JAS_EDEVICE, "planned sort: status buffer too small");
     {
         JAS_TIMED("digit_starts", s);
-        k_digit_starts<<<1, kNT, 0, s>>>(ghist, npass, b.gstart, b.maxima, err);
+        k_digit_starts<<<npass, kOsNT, 0, s>>>(ghist, radix, b.gstart, b.maxima, err);
     }
     check_launch("digit starts");
-    if (src) tile_samples(*src, Ncap, (uint32_t)kOsNT * Rounds, dN, s);
-    const uint32_t grid = (uint32_t)std::min<uint64_t>(ntiles, 256 * 2);
-    for (uint32_t q = 0; q < npass; ++q) {
-        const uint32_t bit = lo_bit + width * q;
-        const uint32_t nbits = min(width, hi_bit - bit);
-        {
-            JAS_TIMED("fill_status", s);
-            k_fill32<<<(uint32_t)std::min<uint64_t>(div_up(onesweep::status_words(ntiles), 256), 65536), 256, 0, s>>>(
-                b.status, onesweep::status_words(ntiles));
-            k_fill32<<<1, 64, 0, s>>>(b.ticket, 1);
-        }
-        check_launch("look-back reset");
-        {
-            JAS_TIMED(name, s);
-            onesweep_pass<K, Rounds>(src && q == 0, keys, alt, Ncap, bit, nbits, b.gstart + q * kRadix,
-                                            b.status, b.ticket, (uint32_t)ntiles, err, dN, src, grid, s);
-        }
-        check_launch("radix scatter (planned)");
-        std::swap(keys, alt);
-    }
+    if (src) tile_samples(*src, Ncap, (uint32_t)kOsNT * tile_rounds(Ncap, true), dN, s);
+    PassArgs a;
+    a.N = Ncap;
+    a.look_back = b.status;
+    a.err = err;
+    a.radix = radix;
+    a.dN = dN;
+    a.gstart = b.gstart;
+    a.src = src;
+    a.s = s;
+    onesweep_passes<K>(a, lo_bit, hi_bit, width, name, keys, alt, [&] { std::swap(keys, alt); });
 }
 
 }  // namespace
 
-uint64_t onesweep_status_words(uint64_t N, bool u32) {
-    (void)u32;  // both key widths take 16 keys per lane
-    return onesweep::status_words(onesweep::num_tiles(N, (uint32_t)kOsNT * 16));
+uint64_t onesweep_tile_keys_from_ids(uint64_t N) { return (uint64_t)kOsNT * tile_rounds(N, true); }
+
+uint64_t onesweep_look_back_words(uint64_t N, uint32_t width) {
+    return look_back_words(most_tiles(N), onesweep::radix_of(width));
 }
 
 void radix_sort_onesweep_planned(uint64_t *&keys, uint64_t *&alt, const uint64_t *dN, uint64_t Ncap,
                                  uint32_t lo_bit, uint32_t hi_bit, uint32_t width, const unsigned long long *ghist,
                                  uint32_t *err, const OnesweepBufs &b, hipStream_t s, const KeySource *src) {
-    onesweep_sort_planned<uint64_t, 16>(keys, alt, dN, Ncap, lo_bit, hi_bit, width, ghist, err, b, s,
-                                               "radix_onesweep", src);
+    onesweep_sort_planned<uint64_t>(keys, alt, dN, Ncap, lo_bit, hi_bit, width, ghist, err, b, s, "radix_onesweep",
+                                    src);
 }
 
 void radix_sort_onesweep_u32_planned(uint32_t *&keys, uint32_t *&alt, const uint64_t *dN, uint64_t Ncap,
                                      uint32_t lo_bit, uint32_t hi_bit, uint32_t width,
                                      const unsigned long long *ghist, uint32_t *err, const OnesweepBufs &b,
                                      hipStream_t s) {
-    onesweep_sort_planned<uint32_t, 16>(keys, alt, dN, Ncap, lo_bit, hi_bit, width, ghist, err, b, s,
-                                              "pair_sort");
+    onesweep_sort_planned<uint32_t>(keys, alt, dN, Ncap, lo_bit, hi_bit, width, ghist, err, b, s, "pair_sort");
 }
-
-constexpr int kU64Rounds = 16;  // keys per lane
-
-uint64_t onesweep_tile_keys_u64() { return (uint64_t)kOsNT * kU64Rounds; }
 
 bool radix_sort_onesweep(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, uint32_t lo_bit,
                          uint32_t hi_bit, uint32_t width, const unsigned long long *ghist, uint32_t *err,
                          hipStream_t s, Budget *b, Arena *ar, const KeySource *src) {
-    return onesweep_sort<uint64_t, kU64Rounds>(keys, alt, N, lo_bit, hi_bit, width, ghist, err, s, b, ar,
-                                                          "radix_onesweep", src);
+    return onesweep_sort<uint64_t>(keys, alt, N, lo_bit, hi_bit, width, ghist, err, s, b, ar, "radix_onesweep", src);
 }
 
 bool radix_sort_onesweep_u32(DevBuf<uint32_t> &keys, DevBuf<uint32_t> &alt, uint64_t N, uint32_t lo_bit,
                              uint32_t hi_bit, uint32_t width, const unsigned long long *ghist, uint32_t *err,
                              hipStream_t s, Budget *b, Arena *ar) {
-    return onesweep_sort<uint32_t, 16>(keys, alt, N, lo_bit, hi_bit, width, ghist, err, s, b, ar, "pair_sort");
+    return onesweep_sort<uint32_t>(keys, alt, N, lo_bit, hi_bit, width, ghist, err, s, b, ar, "pair_sort");
 }
 
 }  // namespace jas

@@ -329,6 +329,25 @@ def test_scatter_tile_edges(N):
     assert "radix_onesweep" in names and "count_digits" in names
 
 
+@pytest.mark.parametrize("N", [(1 << 24) - 1, 1 << 24, (1 << 24) + 1, (1 << 24) + 16383])
+def test_scatter_large_tiles(N):
+    """From 2^24 keys on the scatter's tiles hold 32 keys per thread (16384 in
+    all, reordered in LDS in halves), or 24 in the pass that forms the keys:
+    sizes just below that, exactly whole tiles, one key more and one key less
+    than another tile, through jas_relabel (sorted keys: ranks against
+    numpy's) and an encode of three sets (against the oracle)."""
+    rng = np.random.default_rng(N)
+    ids = rng.integers(0, 1 << 30, N, dtype=np.uint64)
+    out = torch.empty(N, dtype=torch.int64, device="cuda")
+    D, _ = cabi.jas_relabel(dev(ids), N, 30, None, out)
+    distinct, rank = np.unique(ids, return_inverse=True)
+    assert D == distinct.size
+    assert np.array_equal(out.cpu().numpy(), rank)
+    off = np.array([0, N // 3, N // 3 + 1, N], np.uint64)
+    res, st = gpu_all_pairs(ids, off, 30, upper=True)
+    assert_matches(res, oracle.all_pairs(ids, off), upper=True)
+
+
 def test_every_id_bit_sorted_globally():
     """A small universe and many entries (U = 8, 90,000 entries with repeats):
     the global sort covers every ID bit, so each bucket is one ID with its
