@@ -431,26 +431,64 @@ __global__ void k_range_check(const uint64_t *__restrict__ K, const uint64_t *rs
 
 // KT is the LDS form of a key, relative to the range's first bucket:
 // uint32_t when every range fits 32 bits (k_range_check), else uint64_t.
-// Cap is the most keys of a range.  Blocks per CU (by LDS): 4 for 32-bit keys
-// and Cap 4096, 3 for 32-bit keys and Cap 6144 or 64-bit keys and Cap 4096,
-// 2 for 64-bit keys and Cap 6144; the register budget matches.
+// Cap is the most keys of a range.  Blocks per CU (by LDS and registers): 4
+// for 32-bit keys and Cap 4096, 3 for 32-bit keys and Cap 6144 or 64-bit keys
+// and Cap 4096, 2 for 64-bit keys and Cap 6144; the register budget matches.
+//
+// The in-LDS sort bounds it, not the 8 bytes read per key.  Keys stay in
+// registers from the load to the first pass and between passes; ranks come
+// from ballots (VALU), which leaves LDS five operations per key and pass where
+// finding the lanes of one digit through an LDS table took eight; passes of up
+// to 9 bits take the ID bits in the fewest, equal parts (18 bits: two, where
+// 8-bit passes took three).  1.78 G keys of 22 relative ID bits 18.2 -> 12.9 ms,
+// 1.60 G of 15 bits 16.3 -> 11.2, 1.47 G of 18 bits 14.7 -> 9.1, 336 M of 9 bits
+// 2.85 -> 1.63.
 constexpr int local_cls_waves(size_t kt, uint32_t cap) { return kt == 4 ? (cap <= 4096 ? 8 : 6) : (cap <= 4096 ? 6 : 4); }
+constexpr uint32_t kLDigits = 512;  // an LDS pass sorts at most 9 bits
+typedef uint16_t __attribute__((may_alias)) u16_alias;
+
+// Ranks of a wave's keys (R rounds of 64, of which `rounds` hold any) by digit
+// (key >> dsh) & mask < 2^NB: lanes of a round with the same digit take
+// consecutive slots after the digit's count so far in cnt (16 bits per digit),
+// and the lowest of them adds the group to the count.  One wave's LDS
+// operations run in order, so no round waits for another's.
+template <int NB, uint32_t R, class KT>
+__device__ __forceinline__ void rank_keys(const KT (&key)[R], uint32_t (&rank)[R], uint32_t rounds, uint32_t dsh,
+                                          uint32_t mask, uint32_t *cnt) {
+    uint32_t before[R];
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j) {
+        if (j < rounds) {  // uniform
+            const uint32_t d = (uint32_t)(key[j] >> dsh) & mask;
+            const uint64_t peers = wave_match<NB>(d);
+            before[j] = lanes_before(peers);
+            rank[j] = __hip_atomic_load(&cnt[d >> 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> (16 * (d & 1));
+            if (before[j] == 0)
+                __hip_atomic_fetch_add(&cnt[d >> 1], (uint32_t)__popcll(peers) << (16 * (d & 1)), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < R; ++j)
+        if (j < rounds) rank[j] = (rank[j] & 0xFFFFu) + before[j];
+}
+
 template <class KT, uint32_t Cap>
 __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(local_cls_waves(sizeof(KT), Cap)))) void k_local_cls(
     uint64_t *__restrict__ K, uint32_t sbits, uint64_t smask, uint32_t bsh, uint32_t lowbits,
     const uint64_t *__restrict__ rs, uint32_t nlc, uint32_t *__restrict__ cnt, int keep, uint32_t *__restrict__ Sg,
     uint64_t *__restrict__ rid_g, uint64_t *__restrict__ rptr_g, unsigned long long *__restrict__ dupc,
     unsigned long long *__restrict__ rows_rep, const uint64_t *__restrict__ dsz, uint64_t stride, uint32_t *err) {
-    static_assert(Cap <= kLocalCapKeys && Cap % kLNT == 0, "range cap");
+    static_assert(Cap <= kLocalCapKeys && Cap % kLNT == 0 && kLDigits == kLNT, "range cap");
     constexpr uint32_t kLRounds = Cap / kLNT;  // keys per thread
     __shared__ KT A[Cap];
-    // per wave and digit d: a 16-bit count (then start) in half d & 1 of word d >> 1
-    // (positions < 2^16; counts per wave <= Cap / kLWaves rounded up to 64 < 2^10)
-    __shared__ uint32_t wcnt[kLWaves][128];
-    __shared__ uint64_t T[kLWaves][256];  // per wave: lanes of the current round with digit d
+    // per wave and digit d: a 16-bit count (then start) in half d & 1 of word
+    // d >> 1; a wave adds to and reads only its own row
+    __shared__ uint32_t wcnt[kLWaves][kLDigits / 2];
     __shared__ uint64_t sh[kLWaves];
+    __shared__ uint32_t sh32[kLWaves];
     __shared__ uint32_t wc[3][kLWaves];
-    const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid / kWave);
     const uint64_t lt = lanemask_lt();
     const uint32_t c = blockIdx.x;
     if (plan_aborted(dsz)) return;
@@ -470,9 +508,12 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(local_cls_
             return;
         }
     }
-    for (uint32_t i = tid; i < kLWaves * 256; i += kLNT) (&T[0][0])[i] = 0;
     const uint64_t s0 = rs[c], s1 = rs[c + 1];
     const uint32_t L = (uint32_t)(s1 - s0);  // <= Cap (k_range_check)
+    // wave w owns positions [w*seg, (w+1)*seg), 64 per round, in order
+    const uint32_t seg = ((L + kLWaves - 1) / kLWaves + kWave - 1) / kWave * kWave;
+    const uint32_t rounds = seg / kWave;
+    const uint32_t wb = w * seg;
     // relative keys: key - kbase = ((id - rbase) << sbits) | sample < 2^(nb + sbits)
     uint64_t kbase = 0;
     uint32_t nb = 0;
@@ -484,111 +525,65 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(local_cls_
         nb = lowbits == 0 ? 0u : lowbits + dev_ceil_log2(bl - bf + 1);
     }
     {
-        // every load of the range in flight at once, then the LDS stores
-        uint64_t v[kLRounds];
+        // the wave's keys, all loads in flight at once.  Entries past the range's
+        // end are all ones: they take the largest digit in every pass and come
+        // last in it, so they stay past the range's keys (kLWaves * seg <= Cap).
+        KT key[kLRounds];
+        {
+            uint64_t v[kLRounds];
+            const uint64_t *src = K + s0 + wb;
 #pragma unroll
-        for (uint32_t j = 0; j < kLRounds; ++j) {
-            const uint32_t i = tid + j * kLNT;
-            v[j] = i < L ? K[s0 + i] : 0;
-        }
+            for (uint32_t j = 0; j < kLRounds; ++j)
+                v[j] = wb + j * kWave + lane < L ? src[j * kWave + lane] : ~0ull;
 #pragma unroll
-        for (uint32_t j = 0; j < kLRounds; ++j) {
-            const uint32_t i = tid + j * kLNT;
-            if (i < L) A[i] = (KT)(v[j] - kbase);
+            for (uint32_t j = 0; j < kLRounds; ++j)
+                key[j] = wb + j * kWave + lane < L ? (KT)(v[j] - kbase) : ~(KT)0;
         }
-    }
-    // wave w owns positions [w*seg, (w+1)*seg), 64 per round, in order
-    const uint32_t seg = ((L + kLWaves - 1) / kLWaves + kWave - 1) / kWave * kWave;
-    const uint32_t rounds = seg / kWave;
-    const uint32_t wb = w * seg;
-    __syncthreads();
-
-    // --- finish the sort: stable LSD passes (8-bit digits) over the relative ID
-    if (L > 1) {
-        for (uint32_t p = 0; p < nb; p += 8) {
-            const uint32_t dsh = sbits + p;
-            for (uint32_t i = tid; i < kLWaves * 128; i += kLNT) (&wcnt[0][0])[i] = 0;
-            KT key[kLRounds];
+        // --- finish the sort: stable LSD passes over the relative ID, of equal
+        // width, at most 9 bits
+        const uint32_t npass = L > 1 ? (nb + 8) / 9 : 0, width = npass ? (nb + npass - 1) / npass : 0;
+        for (uint32_t p = 0; p < npass; ++p) {
+            const uint32_t dsh = sbits + p * width, mask = (1u << width) - 1u;
             uint32_t rank[kLRounds];
 #pragma unroll
-            for (uint32_t j = 0; j < kLRounds; ++j) {
-                const uint32_t t = wb + j * kWave + lane;
-                key[j] = (j < rounds && t < L) ? A[t] : 0;
-            }
+            for (uint32_t i = 0; i < kLDigits / 2; i += kWave) wcnt[w][i + lane] = 0;
+            if (width <= 7) rank_keys<7>(key, rank, rounds, dsh, mask, wcnt[w]);
+            else if (width == 8) rank_keys<8>(key, rank, rounds, dsh, mask, wcnt[w]);
+            else rank_keys<9>(key, rank, rounds, dsh, mask, wcnt[w]);
             __syncthreads();
-            // Rank within the wave: the lanes of a round with the same digit
-            // find each other through T[w][d] (each ORs in its lane bit, reads
-            // the set back, and clears it; one wave's LDS operations run in
-            // order, so the rounds of a half are issued back to back and
-            // their sets read afterwards), take consecutive slots after the
-            // digit's count so far, and the lowest of them adds the group to
-            // the count with one LDS atomic (in round order) whose return its
-            // peers fetch later.  rank[j] = that return | leader << 10 |
-            // lanes before << 16 until the fetch (counts per wave < 2^10).
-            constexpr uint32_t kHalf = (kLRounds + 1) / 2;
+            // thread tid owns digit tid: its count per wave becomes where the wave's keys of it start
+            uint32_t n_d[kLWaves], tot = 0;
 #pragma unroll
-            for (uint32_t h = 0; h < 2; ++h) {
-                uint64_t peers[kHalf];
-#pragma unroll
-                for (uint32_t jj = 0; jj < kHalf; ++jj) {
-                    const uint32_t j = h * kHalf + jj;
-                    peers[jj] = 0;
-                    if (j < kLRounds && j < rounds && wb + j * kWave + lane < L) {
-                        const uint32_t d = (uint32_t)(key[j] >> dsh) & 255u;
-                        atomicOr((unsigned long long *)&T[w][d], 1ull << lane);
-                        peers[jj] = __hip_atomic_load(&T[w][d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        __hip_atomic_store(&T[w][d], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
-                }
-#pragma unroll
-                for (uint32_t jj = 0; jj < kHalf; ++jj) {
-                    const uint32_t j = h * kHalf + jj;
-                    if (j < kLRounds && j < rounds) {
-                        const uint64_t pr = peers[jj];
-                        const uint32_t before = __popcll(pr & lt);
-                        const uint32_t leader = pr ? (uint32_t)__builtin_ctzll(pr) : lane;
-                        uint32_t old = 0;
-                        if (pr && before == 0) {
-                            const uint32_t d = (uint32_t)(key[j] >> dsh) & 255u, hs = (d & 1u) * 16u;
-                            old = (atomicAdd(&wcnt[w][d >> 1], (uint32_t)__popcll(pr) << hs) >> hs) & 0xFFFFu;
-                        }
-                        rank[j] = old | (leader << 10) | (before << 16);
-                    }
-                }
+            for (int k = 0; k < kLWaves; ++k) {
+                n_d[k] = reinterpret_cast<const u16_alias *>(wcnt[k])[tid];
+                tot += n_d[k];
             }
-#pragma unroll
-            for (uint32_t j = 0; j < kLRounds; ++j)
-                if (j < rounds) {
-                    const uint32_t f = rank[j];
-                    rank[j] = ((uint32_t)__shfl((int)f, (int)((f >> 10) & 63u), kWave) & 1023u) + (f >> 16);
-                }
+            uint32_t run = wave_incl_scan_u32(tot);
+            if (lane == kWave - 1) sh32[w] = run;
             __syncthreads();
-            // thread tid < 128 owns digits 2 tid and 2 tid + 1
-            uint32_t tlo = 0, thi = 0;
-            if (tid < 128)
-                for (int k = 0; k < kLWaves; ++k) {
-                    const uint32_t v = wcnt[k][tid];
-                    tlo += v & 0xFFFFu;
-                    thi += v >> 16;
-                }
-            uint64_t all;
-            const uint32_t ex = (uint32_t)block_excl_scan<kLNT>(tlo + thi, sh, &all);
-            if (tid < 128) {  // the halves become where wave k's keys of each digit start in the range
-                uint32_t rlo = ex, rhi = ex + tlo;
-                for (int k = 0; k < kLWaves; ++k) {
-                    const uint32_t v = wcnt[k][tid];
-                    wcnt[k][tid] = rlo | (rhi << 16);
-                    rlo += v & 0xFFFFu;
-                    rhi += v >> 16;
-                }
+            run -= tot;
+            for (uint32_t k = 0; k < w; ++k) run += sh32[k];
+#pragma unroll
+            for (int k = 0; k < kLWaves; ++k) {
+                reinterpret_cast<u16_alias *>(wcnt[k])[tid] = (uint16_t)run;
+                run += n_d[k];
             }
             __syncthreads();
 #pragma unroll
             for (uint32_t j = 0; j < kLRounds; ++j)
-                if (j < rounds && wb + j * kWave + lane < L) {
-                    const uint32_t d = (uint32_t)(key[j] >> dsh) & 255u;
-                    A[((wcnt[w][d >> 1] >> ((d & 1u) * 16u)) & 0xFFFFu) + rank[j]] = key[j];
-                }
+                if (j < rounds)
+                    A[reinterpret_cast<const u16_alias *>(wcnt[w])[(uint32_t)(key[j] >> dsh) & mask] + rank[j]] = key[j];
+            __syncthreads();
+            if (p + 1 < npass) {
+#pragma unroll
+                for (uint32_t j = 0; j < kLRounds; ++j)
+                    if (j < rounds) key[j] = A[wb + j * kWave + lane];
+            }
+        }
+        if (npass == 0) {
+#pragma unroll
+            for (uint32_t j = 0; j < kLRounds; ++j)
+                if (j < rounds) A[wb + j * kWave + lane] = key[j];
             __syncthreads();
         }
     }

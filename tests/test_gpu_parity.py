@@ -348,6 +348,22 @@ def test_scatter_large_tiles(N):
     assert_matches(res, oracle.all_pairs(ids, off), upper=True)
 
 
+@pytest.mark.parametrize("U", [9, 10, 14, 17, 18, 19, 26, 40, 55])
+def test_lds_pass_widths(U):
+    """The ID bits a range leaves for LDS are sorted in the fewest passes of at
+    most 9 bits: universes whose ranges need one pass up to six, with keys in
+    32 or 64 bits, repeats and sets of one ID."""
+    rng = np.random.default_rng(U)
+    n = 40
+    sets = [rng.integers(0, 1 << U, int(rng.integers(1, 700)), dtype=np.uint64) for _ in range(n)]
+    core = rng.integers(0, 1 << U, 90, dtype=np.uint64)
+    sets = [np.concatenate([x, rng.choice(core, 30)]) for x in sets]
+    sets[3] = core[:1].copy()
+    ids, off = csr(sets)
+    res, st = gpu_all_pairs(ids, off, U)
+    assert_matches(res, oracle.all_pairs(ids, off))
+
+
 def test_every_id_bit_sorted_globally():
     """A small universe and many entries (U = 8, 90,000 entries with repeats):
     the global sort covers every ID bit, so each bucket is one ID with its
