@@ -432,7 +432,7 @@ jas_status jas_query(const jas_db *db, const uint64_t *q_ids, const uint64_t *q_
         const uint64_t n = (uint64_t)db->n;
         const uint64_t len = (uint64_t)nq * n;
         if (!host) {
-            query(db, q_ids, q_offsets, nq, NQ, s, B, q_card, den, J);
+            query(db, q_ids, q_offsets, nq, hoff, s, B, q_card, den, J);
             return;
         }
         DevBuf<uint64_t> di, doff;
@@ -447,7 +447,7 @@ jas_status jas_query(const jas_db *db, const uint64_t *q_ids, const uint64_t *q_
         if (q_card) dC.alloc(nq, s, nullptr, true, "q_card staging");
         if (den) dD.alloc(std::max<uint64_t>(len, 1), s, nullptr, true, "den staging");
         if (J) dJ.alloc(std::max<uint64_t>(len, 1), s, nullptr, true, "J staging");
-        query(db, di.p, doff.p, nq, NQ, s, dB.p, q_card ? dC.p : nullptr, den ? dD.p : nullptr, J ? dJ.p : nullptr);
+        query(db, di.p, doff.p, nq, hoff, s, dB.p, q_card ? dC.p : nullptr, den ? dD.p : nullptr, J ? dJ.p : nullptr);
         if (len) JAS_HIP(hipMemcpyAsync(B, dB.p, len * 4, hipMemcpyDeviceToHost, s));
         if (q_card) JAS_HIP(hipMemcpyAsync(q_card, dC.p, 8 * (uint64_t)nq, hipMemcpyDeviceToHost, s));
         if (den && len) JAS_HIP(hipMemcpyAsync(den, dD.p, len * 8, hipMemcpyDeviceToHost, s));
@@ -484,7 +484,7 @@ jas_status jas_query_noalloc(const jas_db *db, const uint64_t *q_ids, const uint
                                  std::to_string(noalloc_max_ids()) + ")");
         if (NQ > 0 && !q_ids) fail(JAS_EINVAL, "jas_query_noalloc: q_ids is NULL");
         try {
-            query(db, q_ids, q_offsets, nq, NQ, s, B, q_card, den, J, &ar);
+            query(db, q_ids, q_offsets, nq, hoff, s, B, q_card, den, J, &ar);
         } catch (...) {
             (void)hipStreamSynchronize(s);  // the workspace is free again only when its kernels are done
             throw;

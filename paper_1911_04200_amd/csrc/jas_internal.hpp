@@ -419,9 +419,10 @@ int32_t gram_variants();
 uint64_t relabel(const uint64_t *ids, uint64_t N, uint32_t U, hipStream_t s, uint64_t *out);
 
 // Query (see query.hip).
-// ar: take every temporary from this region instead of the cache (nothing is allocated).
-void query(const jas_db *db, const uint64_t *q_ids, const uint64_t *q_offsets, int32_t nq, uint64_t NQ,
-           hipStream_t s, int32_t *B, int64_t *q_card, int64_t *den, double *J, Arena *ar = nullptr);
+// hoff: the offsets on the host.  ar: take every temporary from this region
+// instead of the cache (nothing is allocated).  Synchronises s.
+void query(const jas_db *db, const uint64_t *q_ids, const uint64_t *q_offsets, int32_t nq,
+           const std::vector<uint64_t> &hoff, hipStream_t s, int32_t *B, int64_t *q_card, int64_t *den, double *J, Arena *ar = nullptr);
 uint64_t query_workspace_bytes(const jas_db *db, int32_t nq, uint64_t n_q_ids);
 
 // The fixed workspace of jas_query_noalloc (noalloc.hip): the largest query

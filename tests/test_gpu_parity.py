@@ -707,6 +707,58 @@ def test_query_matches_oracle(query_only):
     assert np.array_equal(res["J"].view(np.uint64), ref["J"].view(np.uint64))
 
 
+def check_query(db, qsets, ids, off, flags=0):
+    qi, qo = csr(qsets)
+    out = jas.query(db, dev(qi), dev(qo), flags=flags)
+    torch.cuda.synchronize()
+    res = {k: v.cpu().numpy() for k, v in out.items()}
+    ref = oracle.cross(qi, qo, ids, off)
+    assert np.array_equal(res["q_card"], ref["q_card"])
+    assert np.array_equal(res["B"], ref["inter"]) and np.array_equal(res["den"], ref["union"])
+    assert np.array_equal(res["J"].view(np.uint64), ref["J"].view(np.uint64))
+
+
+@pytest.mark.parametrize("sizes", [[1], [0, 15, 16, 17], [511, 512, 513, 0], [4095, 4097, 1], [32768], [32768, 32769],
+                                   [20000] * 60])
+def test_query_set_sizes_on_both_paths(sizes):
+    """Requests whose sets have at most 32768 IDs and 2^20 in all are made sets
+    through LDS hash tables, the others by a sort: sizes around a block's share
+    and both limits, with repeats inside a set and IDs the database lacks."""
+    rng = np.random.default_rng(sum(sizes))
+    pool = rng.integers(0, 1 << 36, 60000, dtype=np.uint64)
+    sets = [rng.choice(pool, 3000) for _ in range(60)]
+    ids, off = csr(sets)
+    db, _ = jas.encode(dev(ids), dev(off), universe_bits=36, keep_ids=True)
+    q = [np.concatenate([rng.choice(pool, z // 2), rng.integers(0, 1 << 36, z - z // 2, dtype=np.uint64)]) for z in sizes]
+    check_query(db, q, ids, off)
+    for k, z in enumerate(sizes):  # one ID throughout, and IDs in a row
+        q[k] = np.full(z, pool[k], np.uint64) if k % 2 else np.arange(z, dtype=np.uint64) << np.uint64(20)
+    check_query(db, q, ids, off)
+    if max(sizes) > 0:  # an ID outside the universe is refused on either path
+        q[int(np.argmax(sizes))][-1] = 1 << 36
+        with pytest.raises(cabi.JasError) as e:
+            check_query(db, q, ids, off)
+        assert e.value.status == cabi.JAS_EINVAL
+    db.close()
+
+
+@pytest.mark.parametrize("n", [513, 3000, 20000])
+def test_query_ids_most_samples_hold(n):
+    """A database ID in every one of n samples: beyond the 512 entries a thread
+    reads itself, the block reads the run (with the row of B in LDS up to 16384
+    samples, else in memory), next to IDs of other lengths and of none."""
+    rng = np.random.default_rng(n)
+    hubs = np.array([7, 1 << 19, (1 << 20) - 1], np.uint64)  # the universe's last ID ends the key array
+    sets = [np.concatenate([hubs[: 1 + i % 3] if i else hubs, rng.integers(8, 1 << 18, 5, dtype=np.uint64)])
+            for i in range(n)]
+    ids, off = csr(sets)
+    db, _ = jas.encode(dev(ids), dev(off), universe_bits=20, keep_ids=True, query_only=True)
+    check_query(db, [hubs, np.array([7, 9, 7], np.uint64), np.zeros(0, np.uint64),
+                     rng.integers(0, 1 << 20, 40000, dtype=np.uint64)], ids, off)
+    check_query(db, [hubs[::-1].copy(), sets[5]], ids, off)
+    db.close()
+
+
 def test_query_row_equals_gram_row():
     spec = synth.scaled(synth.workload("batching"), n=120, size_scale=0.004, pool_scale=0.004)
     ids, off = synth.generate(spec)
