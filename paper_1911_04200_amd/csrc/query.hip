@@ -275,7 +275,10 @@ __global__ __launch_bounds__(kNT) void k_query_small(const uint64_t *__restrict_
 #pragma unroll
         for (uint32_t u = 0; u < 8; ++u) {
             const uint64_t id = v[u];
-            bad |= (id >> ix.U) != 0;
+            if (id >> ix.U) {  // refused, and not looked up: it has no bucket
+                bad |= 1u;
+                continue;
+            }
             // a multiplicative hash (Knuth): its high half picks the block, both halves the slot
             const uint64_t h = (id ^ (id >> 32)) * 0x9E3779B97F4A7C15ull;
             if (i0 + u * kNT >= len || (uint32_t)(((h >> 32) * parts) >> 32) != p) continue;
