@@ -104,6 +104,47 @@ __device__ __forceinline__ int32_t find_sample(const uint64_t *off, int32_t lo, 
     return lo;
 }
 
+// First position in [lo, hi) of the ascending array v whose value is >= target
+// (hi if none).  The search starts at the place `frac` (a fraction of 2^64) of the
+// range and widens from there: where the values are spread evenly it reads the
+// one or two cache lines around its target, and however they are spread it
+// takes a logarithmic number of steps.
+__device__ __forceinline__ uint64_t lower_bound_from(const uint64_t *__restrict__ v, uint64_t lo, uint64_t hi,
+                                                     uint64_t target, uint64_t frac) {
+    if (lo >= hi) return lo;
+    const uint64_t m = lo + __umul64hi(frac, hi - lo);  // < hi
+    uint64_t step = 4;
+    if (v[m] < target) {
+        lo = m + 1;
+        while (lo < hi) {
+            const uint64_t t = min(lo + step, hi) - 1;
+            if (v[t] >= target) {
+                hi = t;
+                break;
+            }
+            lo = t + 1;
+            step *= 2;
+        }
+    } else {
+        hi = m;
+        while (lo < hi) {
+            const uint64_t t = hi - lo > step ? hi - step : lo;
+            if (v[t] < target) {
+                lo = t + 1;
+                break;
+            }
+            hi = t;
+            step *= 2;
+        }
+    }
+    while (lo < hi) {
+        const uint64_t t = (lo + hi) >> 1;
+        if (v[t] < target) lo = t + 1;
+        else hi = t;
+    }
+    return lo;
+}
+
 // Position of (i, j), i <= j, in an n x n output: row-major full or packed upper.
 __device__ __forceinline__ uint64_t out_index(uint32_t i, uint32_t j, uint32_t n, bool upper) {
     return upper ? (uint64_t)i * n - (uint64_t)i * (i - 1) / 2 + (j - i) : (uint64_t)i * n + j;

@@ -519,7 +519,7 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(local_cls_
     uint32_t nb = 0;
     if (L > 0) {
         const uint64_t bf = bucket_of(K[s0], bsh), bl = bucket_of(K[s1 - 1], bsh);
-        kbase = (bf << lowbits) << sbits;  // bf > 0 only when lowbits < U <= 63
+        kbase = bf ? (bf << lowbits) << sbits : 0;  // bf > 0 only when lowbits < U
         // with no ID bits below the buckets (every ID bit sorted globally)
         // the range is sorted already: a bucket is one ID, its keys in sample order
         nb = lowbits == 0 ? 0u : lowbits + dev_ceil_log2(bl - bf + 1);
@@ -609,7 +609,7 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(local_cls_
             sh_ = first && (left || right);
             r = sh_ && !left;
             rows += first && !left;
-            if (!first) atomicAdd(&dupc[key & smask], 1ull);
+            if (!first && dupc) atomicAdd(&dupc[key & smask], 1ull);
         }
         fD |= (uint32_t)d << j;
         fS |= (uint32_t)sh_ << j;
@@ -1408,6 +1408,87 @@ void build_keys(const uint64_t *ids, const uint64_t *offsets, int32_t n, uint64_
     check_launch("build keys");
 }
 
+namespace {
+// The ranges k_local_cls finishes: their starts rs[0 .. nlc], the most keys of
+// one (cap, one of the kernel's), and the flags of k_range_check (bit 8: no
+// stride gives ranges that fit LDS; bit 16: their keys need 64 bits).
+struct Ranges {
+    uint64_t nlc = 0, stride = 0, err = 8;
+    uint32_t cap = kLocalCapKeys;
+};
+constexpr uint64_t kMinStride = kLocalStrides[sizeof(kLocalStrides) / sizeof(kLocalStrides[0]) - 1];
+
+Ranges find_ranges(const uint64_t *keys, uint64_t N, uint32_t bsh, uint32_t lowbits, uint32_t sbits,
+                   DevBuf<uint64_t> &rs, DevBuf<uint64_t> &flags, hipStream_t s, Budget *tb) {
+    Ranges r;
+    rs.alloc(div_up(N, kMinStride) + 1, s, tb, true, "range starts");
+    flags.alloc(1, s, tb, true, "range error flag");
+    uint32_t *err = reinterpret_cast<uint32_t *>(flags.p);
+    // with every ID bit sorted globally the ranges need no LDS passes, and
+    // longer ranges (fewer blocks) pay: 4096 is tried first
+    const uint64_t strides[] = {kLocalWideStride, kLocalStrides[0], kLocalStrides[1]};
+    for (const uint64_t stride : strides) {
+        if (stride == kLocalWideStride && lowbits != 0) continue;
+        r.nlc = div_up(N, stride);
+        {
+            JAS_TIMED("fill_u64", s);
+            k_fill_u64<<<1, 64, 0, s>>>(flags.p, 1, 0);
+        }
+        {
+            JAS_TIMED("range_starts", s);
+            k_range_starts<<<(uint32_t)div_up(r.nlc + 1, 256 / kWave), 256, 0, s>>>(keys, N, bsh, stride, r.nlc, rs.p,
+                                                                                     err, nullptr, r.cap);
+            k_range_check<<<(uint32_t)std::min<uint64_t>(div_up(r.nlc, 256), 4096), 256, 0, s>>>(
+                keys, rs.p, r.nlc, bsh, lowbits, sbits, err, nullptr, 0, r.cap);
+        }
+        check_launch("range starts");
+        JAS_HIP(hipMemcpyAsync(&r.err, flags.p, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+        JAS_HIP(hipStreamSynchronize(s));
+        if ((r.err & 8u) == 0) {
+            r.cap = r.err & 128u ? kLocalCapKeys : kLocalShortCap;
+            r.stride = stride;
+            break;
+        }
+    }
+    return r;
+}
+}  // namespace
+
+uint64_t distinct_sorted(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, uint32_t U, const SortPlan &plan,
+                         hipStream_t s) {
+    if (div_up(N, kMinStride) > 0xFFFFFFFFull || keys.n < N || alt.n < N) return ~0ull;
+    const uint32_t lowbits = U - plan.top_bits;
+    DevBuf<uint64_t> rs, flags;
+    const Ranges rg = find_ranges(keys.p, N, lowbits, lowbits, 0, rs, flags, s, nullptr);
+    if (rg.err & 8u) return ~0ull;
+    DevBuf<unsigned long long> rows;
+    DevBuf<uint32_t> cnt;
+    DevBuf<uint64_t> off, zero, tmp;
+    rows.alloc(kStatReplicas, s, nullptr, true, "row counters");
+    cnt.alloc(3 * rg.nlc, s, nullptr, true, "range counts");
+    off.alloc(rg.nlc + 1, s, nullptr, true, "range offsets");
+    zero.alloc(rg.nlc + 1, s, nullptr, true, "range offsets");
+    tmp.alloc(scan_tmp_elems(rg.nlc), s, nullptr, true, "scan scratch");
+    {
+        // without sample bits no two distinct keys share an ID: no rows, no shared pairs
+        JAS_TIMED(rg.err & 16u ? "local_cls_wide" : "local_cls", s);
+        launch_local_cls((rg.err & 16u) != 0, rg.cap, (uint32_t)rg.nlc, s, keys.p, 0u, (uint64_t)0, lowbits, lowbits,
+                         (const uint64_t *)rs.p, (uint32_t)rg.nlc, cnt.p, 1, (uint32_t *)nullptr, (uint64_t *)nullptr,
+                         (uint64_t *)nullptr, (unsigned long long *)nullptr, rows.p, (const uint64_t *)nullptr,
+                         (uint64_t)0, reinterpret_cast<uint32_t *>(flags.p));
+    }
+    check_launch("local distinct");
+    scan_excl_u32(cnt.p, off.p, rg.nlc, tmp.p, s);
+    {
+        JAS_TIMED("local_move", s);
+        k_fill_u64<<<(uint32_t)std::min<uint64_t>(div_up(rg.nlc + 1, 256), 4096), 256, 0, s>>>(zero.p, rg.nlc + 1, 0);
+        k_local_move<<<(uint32_t)std::min<uint64_t>(rg.nlc, 65536), 256, 0, s>>>(
+            rs.p, rg.nlc, off.p, zero.p, zero.p, keys.p, nullptr, nullptr, alt.p, nullptr, nullptr, nullptr, nullptr, 0);
+    }
+    check_launch("local move");
+    return to_host_u64(off.p + rg.nlc, s);
+}
+
 void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, const SortPlan &plan,
                    const uint64_t *offsets, hipStream_t s, Budget *tb) {
     const int32_t n = db->n;
@@ -1442,43 +1523,17 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
     bool done = N == 0;
 
     // --- classify each range of whole buckets in LDS ------------------------
-    constexpr uint64_t kMinStride = kLocalStrides[sizeof(kLocalStrides) / sizeof(kLocalStrides[0]) - 1];
     if (!done && div_up(N, kMinStride) <= 0xFFFFFFFFull && alt.n >= N + 2) {
         const uint32_t lowbits = db->U - plan.top_bits;
         const uint32_t bsh = sbits + lowbits;
         DevBuf<uint64_t> rs, flags;
-        rs.alloc(div_up(N, kMinStride) + 1, s, tb, true, "range starts");
-        flags.alloc(1, s, tb, true, "range error flag");
+        const Ranges rg = find_ranges(keys.p, N, bsh, lowbits, sbits, rs, flags, s, tb);
         uint32_t *errL = reinterpret_cast<uint32_t *>(flags.p);
-        uint64_t herr = 8, nlc = 0;
-        uint32_t cap = kLocalCapKeys;
-        // with every ID bit sorted globally the ranges need no LDS passes, and
-        // longer ranges (fewer blocks) pay: 4096 is tried first
-        const uint64_t strides[] = {kLocalWideStride, kLocalStrides[0], kLocalStrides[1]};
-        for (const uint64_t stride : strides) {
-            if (stride == kLocalWideStride && lowbits != 0) continue;
-            nlc = div_up(N, stride);
-            {
-                JAS_TIMED("fill_u64", s);
-                k_fill_u64<<<1, 64, 0, s>>>(flags.p, 1, 0);
-            }
-            {
-                JAS_TIMED("range_starts", s);
-                k_range_starts<<<(uint32_t)div_up(nlc + 1, 256 / kWave), 256, 0, s>>>(keys.p, N, bsh, stride, nlc,
-                                                                                       rs.p, errL, nullptr, cap);
-                k_range_check<<<(uint32_t)std::min<uint64_t>(div_up(nlc, 256), 4096), 256, 0, s>>>(
-                    keys.p, rs.p, nlc, bsh, lowbits, sbits, errL, nullptr, 0, cap);
-            }
-            check_launch("range starts");
-            JAS_HIP(hipMemcpyAsync(&herr, flags.p, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-            JAS_HIP(hipStreamSynchronize(s));
-            if ((herr & 8u) == 0) {
-                cap = herr & 128u ? kLocalCapKeys : kLocalShortCap;
-                db->trace.stride = stride;
-                db->trace.lcap = cap;
-                break;
-            }
-        }
+        const uint64_t nlc = rg.nlc;
+        const uint32_t cap = rg.cap;
+        uint64_t herr = rg.err;
+        db->trace.stride = rg.stride;
+        db->trace.lcap = cap;
         if ((herr & 8u) == 0) {
             DevBuf<unsigned long long> dupc;
             DevBuf<uint32_t> cnt;

@@ -302,10 +302,12 @@ struct KeySource {
     uint64_t tinfo_words = 0;
 };
 uint64_t onesweep_tile_keys_from_ids(uint64_t N);  // entries per tile of the pass that forms N keys
-// With src, keys.p is not read: the first pass forms the keys from src.
+// With src, keys.p is not read: the first pass forms the keys from src.  With
+// first, the first pass reads the keys there (they are not changed).
 bool radix_sort_onesweep(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, uint32_t lo_bit,
                          uint32_t hi_bit, uint32_t width, const unsigned long long *ghist, uint32_t *err,
-                         hipStream_t s, Budget *b, Arena *ar = nullptr, const KeySource *src = nullptr);
+                         hipStream_t s, Budget *b, Arena *ar = nullptr, const KeySource *src = nullptr,
+                         const uint64_t *first = nullptr);
 bool radix_sort_onesweep_u32(DevBuf<uint32_t> &keys, DevBuf<uint32_t> &alt, uint64_t N, uint32_t lo_bit,
                              uint32_t hi_bit, uint32_t width, const unsigned long long *ghist, uint32_t *err,
                              hipStream_t s, Budget *b, Arena *ar = nullptr);
@@ -367,6 +369,13 @@ void build_keys(const uint64_t *ids, const uint64_t *offsets, int32_t n, uint64_
 // is used as scratch; offsets are the device CSR offsets.
 void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, const SortPlan &plan,
                    const uint64_t *offsets, hipStream_t s, Budget *tmpb);
+
+// The distinct values of N keys of U bits ordered by their top plan.top_bits
+// bits (keys holds them; N >= 1), ascending, in alt (N entries); returns their
+// number, or ~0 when some range of equal top bits is too large for LDS (keys
+// and alt are then as they were).  Synchronises s.
+uint64_t distinct_sorted(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, uint32_t U, const SortPlan &plan,
+                         hipStream_t s);
 
 // A planned encode (plan.hip creates it, encode.hip runs it): the decisions
 // of one eager encode and buffers sized for them with headroom, so a like

@@ -89,47 +89,13 @@ struct Index {
 };
 
 // First position in ix.keys whose ID is >= id (among those of id's bucket, or
-// one past them).  A bucket holds about 32 keys, 256 bytes; IDs are spread
-// evenly in it more often than not, so the search starts where the ID's bits
-// below the bucket's point to and widens from there, which reads one or two
-// lines of the bucket instead of most of them.
+// one past them).  A bucket holds about 32 keys, 256 bytes; the search starts
+// where the ID's bits below the bucket's point to.
 __device__ __forceinline__ uint64_t first_at(const Index &ix, uint64_t id) {
     const uint32_t shift = ix.U - ix.ibits;
-    const uint64_t bk = id >> shift, target = id << ix.sbits;
-    uint64_t lo = ix.bucket[bk], hi = ix.bucket[bk + 1];
-    if (lo >= hi) return lo;
-    const uint64_t frac = shift ? id << (64 - shift) : 0;  // the bits below the bucket's, as a fraction
-    const uint64_t m = lo + __umul64hi(frac, hi - lo);     // < hi
-    uint64_t step = 4;
-    if (ix.keys[m] < target) {
-        lo = m + 1;
-        while (lo < hi) {
-            const uint64_t t = min(lo + step, hi) - 1;
-            if (ix.keys[t] >= target) {
-                hi = t;
-                break;
-            }
-            lo = t + 1;
-            step *= 2;
-        }
-    } else {
-        hi = m;
-        while (lo < hi) {
-            const uint64_t t = hi - lo > step ? hi - step : lo;
-            if (ix.keys[t] < target) {
-                lo = t + 1;
-                break;
-            }
-            hi = t;
-            step *= 2;
-        }
-    }
-    while (lo < hi) {
-        const uint64_t t = (lo + hi) >> 1;
-        if (ix.keys[t] < target) lo = t + 1;
-        else hi = t;
-    }
-    return lo;
+    const uint64_t bk = id >> shift;
+    return lower_bound_from(ix.keys, ix.bucket[bk], ix.bucket[bk + 1], id << ix.sbits,
+                            shift ? id << (64 - shift) : 0);
 }
 
 // What a block keeps while it looks its IDs up.

@@ -471,7 +471,9 @@ SortPlan sort_plan(uint64_t N, uint32_t U, uint32_t sbits) {
     p.top_bits = std::min<uint32_t>(U, ceil_log2_u64(div_up(N, kBucketKeys)));
     const uint32_t fewer = std::min<uint32_t>(U, ceil_log2_u64(div_up(N, 2 * kBucketKeys)));
     if (fewer > 0 && (U - fewer) + kSpanBits + sbits <= 32) p.top_bits = fewer;
-    p.npass = (p.top_bits + 7) / 8;
+    // the fewest passes of at most 9 bits, of equal width: a pass over 18 bits'
+    // halves takes 1.4 times one over 6 (1.78 G keys: 9.0, 6.3 ms), so two beat three
+    p.npass = (p.top_bits + 8) / 9;
     p.width = p.npass ? (p.top_bits + p.npass - 1) / p.npass : 8;
     return p;
 }
@@ -559,6 +561,7 @@ struct PassArgs {
     uint32_t *look_back = nullptr, *err = nullptr, radix = 256;
     const uint64_t *dN = nullptr, *gstart = nullptr;
     const KeySource *src = nullptr;  // null: the keys are in memory
+    const void *first = nullptr;     // where the first pass reads them, if not in the sort's buffer
     hipStream_t s = nullptr;
 };
 
@@ -607,9 +610,10 @@ void onesweep_passes(const PassArgs &a, uint32_t lo_bit, uint32_t hi_bit, uint32
         {
             JAS_TIMED(name, a.s);
             const int rounds = tile_rounds(a.N, a.src && q == 0);
-            if (rounds == 32) onesweep_digits<K, 32>(a, q, keys, alt, bit, nbits);
-            else if (rounds == 24) onesweep_digits<K, 24>(a, q, keys, alt, bit, nbits);
-            else onesweep_digits<K, 16>(a, q, keys, alt, bit, nbits);
+            const K *in = a.first && q == 0 ? static_cast<const K *>(a.first) : keys;
+            if (rounds == 32) onesweep_digits<K, 32>(a, q, in, alt, bit, nbits);
+            else if (rounds == 24) onesweep_digits<K, 24>(a, q, in, alt, bit, nbits);
+            else onesweep_digits<K, 16>(a, q, in, alt, bit, nbits);
         }
         check_launch("radix scatter (look-back)");
         std::swap(keys, alt);
@@ -622,7 +626,7 @@ void onesweep_passes(const PassArgs &a, uint32_t lo_bit, uint32_t hi_bit, uint32
 template <class K>
 bool onesweep_sort(DevBuf<K> &keys, DevBuf<K> &alt, uint64_t N, uint32_t lo_bit, uint32_t hi_bit, uint32_t width,
                    const unsigned long long *ghist, uint32_t *err, hipStream_t s, Budget *b, Arena *ar,
-                   const char *name, const KeySource *src = nullptr) {
+                   const char *name, const KeySource *src = nullptr, const K *first = nullptr) {
     if (N <= 1 || hi_bit <= lo_bit) return true;
     if (width < 1 || width > 9) return false;
     const uint32_t npass = (hi_bit - lo_bit + width - 1) / width, radix = onesweep::radix_of(width);
@@ -662,6 +666,7 @@ bool onesweep_sort(DevBuf<K> &keys, DevBuf<K> &alt, uint64_t N, uint32_t lo_bit,
     a.err = err;
     a.radix = radix;
     a.gstart = gstart.p;
+    a.first = first;
     a.s = s;
     KeySource ks;
     DevBuf<uint32_t> tinfo;
@@ -734,8 +739,9 @@ void radix_sort_onesweep_u32_planned(uint32_t *&keys, uint32_t *&alt, const uint
 
 bool radix_sort_onesweep(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, uint32_t lo_bit,
                          uint32_t hi_bit, uint32_t width, const unsigned long long *ghist, uint32_t *err,
-                         hipStream_t s, Budget *b, Arena *ar, const KeySource *src) {
-    return onesweep_sort<uint64_t>(keys, alt, N, lo_bit, hi_bit, width, ghist, err, s, b, ar, "radix_onesweep", src);
+                         hipStream_t s, Budget *b, Arena *ar, const KeySource *src, const uint64_t *first) {
+    return onesweep_sort<uint64_t>(keys, alt, N, lo_bit, hi_bit, width, ghist, err, s, b, ar, "radix_onesweep", src,
+                                   first);
 }
 
 bool radix_sort_onesweep_u32(DevBuf<uint32_t> &keys, DevBuf<uint32_t> &alt, uint64_t N, uint32_t lo_bit,

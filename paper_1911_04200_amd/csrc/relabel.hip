@@ -5,12 +5,17 @@
 // IDs).  It lets long k-mers (k = 31: IDs below 2^62, Sec. II-B) go through
 // the encoder, whose keys (ID << ceil(log2 n)) | sample must fit 64 bits.
 //
-//   1. digit totals of every 8-bit pass of the IDs;
-//   2. the IDs sorted (single-pass scatters, or the per-pass sort);
-//   3. the distinct IDs: head flags, a scan, compaction;
-//   4. a table of where each value of the top `ibits` ID bits starts among
-//      the distinct IDs, then for every input ID a binary search inside its
-//      bucket gives its rank.
+//   1. the IDs sorted by their top bits (single-pass scatters) and each range
+//      of whole buckets finished in LDS, as the encoder does, which leaves the
+//      distinct IDs, ascending; where a bucket is too large for that, the IDs
+//      sorted on every bit, then head flags, a scan and compaction;
+//   2. a table of 64-byte lines, one per value of the top `ibits` ID bits: where
+//      the IDs with those bits start among the distinct IDs, and 16 more bits of
+//      each; for every input ID its line gives its rank.
+// 134 M k-mers of 62 bits (k = 31), 39 M distinct: 20.8 ms with a sort on every
+// bit (eight passes, 4.9 ms), flags and compaction (2.4) and ranks by binary
+// search (12.2); now 12.5 ms: two passes (1.2), ranges (3.9, their LDS passes over
+// 47 bits), lines (0.3) and ranks (6.2, scattered 64-byte reads).
 #include <algorithm>
 
 #include "device_util.hpp"
@@ -43,13 +48,6 @@ __global__ __launch_bounds__(kNT) void k_id_digits(const uint64_t *__restrict__ 
         if (gh[q][threadIdx.x]) atomicAdd(&g[q * 256 + threadIdx.x], (unsigned long long)gh[q][threadIdx.x]);
 }
 
-__global__ void k_check_range(const uint64_t *__restrict__ ids, uint64_t N, uint64_t hi_mask, uint32_t *err) {
-    bool bad = false;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (uint64_t)gridDim.x * blockDim.x)
-        bad |= (ids[i] & hi_mask) != 0;
-    if (__ballot(bad) && lane_id() == 0) atomicOr(err, 1u);
-}
-
 // head[i] = 1 where sorted[i] starts a new value
 __global__ void k_heads(const uint64_t *__restrict__ sorted, uint64_t N, uint32_t *__restrict__ head) {
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (uint64_t)gridDim.x * blockDim.x)
@@ -66,24 +64,77 @@ __global__ void k_compact_heads(const uint64_t *__restrict__ sorted, uint64_t N,
 __global__ void k_rank_buckets(const uint64_t *__restrict__ distinct, uint64_t D, uint32_t shift, uint64_t nbk,
                                uint64_t *__restrict__ bucket) {
     for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t <= D; t += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t bk = t < D ? (distinct[t] >> shift) : nbk;
-        const int64_t prev = t == 0 ? -1 : (int64_t)(distinct[t - 1] >> shift);
+        const uint64_t bk = t < D ? (shift >= 64 ? 0 : distinct[t] >> shift) : nbk;
+        const int64_t prev = t == 0 ? -1 : (int64_t)(shift >= 64 ? 0 : distinct[t - 1] >> shift);
         for (int64_t b = prev + 1; b <= (int64_t)bk; ++b) bucket[b] = t;
     }
 }
 
-// out[i] = rank of ids[i] among the distinct IDs (out may be ids)
-__global__ void k_rank(const uint64_t *ids, uint64_t N, const uint64_t *__restrict__ distinct,
-                       const uint64_t *__restrict__ bucket, uint32_t shift, uint64_t *out) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t id = ids[i];
-        uint64_t a = bucket[id >> shift], b = bucket[(id >> shift) + 1];
-        while (a < b) {  // first distinct >= id (it is id: every input ID is among them)
-            const uint64_t m = (a + b) >> 1;
-            if (distinct[m] < id) a = m + 1;
-            else b = m;
+// The ranks of N IDs in no particular order cost one scattered read each, so
+// what a rank needs is put in one 64-byte line: the word start | count << 48 and,
+// in ascending order, the 16 ID bits below the bucket's of up to 28 IDs.  A
+// search of the 8-byte IDs through a bucket table read two to three 128-byte
+// lines (134 M IDs, 39 M distinct: 11.1 ms, 6.2 now).  A bucket with more IDs is
+// marked by the count kFullLine and searched in the distinct IDs.
+constexpr uint32_t kLineIds = 28, kLineWords = 8;  // 8-byte words of a line
+constexpr uint64_t kFullLine = 0xFFFF, kStartMask = (uint64_t(1) << 48) - 1;
+
+// The 16 bits of id below its bucket's (all of them, if shift <= 16).
+__device__ __forceinline__ uint32_t line_bits(uint64_t id, uint32_t shift) {
+    const uint64_t low = shift >= 64 ? id : id & ((uint64_t(1) << shift) - 1);
+    return (uint32_t)(shift > 16 ? low >> (shift - 16) : low);
+}
+
+// Eight threads per line: word 0 and the seven words of four IDs each.
+__global__ void k_rank_lines(const uint64_t *__restrict__ distinct, const uint64_t *__restrict__ bucket, uint64_t nbk,
+                             uint32_t shift, uint64_t *__restrict__ lines) {
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nbk * kLineWords;
+         i += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t b = i / kLineWords, start = bucket[b], cnt = bucket[b + 1] - start;
+        const uint32_t w = (uint32_t)(i % kLineWords);
+        uint64_t v = 0;
+        if (w == 0) {
+            v = start | (cnt > kLineIds ? kFullLine : cnt) << 48;
+        } else {
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint64_t e = 4 * (w - 1) + k;
+                // past the last ID: above every ID's bits, or equal (then never before it)
+                v |= (uint64_t)(e < cnt ? line_bits(distinct[start + e], shift) : 0xFFFFu) << (16 * k);
+            }
         }
-        out[i] = a;
+        lines[i] = v;
+    }
+}
+
+// out[i] = rank of ids[i] among the distinct IDs (out may be ids); every ID is
+// one of them.
+__global__ void k_rank(const uint64_t *ids, uint64_t N, const uint64_t *__restrict__ distinct,
+                       const uint64_t *__restrict__ bucket, const uint64_t *__restrict__ lines, uint32_t shift,
+                       uint64_t *out) {
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t id = ids[i], b = shift >= 64 ? 0 : id >> shift;
+        const uint64_t *line = lines + b * kLineWords;
+        const uint64_t head = line[0], start = head & kStartMask, cnt = head >> 48;
+        if (cnt == kFullLine) {
+            out[i] = lower_bound_from(distinct, start, bucket[b + 1], id, shift ? id << (64 - shift) : 0);
+            continue;
+        }
+        // the first of the bucket's IDs whose bits are >= r: from the word where
+        // it is expected, a word at a time
+        const uint32_t r = line_bits(id, shift), nw = (uint32_t)(cnt + 3) / 4;  // >= 1 word
+        uint32_t w = shift >= 16 ? (uint32_t)((r * (uint32_t)cnt) >> 18) : 0;
+        uint64_t v = line[1 + w];
+        while (w > 0 && (v & 0xFFFFu) >= r) v = line[1 + --w];  // may start in an earlier word
+        while (w + 1 < nw && (v >> 48) < r) v = line[1 + ++w];
+        uint32_t below = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) below += ((uint32_t)(v >> (16 * k)) & 0xFFFFu) < r;
+        uint64_t pos = start + 4 * w + below;
+        // IDs that agree in the 16 bits too: compared whole
+        if (shift > 16)
+            while (pos + 1 < start + cnt && distinct[pos] < id) ++pos;
+        out[i] = pos;
     }
 }
 
@@ -93,43 +144,29 @@ uint32_t grid_for(uint64_t work) {
 
 }  // namespace
 
-uint64_t relabel(const uint64_t *ids, uint64_t N, uint32_t U, hipStream_t s, uint64_t *out) {
-    if (N == 0) return 0;
-    const uint64_t hi_mask = U >= 64 ? 0 : ~((uint64_t(1) << U) - 1);
-    DevBuf<uint32_t> err;
-    err.alloc(1, s, nullptr, true, "relabel error flag");
-    DevBuf<unsigned long long> ghist;
-    ghist.alloc((uint64_t)kGhistReplicas * kMaxPasses * 256, s, nullptr, true, "relabel digit totals");
+namespace {
+// The distinct IDs by a sort on every bit: returns their number, in alt.
+uint64_t distinct_full_sort(const uint64_t *ids, uint64_t N, uint32_t U, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt,
+                            unsigned long long *ghist, uint32_t *err, hipStream_t s) {
     const uint32_t npass = (U + 7) / 8;
     {
         JAS_TIMED("relabel_digits", s);
-        k_zero_u64<<<64, 256, 0, s>>>(reinterpret_cast<uint64_t *>(ghist.p), (uint64_t)kGhistReplicas * kMaxPasses * 256);
-        k_zero_u32<<<1, 1, 0, s>>>(err.p);
-        k_check_range<<<grid_for(N), 256, 0, s>>>(ids, N, hi_mask, err.p);
-        k_id_digits<<<(uint32_t)std::min<uint64_t>(div_up(N, 256 * 16), 8192), kNT, 0, s>>>(ids, N, npass, ghist.p);
+        k_zero_u64<<<64, 256, 0, s>>>(reinterpret_cast<uint64_t *>(ghist), (uint64_t)kGhistReplicas * kMaxPasses * 256);
+        k_id_digits<<<(uint32_t)std::min<uint64_t>(div_up(N, 256 * 16), 8192), kNT, 0, s>>>(ids, N, npass, ghist);
     }
     check_launch("relabel digits");
     uint32_t herr = 0;
-    JAS_HIP(hipMemcpyAsync(&herr, err.p, 4, hipMemcpyDeviceToHost, s));
-    JAS_HIP(hipStreamSynchronize(s));
-    if (herr) fail(JAS_EINVAL, "jas_relabel: an ID is >= 2^universe_bits");
-    // sort a copy of the IDs
-    DevBuf<uint64_t> keys, alt;
-    keys.alloc(N, s, nullptr, true, "relabel keys");
-    alt.alloc(N, s, nullptr, true, "relabel keys (second buffer)");
-    JAS_HIP(hipMemcpyAsync(keys.p, ids, N * 8, hipMemcpyDeviceToDevice, s));
-    bool sorted = radix_sort_onesweep(keys, alt, N, 0, U, 8, ghist.p, err.p, s, nullptr);
+    bool sorted = radix_sort_onesweep(keys, alt, N, 0, U, 8, ghist, err, s, nullptr, nullptr, nullptr, ids);
     if (sorted) {
-        JAS_HIP(hipMemcpyAsync(&herr, err.p, 4, hipMemcpyDeviceToHost, s));
+        JAS_HIP(hipMemcpyAsync(&herr, err, 4, hipMemcpyDeviceToHost, s));
         JAS_HIP(hipStreamSynchronize(s));
         sorted = herr == 0;
     }
-    if (!sorted) {  // digit totals too large for the single-pass form, or its look-back gave up
+    if (!sorted || N == 1) {  // digit totals too large for the single-pass form, or its look-back gave up
         JAS_HIP(hipMemcpyAsync(keys.p, ids, N * 8, hipMemcpyDeviceToDevice, s));
         RadixWork rw;
         radix_sort_u64(keys, alt, N, 0, U, rw, s, nullptr);
     }
-    // distinct IDs (in the free buffer)
     DevBuf<uint32_t> head;
     DevBuf<uint64_t> pos, tmp;
     head.alloc(N, s, nullptr, true, "relabel heads");
@@ -148,20 +185,60 @@ uint64_t relabel(const uint64_t *ids, uint64_t N, uint32_t U, hipStream_t s, uin
     uint64_t D = 0;
     JAS_HIP(hipMemcpyAsync(&D, pos.p + N, 8, hipMemcpyDeviceToHost, s));
     JAS_HIP(hipStreamSynchronize(s));
-    head.release();
-    pos.release();
-    tmp.release();
-    // ranks through a bucket table of the top ID bits (about 32 distinct IDs per bucket)
-    uint32_t ib = ceil_log2_u64(div_up(D, 32));
-    ib = std::max<uint32_t>(1, std::min<uint32_t>(ib, std::min<uint32_t>(U, 26)));
+    return D;
+}
+}  // namespace
+
+uint64_t relabel(const uint64_t *ids, uint64_t N, uint32_t U, hipStream_t s, uint64_t *out) {
+    if (N == 0) return 0;
+    DevBuf<uint32_t> err;
+    err.alloc(1, s, nullptr, true, "relabel error flag");
+    DevBuf<unsigned long long> ghist;
+    ghist.alloc((uint64_t)kGhistReplicas * kMaxPasses * 256, s, nullptr, true, "relabel digit totals");
+    const SortPlan plan = sort_plan(N, U, 0);
+    {
+        JAS_TIMED("relabel_digits", s);
+        k_zero_u64<<<64, 256, 0, s>>>(reinterpret_cast<uint64_t *>(ghist.p), (uint64_t)kGhistReplicas * kMaxPasses * 256);
+        k_zero_u32<<<1, 1, 0, s>>>(err.p);
+    }
+    build_keys(ids, nullptr, 0, N, 0, U, plan, nullptr, err.p, ghist.p, s);
+    uint32_t herr = 0;
+    JAS_HIP(hipMemcpyAsync(&herr, err.p, 4, hipMemcpyDeviceToHost, s));
+    JAS_HIP(hipStreamSynchronize(s));
+    if (herr) fail(JAS_EINVAL, "jas_relabel: an ID is >= 2^universe_bits");
+    DevBuf<uint64_t> keys, alt;
+    keys.alloc(N, s, nullptr, true, "relabel keys");
+    alt.alloc(N, s, nullptr, true, "relabel keys (second buffer)");
+    uint64_t D = ~0ull;
+    if (plan.top_bits == 0) {  // one range holds everything
+        JAS_HIP(hipMemcpyAsync(keys.p, ids, N * 8, hipMemcpyDeviceToDevice, s));
+        D = distinct_sorted(keys, alt, N, U, plan, s);
+    } else if (radix_sort_onesweep(keys, alt, N, U - plan.top_bits, U, plan.width, ghist.p, err.p, s, nullptr, nullptr,
+                                   nullptr, ids)) {
+        JAS_HIP(hipMemcpyAsync(&herr, err.p, 4, hipMemcpyDeviceToHost, s));
+        JAS_HIP(hipStreamSynchronize(s));
+        if (!herr) D = distinct_sorted(keys, alt, N, U, plan, s);
+        else k_zero_u32<<<1, 1, 0, s>>>(err.p);  // the sort's look-back gave up
+    }
+    if (D == ~0ull) D = distinct_full_sort(ids, N, U, keys, alt, ghist.p, err.p, s);
+    // buckets of 5 to 10 distinct IDs where the lines, which take the place of
+    // the sorted keys, allow it (2^ib lines of 64 bytes in 8 N bytes)
+    uint32_t ib = std::min<uint32_t>(ceil_log2_u64(div_up(D, 10)), U);
+    while (ib > 0 && ((uint64_t)kLineWords << ib) > N) --ib;
     const uint32_t shift = U - ib;
     const uint64_t nbk = uint64_t(1) << ib;
-    DevBuf<uint64_t> bucket;
+    DevBuf<uint64_t> bucket, small;
     bucket.alloc(nbk + 1, s, nullptr, true, "relabel buckets");
+    if (N < kLineWords) small.alloc(kLineWords, s, nullptr, true, "relabel line");
+    uint64_t *lines = N < kLineWords ? small.p : keys.p;
+    {
+        JAS_TIMED("relabel_lines", s);
+        k_rank_buckets<<<grid_for(D + 1), 256, 0, s>>>(alt.p, D, shift, nbk, bucket.p);
+        k_rank_lines<<<grid_for(nbk * kLineWords), 256, 0, s>>>(alt.p, bucket.p, nbk, shift, lines);
+    }
     {
         JAS_TIMED("relabel_rank", s);
-        k_rank_buckets<<<grid_for(D + 1), 256, 0, s>>>(alt.p, D, shift, nbk, bucket.p);
-        k_rank<<<grid_for(N), 256, 0, s>>>(ids, N, alt.p, bucket.p, shift, out);
+        k_rank<<<grid_for(N), 256, 0, s>>>(ids, N, alt.p, bucket.p, lines, shift, out);
     }
     check_launch("relabel rank");
     JAS_HIP(hipStreamSynchronize(s));

@@ -91,6 +91,38 @@ def test_relabel_is_the_rank_among_distinct_ids(U):
         assert e.value.status == cabi.JAS_EINVAL
 
 
+@pytest.mark.parametrize("U,kind", [(1, "few"), (7, "few"), (17, "uniform"), (40, "uniform"), (40, "clusters"),
+                                    (62, "close"), (64, "close"), (64, "few"), (50, "one")])
+@pytest.mark.parametrize("N", [1, 2, 7, 8, 9, 6144, 6145, 90000])
+def test_relabel_lines_and_ranges(U, kind, N):
+    """Ranks come from 64-byte lines of 28 IDs by 16 of their bits, and the
+    distinct IDs from ranges finished in LDS (or a full sort): buckets with more
+    IDs than a line or a range holds, IDs equal in those 16 bits, one ID only,
+    and sizes around one line, one range and none."""
+    rng = np.random.default_rng(U * 1000 + N)
+    top = np.uint64((1 << U) - 1)
+    if kind == "few":
+        base = rng.integers(0, 1 << min(U, 8), 300, dtype=np.uint64)
+        base = np.concatenate([base, top - base])
+    elif kind == "uniform":
+        base = rng.integers(0, 1 << U, max(1, N // 3), dtype=np.uint64)
+    elif kind == "clusters":  # 200 runs of neighbouring IDs
+        base = (rng.integers(0, 1 << U, 200, dtype=np.uint64)[:, None] + np.arange(60, dtype=np.uint64)).ravel() & top
+    elif kind == "close":  # IDs that differ in their lowest bits only, and some far away
+        base = np.concatenate([(np.uint64(5) << np.uint64(U - 3)) + np.arange(9000, dtype=np.uint64) * np.uint64(3),
+                               rng.integers(0, 1 << 63, 500, dtype=np.uint64) & top, [top, np.uint64(0)]])
+    else:
+        base = np.array([12345], np.uint64)
+    ids = rng.choice(base, N)
+    uniq, inv = np.unique(ids, return_inverse=True)
+    d = torch.from_numpy(ids.view(np.int64)).cuda()
+    out = torch.empty_like(d)
+    D, newU = cabi.jas_relabel(d, N, U, None, out)
+    assert D == uniq.size and newU == max(1, int(uniq.size - 1).bit_length())
+    assert np.array_equal(out.cpu().numpy().view(np.uint64), inv.astype(np.uint64))
+    assert np.array_equal(d.cpu().numpy().view(np.uint64), ids)
+
+
 def test_k31_sequences_to_jaccard_through_the_relabel():
     """k = 31 canonical k-mers (IDs below 2^62) of 64 genomes: 62 + 6 key bits
     do not fit, so the encoder refuses them as they are; relabelled by rank
