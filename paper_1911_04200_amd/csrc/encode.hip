@@ -1106,6 +1106,10 @@ __global__ void k_list_wave_pairs(const uint64_t *Lrow, const uint32_t *row_deg,
 // the pair loops read LDS rather than memory.  Per-block LDS totals of the
 // sort digits (digit q = bits [16 + width*q, 16 + width*(q+1)) of the word)
 // come from one pass over each row's entries.
+// With few rows (gridDim.y > 1) that many waves take the same 64 rows and deal
+// the output words among them, 64 at a time: 1231 rows of degree 60 to 67 (2.6 M
+// pairs) fill 20 waves, 1.79 ms, and 0.075 ms shared; 4610 rows (778 K pairs)
+// 0.15 and 0.026 ms.
 // Stage sizes measured best of 256..3072 for one-lane-per-row emission.
 constexpr uint32_t kEmitStage = 1024;  // output words per wave
 constexpr uint32_t kEmitIn = 512;      // sample entries per wave
@@ -1145,16 +1149,16 @@ __device__ __forceinline__ void stage_row_pairs(Src src, uint64_t sb, uint32_t d
     }
 }
 
-// The wave's pairs from its rows' entries src[sb + i] (LDS or global), one
-// output word per lane at a time.  rst[0..64] are the rows' first words
-// (rst[64] = total); a lane's words ascend, so its row only moves forward.
+// The wave's pairs from its rows' entries src[sb + i] (LDS or global): output
+// words first, first + step, ... of this lane.  rst[0..64] are the rows' first
+// words (rst[64] = total); a lane's words ascend, so its row only moves forward.
 template <class Src>
-__device__ __forceinline__ void emit_wave_pairs(Src src, uint32_t total, uint32_t lane, const uint32_t *rst,
-                                                const uint32_t *rdg, const uint64_t *rsb,
+__device__ __forceinline__ void emit_wave_pairs(Src src, uint32_t total, uint32_t first, uint32_t step,
+                                                const uint32_t *rst, const uint32_t *rdg, const uint64_t *rsb,
                                                 uint32_t *__restrict__ out) {
     uint32_t t = 0, d = rdg[0], k0 = 0;
     uint64_t s0 = rsb[0];
-    for (uint32_t o = lane; o < total; o += kWave) {
+    for (uint32_t o = first; o < total; o += step) {
         // row t: the largest with rst[t] <= o (a row without pairs shares its
         // successor's start, so it is never the largest)
         if (rst[t + 1] <= o) {
@@ -1253,18 +1257,22 @@ __global__ __launch_bounds__(256) void k_pair_emit(const uint64_t *__restrict__ 
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        if (staged_in) row_digit_totals(sin, sb, deg, gh, npass, width, dmask);
-        else row_digit_totals(ls, sb, deg, gh, npass, width, dmask);
-        if (fits) {
+        if (blockIdx.y == 0) {
+            if (staged_in) row_digit_totals(sin, sb, deg, gh, npass, width, dmask);
+            else row_digit_totals(ls, sb, deg, gh, npass, width, dmask);
+        }
+        if (fits && blockIdx.y > 0) {
+            // the first of the waves that share these rows writes them
+        } else if (fits) {
             if (staged_in) stage_row_pairs(sin, sb, deg, incl - np, stg);
             else stage_row_pairs(ls, sb, deg, incl - np, stg);
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
             for (uint32_t k = lane; k < total; k += kWave) pairs[base + k] = stg[k];
         } else if (staged_in) {
-            emit_wave_pairs(sin, total, lane, rst, rdg, rsb, pairs + base);
+            emit_wave_pairs(sin, total, blockIdx.y * kWave + lane, gridDim.y * kWave, rst, rdg, rsb, pairs + base);
         } else {
-            emit_wave_pairs(ls, total, lane, rst, rdg, rsb, pairs + base);
+            emit_wave_pairs(ls, total, blockIdx.y * kWave + lane, gridDim.y * kWave, rst, rdg, rsb, pairs + base);
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1372,6 +1380,14 @@ __global__ void k_plan_card(const int64_t *card, int32_t n, int64_t limit, uint3
     bool over = false;
     for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) over |= card[i] >= limit;
     if (__ballot(over) && lane_id() == 0) atomicOr(err, 64u);
+}
+
+// Grid of k_pair_emit over QL list rows: a wave per 64 rows, and as many waves
+// sharing the same rows as bring the chip to about 8192 waves.
+dim3 pair_emit_grid(uint64_t QL) {
+    const uint64_t waves = div_up(QL, (uint64_t)kWave);
+    return dim3((uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(div_up(QL, 256), 8192)),
+                (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(8192 / std::max<uint64_t>(waves, 1), 64)));
 }
 
 template <class F>
@@ -1808,7 +1824,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         }
         {
             JAS_TIMED("pair_emit", s2);
-            k_pair_emit<<<(uint32_t)std::min<uint64_t>(div_up(QL, 256), 8192), 256, 0, s2>>>(
+            k_pair_emit<<<pair_emit_grid(QL), 256, 0, s2>>>(
                 Lrow.p, rptrp, rdegp, Sp, QL, npo.p, pk.p, npass, pwidth, pgh.p, nullptr);
         }
         check_launch("pair emit");
@@ -2146,7 +2162,7 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
         fill(p.gh.p, (uint64_t)kGhistReplicas * kMaxPasses * 256);
         {
             JAS_TIMED("pair_emit", s);
-            k_pair_emit<<<(uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(div_up(QLc, 256), 8192)), 256, 0, s>>>(
+            k_pair_emit<<<pair_emit_grid(QLc), 256, 0, s>>>(
                 p.Lrow.p, p.rptr.p, p.rdeg.p, reinterpret_cast<const uint32_t *>(F), QLc, p.npo.p, p.pk.p,
                 p.pair_npass, p.pair_width, p.gh.p, dsz);
         }

@@ -497,6 +497,23 @@ def test_row_lists_by_sample_and_by_row(n, dmin):
     assert_matches(res, ref, upper=True)
 
 
+@pytest.mark.parametrize("rows,most", [(1, 200), (5, 60), (64, 40), (65, 200), (130, 120)])
+def test_few_long_list_rows(rows, most):
+    """Few list rows of many samples: several waves deal out the pairs of the same
+    64 rows, and the pairs of one sample cross many short counting chunks."""
+    rng = np.random.default_rng(rows)
+    n = 200
+    ids = np.sort(rng.choice(1 << 20, rows, replace=False).astype(np.uint64))
+    deg = np.concatenate([[most], rng.integers(0, most + 1, rows - 1)]).astype(int)
+    holders = [set(rng.choice(n, d, replace=False).tolist()) for d in deg]
+    sets = [np.array([x for x, h in zip(ids, holders) if s in h], dtype=np.uint64) for s in range(n)]
+    cids, off = csr(sets)
+    ref = oracle.all_pairs(cids, off)
+    res, st = gpu_all_pairs(cids, off, 20, 0, 1000)
+    assert st["n_packed_rows"] == 0 and st["n_list_rows"] > 0
+    assert_matches(res, ref)
+
+
 @pytest.mark.parametrize("n", [1, 2, 127, 128, 129, 255, 257])
 @pytest.mark.parametrize("path", ["popcount", "mfma"])
 def test_tile_edges(n, path):
