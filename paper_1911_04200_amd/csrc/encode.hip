@@ -55,7 +55,7 @@ constexpr uint32_t kStatReplicas = 64;
 static_assert(kStatReplicas == kStatReplicasPub, "counter replicas");
 
 // ---------------------------------------------------------------------------
-// Keys of one chunk (kChunk entries) per block, and the totals of every digit
+// Keys of one chunk of entries per block, and the totals of every digit
 // of every global sort pass (ghist, kGhistReplicas copies summed later, a row
 // of 256 digits per pass, or 512 for 9-bit passes), which the single-pass
 // scatter needs.  Pass q's digit is ID bits [idlo + width*q, idlo + width*(q+1)).  k_count_digits only counts (and
@@ -66,16 +66,16 @@ __device__ __forceinline__ void build_keys_chunk(const uint64_t *__restrict__ id
                                                  uint64_t *__restrict__ keys, uint32_t *err, uint32_t npass,
                                                  uint32_t idlo, uint32_t width,
                                                  unsigned long long *__restrict__ ghist,
-                                                 const uint64_t *__restrict__ dsz) {
+                                                 const uint64_t *__restrict__ dsz, uint32_t chunk) {
     __shared__ int32_t s_lo, s_hi;
     __shared__ uint32_t gh[kMaxPasses * 256];
     const uint32_t tid = threadIdx.x;
     const uint32_t radix = onesweep::radix_of(width);  // npass * radix <= kMaxPasses * 256
     if (plan_aborted(dsz)) return;
     if (dsz) N = dsz[PZ_N];
-    const uint64_t b0 = (uint64_t)blockIdx.x * kChunk;
+    const uint64_t b0 = (uint64_t)blockIdx.x * chunk;
     if (b0 >= N) return;  // a planned launch covers the largest N
-    const uint64_t b1 = min(N, b0 + kChunk);
+    const uint64_t b1 = min(N, b0 + chunk);
     const uint32_t dmask = (1u << width) - 1u;
     for (uint32_t i = tid; i < npass * radix; i += kNT) gh[i] = 0;
     if (kWrite && tid == 0) {
@@ -130,15 +130,24 @@ __global__ __launch_bounds__(kNT) void k_build_keys(const uint64_t *__restrict__
                                                      uint32_t sbits, uint64_t hi_mask, uint64_t *__restrict__ keys,
                                                      uint32_t *err, uint32_t npass, uint32_t idlo, uint32_t width,
                                                      unsigned long long *__restrict__ ghist,
-                                                     const uint64_t *__restrict__ dsz) {
-    build_keys_chunk<true>(ids, off, n, N, sbits, hi_mask, keys, err, npass, idlo, width, ghist, dsz);
+                                                     const uint64_t *__restrict__ dsz, uint32_t chunk) {
+    build_keys_chunk<true>(ids, off, n, N, sbits, hi_mask, keys, err, npass, idlo, width, ghist, dsz, chunk);
 }
 
 __global__ __launch_bounds__(kNT) void k_count_digits(const uint64_t *__restrict__ ids, uint64_t N, uint64_t hi_mask,
                                                        uint32_t *err, uint32_t npass, uint32_t idlo, uint32_t width,
                                                        unsigned long long *__restrict__ ghist,
-                                                       const uint64_t *__restrict__ dsz) {
-    build_keys_chunk<false>(ids, nullptr, 0, N, 0, hi_mask, nullptr, err, npass, idlo, width, ghist, dsz);
+                                                       const uint64_t *__restrict__ dsz, uint32_t chunk) {
+    build_keys_chunk<false>(ids, nullptr, 0, N, 0, hi_mask, nullptr, err, npass, idlo, width, ghist, dsz, chunk);
+}
+
+// Entries per block of the two kernels above: 2048 blocks are resident at once,
+// and a block's threads take their entries one after another (about 0.55 us
+// each), so fewer than 128 M entries are dealt out in shorter chunks.
+// 638 K entries: 0.146 ms as 10 chunks of 65536, 0.012 ms as 312.  Longer chunks
+// add fewer totals to memory.
+uint32_t key_chunk(uint64_t N) {
+    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(div_up(div_up(N, 2048), kNT) * kNT, 8 * kNT), kChunk);
 }
 
 __global__ void k_fill_u64(uint64_t *p, uint64_t len, uint64_t v) {
@@ -1410,16 +1419,17 @@ void build_keys(const uint64_t *ids, const uint64_t *offsets, int32_t n, uint64_
                 const SortPlan &plan, uint64_t *keys, uint32_t *err, unsigned long long *ghist, hipStream_t s) {
     if (N == 0) return;
     const uint64_t hi_mask = U >= 64 ? 0 : ~((uint64_t(1) << U) - 1);
-    const uint64_t blocks = div_up(N, kChunk);
+    const uint32_t chunk = key_chunk(N);
+    const uint64_t blocks = div_up(N, (uint64_t)chunk);
     if (blocks > 0xFFFFFFFFull) fail(JAS_EUNSUPPORTED, "too many IDs");
     if (keys) {
         JAS_TIMED("build_keys", s);
         k_build_keys<<<(uint32_t)blocks, kNT, 0, s>>>(ids, offsets, n, N, sbits, hi_mask, keys, err, plan.npass,
-                                                      U - plan.top_bits, plan.width, ghist, nullptr);
+                                                      U - plan.top_bits, plan.width, ghist, nullptr, chunk);
     } else {
         JAS_TIMED("count_digits", s);
         k_count_digits<<<(uint32_t)blocks, kNT, 0, s>>>(ids, N, hi_mask, err, plan.npass, U - plan.top_bits,
-                                                        plan.width, ghist, nullptr);
+                                                        plan.width, ghist, nullptr, chunk);
     }
     check_launch("build keys");
 }
@@ -2022,16 +2032,17 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
     check_launch("plan begin");
     // keys and the global sort on the top ID bits
     const uint64_t hi_mask = U >= 64 ? 0 : ~((uint64_t(1) << U) - 1);
+    const uint32_t chunk = key_chunk(Ncap), key_blocks = (uint32_t)div_up(Ncap, (uint64_t)chunk);
     if (p.sort.top_bits > 0) {  // the sort's first pass forms the keys
         JAS_TIMED("count_digits", s);
-        k_count_digits<<<(uint32_t)div_up(Ncap, kChunk), kNT, 0, s>>>(ids, Ncap, hi_mask, err, p.sort.npass,
+        k_count_digits<<<key_blocks, kNT, 0, s>>>(ids, Ncap, hi_mask, err, p.sort.npass,
                                                                        U - p.sort.top_bits, p.sort.width, p.ghist.p,
-                                                                       dsz);
+                                                                       dsz, chunk);
     } else {
         JAS_TIMED("build_keys", s);
-        k_build_keys<<<(uint32_t)div_up(Ncap, kChunk), kNT, 0, s>>>(ids, offsets, n, Ncap, sbits, hi_mask, p.keys.p,
+        k_build_keys<<<key_blocks, kNT, 0, s>>>(ids, offsets, n, Ncap, sbits, hi_mask, p.keys.p,
                                                                      err, p.sort.npass, U - p.sort.top_bits,
-                                                                     p.sort.width, p.ghist.p, dsz);
+                                                                     p.sort.width, p.ghist.p, dsz, chunk);
     }
     check_launch("build keys (planned)");
     uint64_t *K = p.keys.p, *F = p.alt.p;
