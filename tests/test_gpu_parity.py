@@ -514,6 +514,17 @@ def test_few_long_list_rows(rows, most):
     assert_matches(res, ref)
 
 
+@pytest.mark.parametrize("n", [3, 63, 64, 65, 128, 191, 449])
+def test_full_outputs_mirror_across_tiles(n):
+    """The full layout's lower triangle, union sizes and similarities come from the
+    upper triangle tile by tile: every entry, at the edges of a tile."""
+    rng = np.random.default_rng(n)
+    sets = [np.unique(rng.integers(0, 300, int(rng.integers(0, 80)))).astype(np.uint64) for _ in range(n)]
+    ids, off = csr(sets)
+    res, _ = gpu_all_pairs(ids, off, 9)
+    assert_matches(res, oracle.all_pairs(ids, off))
+
+
 @pytest.mark.parametrize("n", [1, 2, 127, 128, 129, 255, 257])
 @pytest.mark.parametrize("path", ["popcount", "mfma"])
 def test_tile_edges(n, path):
