@@ -1589,10 +1589,8 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
             offD.alloc(nlc + 1, s, tb, true, "range offsets");
             offS.alloc(nlc + 1, s, tb, true, "range offsets");
             offR.alloc(nlc + 1, s, tb, true, "range offsets");
-            stmp.alloc(scan_tmp_elems(nlc), s, tb, true, "scan scratch");
-            scan_excl_u32(cnt.p, offD.p, nlc, stmp.p, s);
-            scan_excl_u32(cnt.p + nlc, offS.p, nlc, stmp.p, s);
-            scan_excl_u32(cnt.p + 2 * nlc, offR.p, nlc, stmp.p, s);
+            stmp.alloc(scan_tmp_elems(nlc, kScanRows), s, tb, true, "scan scratch");
+            scan_excl_u32_rows(cnt.p, nlc, {offD.p, offS.p, offR.p}, nlc, stmp.p, s);
             uint64_t t3[3];
             JAS_HIP(hipMemcpyAsync(&t3[0], offD.p + nlc, 8, hipMemcpyDeviceToHost, s));
             JAS_HIP(hipMemcpyAsync(&t3[1], offS.p + nlc, 8, hipMemcpyDeviceToHost, s));
@@ -1654,10 +1652,8 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         offD.alloc(nch + 1, s, tb, true, "classify offsets");
         offS.alloc(nch + 1, s, tb, true, "classify offsets");
         offR.alloc(nch + 1, s, tb, true, "classify offsets");
-        stmp.alloc(scan_tmp_elems(nch), s, tb, true, "scan scratch");
-        scan_excl_u32(cnt.p, offD.p, nch, stmp.p, s);
-        scan_excl_u32(cnt.p + nch, offS.p, nch, stmp.p, s);
-        scan_excl_u32(cnt.p + 2 * nch, offR.p, nch, stmp.p, s);
+        stmp.alloc(scan_tmp_elems(nch, kScanRows), s, tb, true, "scan scratch");
+        scan_excl_u32_rows(cnt.p, nch, {offD.p, offS.p, offR.p}, nch, stmp.p, s);
         uint64_t t3[3];
         JAS_HIP(hipMemcpyAsync(&t3[0], offD.p + nch, 8, hipMemcpyDeviceToHost, s));
         JAS_HIP(hipMemcpyAsync(&t3[1], offS.p + nch, 8, hipMemcpyDeviceToHost, s));
@@ -2085,9 +2081,7 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
         k_sum_replicas<<<1, 64, 0, s>>>(rowsrep, kStatReplicas, p.st.p + ST_ROWS);
     }
     check_launch("local classify (planned)");
-    scan_excl_u32(p.cnt.p, p.offD.p, nlc, p.stmp.p, s);
-    scan_excl_u32(p.cnt.p + nlc, p.offS.p, nlc, p.stmp.p, s);
-    scan_excl_u32(p.cnt.p + 2 * nlc, p.offR.p, nlc, p.stmp.p, s);
+    scan_excl_u32_rows(p.cnt.p, nlc, {p.offD.p, p.offS.p, p.offR.p}, nlc, p.stmp.p, s);
     {
         JAS_TIMED("plan_sizes", s);
         k_plan_rows<<<1, 1, 0, s>>>(p.offR.p, p.offS.p, nlc, p.Rcap, p.rptr.p, dsz, err);

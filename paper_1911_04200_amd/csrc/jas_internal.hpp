@@ -268,8 +268,12 @@ namespace jas {
 
 // out[i] = sum_{k<i} in[k] for i in [0, len]; out has len + 1 entries (out[len] = total).
 // tmp: scratch from scan_tmp_elems(len).
-size_t scan_tmp_elems(size_t len);
+size_t scan_tmp_elems(size_t len, uint32_t rows = 1);
 void scan_excl_u32(const uint32_t *in, uint64_t *out, size_t len, uint64_t *tmp, hipStream_t s);
+// The same of kScanRows arrays at once: in + y * stride to out[y] (tmp for that many rows).
+constexpr uint32_t kScanRows = 3;
+void scan_excl_u32_rows(const uint32_t *in, uint64_t stride, uint64_t *const (&out)[kScanRows], size_t len,
+                        uint64_t *tmp, hipStream_t s);
 void scan_excl_u64(const uint64_t *in, uint64_t *out, size_t len, uint64_t *tmp, hipStream_t s);
 
 // LSD radix sort of 64-bit keys on bits [lo_bit, hi_bit), stable.  Result in

@@ -175,7 +175,7 @@ jas_status jas_plan_create(const uint64_t *ids, const uint64_t *offsets, int32_t
         plan_buf(p.offS, p.nlc_cap + 1, s, &bud, "plan range offsets");
         plan_buf(p.offR, p.nlc_cap + 1, s, &bud, "plan range offsets");
         const uint64_t scan_len = std::max({p.nlc_cap, p.tile_cap, p.QDcap, p.gcap, (uint64_t)1});
-        plan_buf(p.stmp, scan_tmp_elems(scan_len), s, &bud, "plan scan scratch");
+        plan_buf(p.stmp, std::max(scan_tmp_elems(scan_len), scan_tmp_elems(p.nlc_cap, kScanRows)), s, &bud, "plan scan scratch");
         plan_buf(p.rid, p.Rcap + 1, s, &bud, "plan row ids");
         plan_buf(p.rptr, p.Rcap + 1, s, &bud, "plan row pointers");
         plan_buf(p.rdeg, p.Rcap + 1, s, &bud, "plan row degrees");
