@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kOsNT) __attribute__((amdgpu_waves_per_eu(4))) void
             if (tid == mask) tc -= kTileKeys - cnt_tile;  // the entries past the last tile's end
             // publish the tile's count of digit tid at once, and clear its word for the next pass
             status_store(status + onesweep::status_index(tile, tid, kDigits), (tile == 0 ? kFlagP : kFlagA) | tc);
-            next_status[onesweep::status_index(tile, tid, kDigits)] = 0;
+            if (next_status) next_status[onesweep::status_index(tile, tid, kDigits)] = 0;
         }
         const uint32_t ex = block_excl_scan_u32<kOsNT>(tc, sh);  // digit tid's first position in the tile
         if (digit) {  // the counts become where wave k's keys of digit tid start in the tile
@@ -564,11 +564,13 @@ uint64_t most_tiles(uint64_t N) { return onesweep::num_tiles(N, (uint32_t)kOsNT 
 
 // The look-back words of a sort: a ticket per pass, then the status words of
 // two passes (a pass clears the other's while it runs, so only the first
-// pass's and the tickets are cleared beforehand).
+// pass's and the tickets are cleared beforehand), or of one (cleared again
+// before each pass: a launch more, 5 us, but half the bytes, so a caller's
+// memory budget decides for it).
 constexpr uint64_t kTicketWords = 64;
 static_assert(kTicketWords >= kMaxPasses, "tickets");
-uint64_t look_back_words(uint64_t ntiles, uint32_t radix) {
-    return kTicketWords + 2 * onesweep::status_words(ntiles, radix);
+uint64_t look_back_words(uint64_t ntiles, uint32_t radix, bool two = true) {
+    return kTicketWords + (two ? 2 : 1) * onesweep::status_words(ntiles, radix);
 }
 
 // What every pass of one sort is launched with.
@@ -578,6 +580,7 @@ struct PassArgs {
     const uint64_t *dN = nullptr, *gstart = nullptr;
     const KeySource *src = nullptr;  // null: the keys are in memory
     const void *first = nullptr;     // where the first pass reads them, if not in the sort's buffer
+    bool two = true;                 // look_back holds the status words of two passes
     hipStream_t s = nullptr;
 };
 
@@ -590,7 +593,8 @@ void onesweep_launch(const PassArgs &a, uint32_t q, const K *in, K *out, uint32_
     // persistent blocks: two per CU (256 CUs) fit, never more than there are tiles
     const uint32_t grid = std::min<uint32_t>(ntiles, 256 * 2);
     uint32_t *st0 = a.look_back + kTicketWords, *st1 = st0 + onesweep::status_words(most_tiles(a.N), a.radix);
-    uint32_t *st = q & 1 ? st1 : st0, *next = q & 1 ? st0 : st1, *ticket = a.look_back + q;
+    uint32_t *st = a.two && (q & 1) ? st1 : st0, *next = a.two ? (q & 1 ? st0 : st1) : nullptr;
+    uint32_t *ticket = a.look_back + q;
     const uint64_t *gs = a.gstart + (uint64_t)q * a.radix;
     if constexpr (sizeof(K) == 8 && Rounds != 32) {
         if (a.src && q == 0) {
@@ -617,14 +621,16 @@ template <class K, class Swap>
 void onesweep_passes(const PassArgs &a, uint32_t lo_bit, uint32_t hi_bit, uint32_t width, const char *name, K *keys,
                      K *alt, Swap swap) {
     if (a.src && (sizeof(K) != 8 || lo_bit < a.src->sbits)) fail(JAS_EDEVICE, "sort from IDs: bad digits or keys");
-    {
+    const auto clear = [&](uint32_t *p, uint64_t len) {
         JAS_TIMED("fill_status", a.s);
-        const uint64_t len = kTicketWords + onesweep::status_words(most_tiles(a.N), a.radix);
-        k_fill32<<<(uint32_t)std::min<uint64_t>(div_up(len, 256), 65536), 256, 0, a.s>>>(a.look_back, len);
-    }
-    check_launch("look-back reset");
+        k_fill32<<<(uint32_t)std::min<uint64_t>(div_up(len, 256), 65536), 256, 0, a.s>>>(p, len);
+        check_launch("look-back reset");
+    };
+    const uint64_t status = onesweep::status_words(most_tiles(a.N), a.radix);
+    clear(a.look_back, kTicketWords + status);
     for (uint32_t q = 0; lo_bit + width * q < hi_bit; ++q) {
         const uint32_t bit = lo_bit + width * q, nbits = std::min(width, hi_bit - bit);
+        if (!a.two && q > 0) clear(a.look_back + kTicketWords, status);
         {
             JAS_TIMED(name, a.s);
             const int rounds = tile_rounds(a.N, a.src && q == 0);
@@ -668,17 +674,19 @@ bool onesweep_sort(DevBuf<K> &keys, DevBuf<K> &alt, uint64_t N, uint32_t lo_bit,
     }
     // What the kernel's indexing relies on (see onesweep_index.hpp): the key
     // buffers hold N keys, tiles are numbered in 32 bits and cover exactly
-    // [0, N), the status array has a word for every (tile, digit) of two passes,
+    // [0, N), the status array has a word for every (tile, digit) of two passes
+    // (or of the one it is cleared for),
     // every pass has a row of digit starts, and no 30-bit status count can wrap
     // (checked above).
     const uint64_t ntiles = most_tiles(N);
     if (ntiles > 0xFFFFFFFFull) return false;
     DevBuf<uint32_t> look_back;
-    temp_buf(look_back, look_back_words(ntiles, radix), s, b, ar, "look-back status");
-    if (keys.n < N || alt.n < N || look_back.n < look_back_words(ntiles, radix) ||
+    PassArgs a;
+    a.two = npass > 1 && !(b && b->limit);
+    temp_buf(look_back, look_back_words(ntiles, radix, a.two), s, b, ar, "look-back status");
+    if (keys.n < N || alt.n < N || look_back.n < look_back_words(ntiles, radix, a.two) ||
         gstart.n < (uint64_t)npass * radix)
         fail(JAS_EDEVICE, "single-pass scatter: buffer sizes do not cover its indexing");
-    PassArgs a;
     a.N = N;
     a.look_back = look_back.p;
     a.err = err;
