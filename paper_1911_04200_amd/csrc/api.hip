@@ -36,12 +36,6 @@ jas_status guard(F &&f) {
     }
 }
 
-__global__ void k_zero_u32(uint32_t *p) { *p = 0; }
-__global__ void k_zero_u64(unsigned long long *p, uint64_t len) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < len; i += (uint64_t)gridDim.x * blockDim.x)
-        p[i] = 0;
-}
-
 // Offsets to the host and validated: offsets[0] = 0, non-decreasing.
 std::vector<uint64_t> host_offsets(const uint64_t *offsets, int32_t n, bool host, hipStream_t s, const char *what) {
     std::vector<uint64_t> h((size_t)n + 1);
@@ -245,29 +239,19 @@ jas_status jas_encode(const uint64_t *ids, const uint64_t *offsets, int32_t n, c
         // range in LDS by encode_sorted).  Both buffers get two spare entries:
         // after the sort the free one holds the shared pairs and row pointers.
         DevBuf<uint64_t> keys, alt;
+        DevBuf<uint32_t> err;  // flags of the ID check and of the sort, checked by encode_sorted
         const SortPlan plan = sort_plan(N, U, sbits);
         if (N > 0) {
-            DevBuf<uint32_t> err;
             keys.alloc(N + 2, s, &tb, true, "sort keys");
             alt.alloc(N + 2, s, &tb, true, "sort keys (second buffer)");
-            err.alloc(1, s, &tb, true, "error flag");
-            {
-                JAS_TIMED("zero_u32", s);
-                k_zero_u32<<<1, 1, 0, s>>>(err.p);
-            }
+            err.alloc(2, s, &tb, true, "error flag");
             DevBuf<unsigned long long> ghist;
             ghist.alloc((uint64_t)kGhistReplicas * kMaxPasses * 256, s, &tb, true, "digit totals");
-            {
-                JAS_TIMED("zero_u32", s);
-                k_zero_u64<<<64, 256, 0, s>>>(ghist.p, (uint64_t)kGhistReplicas * kMaxPasses * 256);
-            }
+            clear_words(Clear().add(err.p, 1).add(ghist.p, (uint64_t)kGhistReplicas * kMaxPasses * 256), s);
             // with a global sort its first pass forms the keys from the IDs
             const bool from_ids = plan.top_bits > 0 && N > 1;
             build_keys(dids, doff, n, N, sbits, U, plan, from_ids ? nullptr : keys.p, err.p, ghist.p, s);
-            uint32_t herr = 0;
-            JAS_HIP(hipMemcpyAsync(&herr, err.p, 4, hipMemcpyDeviceToHost, s));
-            JAS_HIP(hipStreamSynchronize(s));
-            if (herr) fail(JAS_EINVAL, "jas_encode: an ID is >= 2^universe_bits");
+            // (an ID >= 2^U is sorted by the digits it was counted by, so the check can wait)
             JAS_HOST_TIMED("sort_enqueue");
             const uint32_t lo = sbits + U - plan.top_bits, hi = sbits + U;
             KeySource src;
@@ -284,12 +268,9 @@ jas_status jas_encode(const uint64_t *ids, const uint64_t *offsets, int32_t n, c
                 radix_sort_u64(keys, alt, N, lo, hi, rw, s, &tb);
             }
             ids_d.release();
-            JAS_HIP(hipMemcpyAsync(&herr, err.p, 4, hipMemcpyDeviceToHost, s));
-            JAS_HIP(hipStreamSynchronize(s));
-            if (herr) fail(JAS_EDEVICE, "jas_encode: the radix sort's look-back waited too long (result discarded)");
         }
         try {
-            encode_sorted(db.get(), keys, alt, N, plan, doff, s, &tb);
+            encode_sorted(db.get(), keys, alt, N, plan, doff, err.p, s, &tb);
         } catch (...) {
             // the db's buffers return to the cache as idle: let their kernels finish first
             (void)hipStreamSynchronize(s);

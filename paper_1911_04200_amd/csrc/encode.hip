@@ -44,16 +44,6 @@ constexpr uint32_t kPackCols = 8192;       // LDS words per pack pass, at most
 constexpr uint32_t kPackLoads = 8;         // sample loads in flight per lane in k_pack
 constexpr uint32_t kPackFlat = 4096;       // k_pack: word rows with at most this many entries spread them over the block
 
-enum { ST_PAIRS = 0, ST_ROWS, ST_NNZW, ST_F, ST_LISTPAIRS, ST_N };
-static_assert(ST_N == ST_N_ && ST_ROWS == ST_ROWS_ && ST_NNZW == ST_NNZW_ && ST_F == ST_F_ &&
-                  ST_LISTPAIRS == ST_LISTPAIRS_,
-              "encode counters");
-// Counters that many blocks add to are spread over kStatReplicas slots (one
-// counter would serialise an atomic from every block) and summed into st by
-// k_sum_replicas.
-constexpr uint32_t kStatReplicas = 64;
-static_assert(kStatReplicas == kStatReplicasPub, "counter replicas");
-
 // ---------------------------------------------------------------------------
 // Keys of one chunk of entries per block, and the totals of every digit
 // of every global sort pass (ghist, kGhistReplicas copies summed later, a row
@@ -724,11 +714,17 @@ __global__ void k_row_deg(const uint64_t *row_ptr, uint64_t R, uint32_t *row_deg
         row_deg[r] = (uint32_t)(row_ptr[r + 1] - row_ptr[r]);
 }
 
-// |X_i| = entries of sample i minus its repeated (ID, sample) entries.
-__global__ void k_card_from_dups(const uint64_t *off, const unsigned long long *dupc, int32_t n,
-                                 unsigned long long *card) {
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        card[i] = (off[i + 1] - off[i]) - dupc[i];
+// |X_i| = entries of sample i minus its repeated (ID, sample) entries; err |= 64
+// when one reaches the limit (int32 B needs every |X_i| < 2^31).
+__global__ void k_card_from_dups(const uint64_t *off, const unsigned long long *dupc, int32_t n, int64_t *card,
+                                 int64_t limit, uint32_t *err) {
+    bool over = false;
+    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+        const int64_t c = (int64_t)((off[i + 1] - off[i]) - dupc[i]);
+        card[i] = c;
+        over |= c >= limit;
+    }
+    if (__ballot(over) && lane_id() == 0) atomicOr(err, 64u);
 }
 
 // Row degree histogram (degrees are <= n): input of the degree threshold choice.
@@ -809,14 +805,6 @@ __global__ __launch_bounds__(kNT) void k_row_count(const uint32_t *__restrict__ 
         }
         tcnt[blockIdx.x] = (uint32_t)tot_d;
         if (tot_p) atomicAdd(&lp_rep[blockIdx.x % kStatReplicas], (unsigned long long)tot_p);
-    }
-}
-
-__global__ void k_sum_replicas(const unsigned long long *rep, uint32_t nrep, unsigned long long *dst) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        unsigned long long t = 0;
-        for (uint32_t k = 0; k < nrep; ++k) t += rep[k];
-        *dst += t;
     }
 }
 
@@ -922,10 +910,11 @@ __global__ void k_word_rows(uint64_t QD, const uint64_t *bpos, const uint64_t *b
 // sum over its two halves).  Wave 0 loads the rows' list starts and degrees
 // (lane t: the row of bit t) and scans them, then all threads walk the rows'
 // (row, sample) pairs in parallel (consecutive threads read consecutive
-// samples of a row).  Hw = word rows of b bits.
+// samples of a row).  Hw = word rows of b bits.  With a single batch (null wq0)
+// word row w simply holds packed rows [w * b, (w + 1) * b) of the QD there are.
 __global__ __launch_bounds__(kNT) void k_pack(uint64_t *__restrict__ W, uint64_t ldw, uint64_t H, uint64_t Hw,
                                                uint32_t wb, const uint64_t *__restrict__ wq0,
-                                               const uint64_t *__restrict__ wq1,
+                                               const uint64_t *__restrict__ wq1, uint64_t QD,
                                                const uint64_t *__restrict__ Drow,
                                                const uint64_t *__restrict__ row_ptr,
                                                const uint32_t *__restrict__ row_deg,
@@ -951,18 +940,12 @@ __global__ __launch_bounds__(kNT) void k_pack(uint64_t *__restrict__ W, uint64_t
         }
         if (tid < kWave) {
             uint64_t q0 = 0, q1 = 0, qi = 0;  // this lane's row: qi, if below q1
-            if (wb == 64) {
-                q0 = wq0[w];
-                q1 = wq1[w];
-                qi = q0 + lane;
-            } else {
-                const uint64_t ww = 2 * w + (lane >> 5);
-                if (ww < Hw) {
-                    q0 = wq0[ww];
-                    q1 = wq1[ww];
-                }
-                qi = q0 + (lane & 31);
+            const uint64_t ww = wb == 64 ? w : 2 * w + (lane >> 5);
+            if (ww < Hw) {
+                q0 = wq0 ? wq0[ww] : ww * wb;
+                q1 = wq0 ? wq1[ww] : min(q0 + wb, QD);
             }
+            qi = q0 + (wb == 64 ? lane : lane & 31);
             uint64_t base = 0, deg = 0;
             if (qi < q1) {
                 const uint64_t r = Drow ? Drow[qi] : qi;
@@ -1304,8 +1287,14 @@ __global__ void k_bucket(const uint64_t *D, uint64_t ND, uint32_t sbits, uint32_
 
 // --- planned encode: sizes after each scan, checked against the capacities.
 // One thread each; a size above its capacity sets PZ_ABORT (every later
-// kernel of the encode then returns at once) and err bit 32.
-__global__ void k_plan_begin(const uint64_t *off, int32_t n, uint64_t Ncap, uint64_t *dsz, uint32_t *err) {
+// kernel of the encode then returns at once) and err bit 32.  (k_plan_begin:
+// the other threads clear the counters.)
+__global__ void k_plan_begin(const uint64_t *off, int32_t n, uint64_t Ncap, uint64_t *dsz, uint32_t *err, Clear c) {
+    for (int k = 0; k < Clear::kMax; ++k)
+        for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < c.words[k];
+             i += (uint64_t)gridDim.x * blockDim.x)
+            c.p[k][i] = 0;
+    if (blockIdx.x || threadIdx.x) return;
     uint64_t N = n > 0 ? off[n] : 0;
     for (int k = 0; k < PZ_COUNT; ++k) dsz[k] = 0;
     err[0] = 0;
@@ -1385,12 +1374,6 @@ __global__ void k_plan_pairs(const uint64_t *npo, uint64_t gcap, uint64_t Pcap, 
 }
 
 // err bit 64: a set reaches the int32 bound (|X_i| >= limit)
-__global__ void k_plan_card(const int64_t *card, int32_t n, int64_t limit, uint32_t *err) {
-    bool over = false;
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) over |= card[i] >= limit;
-    if (__ballot(over) && lane_id() == 0) atomicOr(err, 64u);
-}
-
 // Grid of k_pair_emit over QL list rows: a wave per 64 rows, and as many waves
 // sharing the same rows as bring the chip to about 8192 waves.
 dim3 pair_emit_grid(uint64_t QL) {
@@ -1406,10 +1389,8 @@ void launch_1d(uint64_t work, hipStream_t s, F f) {
 }
 
 uint64_t to_host_u64(const uint64_t *dptr, hipStream_t s) {
-    JAS_HOST_TIMED("readback_sync");
     uint64_t v = 0;
-    JAS_HIP(hipMemcpyAsync(&v, dptr, sizeof(v), hipMemcpyDeviceToHost, s));
-    JAS_HIP(hipStreamSynchronize(s));
+    read_back(ReadBack().add(dptr), &v, s);
     return v;
 }
 
@@ -1441,11 +1422,15 @@ namespace {
 struct Ranges {
     uint64_t nlc = 0, stride = 0, err = 8;
     uint32_t cap = kLocalCapKeys;
+    uint32_t sort_err = 0;
 };
 constexpr uint64_t kMinStride = kLocalStrides[sizeof(kLocalStrides) / sizeof(kLocalStrides[0]) - 1];
 
+// Clears `clear` too, and reads sort_err (if given) along with its own flags:
+// keys out of order only make it find ranges that nothing then uses.
 Ranges find_ranges(const uint64_t *keys, uint64_t N, uint32_t bsh, uint32_t lowbits, uint32_t sbits,
-                   DevBuf<uint64_t> &rs, DevBuf<uint64_t> &flags, hipStream_t s, Budget *tb) {
+                   DevBuf<uint64_t> &rs, DevBuf<uint64_t> &flags, Clear clear, const uint32_t *sort_err, hipStream_t s,
+                   Budget *tb) {
     Ranges r;
     rs.alloc(div_up(N, kMinStride) + 1, s, tb, true, "range starts");
     flags.alloc(1, s, tb, true, "range error flag");
@@ -1456,10 +1441,8 @@ Ranges find_ranges(const uint64_t *keys, uint64_t N, uint32_t bsh, uint32_t lowb
     for (const uint64_t stride : strides) {
         if (stride == kLocalWideStride && lowbits != 0) continue;
         r.nlc = div_up(N, stride);
-        {
-            JAS_TIMED("fill_u64", s);
-            k_fill_u64<<<1, 64, 0, s>>>(flags.p, 1, 0);
-        }
+        clear_words(clear.add(flags.p, 1), s);
+        clear = Clear();
         {
             JAS_TIMED("range_starts", s);
             k_range_starts<<<(uint32_t)div_up(r.nlc + 1, 256 / kWave), 256, 0, s>>>(keys, N, bsh, stride, r.nlc, rs.p,
@@ -1468,8 +1451,14 @@ Ranges find_ranges(const uint64_t *keys, uint64_t N, uint32_t bsh, uint32_t lowb
                 keys, rs.p, r.nlc, bsh, lowbits, sbits, err, nullptr, 0, r.cap);
         }
         check_launch("range starts");
-        JAS_HIP(hipMemcpyAsync(&r.err, flags.p, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-        JAS_HIP(hipStreamSynchronize(s));
+        uint64_t got[2] = {0, 0};
+        ReadBack rb;
+        rb.add(flags.p);
+        if (sort_err) rb.add(sort_err);
+        read_back(rb, got, s);
+        r.err = got[0];
+        r.sort_err = (uint32_t)got[1];
+        if (r.sort_err) break;
         if ((r.err & 8u) == 0) {
             r.cap = r.err & 128u ? kLocalCapKeys : kLocalShortCap;
             r.stride = stride;
@@ -1485,7 +1474,7 @@ uint64_t distinct_sorted(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t
     if (div_up(N, kMinStride) > 0xFFFFFFFFull || keys.n < N || alt.n < N) return ~0ull;
     const uint32_t lowbits = U - plan.top_bits;
     DevBuf<uint64_t> rs, flags;
-    const Ranges rg = find_ranges(keys.p, N, lowbits, lowbits, 0, rs, flags, s, nullptr);
+    const Ranges rg = find_ranges(keys.p, N, lowbits, lowbits, 0, rs, flags, Clear(), nullptr, s, nullptr);
     if (rg.err & 8u) return ~0ull;
     DevBuf<unsigned long long> rows;
     DevBuf<uint32_t> cnt;
@@ -1516,7 +1505,7 @@ uint64_t distinct_sorted(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t
 }
 
 void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, const SortPlan &plan,
-                   const uint64_t *offsets, hipStream_t s, Budget *tb) {
+                   const uint64_t *offsets, const uint32_t *sort_err, hipStream_t s, Budget *tb) {
     const int32_t n = db->n;
     const uint32_t sbits = db->sbits;
     const uint64_t smask = sbits ? ((uint64_t(1) << sbits) - 1) : 0;
@@ -1524,18 +1513,26 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
     const bool query_only = db->flags & JAS_QUERY_ONLY;  // no packed words or row lists
 
     DevBuf<unsigned long long> st;
-    st.alloc(ST_N, s, tb, true, "encode counters");
-    {
-        JAS_TIMED("fill_u64", s);
-        k_fill_u64<<<1, 64, 0, s>>>((uint64_t *)st.p, ST_N, 0);
-    }
-    DevBuf<unsigned long long> cardc;
-    cardc.alloc(std::max<int32_t>(n, 1), s, tb, true, "column sums");
-    {
-        JAS_TIMED("fill_u64", s);
-        k_fill_u64<<<64, 256, 0, s>>>((uint64_t *)cardc.p, (uint64_t)std::max<int32_t>(n, 1), 0);
-    }
-    check_launch("fill");
+    st.alloc(kStatWords, s, tb, true, "encode counters");
+    Clear clear;  // by the first launch below
+    clear.add(st.p, kStatWords);
+    const auto check_sort = [](uint32_t e) {
+        if (e & 1u) fail(JAS_EINVAL, "jas_encode: an ID is >= 2^universe_bits");
+        if (e) fail(JAS_EDEVICE, "jas_encode: the radix sort's look-back waited too long (result discarded)");
+    };
+    // |X_i|, all checked against the limit by the kernels that write it
+    db->card.alloc(std::max<int32_t>(n, 1), s, &db->budget, false, "card");
+    const auto check_card = [&](bool over) {
+        if (!over) return;
+        std::vector<int64_t> hc((size_t)n);
+        JAS_HIP(hipMemcpyAsync(hc.data(), db->card.p, sizeof(int64_t) * n, hipMemcpyDeviceToHost, s));
+        JAS_HIP(hipStreamSynchronize(s));
+        const uint64_t lim = card_limit();
+        for (int32_t i = 0; i < n; ++i)
+            if ((uint64_t)hc[i] >= lim)
+                fail(JAS_EOVERFLOW, "sample " + std::to_string(i) + " has " + std::to_string(hc[i]) +
+                                        " distinct IDs (limit " + std::to_string(lim - 1) + ")");
+    };
 
     // Outputs of the classification: distinct keys (query index), shared
     // pairs S in row order, and per shared row its ID and first pair.
@@ -1547,13 +1544,21 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
     uint64_t *ridp = nullptr, *rptrp = nullptr;
     uint32_t *rdegp = nullptr;
     bool done = N == 0;
+    if (done) clear_words(clear.add(db->card.p, std::max<int32_t>(n, 1)), s);
+    bool checked = done;  // sort_err
 
     // --- classify each range of whole buckets in LDS ------------------------
     if (!done && div_up(N, kMinStride) <= 0xFFFFFFFFull && alt.n >= N + 2) {
         const uint32_t lowbits = db->U - plan.top_bits;
         const uint32_t bsh = sbits + lowbits;
         DevBuf<uint64_t> rs, flags;
-        const Ranges rg = find_ranges(keys.p, N, bsh, lowbits, sbits, rs, flags, s, tb);
+        DevBuf<unsigned long long> dupc;  // repeat counts per sample
+        dupc.alloc(std::max<int32_t>(n, 1), s, tb, true, "repeat counts");
+        clear.add(dupc.p, std::max<int32_t>(n, 1));
+        const Ranges rg = find_ranges(keys.p, N, bsh, lowbits, sbits, rs, flags, clear, sort_err, s, tb);
+        check_sort(rg.sort_err);
+        checked = true;
+        clear = Clear();
         uint32_t *errL = reinterpret_cast<uint32_t *>(flags.p);
         const uint64_t nlc = rg.nlc;
         const uint32_t cap = rg.cap;
@@ -1561,19 +1566,10 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         db->trace.stride = rg.stride;
         db->trace.lcap = cap;
         if ((herr & 8u) == 0) {
-            DevBuf<unsigned long long> dupc;
             DevBuf<uint32_t> cnt;
             DevBuf<uint64_t> rid_g, offD, offS, offR, stmp;
-            // repeat counts per sample, then the row counters (kStatReplicas)
-            const uint64_t ndup = (uint64_t)std::max<int32_t>(n, 1);
-            dupc.alloc(ndup + kStatReplicas, s, tb, true, "repeat counts");
-            unsigned long long *rowsrep = dupc.p + ndup;
             cnt.alloc(3 * nlc, s, tb, true, "range counts");
             rid_g.alloc(N / 2 + 1, s, tb, true, "row ids (by range)");
-            {
-                JAS_TIMED("fill_u64", s);
-                k_fill_u64<<<64, 256, 0, s>>>((uint64_t *)dupc.p, ndup + kStatReplicas, 0);
-            }
             // shared pairs at the range starts in the first half of the free sort
             // buffer, row pointers (relative to the range) after it
             uint32_t *Sg = reinterpret_cast<uint32_t *>(alt.p);
@@ -1582,22 +1578,25 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
                 JAS_TIMED(herr & 16u ? "local_cls_wide" : "local_cls", s);
                 launch_local_cls((herr & 16u) != 0, cap, (uint32_t)nlc, s, keys.p, sbits, smask, bsh, lowbits,
                                  (const uint64_t *)rs.p, (uint32_t)nlc, cnt.p, keep ? 1 : 0, Sg, rid_g.p, rptr_g,
-                                 dupc.p, rowsrep, (const uint64_t *)nullptr, (uint64_t)0, errL);
-                k_sum_replicas<<<1, 64, 0, s>>>(rowsrep, kStatReplicas, st.p + ST_ROWS);
+                                 dupc.p, st.p + kStatRows, (const uint64_t *)nullptr, (uint64_t)0, errL);
             }
             check_launch("local classify");
+            if (n > 0) {
+                JAS_TIMED("card", s);
+                k_card_from_dups<<<(uint32_t)std::min<uint64_t>(div_up(n, 256), 1024), 256, 0, s>>>(
+                    offsets, dupc.p, n, db->card.p, (int64_t)card_limit(), errL);
+            }
+            check_launch("column sums");
             offD.alloc(nlc + 1, s, tb, true, "range offsets");
             offS.alloc(nlc + 1, s, tb, true, "range offsets");
             offR.alloc(nlc + 1, s, tb, true, "range offsets");
             stmp.alloc(scan_tmp_elems(nlc, kScanRows), s, tb, true, "scan scratch");
             scan_excl_u32_rows(cnt.p, nlc, {offD.p, offS.p, offR.p}, nlc, stmp.p, s);
-            uint64_t t3[3];
-            JAS_HIP(hipMemcpyAsync(&t3[0], offD.p + nlc, 8, hipMemcpyDeviceToHost, s));
-            JAS_HIP(hipMemcpyAsync(&t3[1], offS.p + nlc, 8, hipMemcpyDeviceToHost, s));
-            JAS_HIP(hipMemcpyAsync(&t3[2], offR.p + nlc, 8, hipMemcpyDeviceToHost, s));
-            JAS_HIP(hipMemcpyAsync(&herr, flags.p, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-            JAS_HIP(hipStreamSynchronize(s));
+            uint64_t t3[4];
+            read_back(ReadBack().add(offD.p + nlc).add(offS.p + nlc).add(offR.p + nlc).add(flags.p), t3, s);
+            herr = t3[3];
             if (herr & 8u) fail(JAS_EDEVICE, "local classify: a range exceeds the kernel's capacity");
+            check_card((herr & 64u) != 0);
             NDk = t3[0];
             NS = t3[1];
             R = t3[2];
@@ -1619,12 +1618,6 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
                     rdegp, nullptr, 0);
             }
             check_launch("local move");
-            {
-                JAS_TIMED("card", s);
-                k_card_from_dups<<<(uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(div_up(n, 256), 1024)), 256, 0,
-                                   s>>>(offsets, dupc.p, n, cardc.p);
-            }
-            check_launch("column sums");
             done = true;
         }
     }
@@ -1632,6 +1625,12 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
     // --- otherwise: sort every ID bit, classify with neighbours in global memory
     if (!done) {
         JAS_HOST_TIMED("classify_fallback");
+        if (!checked) {
+            uint64_t e = 0;
+            read_back(ReadBack().add(sort_err), &e, s);
+            check_sort((uint32_t)e);
+        }
+        clear_words(clear.add(db->card.p, std::max<int32_t>(n, 1)), s);
         {
             RadixWork rw;
             radix_sort_u64(keys, alt, N, sbits, sbits + db->U, rw, s, tb);
@@ -1646,7 +1645,8 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         {
             JAS_TIMED("cls_count", s);
             k_cls_count<<<(uint32_t)nch, kNT, shmem, s>>>(K, N, sbits, smask, n, lds_hist, cnt.p, cnt.p + nch,
-                                                          cnt.p + 2 * nch, cardc.p, st.p);
+                                                          cnt.p + 2 * nch,
+                                                          reinterpret_cast<unsigned long long *>(db->card.p), st.p);
         }
         check_launch("classify count");
         offD.alloc(nch + 1, s, tb, true, "classify offsets");
@@ -1655,10 +1655,8 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         stmp.alloc(scan_tmp_elems(nch, kScanRows), s, tb, true, "scan scratch");
         scan_excl_u32_rows(cnt.p, nch, {offD.p, offS.p, offR.p}, nch, stmp.p, s);
         uint64_t t3[3];
-        JAS_HIP(hipMemcpyAsync(&t3[0], offD.p + nch, 8, hipMemcpyDeviceToHost, s));
-        JAS_HIP(hipMemcpyAsync(&t3[1], offS.p + nch, 8, hipMemcpyDeviceToHost, s));
-        JAS_HIP(hipMemcpyAsync(&t3[2], offR.p + nch, 8, hipMemcpyDeviceToHost, s));
-        JAS_HIP(hipStreamSynchronize(s));
+        read_back(ReadBack().add(offD.p + nch).add(offS.p + nch).add(offR.p + nch), t3, s);
+        check_card(true);  // (looks at every sum)
         NDk = t3[0];
         NS = t3[1];
         R = t3[2];
@@ -1676,12 +1674,12 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         }
         check_launch("classify write");
     }
-    if (N > 0) {
-        JAS_TIMED("fill_u64", s);
-        k_fill_u64<<<1, 1, 0, s>>>(rptrp + R, 1, NS);
-    }
-    check_launch("fill");
     if (!rdegp) {  // the global classification wrote the rows contiguously
+        if (N > 0) {
+            JAS_TIMED("fill_u64", s);
+            k_fill_u64<<<1, 1, 0, s>>>(rptrp + R, 1, NS);
+        }
+        check_launch("fill");
         rdeg_own.alloc(R + 1, s, tb, true, "row degrees");
         rdegp = rdeg_own.p;
         launch_1d(std::max<uint64_t>(R, 1), s, [&](uint32_t b, hipStream_t st_) {
@@ -1691,23 +1689,9 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         check_launch("row degrees");
     }
 
-    // column sums -> |X_i| (int32 B needs every |X_i| < 2^31)
-    db->card.alloc(std::max<int32_t>(n, 1), s, &db->budget, false, "card");
-    if (n > 0) {
-        std::vector<uint64_t> hc(n);
-        JAS_HIP(hipMemcpyAsync(hc.data(), cardc.p, sizeof(uint64_t) * n, hipMemcpyDeviceToHost, s));
-        JAS_HIP(hipStreamSynchronize(s));
-        const uint64_t lim = card_limit();
-        for (int32_t i = 0; i < n; ++i)
-            if (hc[i] >= lim)
-                fail(JAS_EOVERFLOW, "sample " + std::to_string(i) + " has " + std::to_string(hc[i]) +
-                                        " distinct IDs (limit " + std::to_string(lim - 1) + ")");
-        JAS_HIP(hipMemcpyAsync(db->card.p, cardc.p, sizeof(int64_t) * n, hipMemcpyDeviceToDevice, s));
-    }
-    cardc.release();
-
     // --- split rows by degree ------------------------------------------------
-    uint64_t QD = 0, QL = 0;
+    uint64_t QD = 0, QL = 0, P = 0, list_pairs = 0;
+    bool sized = false;  // QD and P come from the degree histogram, not from the device
     DevBuf<uint64_t> Drow, Lrow;
     if (R > 0 && !query_only && db->dmin == 0) {
         // choose the degree threshold from the row degree histogram
@@ -1715,7 +1699,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         const uint32_t nb = (uint32_t)n + 2;
         DevBuf<unsigned long long> hist;
         hist.alloc(nb, s, tb, true, "degree histogram");
-        k_fill_u64<<<64, 256, 0, s>>>((uint64_t *)hist.p, nb, 0);
+        clear_words(Clear().add(hist.p, nb), s);
         const int lds = nb <= 16384;
         const uint32_t blocks = (uint32_t)std::min<uint64_t>(div_up(R, 256), 2048);
         {
@@ -1736,32 +1720,34 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         const uint32_t bb = db->batch_bits, U = db->U;
         const uint64_t nbatches = (U - bb >= 63) ? ~0ull : (uint64_t(1) << (U - bb));
         db->dmin = choose_dense_min_degree(hh, (uint32_t)n, nbatches, cap);
+        for (uint64_t d = 0; d < nb; ++d) {
+            if (d >= db->dmin) QD += hh[d];
+            else if (d > 1) P += hh[d] * (d * (d - 1) / 2);
+        }
+        QL = R - QD;
+        list_pairs = P;
+        sized = true;
     }
     db->stats.dense_min_degree = db->dmin;
-    if (R > 0 && !query_only) {
+    if (R > 0 && !query_only && !(sized && (QD == 0 || QL == 0))) {
         const uint64_t nt = div_up(R, kSplitTile);
         if (nt > 0xFFFFFFFFull) fail(JAS_EUNSUPPORTED, "too many rows");
         DevBuf<uint32_t> tcnt;
-        DevBuf<uint64_t> toff, tmp, lprep;
+        DevBuf<uint64_t> toff, tmp;
         tcnt.alloc(nt, s, tb, true, "row tile counts");
-        lprep.alloc(kStatReplicas, s, tb, true, "list pair counters");
-        {
-            JAS_TIMED("fill_u64", s);
-            k_fill_u64<<<1, 64, 0, s>>>(lprep.p, kStatReplicas, 0);
-        }
         toff.alloc(nt + 1, s, tb, true, "row tile offsets");
         tmp.alloc(scan_tmp_elems(nt), s, tb, true, "scan scratch");
         {
             JAS_TIMED("row_count", s);
             k_row_count<<<(uint32_t)nt, kNT, 0, s>>>(rdegp, R, db->dmin, tcnt.p,
-                                                      reinterpret_cast<unsigned long long *>(lprep.p), nullptr);
-            k_sum_replicas<<<1, 64, 0, s>>>(reinterpret_cast<const unsigned long long *>(lprep.p), kStatReplicas,
-                                            st.p + ST_LISTPAIRS);
+                                                      st.p + kStatLists, nullptr);
         }
         check_launch("row count");
         scan_excl_u32(tcnt.p, toff.p, nt, tmp.p, s);
-        QD = to_host_u64(toff.p + nt, s);
-        QL = R - QD;
+        if (!sized) {
+            QD = to_host_u64(toff.p + nt, s);
+            QL = R - QD;
+        }
         // when every shared row is of one form the split is the identity: the
         // kernels take a null Drow / Lrow as row q = q
         if (QD > 0 && QL > 0) {
@@ -1774,6 +1760,9 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
             check_launch("row split");
         }
     }
+
+    // only the batches of packed rows are told apart by the rows' IDs
+    if (QD == 0 || db->batch_bits >= db->U) rid_own.release();
 
     // --- row lists, first part -------------------------------------------------
     // Up to kSampleMajorMaxN samples: the rows' pairs, sorted by their smaller
@@ -1789,7 +1778,6 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
     DevBuf<uint64_t> npo;
     DevBuf<uint32_t> pk, palt, perr;
     DevBuf<unsigned long long> pgh;
-    uint64_t P = 0;
     uint32_t psb = 0, pwidth = 0;
     hipStream_t s2 = nullptr;
     StreamJoin join;  // after the buffers: on an error s waits for s2 before they are freed
@@ -1808,7 +1796,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         npo.alloc(nw + 1, s, tb, true, "row group pair offsets");
         tmp2.alloc(scan_tmp_elems(nw), s, tb, true, "scan scratch");
         scan_excl_u64(np.p, npo.p, nw, tmp2.p, s);
-        P = to_host_u64(npo.p + nw, s);
+        if (!sized) P = to_host_u64(npo.p + nw, s);
         np.release();
         tmp2.release();
         psb = std::max<uint32_t>(1, ceil_log2_u64((uint64_t)n));
@@ -1823,11 +1811,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         stream_after(s2, s);  // everything the pair path reads is on s so far
         join.waiter = s;
         join.on = s2;
-        {
-            JAS_TIMED("fill_u64", s2);
-            k_fill_u64<<<64, 256, 0, s2>>>((uint64_t *)pgh.p, (uint64_t)kGhistReplicas * kMaxPasses * 256, 0);
-            k_fill_u64<<<1, 64, 0, s2>>>((uint64_t *)perr.p, 1, 0);
-        }
+        clear_words(Clear().add(pgh.p, (uint64_t)kGhistReplicas * kMaxPasses * 256).add(perr.p, 1), s2);
         {
             JAS_TIMED("pair_emit", s2);
             k_pair_emit<<<pair_emit_grid(QL), 256, 0, s2>>>(
@@ -1843,44 +1827,51 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
     if (QD > 0) {
         DevBuf<uint32_t> bs;
         DevBuf<uint64_t> bpos, bq, nw, wbase, tmp, wq0, wq1;
-        bs.alloc(QD, s, tb, true, "batch flags");
-        const uint32_t bbits = db->batch_bits;
-        launch_1d(QD, s, [&](uint32_t b, hipStream_t st_) {
+        if (db->batch_bits >= db->U) {
+            // a single batch: its word rows need no table (six launches and two
+            // waits fewer, 0.1 ms of a small call)
+            nb = 1;
+            Hw = div_up(QD, (uint64_t)wb);
+        } else {
+            bs.alloc(QD, s, tb, true, "batch flags");
+            const uint32_t bbits = db->batch_bits;
+            launch_1d(QD, s, [&](uint32_t b, hipStream_t st_) {
+                {
+                    JAS_TIMED("batch_flag", st_);
+                    k_batch_flag<<<b, 256, 0, st_>>>(Drow.p, ridp, QD, bbits, bs.p, nullptr);
+                }
+            });
+            check_launch("batch flags");
+            bpos.alloc(QD + 1, s, tb, true, "batch scan");
+            tmp.alloc(scan_tmp_elems(QD), s, tb, true, "scan scratch");
+            scan_excl_u32(bs.p, bpos.p, QD, tmp.p, s);
+            nb = to_host_u64(bpos.p + QD, s);
+            bq.alloc(nb + 1, s, tb, true, "batch starts");
+            launch_1d(QD, s, [&](uint32_t b, hipStream_t st_) { { JAS_TIMED("batch_start", st_); k_batch_start<<<b, 256, 0, st_>>>(bs.p, bpos.p, QD, bq.p, nullptr); } });
             {
-                JAS_TIMED("batch_flag", st_);
-                k_batch_flag<<<b, 256, 0, st_>>>(Drow.p, ridp, QD, bbits, bs.p, nullptr);
+                JAS_TIMED("fill_u64", s);
+                k_fill_u64<<<1, 1, 0, s>>>(bq.p + nb, 1, QD);
             }
-        });
-        check_launch("batch flags");
-        bpos.alloc(QD + 1, s, tb, true, "batch scan");
-        tmp.alloc(scan_tmp_elems(QD), s, tb, true, "scan scratch");
-        scan_excl_u32(bs.p, bpos.p, QD, tmp.p, s);
-        nb = to_host_u64(bpos.p + QD, s);
-        bq.alloc(nb + 1, s, tb, true, "batch starts");
-        launch_1d(QD, s, [&](uint32_t b, hipStream_t st_) { { JAS_TIMED("batch_start", st_); k_batch_start<<<b, 256, 0, st_>>>(bs.p, bpos.p, QD, bq.p, nullptr); } });
-        {
-            JAS_TIMED("fill_u64", s);
-            k_fill_u64<<<1, 1, 0, s>>>(bq.p + nb, 1, QD);
+            check_launch("batch starts");
+            nw.alloc(nb, s, tb, true, "batch words");
+            launch_1d(nb, s, [&](uint32_t b, hipStream_t st_) { { JAS_TIMED("batch_words", st_); k_batch_words<<<b, 256, 0, st_>>>(bq.p, nb, wb, nw.p, nullptr); } });
+            check_launch("batch words");
+            wbase.alloc(nb + 1, s, tb, true, "word bases");
+            tmp.release();
+            tmp.alloc(scan_tmp_elems(nb), s, tb, true, "scan scratch");
+            scan_excl_u64(nw.p, wbase.p, nb, tmp.p, s);
+            Hw = to_host_u64(wbase.p + nb, s);
+            wq0.alloc(Hw, s, tb, true, "word rows");
+            wq1.alloc(Hw, s, tb, true, "word rows");
+            launch_1d(QD, s, [&](uint32_t b, hipStream_t st_) {
+                {
+                    JAS_TIMED("word_rows", st_);
+                    k_word_rows<<<b, 256, 0, st_>>>(QD, bpos.p, bq.p, wbase.p, wb, wq0.p, wq1.p, nullptr);
+                }
+            });
+            check_launch("word rows");
         }
-        check_launch("batch starts");
-        nw.alloc(nb, s, tb, true, "batch words");
-        launch_1d(nb, s, [&](uint32_t b, hipStream_t st_) { { JAS_TIMED("batch_words", st_); k_batch_words<<<b, 256, 0, st_>>>(bq.p, nb, wb, nw.p, nullptr); } });
-        check_launch("batch words");
-        wbase.alloc(nb + 1, s, tb, true, "word bases");
-        tmp.release();
-        tmp.alloc(scan_tmp_elems(nb), s, tb, true, "scan scratch");
-        scan_excl_u64(nw.p, wbase.p, nb, tmp.p, s);
-        Hw = to_host_u64(wbase.p + nb, s);
         H = wb == 64 ? Hw : div_up(Hw, 2);
-        wq0.alloc(Hw, s, tb, true, "word rows");
-        wq1.alloc(Hw, s, tb, true, "word rows");
-        launch_1d(QD, s, [&](uint32_t b, hipStream_t st_) {
-            {
-                JAS_TIMED("word_rows", st_);
-                k_word_rows<<<b, 256, 0, st_>>>(QD, bpos.p, bq.p, wbase.p, wb, wq0.p, wq1.p, nullptr);
-            }
-        });
-        check_launch("word rows");
         db->W.alloc(H * ldw, s, &db->budget, false, "packed words");
         // column chunks of equal size (multiples of 128): fewer LDS bytes per
         // block than a full kPackCols chunk when ldw is not a multiple of it
@@ -1889,7 +1880,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         const uint32_t grid = (uint32_t)std::min<uint64_t>(H, 4096);
         {
             JAS_TIMED("pack", s);
-            k_pack<<<grid, kNT, cols * sizeof(unsigned long long), s>>>(db->W.p, ldw, H, Hw, wb, wq0.p, wq1.p,
+            k_pack<<<grid, kNT, cols * sizeof(unsigned long long), s>>>(db->W.p, ldw, H, Hw, wb, wq0.p, wq1.p, QD,
                                                                         Drow.p, rptrp, rdegp, Sp, cols, st.p, nullptr);
         }
         check_launch("pack");
@@ -1897,14 +1888,18 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
     db->H = H;
 
     // --- row lists, second part: the pair sort (side stream), then s waits --
+    uint64_t hst[kStatWords];
+    bool have_st = false;  // hst holds the final counters
     if (pair_form) {
         const bool ok = radix_sort_onesweep_u32(pk, palt, P, 16, 16 + psb, pwidth, pgh.p, perr.p, s2, tb);
-        uint32_t herr = 0;
-        JAS_HIP(hipMemcpyAsync(&herr, perr.p, 4, hipMemcpyDeviceToHost, s2));
         JAS_HIP(hipStreamSynchronize(s2));
         stream_after(s, s2);
         join.waiter = nullptr;
-        if (ok && herr == 0) {
+        uint64_t got[1 + kStatWords];
+        read_back(ReadBack().add(perr.p).add(st.p, kStatWords), got, s);
+        std::copy(got + 1, got + 1 + kStatWords, hst);
+        have_st = true;
+        if (ok && (uint32_t)got[0] == 0) {
             db->n_lpairs = P;
             db->pairs = std::move(pk);
             pairs_done = true;
@@ -1966,9 +1961,9 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
     }
 
     // --- stats -----------------------------------------------------------------
-    uint64_t hst[ST_N];
-    JAS_HIP(hipMemcpyAsync(hst, st.p, sizeof(hst), hipMemcpyDeviceToHost, s));
-    JAS_HIP(hipStreamSynchronize(s));
+    if (!have_st) read_back(ReadBack().add(st.p, kStatWords), hst, s);
+    add_replicas(hst);
+    if (sized) hst[ST_LISTPAIRS] = list_pairs;
     jas_encode_stats &o = db->stats;
     db->trace.N = N;
     db->trace.ND = NDk;
@@ -2012,19 +2007,15 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
     uint64_t *dsz = p.dsz.p;
     uint32_t *err = p.err.p;
     const uint64_t Ncap = p.Ncap;
-    auto fill = [&](void *ptr, uint64_t words) {
-        JAS_TIMED("fill_u64", s);
-        k_fill_u64<<<(uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(div_up(words, 256), 1024)), 256, 0, s>>>(
-            (uint64_t *)ptr, words, 0);
-    };
     {
         JAS_TIMED("plan_sizes", s);
-        k_plan_begin<<<1, 1, 0, s>>>(offsets, n, Ncap, dsz, err);
+        Clear c;
+        c.add(p.ghist.p, (uint64_t)kGhistReplicas * kMaxPasses * 256);
+        c.add(p.st.p, kStatWords);
+        c.add(p.dupc.p, (uint64_t)std::max<int32_t>(n, 1));
+        if (p.QLcap > 0) c.add(p.gh.p, (uint64_t)kGhistReplicas * kMaxPasses * 256);
+        k_plan_begin<<<256, 256, 0, s>>>(offsets, n, Ncap, dsz, err, c);
     }
-    fill(p.ghist.p, (uint64_t)kGhistReplicas * kMaxPasses * 256);
-    fill(p.st.p, ST_N);
-    fill(p.dupc.p, (uint64_t)std::max<int32_t>(n, 1) + kStatReplicas);
-    fill(p.lprep.p, kStatReplicas);
     check_launch("plan begin");
     // keys and the global sort on the top ID bits
     const uint64_t hi_mask = U >= 64 ? 0 : ~((uint64_t(1) << U) - 1);
@@ -2070,15 +2061,13 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
             K, p.rs.p, nlc, bsh, lowbits, sbits, err, dsz, p.stride, p.lcap);  // bit 16 matters only to narrow plans
     }
     check_launch("range starts (planned)");
-    const uint64_t ndup = (uint64_t)std::max<int32_t>(n, 1);
-    unsigned long long *rowsrep = p.dupc.p + ndup;
     uint32_t *Sg = reinterpret_cast<uint32_t *>(F);
     uint64_t *rptr_g = F + div_up(Ncap, 2);
     {
         JAS_TIMED(p.wide ? "local_cls_wide" : "local_cls", s);
         launch_local_cls(p.wide, p.lcap, (uint32_t)nlc, s, K, sbits, smask, bsh, lowbits, (const uint64_t *)p.rs.p,
-                         (uint32_t)nlc, p.cnt.p, 0, Sg, p.rid_g.p, rptr_g, p.dupc.p, rowsrep, dsz, p.stride, err);
-        k_sum_replicas<<<1, 64, 0, s>>>(rowsrep, kStatReplicas, p.st.p + ST_ROWS);
+                         (uint32_t)nlc, p.cnt.p, 0, Sg, p.rid_g.p, rptr_g, p.dupc.p, p.st.p + kStatRows, dsz, p.stride,
+                         err);
     }
     check_launch("local classify (planned)");
     scan_excl_u32_rows(p.cnt.p, nlc, {p.offD.p, p.offS.p, p.offR.p}, nlc, p.stmp.p, s);
@@ -2095,16 +2084,13 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
     {
         JAS_TIMED("card", s);
         k_card_from_dups<<<(uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(div_up(n, 256), 1024)), 256, 0, s>>>(
-            offsets, p.dupc.p, n, reinterpret_cast<unsigned long long *>(p.card.p));
-        k_plan_card<<<(uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(div_up(n, 256), 1024)), 256, 0, s>>>(
-            p.card.p, n, (int64_t)card_limit(), err);
+            offsets, p.dupc.p, n, p.card.p, (int64_t)card_limit(), err);
     }
     check_launch("local move (planned)");
     // rows by degree
     {
         JAS_TIMED("row_count", s);
-        k_row_count<<<(uint32_t)p.tile_cap, kNT, 0, s>>>(p.rdeg.p, p.Rcap, p.dmin, p.tcnt.p, p.lprep.p, dsz);
-        k_sum_replicas<<<1, 64, 0, s>>>(p.lprep.p, kStatReplicas, p.st.p + ST_LISTPAIRS);
+        k_row_count<<<(uint32_t)p.tile_cap, kNT, 0, s>>>(p.rdeg.p, p.Rcap, p.dmin, p.tcnt.p, p.st.p + kStatLists, dsz);
     }
     scan_excl_u32(p.tcnt.p, p.toff.p, p.tile_cap, p.stmp.p, s);
     {
@@ -2147,7 +2133,7 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
         {
             JAS_TIMED("pack", s);
             k_pack<<<(uint32_t)std::min<uint64_t>(p.Hcap, 4096), kNT, cols * sizeof(unsigned long long), s>>>(
-                p.W.p, p.ldw, p.Hcap, p.Hwcap, p.word_bits, p.wq0.p, p.wq1.p, p.Drow.p, p.rptr.p, p.rdeg.p,
+                p.W.p, p.ldw, p.Hcap, p.Hwcap, p.word_bits, p.wq0.p, p.wq1.p, p.QDcap, p.Drow.p, p.rptr.p, p.rdeg.p,
                 reinterpret_cast<const uint32_t *>(F), cols, p.st.p, dsz);
         }
         check_launch("pack (planned)");
@@ -2164,7 +2150,6 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
             JAS_TIMED("plan_sizes", s);
             k_plan_pairs<<<1, 1, 0, s>>>(p.npo.p, p.gcap, p.Pcap, dsz, err);
         }
-        fill(p.gh.p, (uint64_t)kGhistReplicas * kMaxPasses * 256);
         {
             JAS_TIMED("pair_emit", s);
             k_pair_emit<<<pair_emit_grid(QLc), 256, 0, s>>>(

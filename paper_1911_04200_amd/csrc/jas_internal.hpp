@@ -266,6 +266,41 @@ namespace jas {
 // ---------------------------------------------------------------------------
 // Device primitives (each in its own translation unit).
 
+// Runs of 64-bit words set to zero by one launch (at most kMax, others empty).
+struct Clear {
+    static constexpr int kMax = 4;
+    uint64_t *p[kMax] = {};
+    uint64_t words[kMax] = {};
+    int n = 0;
+    template <class T>
+    Clear &add(T *ptr, uint64_t count) {  // count words of 64 bits
+        if (n == kMax) fail(JAS_EDEVICE, "clear: too many runs");
+        p[n] = reinterpret_cast<uint64_t *>(ptr);
+        words[n++] = count;
+        return *this;
+    }
+};
+void clear_words(const Clear &c, hipStream_t s);
+
+// Words of device memory brought to the host by one launch and one wait for s:
+// a kernel writes them to a block of pinned memory (kReadWords words; blocks are
+// kept between calls, a few at most, until jas_trim).
+constexpr uint32_t kReadWords = 512;
+struct ReadBack {
+    static constexpr int kMax = 4;
+    const uint64_t *src[kMax] = {};
+    uint32_t words[kMax] = {};
+    int n = 0;
+    template <class T>
+    ReadBack &add(const T *ptr, uint32_t count = 1) {
+        if (n == kMax) fail(JAS_EDEVICE, "read back: too many runs");
+        src[n] = reinterpret_cast<const uint64_t *>(ptr);
+        words[n++] = count;
+        return *this;
+    }
+};
+void read_back(const ReadBack &r, uint64_t *out, hipStream_t s);  // out: the runs one after another
+
 // out[i] = sum_{k<i} in[k] for i in [0, len]; out has len + 1 entries (out[len] = total).
 // tmp: scratch from scan_tmp_elems(len).
 size_t scan_tmp_elems(size_t len, uint32_t rows = 1);
@@ -370,9 +405,11 @@ void build_keys(const uint64_t *ids, const uint64_t *offsets, int32_t n, uint64_
 
 // Encoding after the global sort (see encode.hip).  keys holds the N keys
 // ordered by their top plan.top_bits ID bits; alt (N + 2 entries) is free and
-// is used as scratch; offsets are the device CSR offsets.
+// is used as scratch; offsets are the device CSR offsets.  sort_err (two words,
+// the second zero; N > 0): the flags of build_keys and of the sort, which are
+// read and checked before anything relies on the keys' order.
 void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, const SortPlan &plan,
-                   const uint64_t *offsets, hipStream_t s, Budget *tmpb);
+                   const uint64_t *offsets, const uint32_t *sort_err, hipStream_t s, Budget *tmpb);
 
 // The distinct values of N keys of U bits ordered by their top plan.top_bits
 // bits (keys holds them; N >= 1), ascending, in alt (N entries); returns their
@@ -399,7 +436,7 @@ struct PlanState {
     DevBuf<uint64_t> keys, alt, rs, offD, offS, offR, stmp, rid_g, rid, rptr, toff, Drow, Lrow, bpos, bq, nw, wbase,
         wq0, wq1, npo, np, dsz;
     DevBuf<uint32_t> err, cnt, rdeg, tcnt, bs, pk, palt;
-    DevBuf<unsigned long long> ghist, gh, dupc, lprep, st;
+    DevBuf<unsigned long long> ghist, gh, dupc, st;
     DevBuf<uint64_t> os_gstart, os_maxima, os2_gstart, os2_maxima;
     DevBuf<uint32_t> os_status, os2_status, os_tinfo;
     DevBuf<int64_t> card;
@@ -407,8 +444,18 @@ struct PlanState {
     uint32_t *pairs_final = nullptr;  // the buffer holding the sorted pair words after the pair sort
 };
 void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, hipStream_t s);
-enum { ST_PAIRS_ = 0, ST_ROWS_, ST_NNZW_, ST_F_, ST_LISTPAIRS_, ST_N_ };  // encode counters (encode.hip)
-constexpr uint32_t kStatReplicasPub = 64;
+// Encode counters (encode.hip): the totals, then kStatReplicas slots each for
+// rows and list pairs, which many blocks add to (one counter would serialise an
+// atomic from every block); add_replicas sums them once they are on the host.
+enum { ST_PAIRS = 0, ST_ROWS, ST_NNZW, ST_F, ST_LISTPAIRS, ST_N };
+constexpr uint32_t kStatReplicas = 64;
+constexpr uint32_t kStatRows = ST_N, kStatLists = ST_N + kStatReplicas, kStatWords = ST_N + 2 * kStatReplicas;
+inline void add_replicas(uint64_t (&st)[kStatWords]) {
+    for (uint32_t k = 0; k < kStatReplicas; ++k) {
+        st[ST_ROWS] += st[kStatRows + k];
+        st[ST_LISTPAIRS] += st[kStatLists + k];
+    }
+}
 constexpr uint64_t kSplitTilePub = 256 * 8;  // rows per row-split tile
 
 // Degree threshold: rows of degree >= the result are bit-packed, 2..result-1

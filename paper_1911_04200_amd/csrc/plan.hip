@@ -160,7 +160,7 @@ jas_status jas_plan_create(const uint64_t *ids, const uint64_t *offsets, int32_t
         plan_buf(p.alt, p.Ncap + 2, s, &bud, "plan keys (second buffer)");
         plan_buf(p.dsz, PZ_COUNT, s, &bud, "plan sizes");
         plan_buf(p.err, 4, s, &bud, "plan flags");
-        plan_buf(p.st, ST_N_, s, &bud, "plan counters");
+        plan_buf(p.st, kStatWords, s, &bud, "plan counters");
         plan_buf(p.ghist, (uint64_t)kGhistReplicas * kMaxPasses * 256, s, &bud, "plan digit totals");
         plan_buf(p.os_gstart, (uint64_t)kMaxPasses * 256, s, &bud, "plan digit starts");
         plan_buf(p.os_maxima, kMaxPasses, s, &bud, "plan digit maxima");
@@ -168,7 +168,7 @@ jas_status jas_plan_create(const uint64_t *ids, const uint64_t *offsets, int32_t
         if (p.sort.top_bits > 0)
             plan_buf(p.os_tinfo, 2 * div_up(p.Ncap, onesweep_tile_keys_from_ids(p.Ncap)), s, &bud, "plan tile samples");
         plan_buf(p.rs, p.nlc_cap + 1, s, &bud, "plan range starts");
-        plan_buf(p.dupc, (uint64_t)n + kStatReplicasPub, s, &bud, "plan repeat counts");
+        plan_buf(p.dupc, (uint64_t)std::max<int32_t>(n, 1), s, &bud, "plan repeat counts");
         plan_buf(p.cnt, 3 * p.nlc_cap, s, &bud, "plan range counts");
         plan_buf(p.rid_g, p.Ncap / 2 + 1, s, &bud, "plan row ids (by range)");
         plan_buf(p.offD, p.nlc_cap + 1, s, &bud, "plan range offsets");
@@ -182,7 +182,6 @@ jas_status jas_plan_create(const uint64_t *ids, const uint64_t *offsets, int32_t
         plan_buf(p.card, (uint64_t)n, s, &bud, "plan card");
         plan_buf(p.tcnt, p.tile_cap, s, &bud, "plan row tile counts");
         plan_buf(p.toff, p.tile_cap + 1, s, &bud, "plan row tile offsets");
-        plan_buf(p.lprep, kStatReplicasPub, s, &bud, "plan list pair counters");
         plan_buf(p.Drow, p.QDcap, s, &bud, "plan packed rows");
         plan_buf(p.Lrow, p.QLcap, s, &bud, "plan list rows");
         if (p.QDcap) {
@@ -256,22 +255,23 @@ jas_status jas_plan_check(jas_plan *plan, void *hip_stream, jas_encode_stats *st
         PlanState &p = plan->st;
         uint32_t err[4] = {0, 0, 0, 0};
         uint64_t sz[PZ_COUNT];
-        unsigned long long cnt[ST_N_];
+        uint64_t cnt[kStatWords];
         JAS_HIP(hipMemcpyAsync(err, p.err.p, sizeof(err), hipMemcpyDeviceToHost, s));
         JAS_HIP(hipMemcpyAsync(sz, p.dsz.p, sizeof(sz), hipMemcpyDeviceToHost, s));
         JAS_HIP(hipMemcpyAsync(cnt, p.st.p, sizeof(cnt), hipMemcpyDeviceToHost, s));
         JAS_HIP(hipStreamSynchronize(s));
+        add_replicas(cnt);
         jas_encode_stats &o = plan->db.stats;
         o.n_ids = sz[PZ_N];
-        o.n_rows = cnt[ST_ROWS_];
+        o.n_rows = cnt[ST_ROWS];
         o.n_shared_rows = sz[PZ_R];
         o.n_packed_rows = sz[PZ_QD];
         o.n_list_rows = sz[PZ_QL];
         o.n_batches = sz[PZ_NB];
         o.n_word_rows = sz[PZ_HW];
-        o.nnz_words = cnt[ST_NNZW_];
-        o.word_pairs_F = cnt[ST_F_];
-        o.list_pairs = cnt[ST_LISTPAIRS_];
+        o.nnz_words = cnt[ST_NNZW];
+        o.word_pairs_F = cnt[ST_F];
+        o.list_pairs = cnt[ST_LISTPAIRS];
         o.n_list_pairs = sz[PZ_P];
         o.w_rows = sz[PZ_H];
         set_tile_stats(o, (uint64_t)p.n);
