@@ -1,5 +1,6 @@
 // Small device helpers shared by the libjas kernels (wave64, gfx950).
 #pragma once
+#include <type_traits>
 
 #include <hip/hip_runtime.h>
 
@@ -92,6 +93,25 @@ __device__ __forceinline__ uint32_t block_excl_scan_u32(uint32_t v, uint32_t *sh
     for (int k = 0; k < NT / kWave; ++k) before += (k < (int)w) ? sh[k] : 0;
     __syncthreads();
     return before + inc - v;
+}
+
+// Largest v of this lane and the ones before it.
+__device__ __forceinline__ uint32_t wave_incl_max(uint32_t v) {
+    const auto from = [](uint32_t x, auto ctrl, auto rows) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+    };
+    using std::integral_constant;
+    v = max(v, from(v, integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{}));  // row_shr:1
+    v = max(v, from(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{}));  // row_shr:2
+    v = max(v, from(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{}));  // row_shr:4
+    v = max(v, from(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{}));  // row_shr:8
+    v = max(v, from(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{}));  // row_bcast:15
+    return max(v, from(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{}));  // row_bcast:31
+}
+
+// The value of the lane before (0 in lane 0).
+__device__ __forceinline__ uint32_t wave_shift_up(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, false);  // wave_shr:1
 }
 
 // Largest s in [lo, hi] with off[s] <= t (CSR sample of entry t).

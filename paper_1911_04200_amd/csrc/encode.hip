@@ -1083,90 +1083,41 @@ __global__ void k_list_wave_pairs(const uint64_t *Lrow, const uint32_t *row_deg,
     }
 }
 
-// A wave takes 64 consecutive rows; their pairs fill one contiguous stretch
-// of the output (the rows' pair counts scanned).  When the stretch fits an
-// LDS stage, each lane writes its own row's pairs there and the wave copies
-// the stage out coalesced.  Otherwise each lane produces output words
-// o = lane, lane + 64, ...: the row that holds o comes from a binary search
-// over the wave's row starts, the pair (i, j) inside the row from the inverse
-// of the triangular count P(i) = i (2d - i - 1) / 2 of the pairs whose smaller
-// entry comes before i, so consecutive lanes write consecutive words whatever
-// the row lengths (one lane per row would leave most lanes idle behind the
-// longest row and scatter the stores).  The rows' samples are one span of the
-// sample array (the rows ascend), read into LDS with coalesced loads first
-// when it fits (else only the rows' own entries, packed, when those fit), so
-// the pair loops read LDS rather than memory.  Per-block LDS totals of the
-// sort digits (digit q = bits [16 + width*q, 16 + width*(q+1)) of the word)
-// come from one pass over each row's entries.
+// A wave takes 64 consecutive rows; their pairs fill one contiguous stretch of
+// the output (the rows' pair counts scanned), row by row, each row's pairs in
+// order.  It works through them a few rows at a time, as many as fit its LDS
+// (kEmitIn entries, kEmitStage pairs): the entries are read into LDS, the pairs
+// formed there and copied out with 16-byte stores.
+//
+// Forming them is what bounds it, not the 4 bytes per pair, so a lane forms four
+// consecutive output words whatever the rows' lengths.  The pairs of one smaller
+// entry are a run of words; each run's start is marked with its position and
+// entry, and a running maximum over the marks (in the lane, then over the wave)
+// tells every word its run, hence both of its entries.  Marks of earlier parts
+// need no clearing: a mark's top bits number its part, and the first word of
+// every part is marked.  Only the marking goes row by row, a lane for each.
+// 1.68 G pairs of 33.5 M rows of about 10: 6.35 ms with a lane per output word
+// that solved for its row and pair (some 140 instructions), 2.7 ms now; 1.85 G of
+// 196 M rows of 2 to 20: 5.28 ms with a lane per row where the pairs fitted,
+// 3.9 ms.
+//
+// A row too long for the stage is written straight to memory, lanes along the
+// pairs of entries k and d - 1 - k.  Per-block LDS totals of the sort digits
+// (digit q = bits [16 + width*q, 16 + width*(q+1)) of the word) are counted by
+// the lane that has the entry.
 // With few rows (gridDim.y > 1) that many waves take the same 64 rows and deal
-// the output words among them, 64 at a time: 1231 rows of degree 60 to 67 (2.6 M
-// pairs) fill 20 waves, 1.79 ms, and 0.075 ms shared; 4610 rows (778 K pairs)
-// 0.15 and 0.026 ms.
-// Stage sizes measured best of 256..3072 for one-lane-per-row emission.
-constexpr uint32_t kEmitStage = 1024;  // output words per wave
-constexpr uint32_t kEmitIn = 512;      // sample entries per wave
+// these parts among them: 1231 rows of degree 60 to 67 (2.6 M pairs) fill 20
+// waves, 1.79 ms, and 0.075 ms shared.
+// (both: sizes from 512 and 256 to 2048 and 512 measured on the two above)
+constexpr uint32_t kEmitStage = 896;  // pairs per wave, at a time
+constexpr uint32_t kEmitIn = 384;     // entries per wave, at a time
+constexpr uint32_t kMarkEntry = 9, kMarkPart = 21;  // a mark: part << 21 | word << 9 | entry
+constexpr uint32_t kMarkParts = (1u << (32 - kMarkPart)) - 1;
+static_assert(kEmitIn <= 1u << kMarkEntry && kEmitStage + 3 < 1u << (kMarkPart - kMarkEntry), "marks");
 constexpr uint32_t kPairPasses = 2;   // 16 sample bits, 8-bit digits
 
-// Largest i in [0, d-2] with P(i) <= k, for 0 <= k < d(d-1)/2 and 2 <= d <= 2^14:
-// the smaller root of i^2 - (2d-1) i + 2k = 0 in float, then corrected by
-// exact integer steps (the estimate is off by at most one).
-__device__ __forceinline__ uint32_t pair_first(uint32_t d, uint32_t k) {
-    const uint32_t b = 2 * d - 1;
-    const float disc = (float)(b * b - 8u * k);
-    int32_t i = (int32_t)(((float)b - sqrtf(disc)) * 0.5f);
-    i = max(0, min(i, (int32_t)d - 2));
-    const auto P = [d](int32_t x) { return (uint32_t)x * (2 * d - (uint32_t)x - 1) / 2; };
-    while (i + 1 <= (int32_t)d - 2 && P(i + 1) <= k) ++i;
-    while (i > 0 && P(i) > k) --i;
-    return (uint32_t)i;
-}
-
-// Digit totals of one row: entry i is the smaller sample of deg - 1 - i pairs.
-template <class Src>
-__device__ __forceinline__ void row_digit_totals(Src src, uint64_t sb, uint32_t deg, uint32_t (*gh)[256],
-                                                 uint32_t npass, uint32_t width, uint32_t dmask) {
-    for (uint32_t i = 0; i + 1 < deg; ++i) {
-        const uint32_t a = src[sb + i];
-        for (uint32_t q = 0; q < npass; ++q) atomicAdd(&gh[q][(a >> (width * q)) & dmask], deg - 1 - i);
-    }
-}
-
-// A wave whose pairs fit the stage: this lane's row's pairs, in order, at
-// stage word o onwards.
-template <class Src>
-__device__ __forceinline__ void stage_row_pairs(Src src, uint64_t sb, uint32_t deg, uint32_t o, uint32_t *st) {
-    for (uint32_t i = 0; i + 1 < deg; ++i) {
-        const uint32_t a = src[sb + i] << 16;
-        for (uint32_t j = i + 1; j < deg; ++j) st[o++] = a | src[sb + j];
-    }
-}
-
-// The wave's pairs from its rows' entries src[sb + i] (LDS or global): output
-// words first, first + step, ... of this lane.  rst[0..64] are the rows' first
-// words (rst[64] = total); a lane's words ascend, so its row only moves forward.
-template <class Src>
-__device__ __forceinline__ void emit_wave_pairs(Src src, uint32_t total, uint32_t first, uint32_t step,
-                                                const uint32_t *rst, const uint32_t *rdg, const uint64_t *rsb,
-                                                uint32_t *__restrict__ out) {
-    uint32_t t = 0, d = rdg[0], k0 = 0;
-    uint64_t s0 = rsb[0];
-    for (uint32_t o = first; o < total; o += step) {
-        // row t: the largest with rst[t] <= o (a row without pairs shares its
-        // successor's start, so it is never the largest)
-        if (rst[t + 1] <= o) {
-            do {
-                ++t;
-            } while (rst[t + 1] <= o);
-            d = rdg[t];
-            k0 = rst[t];
-            s0 = rsb[t];
-        }
-        const uint32_t k = o - k0;
-        const uint32_t i = pair_first(d, k);
-        const uint32_t j = i + 1 + (k - i * (2 * d - i - 1) / 2);
-        out[o] = (src[s0 + i] << 16) | src[s0 + j];
-    }
-}
+// Pairs of a row of d entries whose smaller entry comes before entry i.
+__device__ __forceinline__ uint32_t pairs_before(uint32_t d, uint32_t i) { return i * (2 * d - i - 1) / 2; }
 
 __global__ __launch_bounds__(256) void k_pair_emit(const uint64_t *__restrict__ Lrow,
                                                     const uint64_t *__restrict__ row_ptr,
@@ -1176,98 +1127,138 @@ __global__ __launch_bounds__(256) void k_pair_emit(const uint64_t *__restrict__ 
                                                     uint32_t *__restrict__ pairs, uint32_t npass, uint32_t width,
                                                     unsigned long long *__restrict__ ghist,
                                                     const uint64_t *__restrict__ dsz) {
+    constexpr uint32_t kWavesHere = 256 / kWave;
     __shared__ uint32_t gh[kPairPasses][256];
+    __shared__ uint32_t entb[kWavesHere][kEmitIn];
+    __shared__ __attribute__((aligned(16))) uint32_t markb[kWavesHere][kEmitStage + 4];
     if (plan_aborted(dsz)) return;
     if (dsz) QL = dsz[PZ_QL];
     if (!list_map_used(Lrow, dsz)) Lrow = nullptr;
-    // per wave: the output stage, or (for waves whose pairs do not fit it)
-    // the rows' first output words, degrees and first entries
-    __shared__ uint64_t stgb[256 / kWave][kEmitStage / 2];
-    __shared__ uint32_t sinb[256 / kWave][kEmitIn];
-    static_assert(2 * kWave + (kWave + 2) + kWave <= kEmitStage, "row tables exceed the stage");  // 32-bit words
     const uint32_t tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
     const uint32_t dmask = (1u << width) - 1u;
 #pragma unroll
-    for (int k = 0; k < kPairPasses; ++k) gh[k][tid] = 0;
+    for (int k = 0; k < (int)kPairPasses; ++k) gh[k][tid] = 0;
     __syncthreads();
-    uint32_t *sin = sinb[w];
-    uint32_t *stg = reinterpret_cast<uint32_t *>(stgb[w]);
-    uint64_t *rsb = stgb[w];                                  // kWave entries
-    uint32_t *rst = reinterpret_cast<uint32_t *>(rsb + kWave);  // kWave + 1 entries
-    uint32_t *rdg = rst + kWave + 2;                          // kWave entries
-    for (uint64_t r0 = ((uint64_t)blockIdx.x * (256 / kWave) + w) * kWave; r0 < QL;
-         r0 += (uint64_t)gridDim.x * 256) {
+    uint32_t *ent = entb[w], *mark = markb[w];
+    uint32_t marked = kMarkParts;  // parts marked since the marks were cleared (at first: not cleared yet)
+    const auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    const auto count = [&](uint32_t a, uint32_t c) {
+        for (uint32_t q = 0; q < npass; ++q) atomicAdd(&gh[q][(a >> (width * q)) & dmask], c);
+    };
+    for (uint64_t r0 = ((uint64_t)blockIdx.x * kWavesHere + w) * kWave; r0 < QL; r0 += (uint64_t)gridDim.x * 256) {
         const uint64_t r = r0 + lane;
-        const uint32_t last = (uint32_t)(min(r0 + kWave, QL) - 1 - r0);  // lane of the wave's last row
-        uint64_t e0 = 0, e1 = 0;
+        uint64_t e0 = 0;
+        uint32_t deg = 0;
         if (r < QL) {
             const uint64_t rr = Lrow ? Lrow[r] : r;
             e0 = row_ptr[rr];
-            e1 = e0 + row_deg[rr];
+            deg = row_deg[rr];
         }
-        // the wave's first pair (wpo: scan of the 64-row groups' pair counts)
-        // and this row's pairs before it within the group; a list row has at
-        // most n <= kSampleMajorMaxN entries, so a wave's 64 rows hold fewer
-        // than 2^32 pairs
+        // the wave's first pair (wpo: scan of the 64-row groups' pair counts); a
+        // list row has at most n <= kSampleMajorMaxN entries, so 64 rows hold
+        // fewer than 2^32 pairs
         const uint64_t base = wpo[r0 / kWave];
-        const uint32_t deg = (uint32_t)(e1 - e0);
-        const uint32_t np = deg * (deg - (deg ? 1u : 0u)) / 2;
-        const uint32_t incl = (uint32_t)wave_incl_scan((uint64_t)np);
-        const uint32_t total = __shfl(incl, kWave - 1, kWave);
-        // the rows' samples in LDS: the whole span of the sample array when it
-        // fits (coalesced), else only the rows' own entries packed one after
-        // another (when the span has gaps: rows of other kinds or the ends of
-        // LDS ranges)
-        const uint64_t dincl = wave_incl_scan((uint64_t)deg);
-        const uint64_t dtot = __shfl(dincl, kWave - 1, kWave);
-        const uint64_t span0 = __shfl(e0, 0, kWave);
-        const uint64_t span1 = __shfl(e1, (int)last, kWave);
-        const bool whole = span1 - span0 <= kEmitIn;       // wave-uniform
-        const bool staged_in = whole || dtot <= kEmitIn;  // wave-uniform
-        uint64_t sb = e0;                                  // entry i of this row: src[sb + i]
-        if (whole) {
-            for (uint64_t k = lane; k < span1 - span0; k += kWave) sin[k] = ls[span0 + k];
-            sb = e0 - span0;
-        } else if (staged_in) {
-            const uint64_t off = dincl - deg;
-            for (uint32_t k = 0; k < deg; k += 4) {
-                uint32_t v[4];
+        const uint32_t np = deg > 1 ? deg * (deg - 1) / 2 : 0;
+        const uint32_t pin = wave_incl_scan_u32(np), ein = wave_incl_scan_u32(deg);
+        uint32_t b = 0, pb = 0, eb = 0, part = 0;  // rows, pairs, entries and parts before the part in hand
+        while (b < kWave) {
+            const uint64_t fit = __ballot(lane >= b && pin - pb <= kEmitStage && ein - eb <= kEmitIn);
+            const uint32_t c = (uint32_t)__popcll(fit);
+            if (c == 0) {  // row b alone, straight to memory
+                const uint32_t d = __shfl(deg, (int)b, kWave);
+                const uint32_t *s = ls + __shfl(e0, (int)b, kWave);
+                uint32_t *out = pairs + base + pb;
+                for (uint32_t k = (blockIdx.y + part) % gridDim.y; 2 * k < d; k += gridDim.y) {
+                    const uint32_t m = d - 1 - k, len = k == m ? m : d - 1;
+                    const uint32_t a1 = s[k], a2 = s[m];
+                    if (lane < 2 && (lane == 0 || k != m)) count(lane ? a2 : a1, lane ? k : m);
+                    uint32_t *o1 = out + pairs_before(d, k), *o2 = out + pairs_before(d, m);
+                    for (uint32_t u = lane; u < len; u += kWave) {
+                        const uint32_t v = s[u + 1 + (u < m ? k : 0)];
+                        if (u < m) o1[u] = a1 << 16 | v;
+                        else o2[u - m] = a2 << 16 | v;
+                    }
+                }
+            } else if (part % gridDim.y == blockIdx.y) {
+                const uint32_t end = b + c;
+                // the entries: one span of the sample array (the rows ascend), or,
+                // where rows of other kinds or the ends of ranges leave gaps that
+                // do not fit, row after row
+                const uint64_t span0 = __shfl(e0, (int)b, kWave);
+                const uint32_t lastrow = (uint32_t)(min(r0 + end, QL) - 1 - r0);
+                const uint64_t span = __shfl(e0 + deg, (int)lastrow, kWave) - span0;
+                const bool whole = span <= kEmitIn;  // wave-uniform
+                const bool mine = lane >= b && lane < end && r < QL;
+                uint32_t at = whole ? (uint32_t)(e0 - span0) : ein - deg - eb;
+                if (whole) {
+                    for (uint32_t k = lane; k < (uint32_t)span; k += kWave) ent[k] = ls[span0 + k];
+                } else if (mine) {
+                    for (uint32_t k = 0; k < deg; k += 4) {
+                        uint32_t v[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = k + u < deg ? ls[e0 + k + u] : 0u;
+                        for (int u = 0; u < 4; ++u) v[u] = k + u < deg ? ls[e0 + k + u] : 0u;
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (k + u < deg) sin[off + k + u] = v[u];
+                        for (int u = 0; u < 4; ++u)
+                            if (k + u < deg) ent[at + k + u] = v[u];
+                    }
+                }
+                if (marked == kMarkParts) {
+                    for (uint32_t k = lane; k < kEmitStage + 4; k += kWave) mark[k] = 0;
+                    marked = 0;
+                }
+                wave_sync();
+                const uint32_t gen = ++marked << kMarkPart;
+                // words are numbered from the 16-byte boundary before the first
+                const uint64_t first = base + pb;
+                const uint32_t shift = (uint32_t)first & 3u;
+                if (mine) {
+                    uint32_t o = pin - np - pb + shift;
+                    for (uint32_t i = 0; i + 1 < deg; ++i) {
+                        mark[o] = gen | o << kMarkEntry | (at + i);
+                        count(ent[at + i], deg - 1 - i);
+                        o += deg - 1 - i;
+                    }
+                }
+                wave_sync();
+                const uint32_t stop = shift + __shfl(pin, (int)end - 1, kWave) - pb;
+                uint32_t *out = pairs + (first - shift);
+                uint32_t carry = 0;
+                for (uint32_t o0 = 0; o0 < stop; o0 += 4 * kWave) {
+                    const uint32_t o = o0 + 4 * lane;
+                    uint4 m = o < stop ? *reinterpret_cast<const uint4 *>(mark + o) : uint4{0, 0, 0, 0};
+                    m.y = max(m.x, m.y);
+                    m.z = max(m.y, m.z);
+                    m.w = max(m.z, m.w);
+                    const uint32_t all = wave_incl_max(m.w);
+                    const uint32_t before = max(carry, wave_shift_up(all));
+                    carry = max(carry, (uint32_t)__builtin_amdgcn_readlane((int)all, kWave - 1));
+                    const auto word = [&](uint32_t v, uint32_t at_o) {
+                        v = max(v, before);
+                        const uint32_t e = v & ((1u << kMarkEntry) - 1u);
+                        const uint32_t start = (v >> kMarkEntry) & ((1u << (kMarkPart - kMarkEntry)) - 1u);
+                        return ent[e] << 16 | ent[min(e + 1 + (at_o - start), kEmitIn - 1)];
+                    };
+                    const uint4 v{word(m.x, o), word(m.y, o + 1), word(m.z, o + 2), word(m.w, o + 3)};
+                    if (o >= shift && o + 4 <= stop) {
+                        *reinterpret_cast<uint4 *>(out + o) = v;
+                    } else {
+                        if (o >= shift && o < stop) out[o] = v.x;
+                        if (o + 1 >= shift && o + 1 < stop) out[o + 1] = v.y;
+                        if (o + 2 >= shift && o + 2 < stop) out[o + 2] = v.z;
+                        if (o + 3 >= shift && o + 3 < stop) out[o + 3] = v.w;
+                    }
+                }
+                wave_sync();
             }
-            sb = off;
+            const uint32_t done = c ? c : 1;
+            b += done;
+            ++part;
+            pb = __shfl(pin, (int)b - 1, kWave);
+            eb = __shfl(ein, (int)b - 1, kWave);
         }
-        const bool fits = total <= kEmitStage;  // wave-uniform
-        if (!fits) {
-            rsb[lane] = sb;
-            rst[lane] = incl - np;
-            rdg[lane] = deg;
-            if (lane == 0) rst[kWave] = total;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (blockIdx.y == 0) {
-            if (staged_in) row_digit_totals(sin, sb, deg, gh, npass, width, dmask);
-            else row_digit_totals(ls, sb, deg, gh, npass, width, dmask);
-        }
-        if (fits && blockIdx.y > 0) {
-            // the first of the waves that share these rows writes them
-        } else if (fits) {
-            if (staged_in) stage_row_pairs(sin, sb, deg, incl - np, stg);
-            else stage_row_pairs(ls, sb, deg, incl - np, stg);
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            for (uint32_t k = lane; k < total; k += kWave) pairs[base + k] = stg[k];
-        } else if (staged_in) {
-            emit_wave_pairs(sin, total, blockIdx.y * kWave + lane, gridDim.y * kWave, rst, rdg, rsb, pairs + base);
-        } else {
-            emit_wave_pairs(ls, total, blockIdx.y * kWave + lane, gridDim.y * kWave, rst, rdg, rsb, pairs + base);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     unsigned long long *g = ghist + (uint64_t)(blockIdx.x % kGhistReplicas) * kMaxPasses * 256;

@@ -514,6 +514,40 @@ def test_few_long_list_rows(rows, most):
     assert_matches(res, ref)
 
 
+@pytest.mark.parametrize("deg", [(2, 2), (2, 9), (30, 60), (43, 44), (64, 65), (150, 200)])
+def test_list_pairs_word_by_word(deg):
+    """Pairs of list rows from two samples to more than one LDS stage of pairs
+    (896) and from few to many rows per wave, with gaps between the rows (IDs of
+    one sample): every stored pair word, ordered by the smaller sample."""
+    rng = np.random.default_rng(deg[1])
+    n, rows = 211, 700 if deg[1] < 100 else 150
+    ids = rng.choice(1 << 24, rows, replace=False).astype(np.uint64)
+    holders = [np.sort(rng.choice(n, int(rng.integers(deg[0], deg[1] + 1)), replace=False)) for _ in range(rows)]
+    member = np.zeros((n, rows), bool)
+    for r, h in enumerate(holders):
+        member[h, r] = True
+    sets = [np.unique(np.concatenate([ids[member[s]], rng.integers(1 << 24, 1 << 25, 20).astype(np.uint64)]))
+            for s in range(n)]
+    cids, off = csr(sets)
+    db, st = jas.encode(dev(cids), dev(off), universe_bits=25, dense_min_degree=1000)
+    pairs = cabi.jas_db_read(db, cabi.JAS_DB_LIST_PAIRS)
+    out = jas.gram(db)
+    torch.cuda.synchronize()
+    db.close()
+    assert_matches({k: v.cpu().numpy() for k, v in out.items()}, oracle.all_pairs(cids, off))
+    uniq, inv = np.unique(cids, return_inverse=True)
+    smp = np.repeat(np.arange(n), np.diff(off.astype(np.int64)))
+    want = []
+    for r in np.flatnonzero(np.bincount(inv) > 1):
+        h = np.sort(smp[inv == r])
+        i, j = np.triu_indices(h.size, 1)
+        want.append((h[i] << 16 | h[j]).astype(np.uint32))
+    want = np.concatenate(want)
+    assert st["n_list_pairs"] == want.size
+    assert np.all(np.diff((pairs >> np.uint32(16)).astype(np.int64)) >= 0)
+    assert np.array_equal(np.sort(pairs), np.sort(want))
+
+
 @pytest.mark.parametrize("rows", [1, 31, 33, 64, 65, 129])
 @pytest.mark.parametrize("word_bits", [32, 64])
 @pytest.mark.parametrize("dmin", [0, 2])
