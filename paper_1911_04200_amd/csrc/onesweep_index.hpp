@@ -24,7 +24,7 @@ JAS_HD inline uint32_t radix_of(uint32_t width) { return width > 8 ? kWideRadix 
 constexpr uint32_t kFlagA = 1u << 30;  // the tile's own count is available
 constexpr uint32_t kFlagP = 2u << 30;  // the inclusive prefix over tiles 0..t is available
 constexpr uint32_t kValMask = (1u << 30) - 1u;
-constexpr int kLookWindow = 4;  // predecessor tiles read per look-back step
+constexpr int kLookWindow = 3;  // predecessor tiles read per look-back step
 
 // Keys of tile t: [tile_first(t), tile_end(t)).
 JAS_HD inline uint64_t tile_first(uint64_t tile, uint32_t tile_keys) { return tile * tile_keys; }

@@ -165,7 +165,7 @@ __device__ __forceinline__ T const_load(const T *p) {
 using onesweep::kFlagA;
 using onesweep::kFlagP;
 using onesweep::kValMask;
-using onesweep::kLookWindow;  // 4 measured best of 4, 8, 16
+using onesweep::kLookWindow;  // three passes over 1.78 G keys: 18.9 ms with 3; 20.2 with 4, 19.5 with 2, 20.6 with 8
 constexpr uint32_t kMaxSpin = 1u << 20;  // bounded wait (~0.1 s of polls), then give up and flag
 
 __device__ __forceinline__ void status_store(uint32_t *p, uint32_t v) {
