@@ -40,9 +40,9 @@ constexpr int kRounds = 16;
 constexpr uint32_t kTile = kNT * kRounds;  // 4096
 constexpr uint64_t kChunk = 65536;         // elements per classify block
 constexpr int32_t kHistMax = 16384;        // LDS column histogram up to this n
-constexpr uint32_t kPackCols = 8192;       // LDS words per pack pass, at most
+constexpr uint32_t kPackCols = 10112;      // LDS words per pack pass, at most (two blocks per CU)
 constexpr uint32_t kPackLoads = 8;         // sample loads in flight per lane in k_pack
-constexpr uint32_t kPackFlat = 4096;       // k_pack: word rows with at most this many entries spread them over the block
+constexpr uint32_t kPackFlat = 6144;       // k_pack: word rows with at most this many entries deal them out one by one
 
 // ---------------------------------------------------------------------------
 // Keys of one chunk of entries per block, and the totals of every digit
@@ -902,80 +902,132 @@ __global__ void k_word_rows(uint64_t QD, const uint64_t *bpos, const uint64_t *b
     }
 }
 
-// One block per 64-bit row of W: OR the bits of its <= 64 rows into an LDS
+// G waves per 64-bit row of W: OR the bits of its <= 64 rows into an LDS
 // row of words and write it out.  With b = 64 a row of W is one word row;
 // with b = 32 it holds word rows 2w (bits 0..31) and 2w + 1 (bits 32..63),
 // each a 32-bit word per column, so the Gram kernels read both as one 64-bit
 // step (the AND + popcount, or the dot product, of a 64-bit element is the
-// sum over its two halves).  Wave 0 loads the rows' list starts and degrees
-// (lane t: the row of bit t) and scans them, then all threads walk the rows'
-// (row, sample) pairs in parallel (consecutive threads read consecutive
-// samples of a row).  Hw = word rows of b bits.  With a single batch (null wq0)
-// word row w simply holds packed rows [w * b, (w + 1) * b) of the QD there are.
-__global__ __launch_bounds__(kNT) void k_pack(uint64_t *__restrict__ W, uint64_t ldw, uint64_t H, uint64_t Hw,
-                                               uint32_t wb, const uint64_t *__restrict__ wq0,
-                                               const uint64_t *__restrict__ wq1, uint64_t QD,
-                                               const uint64_t *__restrict__ Drow,
-                                               const uint64_t *__restrict__ row_ptr,
-                                               const uint32_t *__restrict__ row_deg,
-                                               const uint32_t *__restrict__ S, uint32_t cols,
-                                               unsigned long long *st, const uint64_t *__restrict__ dsz) {
-    extern __shared__ unsigned long long lw[];
-    __shared__ uint64_t rstart[kWave + 1];  // exclusive prefix of the rows' degrees
-    __shared__ uint64_t rbase[kWave];       // first pair of each row in S
-    __shared__ uint8_t prow[kPackFlat];  // up to kPackFlat entries: the row of each entry
-    __shared__ uint32_t zsh[2];  // nonzero words of the row (b = 32: of each half)
-    const uint32_t tid = threadIdx.x, lane = lane_id();
+// sum over its two halves).  Hw = word rows of b bits.  With a single batch
+// (null wq0) word row w simply holds packed rows [w * b, (w + 1) * b) of the QD
+// there are.
+//
+// W's bytes bound it once the waits are out of the way, which is what the split
+// is for.  Every wave has the rows in its lanes (lane t: the row of bit t), so
+// nothing is passed through LDS but the words and a bitmap of where the rows'
+// entries start, and the next word row's are read while this one is packed.  An
+// entry's row is the number of starts at or before it.  Words are cleared as
+// they are written out.  Short word rows are a wave's work alone, without block
+// barriers; long ones are spread over a block large enough that two fill a CU.
+// 1.25 M rows of 1024 words (456 entries each): 7.9 ms with a block of 256
+// threads for each and its entries' rows spelled out in LDS, 3.5 ms now (10.2 GB
+// written); 65517 of 10112 (5960): 4.0, 2.1 ms (5.3 GB); 65536 of 4096 (17900):
+// 1.9 both ways; 1090 of 128: 0.033, 0.010 ms.
+template <int G>
+__global__ __launch_bounds__(G < 4 ? 256 : G * kWave) void k_pack(
+    uint64_t *__restrict__ W, uint64_t ldw, uint64_t H, uint64_t Hw, uint32_t wb, const uint64_t *__restrict__ wq0,
+    const uint64_t *__restrict__ wq1, uint64_t QD, const uint64_t *__restrict__ Drow,
+    const uint64_t *__restrict__ row_ptr, const uint32_t *__restrict__ row_deg, const uint32_t *__restrict__ S,
+    uint32_t cols, unsigned long long *st, const uint64_t *__restrict__ dsz) {
+    constexpr uint32_t kTeam = G * kWave, kTeams = kTeam < 256 ? 256 / kTeam : 1;
+    extern __shared__ __attribute__((aligned(16))) unsigned long long lds[];
     if (plan_aborted(dsz)) return;
+    const uint32_t team = threadIdx.x / kTeam, tid = threadIdx.x % kTeam, lane = lane_id(), wv = tid / kWave;
+    unsigned long long *lw = lds + team * cols;
+    unsigned long long *starts = lds + kTeams * cols + team * (kPackFlat / 64 + 1);  // bitmap of the rows' first entries
+    uint32_t *starts32 = reinterpret_cast<uint32_t *>(starts);
+    uint32_t *zsh = starts32 + kPackFlat / 32;  // nonzero words of the row (b = 32: of each half)
+    const auto sync = [] {
+        if constexpr (G == 1) {
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        } else {
+            __syncthreads();
+        }
+    };
     // planned: H is the capacity; rows from the actual count on are written as
     // zeros (they add nothing to the Gram product)
     const uint64_t Hv = dsz ? dsz[PZ_H] : H;
     if (!packed_map_used(Drow, dsz)) Drow = nullptr;
     if (dsz) Hw = dsz[PZ_HW];
-    unsigned long long nnz_acc = 0, f_acc = 0;  // this block's totals (thread 0)
-    for (uint64_t w = blockIdx.x; w < H; w += gridDim.x) {
+    uint64_t next_base = 0;
+    uint32_t next_deg = 0;
+    const auto read_rows = [&](uint64_t w) {
+        next_deg = 0;
+        if (w >= Hv) return;
+        const uint64_t ww = wb == 64 ? w : 2 * w + (lane >> 5);
+        if (ww >= Hw) return;
+        const uint64_t q0 = wq0 ? wq0[ww] : ww * wb, q1 = wq0 ? wq1[ww] : min(q0 + wb, QD);
+        const uint64_t q = q0 + (wb == 64 ? lane : lane & 31);
+        if (q >= q1) return;
+        const uint64_t r = Drow ? Drow[q] : q;
+        next_base = row_ptr[r];
+        next_deg = row_deg[r];
+    };
+    // starts: bits of the rows in next_deg (wave 0)
+    const auto mark_next = [&] {
+        const uint32_t inc = wave_incl_scan_u32(next_deg), at = inc - next_deg;
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+        if (next_deg && total <= kPackFlat) atomicOr(&starts32[at >> 5], 1u << (at & 31));
+    };
+    const uint64_t step = (uint64_t)gridDim.x * kTeams;
+    uint64_t w = (uint64_t)blockIdx.x * kTeams + team;
+    read_rows(w);
+    for (uint32_t i = tid; i < cols; i += kTeam) lw[i] = 0;
+    for (uint32_t i = tid; i < kPackFlat / 64 + 1; i += kTeam) starts[i] = 0;
+    sync();
+    if (wv == 0) mark_next();
+    sync();
+    unsigned long long nnz_acc = 0, f_acc = 0;  // this team's totals (its first thread)
+    for (; w < H; w += step) {
         if (w >= Hv) {
-            for (uint64_t i = tid; i < ldw; i += kNT) W[w * ldw + i] = 0;
+            for (uint64_t i = tid; i < ldw; i += kTeam) W[w * ldw + i] = 0;
             continue;
         }
-        if (tid < kWave) {
-            uint64_t q0 = 0, q1 = 0, qi = 0;  // this lane's row: qi, if below q1
-            const uint64_t ww = wb == 64 ? w : 2 * w + (lane >> 5);
-            if (ww < Hw) {
-                q0 = wq0 ? wq0[ww] : ww * wb;
-                q1 = wq0 ? wq1[ww] : min(q0 + wb, QD);
-            }
-            qi = q0 + (wb == 64 ? lane : lane & 31);
-            uint64_t base = 0, deg = 0;
-            if (qi < q1) {
-                const uint64_t r = Drow ? Drow[qi] : qi;
-                base = row_ptr[r];
-                deg = row_deg[r];
-            }
-            const uint64_t inc = wave_incl_scan(deg);
-            rstart[lane + 1] = inc;
-            if (lane == 0) rstart[0] = 0;
-            rbase[lane] = base;
-        }
-        if (tid < 2) zsh[tid] = 0;
+        const uint64_t base = next_base;
+        const uint32_t deg = next_deg;
+        read_rows(w + step);
+        const uint32_t inc = wave_incl_scan_u32(deg), first = inc - deg;
+        const uint32_t P = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+        const uint64_t delta = base - first;  // S position of entry f of this lane's row: delta + f
+        // rows fill the lanes from 0 on, or of each half (b = 32)
+        const uint32_t low = (uint32_t)__popc((uint32_t)__ballot(deg > 0));
+        uint32_t z0 = 0, z1 = 0;
         for (uint64_t c0 = 0; c0 < ldw; c0 += cols) {
             const uint32_t cn = (uint32_t)min((uint64_t)cols, ldw - c0);
-            for (uint32_t i = tid; i < cn; i += kNT) lw[i] = 0;
-            __syncthreads();
-            const uint64_t P = rstart[kWave];
-            if (P > kPackFlat) {
-                // long rows (more than kPackFlat entries in all): the lanes of
-                // a wave walk one row at a time
-                // (kPackLoads loads in flight per lane before their ORs; a
-                // sample of ~0u lies past every chunk)
-                const uint32_t wv = tid / kWave;
-                for (uint32_t t = wv; t < kWave; t += kNT / kWave) {
-                    const uint64_t rb = rbase[t], dg = rstart[t + 1] - rstart[t];
-                    for (uint64_t e0 = lane; e0 < dg; e0 += (uint64_t)kWave * kPackLoads) {
+            if (P <= kPackFlat) {
+                // kPackLoads entries per lane in flight before their ORs; a sample
+                // of ~0u lies past every chunk
+                for (uint32_t c = wv; c * kWave < P; c += G * kPackLoads) {
+                    uint32_t v[kPackLoads], row[kPackLoads];
+#pragma unroll
+                    for (uint32_t u = 0; u < kPackLoads; ++u) {
+                        const uint32_t f0 = (c + u * G) * kWave, f = f0 + lane;
+                        v[u] = ~0u;
+                        row[u] = 0;
+                        if (f0 < P) {  // wave-uniform
+                            const uint64_t m = starts[f0 / kWave];
+                            uint32_t t = (uint32_t)__popcll(__ballot(deg > 0 && first < f0)) + lanes_before(m) +
+                                         (uint32_t)((m >> lane) & 1) - 1;
+                            t += t >= low ? kWave / 2 - low : 0;
+                            const uint64_t at = __shfl(delta, (int)t, kWave) + f;
+                            row[u] = t;
+                            if (f < P) v[u] = S[at];
+                        }
+                    }
+#pragma unroll
+                    for (uint32_t u = 0; u < kPackLoads; ++u)
+                        if (v[u] >= c0 && v[u] < c0 + cn) atomicOr(&lw[v[u] - c0], 1ull << row[u]);
+                }
+            } else {
+                // many entries: the lanes of a wave walk one row at a time
+                for (uint32_t t = wv; t < kWave; t += G) {
+                    const uint64_t rb = __shfl(base, (int)t, kWave);
+                    const uint32_t dg = __shfl(deg, (int)t, kWave);
+                    for (uint32_t e0 = lane; e0 < dg; e0 += kWave * kPackLoads) {
                         uint32_t v[kPackLoads];
 #pragma unroll
                         for (uint32_t u = 0; u < kPackLoads; ++u) {
-                            const uint64_t e = e0 + (uint64_t)u * kWave;
+                            const uint32_t e = e0 + u * kWave;
                             v[u] = e < dg ? S[rb + e] : ~0u;
                         }
 #pragma unroll
@@ -983,56 +1035,45 @@ __global__ __launch_bounds__(kNT) void k_pack(uint64_t *__restrict__ W, uint64_t
                             if (v[u] >= c0 && v[u] < c0 + cn) atomicOr(&lw[v[u] - c0], 1ull << t);
                     }
                 }
-            } else {
-                // up to kPackFlat entries: one thread per entry, its row read from prow
-                // (filled by the waves a row at a time, once per word row);
-                // kPackLoads entries per thread in flight
-                if (c0 == 0) {
-                    for (uint32_t t = tid / kWave; t < kWave; t += kNT / kWave)
-                        for (uint32_t e = (uint32_t)rstart[t] + lane; e < (uint32_t)rstart[t + 1]; e += kWave)
-                            prow[e] = (uint8_t)t;
-                    __syncthreads();
-                }
-                for (uint64_t p0 = tid; p0 < P; p0 += (uint64_t)kNT * kPackLoads) {
-                    uint32_t v[kPackLoads], row[kPackLoads];
-#pragma unroll
-                    for (uint32_t u = 0; u < kPackLoads; ++u) {
-                        const uint64_t p = p0 + (uint64_t)u * kNT;
-                        const uint32_t lo = p < P ? prow[p] : 0u;
-                        row[u] = lo;
-                        v[u] = p < P ? S[rbase[lo] + (p - rstart[lo])] : ~0u;
-                    }
-#pragma unroll
-                    for (uint32_t u = 0; u < kPackLoads; ++u)
-                        if (v[u] >= c0 && v[u] < c0 + cn) atomicOr(&lw[v[u] - c0], 1ull << row[u]);
-                }
             }
-            __syncthreads();
-            uint32_t zl = 0, zh = 0;
-            for (uint32_t i = tid; i < cn; i += kNT) {
-                const unsigned long long v = lw[i];
-                W[w * ldw + c0 + i] = v;
+            sync();
+            if (wv == 0 && c0 + cn == ldw) {  // the bitmap is the next row's from here on
+                if (deg && P <= kPackFlat) starts32[first >> 5] = 0;
+                mark_next();
+            }
+            // a wave's 128 words of a round are all below cn or all past it
+            for (uint32_t i = 2 * tid; i < cn; i += 2 * kTeam) {
+                const ulonglong2 v = *reinterpret_cast<const ulonglong2 *>(lw + i);
+                *reinterpret_cast<ulonglong2 *>(lw + i) = ulonglong2{0, 0};
+                *reinterpret_cast<ulonglong2 *>(W + w * ldw + c0 + i) = v;
                 if (wb == 64) {
-                    zl += v != 0;
+                    z0 += (uint32_t)(__popcll(__ballot(v.x != 0)) + __popcll(__ballot(v.y != 0)));
                 } else {
-                    zl += (uint32_t)v != 0;
-                    zh += (v >> 32) != 0;
+                    z0 += (uint32_t)(__popcll(__ballot((uint32_t)v.x != 0)) + __popcll(__ballot((uint32_t)v.y != 0)));
+                    z1 += (uint32_t)(__popcll(__ballot((v.x >> 32) != 0)) + __popcll(__ballot((v.y >> 32) != 0)));
                 }
             }
-            if (zl) atomicAdd(&zsh[0], zl);
-            if (zh) atomicAdd(&zsh[1], zh);
-            __syncthreads();
+            if (G > 1 && c0 + cn == ldw && lane == 0) {
+                if (z0) atomicAdd(&zsh[0], z0);
+                if (z1) atomicAdd(&zsh[1], z1);
+            }
+            sync();
         }
         if (tid == 0) {
-            const unsigned long long z0 = zsh[0], z1 = zsh[1];
-            nnz_acc += z0 + z1;
-            f_acc += z0 * (z0 + 1) / 2 + z1 * (z1 + 1) / 2;
+            unsigned long long a = z0, b = z1;
+            if (G > 1) {  // (added to again only after the next row's first barrier)
+                a = zsh[0];
+                b = zsh[1];
+                zsh[0] = zsh[1] = 0;
+            }
+            nnz_acc += a + b;
+            f_acc += a * (a + 1) / 2 + b * (b + 1) / 2;
         }
-        __syncthreads();
     }
     if (tid == 0 && nnz_acc) {
-        atomicAdd(&st[ST_NNZW], nnz_acc);
-        atomicAdd(&st[ST_F], f_acc);
+        const uint32_t rep = (blockIdx.x * kTeams + team) % kStatReplicas;
+        atomicAdd(&st[kStatNnzw + rep], nnz_acc);
+        atomicAdd(&st[kStatF + rep], f_acc);
     }
 }
 
@@ -1365,6 +1406,38 @@ __global__ void k_plan_pairs(const uint64_t *npo, uint64_t gcap, uint64_t Pcap, 
 }
 
 // err bit 64: a set reaches the int32 bound (|X_i| >= limit)
+// k_pack with a wave, 4 or 8 waves per row of W: a wave where the row is short
+// and there are rows enough to fill the chip (16 waves per CU), 8 where its
+// words leave room for few blocks per CU (16 measured the same).  Column chunks
+// are of equal size (multiples of 128 words).
+template <int G>
+void launch_pack_waves(uint64_t H, uint32_t cols, hipStream_t s, uint64_t *W, uint64_t ldw, uint64_t Hw, uint32_t wb,
+                       const uint64_t *wq0, const uint64_t *wq1, uint64_t QD, const uint64_t *Drow,
+                       const uint64_t *row_ptr, const uint32_t *row_deg, const uint32_t *S, unsigned long long *st,
+                       const uint64_t *dsz) {
+    constexpr uint32_t threads = std::max(256, G * kWave), teams = threads / (G * kWave);
+    const size_t lds = teams * ((size_t)cols + kPackFlat / 64 + 1) * sizeof(uint64_t);
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>(div_up(H, (uint64_t)teams), G == 1 ? 2048 : 4096);
+    if (lds > 65536)
+        JAS_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_pack<G>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    k_pack<G><<<blocks, threads, lds, s>>>(W, ldw, H, Hw, wb, wq0, wq1, QD, Drow, row_ptr, row_deg, S, cols, st, dsz);
+}
+
+void launch_pack(uint64_t *W, uint64_t ldw, uint64_t H, uint64_t Hw, uint32_t wb, const uint64_t *wq0,
+                 const uint64_t *wq1, uint64_t QD, const uint64_t *Drow, const uint64_t *row_ptr,
+                 const uint32_t *row_deg, const uint32_t *S, unsigned long long *st, const uint64_t *dsz,
+                 hipStream_t s) {
+    const uint64_t nchunk = div_up(ldw, (uint64_t)kPackCols);
+    const uint32_t cols = (uint32_t)(div_up(div_up(ldw, nchunk), 128) * 128);
+    const auto go = [&](auto launch) {
+        launch(H, cols, s, W, ldw, Hw, wb, wq0, wq1, QD, Drow, row_ptr, row_deg, S, st, dsz);
+    };
+    if (ldw <= 1024 && H >= 4096) go(launch_pack_waves<1>);
+    else if (ldw <= 1024) go(launch_pack_waves<4>);
+    else go(launch_pack_waves<8>);
+}
+
 // Grid of k_pair_emit over QL list rows: a wave per 64 rows, and as many waves
 // sharing the same rows as bring the chip to about 8192 waves.
 dim3 pair_emit_grid(uint64_t QL) {
@@ -1864,15 +1937,9 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         }
         H = wb == 64 ? Hw : div_up(Hw, 2);
         db->W.alloc(H * ldw, s, &db->budget, false, "packed words");
-        // column chunks of equal size (multiples of 128): fewer LDS bytes per
-        // block than a full kPackCols chunk when ldw is not a multiple of it
-        const uint64_t nchunk = div_up(ldw, (uint64_t)kPackCols);
-        const uint32_t cols = (uint32_t)(div_up(div_up(ldw, nchunk), 128) * 128);
-        const uint32_t grid = (uint32_t)std::min<uint64_t>(H, 4096);
         {
             JAS_TIMED("pack", s);
-            k_pack<<<grid, kNT, cols * sizeof(unsigned long long), s>>>(db->W.p, ldw, H, Hw, wb, wq0.p, wq1.p, QD,
-                                                                        Drow.p, rptrp, rdegp, Sp, cols, st.p, nullptr);
+            launch_pack(db->W.p, ldw, H, Hw, wb, wq0.p, wq1.p, QD, Drow.p, rptrp, rdegp, Sp, st.p, nullptr, s);
         }
         check_launch("pack");
     }
@@ -2119,13 +2186,10 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
             JAS_TIMED("word_rows", st_);
             k_word_rows<<<b, 256, 0, st_>>>(QDc, p.bpos.p, p.bq.p, p.wbase.p, p.word_bits, p.wq0.p, p.wq1.p, dsz);
         });
-        const uint64_t nchunk = div_up(p.ldw, (uint64_t)kPackCols);
-        const uint32_t cols = (uint32_t)(div_up(div_up(p.ldw, nchunk), 128) * 128);
         {
             JAS_TIMED("pack", s);
-            k_pack<<<(uint32_t)std::min<uint64_t>(p.Hcap, 4096), kNT, cols * sizeof(unsigned long long), s>>>(
-                p.W.p, p.ldw, p.Hcap, p.Hwcap, p.word_bits, p.wq0.p, p.wq1.p, p.QDcap, p.Drow.p, p.rptr.p, p.rdeg.p,
-                reinterpret_cast<const uint32_t *>(F), cols, p.st.p, dsz);
+            launch_pack(p.W.p, p.ldw, p.Hcap, p.Hwcap, p.word_bits, p.wq0.p, p.wq1.p, p.QDcap, p.Drow.p, p.rptr.p,
+                        p.rdeg.p, reinterpret_cast<const uint32_t *>(F), p.st.p, dsz, s);
         }
         check_launch("pack (planned)");
     }

@@ -445,15 +445,18 @@ struct PlanState {
 };
 void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, hipStream_t s);
 // Encode counters (encode.hip): the totals, then kStatReplicas slots each for
-// rows and list pairs, which many blocks add to (one counter would serialise an
-// atomic from every block); add_replicas sums them once they are on the host.
+// those that many blocks add to (one counter would serialise an atomic from
+// every block); add_replicas sums them once they are on the host.
 enum { ST_PAIRS = 0, ST_ROWS, ST_NNZW, ST_F, ST_LISTPAIRS, ST_N };
 constexpr uint32_t kStatReplicas = 64;
-constexpr uint32_t kStatRows = ST_N, kStatLists = ST_N + kStatReplicas, kStatWords = ST_N + 2 * kStatReplicas;
+constexpr uint32_t kStatRows = ST_N, kStatLists = kStatRows + kStatReplicas, kStatNnzw = kStatLists + kStatReplicas,
+                   kStatF = kStatNnzw + kStatReplicas, kStatWords = kStatF + kStatReplicas;
 inline void add_replicas(uint64_t (&st)[kStatWords]) {
     for (uint32_t k = 0; k < kStatReplicas; ++k) {
         st[ST_ROWS] += st[kStatRows + k];
         st[ST_LISTPAIRS] += st[kStatLists + k];
+        st[ST_NNZW] += st[kStatNnzw + k];
+        st[ST_F] += st[kStatF + k];
     }
 }
 constexpr uint64_t kSplitTilePub = 256 * 8;  // rows per row-split tile

@@ -514,6 +514,35 @@ def test_few_long_list_rows(rows, most):
     assert_matches(res, ref)
 
 
+@pytest.mark.parametrize("n,rows,deg", [(20, 64 * 4096 + 5, (2, 5)), (200, 64 * 4096 - 63, (2, 5)), (300, 700, (90, 102)),
+                                        (1100, 700, (90, 102)), (1100, 130, (300, 700)), (10300, 200, (80, 110))])
+@pytest.mark.parametrize("word_bits", [32, 64])
+def test_packed_words_on_every_split(n, rows, deg, word_bits):
+    """W word by word: a wave, 4 or 8 waves per row of it, entries dealt out one by
+    one (up to 6144 in a row of W) or a packed row per wave, one and two column
+    chunks, a last word row that is not full."""
+    rng = np.random.default_rng(rows)
+    ids = np.sort(rng.choice(1 << 24, rows, replace=False).astype(np.uint64))
+    d = rng.integers(deg[0], deg[1] + 1, rows)
+    r = np.repeat(np.arange(rows), d)
+    smp = np.concatenate([rng.choice(n, k, replace=False) for k in d]) if rows < 1000 else None
+    if smp is None:  # distinct by steps below n / deg
+        k = np.arange(r.size) - np.repeat(np.cumsum(d) - d, d)
+        smp = (np.repeat(rng.integers(0, n, rows), d) + k * (n // (deg[1] + 1))) % n
+    order = np.lexsort((r, smp))
+    off = np.zeros(n + 1, np.uint64)
+    off[1:] = np.cumsum(np.bincount(smp, minlength=n))
+    db, st = jas.encode(dev(ids[r[order]]), dev(off), universe_bits=24, dense_min_degree=2, word_bits=word_bits)
+    W = cabi.jas_db_read(db, cabi.JAS_DB_WORDS)
+    db.close()
+    want = np.zeros((-(-rows // 64), -(-n // 128) * 128), np.uint64)
+    np.bitwise_or.at(want, (r // 64, smp), np.uint64(1) << (r % 64).astype(np.uint64))
+    assert st["n_packed_rows"] == rows and np.array_equal(W.reshape(want.shape), want)
+    halves = want.view(np.uint32).reshape(want.shape[0], -1, 2) if word_bits == 32 else want[:, :, None]
+    z = np.count_nonzero(halves, axis=1).astype(np.int64)
+    assert st["nnz_words"] == z.sum() and st["word_pairs_F"] == (z * (z + 1) // 2).sum()
+
+
 @pytest.mark.parametrize("deg", [(2, 2), (2, 9), (30, 60), (43, 44), (64, 65), (150, 200)])
 def test_list_pairs_word_by_word(deg):
     """Pairs of list rows from two samples to more than one LDS stage of pairs
