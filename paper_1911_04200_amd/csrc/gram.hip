@@ -567,13 +567,18 @@ __global__ void k_list_pairs(const uint64_t *__restrict__ lp, const uint32_t *__
 }
 
 // Row-list pairs sorted by their smaller sample a: block g takes pairs
-// [g*chunk, ...); for each run of one a in it, an LDS row cnt[b] counts the
-// rows holding both a and b, and each touched counter is added to row a of B
-// once (one atomic per touched pair and chunk instead of one per row and
-// pair).  Chunks of at least kPairChunk words, at most kPairBlocks of them:
+// [g*chunk, ...); for each run of one a in it of at least n/8 words, an LDS row
+// cnt[b] counts the rows holding both a and b, and each touched counter is added
+// to row a of B once (one atomic per touched pair and chunk instead of one per
+// row and pair).  A shorter run touches few counters twice, and finding its end,
+// waiting and looking through the counters take longer than its own atomics on
+// B; a chunk whose runs are that short on average is counted so as a whole.
+// Chunks of at least kPairChunk words, at most kPairBlocks of them:
 // longer chunks split a sample's run fewer times, so fewer atomics, but a block
-// takes its runs one after another (778 K words of 8192 samples: 0.83 ms as 48 blocks
-// of 16384 words, 0.19 ms as 760; 1.7 G words take the same either way).
+// takes its runs one after another.
+// 778 K words of 8192 samples: 0.83 ms as 48 blocks of 16384 words with LDS
+// counters for every run, 0.19 ms as 760, 0.028 ms directly; 1.7 G words of
+// 10000: 1.9 ms.
 constexpr uint64_t kPairChunk = 1024;
 constexpr uint64_t kPairBlocks = 4096;
 
@@ -583,16 +588,17 @@ __global__ __launch_bounds__(kPairCountNT) void k_pair_count(const uint32_t *__r
                                                      const uint64_t *__restrict__ dsz) {
     extern __shared__ uint32_t lds[];
     uint32_t *cnt = lds;  // n counters
-    // the counters a short run touched (n < 2^16): a short run has fewer than
-    // n/8 words, so at most n/8 entries
-    uint16_t *touched = reinterpret_cast<uint16_t *>(lds + n);
-    __shared__ uint32_t ntouched;
     __shared__ uint64_t seg_end;
     if (dsz) P = min(P, dsz[PZ_P]);  // a plan's db: P is the capacity, the count is on the device
     const uint64_t lo = (uint64_t)blockIdx.x * chunk, hi = min(P, lo + chunk);
     if (lo >= hi) return;
+    const auto add = [&](uint32_t w) { atomicAdd(B + out_index(w >> 16, w & 0xFFFFu, n, upper), 1); };
+    const uint64_t samples = (pairs[hi - 1] >> 16) - (pairs[lo] >> 16) + 1;
+    if ((hi - lo) * 8 < samples * n) {  // block-uniform
+        for (uint64_t p = lo + threadIdx.x; p < hi; p += blockDim.x) add(pairs[p]);
+        return;
+    }
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) cnt[i] = 0;
-    if (threadIdx.x == 0) ntouched = 0;
     __syncthreads();
     for (uint64_t s0 = lo; s0 < hi;) {
         const uint32_t a = pairs[s0] >> 16;
@@ -620,18 +626,16 @@ __global__ __launch_bounds__(kPairCountNT) void k_pair_count(const uint32_t *__r
         }
         __syncthreads();
         const uint64_t s1 = seg_end;
-        // A long run (at least n/8 words) counts without return and then
-        // scans its whole LDS row; a short one keeps a list of the counters it
-        // touched.  Words are read 16 bytes at a time (four per thread in
-        // flight); the buffer is 16-byte aligned, the unaligned ends by word.
-        const bool long_run = (s1 - s0) * 8 >= n;  // block-uniform
-        auto count = [&](uint32_t w) {
-            const uint32_t b = w & 0xFFFFu;
-            if (long_run) {
-                __hip_atomic_fetch_add(&cnt[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            } else if (atomicAdd(&cnt[b], 1u) == 0) {
-                touched[atomicAdd(&ntouched, 1u)] = (uint16_t)b;
-            }
+        if ((s1 - s0) * 8 < n) {  // block-uniform
+            for (uint64_t p = s0 + threadIdx.x; p < s1; p += blockDim.x) add(pairs[p]);
+            s0 = s1;
+            __syncthreads();  // seg_end is read
+            continue;
+        }
+        // Words are read 16 bytes at a time (four per thread in flight); the
+        // buffer is 16-byte aligned, the unaligned ends by word.
+        const auto count = [&](uint32_t w) {
+            __hip_atomic_fetch_add(&cnt[w & 0xFFFFu], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         };
         const uint64_t va = min(s1, (s0 + 3) & ~uint64_t(3));  // first aligned word (or s1)
         const uint64_t vb = max(va, s1 & ~uint64_t(3));        // end of the aligned body
@@ -657,24 +661,13 @@ __global__ __launch_bounds__(kPairCountNT) void k_pair_count(const uint32_t *__r
             }
         }
         __syncthreads();
-        if (long_run) {
-            for (uint32_t b = a + 1 + threadIdx.x; b < n; b += blockDim.x) {
-                const uint32_t c = cnt[b];
-                if (c) {
-                    atomicAdd(B + out_index(a, b, n, upper), (int32_t)c);
-                    cnt[b] = 0;
-                }
-            }
-        } else {
-            const uint32_t nt = ntouched;
-            for (uint32_t k = threadIdx.x; k < nt; k += blockDim.x) {
-                const uint32_t b = touched[k];
-                atomicAdd(B + out_index(a, b, n, upper), (int32_t)cnt[b]);
+        for (uint32_t b = a + 1 + threadIdx.x; b < n; b += blockDim.x) {
+            const uint32_t c = cnt[b];
+            if (c) {
+                atomicAdd(B + out_index(a, b, n, upper), (int32_t)c);
                 cnt[b] = 0;
             }
         }
-        __syncthreads();
-        if (threadIdx.x == 0) ntouched = 0;
         s0 = s1;
         __syncthreads();
     }
@@ -702,7 +695,9 @@ __global__ void k_zero_flag(uint32_t *flag) { *flag = 0; }
 // mirror image.  Memory bound: 4 bytes read and 8 to 36 written per pair; the
 // tile goes through LDS so that the mirror's writes run along rows too, and B
 // is read once.  n = 8192 with J: 0.54 ms a row at a time
-// (the mirror half read B down columns), 0.27 ms by tiles.
+// (the mirror half read B down columns), 0.27 ms by tiles, 0.23 with stores
+// that do not stay in the caches (0.30 with 16 rows of tiles at a time, column by
+// column).
 constexpr uint32_t kFinT = 64;
 constexpr int kFinNT = 256;
 __global__ __launch_bounds__(kFinNT) void k_finalize(int32_t *__restrict__ B, const int64_t *__restrict__ card,
@@ -733,8 +728,8 @@ __global__ __launch_bounds__(kFinNT) void k_finalize(int32_t *__restrict__ B, co
     const auto put = [&](uint32_t i, uint32_t j, int64_t b, int64_t ca, int64_t cb) {
         const uint64_t pos = (uint64_t)i * n + j;
         const int64_t c = ca + cb - b;
-        if (den) den[pos] = c;
-        if (J) J[pos] = c == 0 ? 1.0 : (double)b / (double)c;
+        if (den) __builtin_nontemporal_store(c, den + pos);
+        if (J) __builtin_nontemporal_store(c == 0 ? 1.0 : (double)b / (double)c, J + pos);
     };
 #pragma unroll 4
     for (uint32_t k = 0; k < kSteps; ++k) {
@@ -756,25 +751,40 @@ __global__ __launch_bounds__(kFinNT) void k_finalize(int32_t *__restrict__ B, co
 
 // Packed upper layout: rows i and n-1-i share a row of blocks over their
 // n - i and i + 1 entries (n + 1 in all), so no thread of the grid is idle.
-__global__ void k_finalize_upper(int32_t *__restrict__ B, const int64_t *__restrict__ card, uint32_t n,
-                                 uint32_t jblocks, int64_t *__restrict__ den, double *__restrict__ J) {
+// kFinPer entries per thread, their loads in flight together: n = 10000 with J
+// 0.246 ms one at a time, 0.231 so (600 MB).
+constexpr uint32_t kFinPer = 4;
+__global__ __launch_bounds__(kFinNT) void k_finalize_upper(int32_t *__restrict__ B, const int64_t *__restrict__ card,
+                                                           uint32_t n, uint32_t jblocks, int64_t *__restrict__ den,
+                                                           double *__restrict__ J) {
     const uint32_t i0 = blockIdx.x / jblocks, i1 = n - 1 - i0;
-    const uint32_t t = (blockIdx.x % jblocks) * blockDim.x + threadIdx.x;
+    const uint32_t t0 = (blockIdx.x % jblocks) * kFinNT * kFinPer + threadIdx.x;
     const uint32_t len0 = n - i0;  // entries of row i0
-    if (t >= (i0 == i1 ? len0 : n + 1)) return;
-    const uint32_t i = t < len0 ? i0 : i1;
-    const uint32_t j = t < len0 ? i0 + t : i1 + (t - len0);
-    const uint64_t pos = out_index(i, j, n, true);
-    int64_t b;
-    if (i == j) {
-        b = card[i];
-        B[pos] = (int32_t)b;
-    } else {
-        b = B[pos];
+    const uint32_t len = i0 == i1 ? len0 : n + 1;
+    const uint64_t row0 = out_index(i0, i0, n, true), row1 = out_index(i1, i1, n, true);
+    const int64_t c0 = card[i0], c1 = card[i1];
+    int32_t v[kFinPer];
+    int64_t cj[kFinPer];
+#pragma unroll
+    for (uint32_t k = 0; k < kFinPer; ++k) {
+        const uint32_t t = t0 + k * kFinNT;
+        const bool first = t < len0;
+        v[k] = t < len ? B[first ? row0 + t : row1 + (t - len0)] : 0;
+        cj[k] = t < len ? card[first ? i0 + t : i1 + (t - len0)] : 0;
     }
-    const int64_t c = card[i] + card[j] - b;
-    if (den) den[pos] = c;
-    if (J) J[pos] = c == 0 ? 1.0 : (double)b / (double)c;
+#pragma unroll
+    for (uint32_t k = 0; k < kFinPer; ++k) {
+        const uint32_t t = t0 + k * kFinNT;
+        if (t >= len) break;
+        const bool first = t < len0;
+        const uint32_t off = first ? t : t - len0;  // column minus row
+        const uint64_t pos = (first ? row0 : row1) + off;
+        const int64_t ci = first ? c0 : c1, b = off ? v[k] : ci;
+        if (off == 0) B[pos] = (int32_t)b;
+        const int64_t c = ci + cj[k] - b;
+        if (den) __builtin_nontemporal_store(c, den + pos);
+        if (J) __builtin_nontemporal_store(c == 0 ? 1.0 : (double)b / (double)c, J + pos);
+    }
 }
 
 // Tile variants of the MFMA Gram: word rows per step of the int8 K loops, and
@@ -889,11 +899,12 @@ void finalize(uint32_t n, bool upper, hipStream_t s, int32_t *B, const int64_t *
     if (n == 0) return;
     if (upper) {
         // pairs of rows (i, n-1-i), the middle row alone when n is odd
-        const uint32_t jb = (uint32_t)div_up((uint64_t)n + 1, 256);
+        const uint32_t jb = (uint32_t)div_up((uint64_t)n + 1, kFinNT * kFinPer);
         const uint64_t fb = div_up((uint64_t)n, 2) * jb;
-        if (fb > 0xFFFFFFFFull) fail(JAS_EUNSUPPORTED, "n too large for finalize grid");
+        if (div_up((uint64_t)n, 2) * div_up((uint64_t)n + 1, 256) > 0xFFFFFFFFull)
+            fail(JAS_EUNSUPPORTED, "n too large for finalize grid");
         JAS_TIMED("finalize", s);
-        k_finalize_upper<<<(uint32_t)fb, 256, 0, s>>>(B, card, n, jb, den, J);
+        k_finalize_upper<<<(uint32_t)fb, kFinNT, 0, s>>>(B, card, n, jb, den, J);
     } else {
         const uint32_t nt = (uint32_t)div_up(n, kFinT);
         const uint64_t fb = (uint64_t)nt * (nt + 1) / 2;
@@ -992,7 +1003,7 @@ void gram(const jas_db *db, uint32_t flags, hipStream_t s, int32_t *B, int64_t *
         const uint64_t chunk = std::max<uint64_t>(kPairChunk, div_up(db->n_lpairs, kPairBlocks));
         const uint64_t blocks = div_up(db->n_lpairs, chunk);
         if (blocks > 0xFFFFFFFFull) fail(JAS_EUNSUPPORTED, "row lists too long");
-        const size_t lds = (size_t)n * sizeof(uint32_t) + ((size_t)n / 8 + 1) * sizeof(uint16_t);
+        const size_t lds = (size_t)n * sizeof(uint32_t);
         {
             JAS_TIMED("pair_count", s);
             k_pair_count<<<(uint32_t)blocks, kPairCountNT, lds, s>>>(db->pairs.p, db->n_lpairs, chunk, n, B, upper, db->dsz);

@@ -387,7 +387,7 @@ struct SortPlan {
 };
 constexpr uint64_t kBucketKeys = 512;
 constexpr uint32_t kSpanBits = 4;
-constexpr int32_t kSampleMajorMaxN = 10240;  // LDS row of per-sample counters (6 bytes each); < 2^16
+constexpr int32_t kSampleMajorMaxN = 10240;  // LDS row of per-sample counters (4 bytes each); < 2^16
 constexpr uint32_t kLocalCapKeys = 6144;   // most keys one LDS range can hold
 constexpr uint32_t kLocalShortCap = 4096;  // ranges no longer than this run four blocks per CU (else three)
 // Range strides the encoder tries in turn until no range exceeds

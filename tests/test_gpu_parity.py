@@ -514,6 +514,36 @@ def test_few_long_list_rows(rows, most):
     assert_matches(res, ref)
 
 
+@pytest.mark.parametrize("n", [1, 2, 3, 255, 256, 511, 512, 1023, 1024, 1025])
+def test_upper_outputs_at_block_edges(n):
+    rng = np.random.default_rng(n)
+    sets = [np.unique(rng.integers(0, 2000, int(rng.integers(0, 12)))).astype(np.uint64) for _ in range(n)]
+    ids, off = csr(sets)
+    res, _ = gpu_all_pairs(ids, off, 11, upper=True)
+    assert_matches(res, oracle.all_pairs(ids, off), upper=True)
+
+
+@pytest.mark.parametrize("run", [3, 37, 38, 40, 1500])
+def test_pair_runs_counted_directly_or_in_lds(run):
+    """Runs of one smaller sample just below and above n / 8 pairs (300 samples),
+    alone and among long ones, full and upper layout."""
+    rng = np.random.default_rng(run)
+    n, sets = 300, [[] for _ in range(300)]
+    nid = 0
+    for a in range(0, 290, 2):
+        for k in range(run if a % 10 else 2 * run):
+            b = int(rng.integers(a + 1, n)) if k % 3 else a + 1
+            sets[a].append(nid)
+            sets[b].append(nid)
+            nid += 1
+    ids, off = csr([np.array(s, dtype=np.uint64) for s in sets])
+    ref = oracle.all_pairs(ids, off)
+    for upper in (False, True):
+        res, st = gpu_all_pairs(ids, off, 20, 0, 1000, upper=upper)
+        assert st["n_list_pairs"] == nid
+        assert_matches(res, ref, upper=upper)
+
+
 @pytest.mark.parametrize("n,rows,deg", [(20, 64 * 4096 + 5, (2, 5)), (200, 64 * 4096 - 63, (2, 5)), (300, 700, (90, 102)),
                                         (1100, 700, (90, 102)), (1100, 130, (300, 700)), (10300, 200, (80, 110))])
 @pytest.mark.parametrize("word_bits", [32, 64])
