@@ -74,7 +74,7 @@ __global__ void k_rank_buckets(const uint64_t *__restrict__ distinct, uint64_t D
 // what a rank needs is put in one 64-byte line: the word start | count << 48 and,
 // in ascending order, the 16 ID bits below the bucket's of up to 28 IDs.  A
 // search of the 8-byte IDs through a bucket table read two to three 128-byte
-// lines (134 M IDs, 39 M distinct: 11.1 ms, 6.2 now).  A bucket with more IDs is
+// lines (134 M IDs, 39 M distinct: 11.1 ms, 5.6 now).  A bucket with more IDs is
 // marked by the count kFullLine and searched in the distinct IDs.
 constexpr uint32_t kLineIds = 28, kLineWords = 8;  // 8-byte words of a line
 constexpr uint64_t kFullLine = 0xFFFF, kStartMask = (uint64_t(1) << 48) - 1;
@@ -108,31 +108,42 @@ __global__ void k_rank_lines(const uint64_t *__restrict__ distinct, const uint64
 }
 
 // out[i] = rank of ids[i] among the distinct IDs (out may be ids); every ID is
-// one of them.
+// one of them, so the only one of the bucket with its 16 bits needs no look at
+// the distinct IDs themselves.  The line is read whole, at once: it is gone from
+// the cache when a second read of it would follow.
+// 134 M IDs, 39 M distinct: 6.2 ms with the line's first word, then the one the
+// ID was expected in, then the ID itself; 5.6 ms so.  (Half the lines, 18 IDs each
+// on average: 7.9, too many are full.)
 __global__ void k_rank(const uint64_t *ids, uint64_t N, const uint64_t *__restrict__ distinct,
                        const uint64_t *__restrict__ bucket, const uint64_t *__restrict__ lines, uint32_t shift,
                        uint64_t *out) {
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (uint64_t)gridDim.x * blockDim.x) {
         const uint64_t id = ids[i], b = shift >= 64 ? 0 : id >> shift;
-        const uint64_t *line = lines + b * kLineWords;
-        const uint64_t head = line[0], start = head & kStartMask, cnt = head >> 48;
+        const uint4 *line = reinterpret_cast<const uint4 *>(lines + b * kLineWords);
+        const uint4 q[4] = {line[0], line[1], line[2], line[3]};
+        const uint64_t head = (uint64_t)q[0].y << 32 | q[0].x, start = head & kStartMask, cnt = head >> 48;
         if (cnt == kFullLine) {
             out[i] = lower_bound_from(distinct, start, bucket[b + 1], id, shift ? id << (64 - shift) : 0);
             continue;
         }
-        // the first of the bucket's IDs whose bits are >= r: from the word where
-        // it is expected, a word at a time
-        const uint32_t r = line_bits(id, shift), nw = (uint32_t)(cnt + 3) / 4;  // >= 1 word
-        uint32_t w = shift >= 16 ? (uint32_t)((r * (uint32_t)cnt) >> 18) : 0;
-        uint64_t v = line[1 + w];
-        while (w > 0 && (v & 0xFFFFu) >= r) v = line[1 + --w];  // may start in an earlier word
-        while (w + 1 < nw && (v >> 48) < r) v = line[1 + ++w];
-        uint32_t below = 0;
+        const uint32_t r = line_bits(id, shift);
+        uint32_t below = 0, upto = 0;
+        const auto take = [&](uint32_t v) {
+            below += (uint32_t)((v & 0xFFFFu) < r) + (uint32_t)((v >> 16) < r);
+            upto += (uint32_t)((v & 0xFFFFu) <= r) + (uint32_t)((v >> 16) <= r);
+        };
+        take(q[0].z);
+        take(q[0].w);
 #pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) below += ((uint32_t)(v >> (16 * k)) & 0xFFFFu) < r;
-        uint64_t pos = start + 4 * w + below;
+        for (int k = 1; k < 4; ++k) {
+            take(q[k].x);
+            take(q[k].y);
+            take(q[k].z);
+            take(q[k].w);
+        }
+        uint64_t pos = start + below;
         // IDs that agree in the 16 bits too: compared whole
-        if (shift > 16)
+        if (shift > 16 && upto - below > 1)
             while (pos + 1 < start + cnt && distinct[pos] < id) ++pos;
         out[i] = pos;
     }
