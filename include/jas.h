@@ -148,8 +148,8 @@ jas_status jas_encode(const uint64_t *ids, const uint64_t *offsets, int32_t n, c
  * of word rows, and is used by later calls without the flag.  Not capturable
  * in a HIP graph; calls without it are.  JAS_GRAM_VARIANT(v) runs variant v
  * instead of the kept or default choice (EINVAL for v out of range).  The
- * default, with nothing kept, is fp4 with 128 x 128 tiles below n = 2048 and
- * 256 x 256 tiles from there on.
+ * default, with nothing kept, is fp4 with 128 x 128 tiles and a K split chosen
+ * from the numbers of tiles and word rows.
  * JAS_ACCUMULATE (row batches streamed one db at a time, the sum over batches
  * l of Eq. (4)): B_ij (i < j) and card_i are added to instead of written, and
  * nothing else is written: card is required, den and J must be NULL, and
@@ -238,8 +238,8 @@ jas_status jas_kmers(const uint64_t *seq, const uint64_t *seq_off, int64_t n_seq
  *  out     uint64[n_ids], device; may be ids itself.
  *  n_distinct, new_universe_bits  host outputs (may be NULL): D, and
  *          max(1, ceil(log2 D)), the universe_bits to encode the result with.
- * Sorts a copy of the IDs on hip_stream (2 x 8 bytes per ID of temporaries)
- * and synchronises it.
+ * Sorts a copy of the IDs on hip_stream (two arrays of 8 bytes per ID, and
+ * tables of up to 2 bytes per ID, as temporaries) and synchronises it.
  */
 jas_status jas_relabel(const uint64_t *ids, uint64_t n_ids, uint32_t universe_bits, void *hip_stream, uint64_t *out,
                        uint64_t *n_distinct, uint32_t *new_universe_bits);
