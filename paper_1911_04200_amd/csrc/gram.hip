@@ -575,8 +575,7 @@ __global__ void k_list_pairs(const uint64_t *__restrict__ lp, const uint32_t *__
 // B; a chunk whose runs are that short on average is counted so as a whole.
 // Chunks of at least kPairChunk words, at most kPairBlocks of them:
 // longer chunks split a sample's run fewer times, so fewer atomics, but a block
-// takes its runs one after another.
-// 778 K words of 8192 samples: 0.83 ms as 48 blocks of 16384 words with LDS
+// takes its runs one after another.  778 K words of 8192 samples: 0.83 ms as 48 blocks of 16384 words with LDS
 // counters for every run, 0.19 ms as 760, 0.028 ms directly; 1.7 G words of
 // 10000: 1.9 ms.
 constexpr uint64_t kPairChunk = 1024;

@@ -3,10 +3,11 @@
 // Every device buffer the library uses comes from here.  A freed block is
 // kept, tagged with the stream that last used it and its event, recorded on that
 // stream (an event is made once per block: creating and destroying one per
-// free cost more than recording it); a later request reuses it on the same stream directly, or on another
-// stream after making that stream wait for the event.  Steady-state calls thus
-// never reach hipMalloc/hipFree, whose cost for multi-GB buffers is large and
-// erratic.  jas_trim() hands the cached blocks back to the device.
+// free cost more than recording it); a later request reuses it on the same
+// stream directly, or on another stream after making that stream wait for the
+// event.  Steady-state calls thus never reach hipMalloc/hipFree, whose cost for
+// multi-GB buffers is large and erratic.  jas_trim() hands the cached blocks
+// back to the device.
 #include <algorithm>
 #include <map>
 #include <mutex>

@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kNT) void k_radix_scatter(const uint64_t *__restric
 // Single-pass scatter with decoupled look-back (chained scan: Merrill &
 // Garland, "Single-pass parallel prefix scan with decoupled look-back",
 // 2016; as in Adinets & Merrill's Onesweep, 2022).  Persistent blocks take
-// 8192-key tiles by ticket from an atomic counter in launch order, so every
+// tiles by ticket from an atomic counter in launch order, so every
 // tile a block waits for already belongs to a running block.  Per tile and
 // digit a 32-bit status word holds a flag (aggregate / inclusive prefix) and
 // a 30-bit count; the caller guarantees every digit total is < 2^30.  The
