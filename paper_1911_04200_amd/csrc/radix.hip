@@ -214,7 +214,7 @@ __device__ __forceinline__ K buffer_key(Rsrc r, uint32_t off) {
 // rounds waited for each other's counters and 16 keys per thread, 23.3 with
 // unrolled ballots, 20.7 with 32 (24) keys per thread: 4.1 TB/s of the 6.2 a
 // copy through such tiles reaches.  1.85 G pair words, two passes: 12.2, 11.0,
-// 8.8.  A tile's time (paperlike, 16384 keys): loads and ranks 37 %, look-back
+// 8.8 (8.3 with 64).  A tile's time (paperlike, 16384 keys): loads and ranks 37 %, look-back
 // 23 %, writes 16 %, counts and scan 12 %, placing 8 %.
 template <class K, int R, int NB, bool kFromIds = false>
 __global__ __launch_bounds__(kOsNT) __attribute__((amdgpu_waves_per_eu(4))) void k_radix_onesweep(
@@ -555,9 +555,13 @@ void tile_samples(const KeySource &src, uint64_t Ncap, uint32_t tile_keys, const
 
 // Keys per thread of a tile: 32, or 24 in the pass that forms the keys (it
 // holds more, and 32 would spill), except where that leaves fewer than two
-// tiles for each resident block (then 16: more, shorter tiles).
-int tile_rounds(uint64_t N, bool from_ids) {
-    return N < (uint64_t)4 * 256 * kOsNT * 32 ? 16 : from_ids ? 24 : 32;
+// tiles for each resident block (then 16: more, shorter tiles); 64 for 32-bit
+// keys where that leaves two.  Two passes over 1.68 G pair words: 7.9 ms with 32,
+// 8.0 with 40, 7.7 with 48, 7.6 with 56, 7.5 with 64 (5 registers spilled).
+int tile_rounds(uint64_t N, bool from_ids, size_t key_bytes = 8) {
+    const uint64_t two_tiles = (uint64_t)4 * 256 * kOsNT;
+    if (N < two_tiles * 32) return 16;
+    return from_ids ? 24 : key_bytes == 4 && N >= two_tiles * 64 ? 64 : 32;
 }
 // Most tiles of any pass of a sort of N keys.
 uint64_t most_tiles(uint64_t N) { return onesweep::num_tiles(N, (uint32_t)kOsNT * tile_rounds(N, true)); }
@@ -633,10 +637,11 @@ void onesweep_passes(const PassArgs &a, uint32_t lo_bit, uint32_t hi_bit, uint32
         if (!a.two && q > 0) clear(a.look_back + kTicketWords, status);
         {
             JAS_TIMED(name, a.s);
-            const int rounds = tile_rounds(a.N, a.src && q == 0);
+            const int rounds = tile_rounds(a.N, a.src && q == 0, sizeof(K));
             const K *in = a.first && q == 0 ? static_cast<const K *>(a.first) : keys;
-            if (rounds == 32) onesweep_digits<K, 32>(a, q, in, alt, bit, nbits);
-            else if (rounds == 24) onesweep_digits<K, 24>(a, q, in, alt, bit, nbits);
+            if (rounds == 64) onesweep_digits<K, sizeof(K) == 4 ? 64 : 32>(a, q, in, alt, bit, nbits);
+            else if (rounds == 32) onesweep_digits<K, 32>(a, q, in, alt, bit, nbits);
+            else if (rounds == 24) onesweep_digits<K, sizeof(K) == 8 ? 24 : 32>(a, q, in, alt, bit, nbits);
             else onesweep_digits<K, 16>(a, q, in, alt, bit, nbits);
         }
         check_launch("radix scatter (look-back)");

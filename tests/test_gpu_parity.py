@@ -348,6 +348,27 @@ def test_scatter_large_tiles(N):
     assert_matches(res, oracle.all_pairs(ids, off), upper=True)
 
 
+@pytest.mark.parametrize("rows", [380, 747, 748, 760])
+def test_pair_sort_tile_sizes(rows):
+    """17 M to 34 M pair words of 700 samples, two passes, below and above 2^25
+    words, where tiles hold 64 words per thread."""
+    rng = np.random.default_rng(rows)
+    n, deg = 700, 300
+    member = np.zeros((n, rows), np.int32)
+    for r in range(rows):
+        member[rng.choice(n, deg, replace=False), r] = 1
+    ids = np.sort(rng.choice(1 << 24, rows, replace=False).astype(np.uint64))
+    cids, off = csr([ids[m != 0] for m in member])
+    db, st = jas.encode(dev(cids), dev(off), universe_bits=24, dense_min_degree=1000)
+    out = jas.gram(db)
+    pairs = torch.from_numpy(cabi.jas_db_read(db, cabi.JAS_DB_LIST_PAIRS).view(np.int32)).cuda()
+    torch.cuda.synchronize()
+    db.close()
+    assert st["n_list_pairs"] == rows * deg * (deg - 1) // 2
+    assert bool((pairs[1:] >> 16 >= pairs[:-1] >> 16).all())
+    assert np.array_equal(out["B"].cpu().numpy(), member @ member.T)
+
+
 @pytest.mark.parametrize("U", [9, 10, 14, 17, 18, 19, 26, 40, 55])
 def test_lds_pass_widths(U):
     """The ID bits a range leaves for LDS are sorted in the fewest passes of at

@@ -51,9 +51,9 @@ def test_paperlike_size_in_bounds(emul, giveup):
         assert "giveups 0 " not in out
 
 
-@pytest.mark.parametrize("tile_keys", [12288, 16384])
+@pytest.mark.parametrize("tile_keys", [12288, 16384, 32768])
 def test_larger_tile_sizes_in_bounds(emul, tile_keys):
-    """The tiles of large sorts: 512 threads of 24 or 32 keys."""
+    """The tiles of large sorts: 512 threads of 24, 32 or 64 keys."""
     for n, widths, dist, giveup in ((3 * tile_keys, "8,8,6", "uniform", 0), (3 * tile_keys + 1, "7,7,7", "skew", 0),
                                     (1_000_003, "8,6", "uniform", 300)):
         assert "fails 0" in run(emul, n, tile_keys, widths, dist, giveup, tile_keys + giveup, "exact")
