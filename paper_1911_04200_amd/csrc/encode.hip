@@ -66,6 +66,7 @@ __device__ __forceinline__ void build_keys_chunk(const uint64_t *__restrict__ id
     const uint64_t b0 = (uint64_t)blockIdx.x * chunk;
     if (b0 >= N) return;  // a planned launch covers the largest N
     const uint64_t b1 = min(N, b0 + chunk);
+    constexpr uint32_t kAhead = 4;  // IDs in flight per thread: 1.78 G IDs 2.88 ms with one, 2.63 with 4, 2.68 with 8
     const uint32_t dmask = (1u << width) - 1u;
     for (uint32_t i = tid; i < npass * radix; i += kNT) gh[i] = 0;
     if (kWrite && tid == 0) {
@@ -85,8 +86,7 @@ __device__ __forceinline__ void build_keys_chunk(const uint64_t *__restrict__ id
     }
     uint32_t bad = 0;
     int32_t lo = kWrite ? s_lo : 0;
-    for (uint64_t t = b0 + tid; t < b1; t += kNT) {
-        const uint64_t id = ids[t];
+    const auto take = [&](uint64_t t, uint64_t id) {
         bad |= (id & hi_mask) != 0;
         if constexpr (kWrite) {
             lo = find_sample(off, lo, s_hi, t);  // t only grows, so the search range only shrinks
@@ -107,7 +107,16 @@ __device__ __forceinline__ void build_keys_chunk(const uint64_t *__restrict__ id
             for (uint32_t q = 0; q < npass; ++q)
                 atomicAdd(&gh[q * radix + ((uint32_t)(id >> (idlo + width * q)) & dmask)], 1u);
         }
+    };
+    uint64_t t = b0 + tid;
+    for (; t + (kAhead - 1) * kNT < b1; t += kAhead * kNT) {
+        uint64_t id[kAhead];
+#pragma unroll
+        for (uint32_t u = 0; u < kAhead; ++u) id[u] = ids[t + u * kNT];
+#pragma unroll
+        for (uint32_t u = 0; u < kAhead; ++u) take(t + u * kNT, id[u]);
     }
+    for (; t < b1; t += kNT) take(t, ids[t]);
     if (__ballot(bad) && lane_id() == 0) atomicOr(err, 1u);
     __syncthreads();
     unsigned long long *g = ghist + (uint64_t)(blockIdx.x % kGhistReplicas) * kMaxPasses * 256;
