@@ -1884,6 +1884,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         stream_after(s2, s);  // everything the pair path reads is on s so far
         join.waiter = s;
         join.on = s2;
+        join.armed = true;
         clear_words(Clear().add(pgh.p, (uint64_t)kGhistReplicas * kMaxPasses * 256).add(perr.p, 1), s2);
         {
             JAS_TIMED("pair_emit", s2);
@@ -1961,7 +1962,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         const bool ok = radix_sort_onesweep_u32(pk, palt, P, 16, 16 + psb, pwidth, pgh.p, perr.p, s2, tb);
         JAS_HIP(hipStreamSynchronize(s2));
         stream_after(s, s2);
-        join.waiter = nullptr;
+        join.armed = false;
         uint64_t got[1 + kStatWords];
         read_back(ReadBack().add(perr.p).add(st.p, kStatWords), got, s);
         std::copy(got + 1, got + 1 + kStatWords, hst);

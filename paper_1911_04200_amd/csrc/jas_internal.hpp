@@ -204,11 +204,13 @@ inline void set_tile_stats(jas_encode_stats &o, uint64_t n) {
 hipStream_t side_stream();
 // Makes `waiter` wait for the work enqueued on `on` so far.
 void stream_after(hipStream_t waiter, hipStream_t on);
-// While armed (waiter set), makes waiter wait for on when it goes out of
-// scope: declared after the buffers the work on `on` uses, so that on an
-// error the buffers' stream-ordered release comes after that work.
+// While armed, makes waiter wait for on when it goes out of scope: declared
+// after the buffers the work on `on` uses, so that on an error the buffers'
+// stream-ordered release comes after that work.  (A flag of its own: waiter may
+// be the null stream.)
 struct StreamJoin {
     hipStream_t waiter = nullptr, on = nullptr;
+    bool armed = false;
     StreamJoin() = default;
     StreamJoin(const StreamJoin &) = delete;
     StreamJoin &operator=(const StreamJoin &) = delete;

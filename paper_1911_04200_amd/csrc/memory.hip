@@ -204,7 +204,7 @@ void stream_after(hipStream_t waiter, hipStream_t on) {
 }
 
 StreamJoin::~StreamJoin() {
-    if (!waiter) return;
+    if (!armed) return;
     // an error is on its way out, and the buffers of both streams are freed
     // next: the host waits too
     (void)hipStreamSynchronize(on);

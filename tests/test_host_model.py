@@ -1,0 +1,96 @@
+"""The library's own host and device code run on the CPU under AddressSanitizer
+(tests/host_model): which memory its kernels touch, when its buffers are given
+back, and what is still running when a call returns.  Every buffer has exactly
+the size asked for and holds 0xFF bytes at first, and with lazy streams every
+kernel runs as late as the host's waits allow.  No GPU.
+"""
+import os
+import subprocess
+import sys
+
+import pytest
+
+sys.path.insert(0, os.path.join(os.path.dirname(os.path.abspath(__file__)), "host_model"))
+import model  # noqa: E402
+
+PRELUDE = r"""
+import sys
+import numpy as np
+import model
+jas, lib = model.attach(sys.argv[1])
+
+def collection(n, total, universe_bits, share, seed=3):
+    # about total IDs in n sets, part of each from one pool of a twentieth as many
+    rng = np.random.default_rng(seed)
+    pool = rng.integers(0, 1 << universe_bits, max(8, total // 20))
+    sets = []
+    for _ in range(n):
+        k = max(1, int(total / n * rng.uniform(.5, 1.5)))
+        m = int(k * share)
+        sets.append(np.concatenate([rng.choice(pool, m), rng.integers(0, 1 << universe_bits, k - m)]))
+    off = np.zeros(n + 1, np.uint64)
+    off[1:] = np.cumsum([s.size for s in sets])
+    return np.concatenate(sets).astype(np.uint64), off
+
+def intersections(ids, off):
+    n = off.size - 1
+    smp = np.repeat(np.arange(n), np.diff(off).astype(np.int64))
+    pairs = np.unique(np.stack([ids.astype(np.int64), smp]), axis=1)
+    row = np.unique(pairs[0], return_inverse=True)[1]
+    A = np.zeros((int(row.max()) + 1 if row.size else 1, n), np.float32)
+    A[row, pairs[1]] = 1
+    return (A.T @ A).astype(np.int32)
+
+def gram(db, n):
+    B = np.zeros((n, n), np.int32)
+    jas.jas_gram(db, jas.JAS_FORCE_POPCOUNT, None, B)
+    lib.model_drain()
+    return B
+"""
+
+
+@pytest.fixture(scope="module")
+def library(tmp_path_factory):
+    if model.compiler() is None:
+        pytest.skip("clang's AddressSanitizer runtime is not installed")
+    return model.build(str(tmp_path_factory.mktemp("host_model")))
+
+
+def run(library, script, *args):
+    lib, rt = library
+    r = subprocess.run([sys.executable, "-c", PRELUDE + script + "\nprint('DONE')", lib, *map(str, args)],
+                       env=model.environment(rt), capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0 and r.stdout.endswith("DONE\n"), (r.stdout[-2000:], r.stderr[:6000])
+    return r.stdout
+
+
+REFUSED = r"""
+n, total, ubits, share, batch, dmin, flags, wb = [int(a) for a in sys.argv[2:5]] + [float(sys.argv[5])] + [int(a) for a in sys.argv[6:10]]
+ids, off = collection(n, total, ubits, share)
+want = intersections(ids, off)
+opts = jas.jas_encode_opts(ubits, batch, dmin, flags, 0, wb)
+lib.model_lazy(1)
+for k in [-1] + list(range(lib.model_allocations() + 1000)):
+    lib.model_fail_at(k)
+    try:
+        db, _ = jas.jas_encode(ids, off, n, opts)
+    except jas.JasError as e:
+        assert e.status == jas.JAS_ENOMEM and "refused" in e.message, str(e)
+        lib.model_drain()  # (what is still enqueued uses freed buffers, if any were given back too early)
+        continue
+    lib.model_fail_at(-1)
+    assert np.array_equal(gram(db, n), want)
+    db.close()
+    if k >= 0:
+        break  # no allocation is left to refuse
+assert k > 15
+lib.model_drain()
+assert lib.model_live() == 0
+"""
+
+
+@pytest.mark.parametrize("dmin", [5, 1000])
+def test_encode_refused_at_every_allocation(library, dmin):
+    """Every allocation of an encode on the null stream refused in turn: work of
+    the library's own stream is waited for before its buffers are given back."""
+    run(library, REFUSED, 64, 16000, 30, 0.5, 0, dmin, 0, 64)
