@@ -1608,7 +1608,9 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
     };
 
     // Outputs of the classification: distinct keys (query index), shared
-    // pairs S in row order, and per shared row its ID and first pair.
+    // pairs S in row order, and per shared row its ID and first pair.  (The keys,
+    // and the pair words below, are the call's until the db takes them: on an
+    // error they go back to the cache in stream order, not as idle.)
     uint64_t NDk = 0, NS = 0, R = 0;
     DevBuf<uint64_t> Dk, rid_own, rptr_own;
     DevBuf<uint32_t> rdeg_own;
@@ -1676,7 +1678,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
             db->trace.local = true;
             db->trace.wide = (herr & 16u) != 0;
             db->trace.nlc = nlc;
-            if (keep) Dk.alloc(NDk, s, &db->budget, false, "query index keys");
+            if (keep) Dk.alloc(NDk, s, &db->budget, true, "query index keys");
             rid_own.alloc(R, s, tb, true, "row ids");
             rptr_own.alloc(R + 1, s, tb, true, "row pointers");
             rdeg_own.alloc(R + 1, s, tb, true, "row degrees");
@@ -1733,7 +1735,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         NDk = t3[0];
         NS = t3[1];
         R = t3[2];
-        if (keep) Dk.alloc(NDk, s, &db->budget, false, "query index keys");
+        if (keep) Dk.alloc(NDk, s, &db->budget, true, "query index keys");
         S_own.alloc(NS, s, tb, true, "shared pairs");
         rid_own.alloc(R, s, tb, true, "row ids");
         rptr_own.alloc(R + 1, s, tb, true, "row pointers");
@@ -1876,7 +1878,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         const uint32_t npass = (psb + 7) / 8;
         pwidth = (psb + npass - 1) / npass;
         if (npass > kPairPasses) fail(JAS_EUNSUPPORTED, "row-list pairs: too many sample bits");
-        pk.alloc(P + 2, s, &db->budget, false, "row-list pairs");
+        pk.alloc(P + 2, s, &db->budget, true, "row-list pairs");
         palt.alloc(P + 2, s, tb, true, "row-list pairs (second buffer)");
         pgh.alloc((uint64_t)kGhistReplicas * kMaxPasses * 256, s, tb, true, "pair digit totals");
         perr.alloc(2, s, tb, true, "pair sort flag");
@@ -1970,6 +1972,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         if (ok && (uint32_t)got[0] == 0) {
             db->n_lpairs = P;
             db->pairs = std::move(pk);
+            db->pairs.owned_by_db = true;
             pairs_done = true;
             db->trace.pairs = true;
             db->trace.P = P;
@@ -2024,6 +2027,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
                 }
             });
             db->keys = std::move(Dk);
+            db->keys.owned_by_db = true;
         }
         check_launch("query buckets");
     }

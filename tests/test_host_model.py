@@ -94,3 +94,9 @@ def test_encode_refused_at_every_allocation(library, dmin):
     """Every allocation of an encode on the null stream refused in turn: work of
     the library's own stream is waited for before its buffers are given back."""
     run(library, REFUSED, 64, 16000, 30, 0.5, 0, dmin, 0, 64)
+
+
+def test_query_keys_of_a_refused_encode(library):
+    """The same with a query index: its keys are still being written when a later
+    allocation is refused, so they are not idle when they go back."""
+    run(library, REFUSED, 64, 16000, 30, 0.5, 0, 1000, 2, 64)
