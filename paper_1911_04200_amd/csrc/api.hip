@@ -51,6 +51,19 @@ std::vector<uint64_t> host_offsets(const uint64_t *offsets, int32_t n, bool host
     return h;
 }
 
+// Runs f; on a failure the call's work on s ends before the error goes on: the
+// caller's arrays are then no longer read or written, and a db's buffers, which
+// return to the cache as idle, no longer in use.
+template <class F>
+void waited(hipStream_t s, F &&f) {
+    try {
+        f();
+    } catch (...) {
+        (void)hipStreamSynchronize(s);
+        throw;
+    }
+}
+
 }  // namespace
 
 void fail(jas_status st, const std::string &msg) { throw Error{st, msg}; }
@@ -222,63 +235,56 @@ jas_status jas_encode(const uint64_t *ids, const uint64_t *offsets, int32_t n, c
         db->budget.limit = opts->hbm_budget_bytes;
         db->budget.other = &tb;
 
-        // inputs on the device
-        DevBuf<uint64_t> ids_d, off_d;
-        const uint64_t *dids = ids, *doff = offsets;
-        if (host) {
-            off_d.alloc(n + 1, s, &tb, true, "offsets copy");
-            JAS_HIP(hipMemcpyAsync(off_d.p, hoff.data(), sizeof(uint64_t) * (n + 1), hipMemcpyHostToDevice, s));
-            doff = off_d.p;
+        waited(s, [&] {
+            // inputs on the device
+            DevBuf<uint64_t> ids_d, off_d;
+            const uint64_t *dids = ids, *doff = offsets;
+            if (host) {
+                off_d.alloc(n + 1, s, &tb, true, "offsets copy");
+                JAS_HIP(hipMemcpyAsync(off_d.p, hoff.data(), sizeof(uint64_t) * (n + 1), hipMemcpyHostToDevice, s));
+                doff = off_d.p;
+                if (N > 0) {
+                    ids_d.alloc(N, s, &tb, true, "ids copy");
+                    JAS_HIP(hipMemcpyAsync(ids_d.p, ids, sizeof(uint64_t) * N, hipMemcpyHostToDevice, s));
+                    dids = ids_d.p;
+                }
+            }
+            // Sort the keys on their top ID bits (the rest is finished per bucket
+            // range in LDS by encode_sorted).  Both buffers get two spare entries:
+            // after the sort the free one holds the shared pairs and row pointers.
+            DevBuf<uint64_t> keys, alt;
+            DevBuf<uint32_t> err;  // flags of the ID check and of the sort, checked by encode_sorted
+            const SortPlan plan = sort_plan(N, U, sbits);
             if (N > 0) {
-                ids_d.alloc(N, s, &tb, true, "ids copy");
-                JAS_HIP(hipMemcpyAsync(ids_d.p, ids, sizeof(uint64_t) * N, hipMemcpyHostToDevice, s));
-                dids = ids_d.p;
+                keys.alloc(N + 2, s, &tb, true, "sort keys");
+                alt.alloc(N + 2, s, &tb, true, "sort keys (second buffer)");
+                err.alloc(2, s, &tb, true, "error flag");
+                DevBuf<unsigned long long> ghist;
+                ghist.alloc((uint64_t)kGhistReplicas * kMaxPasses * 256, s, &tb, true, "digit totals");
+                clear_words(Clear().add(err.p, 1).add(ghist.p, (uint64_t)kGhistReplicas * kMaxPasses * 256), s);
+                // with a global sort its first pass forms the keys from the IDs
+                const bool from_ids = plan.top_bits > 0 && N > 1;
+                build_keys(dids, doff, n, N, sbits, U, plan, from_ids ? nullptr : keys.p, err.p, ghist.p, s);
+                // (an ID >= 2^U is sorted by the digits it was counted by, so the check can wait)
+                JAS_HOST_TIMED("sort_enqueue");
+                const uint32_t lo = sbits + U - plan.top_bits, hi = sbits + U;
+                KeySource src;
+                src.ids = dids;
+                src.off = doff;
+                src.n = n;
+                src.sbits = sbits;
+                db->trace.onesweep = !from_ids || radix_sort_onesweep(keys, alt, N, lo, hi, plan.width, ghist.p, err.p,
+                                                                      s, &tb, nullptr, &src);
+                if (!db->trace.onesweep) {
+                    // the single-pass sort declined before any pass: form the keys, then sort them
+                    build_keys(dids, doff, n, N, sbits, U, plan, keys.p, err.p, ghist.p, s);
+                    RadixWork rw;
+                    radix_sort_u64(keys, alt, N, lo, hi, rw, s, &tb);
+                }
+                ids_d.release();
             }
-        }
-        // Sort the keys on their top ID bits (the rest is finished per bucket
-        // range in LDS by encode_sorted).  Both buffers get two spare entries:
-        // after the sort the free one holds the shared pairs and row pointers.
-        DevBuf<uint64_t> keys, alt;
-        DevBuf<uint32_t> err;  // flags of the ID check and of the sort, checked by encode_sorted
-        const SortPlan plan = sort_plan(N, U, sbits);
-        if (N > 0) {
-            keys.alloc(N + 2, s, &tb, true, "sort keys");
-            alt.alloc(N + 2, s, &tb, true, "sort keys (second buffer)");
-            err.alloc(2, s, &tb, true, "error flag");
-            DevBuf<unsigned long long> ghist;
-            ghist.alloc((uint64_t)kGhistReplicas * kMaxPasses * 256, s, &tb, true, "digit totals");
-            clear_words(Clear().add(err.p, 1).add(ghist.p, (uint64_t)kGhistReplicas * kMaxPasses * 256), s);
-            // with a global sort its first pass forms the keys from the IDs
-            const bool from_ids = plan.top_bits > 0 && N > 1;
-            build_keys(dids, doff, n, N, sbits, U, plan, from_ids ? nullptr : keys.p, err.p, ghist.p, s);
-            // (an ID >= 2^U is sorted by the digits it was counted by, so the check can wait)
-            JAS_HOST_TIMED("sort_enqueue");
-            const uint32_t lo = sbits + U - plan.top_bits, hi = sbits + U;
-            KeySource src;
-            src.ids = dids;
-            src.off = doff;
-            src.n = n;
-            src.sbits = sbits;
-            db->trace.onesweep = !from_ids || radix_sort_onesweep(keys, alt, N, lo, hi, plan.width, ghist.p, err.p,
-                                                                  s, &tb, nullptr, &src);
-            if (!db->trace.onesweep) {
-                // the single-pass sort declined before any pass: form the keys, then sort them
-                build_keys(dids, doff, n, N, sbits, U, plan, keys.p, err.p, ghist.p, s);
-                RadixWork rw;
-                radix_sort_u64(keys, alt, N, lo, hi, rw, s, &tb);
-            }
-            ids_d.release();
-        }
-        try {
             encode_sorted(db.get(), keys, alt, N, plan, doff, err.p, s, &tb);
-        } catch (...) {
-            // the db's buffers return to the cache as idle: let their kernels finish first
-            (void)hipStreamSynchronize(s);
-            throw;
-        }
-        alt.release();
-        off_d.release();
-        keys.release();
+        });
         db->budget.limit = 0;
         db->budget.other = nullptr;
         JAS_HIP(hipStreamSynchronize(s));

@@ -69,6 +69,7 @@ n, total, ubits, share, batch, dmin, flags, wb = [int(a) for a in sys.argv[2:5]]
 ids, off = collection(n, total, ubits, share)
 want = intersections(ids, off)
 opts = jas.jas_encode_opts(ubits, batch, dmin, flags, 0, wb)
+refused = []
 lib.model_lazy(1)
 for k in [-1] + list(range(lib.model_allocations() + 1000)):
     lib.model_fail_at(k)
@@ -76,6 +77,7 @@ for k in [-1] + list(range(lib.model_allocations() + 1000)):
         db, _ = jas.jas_encode(ids, off, n, opts)
     except jas.JasError as e:
         assert e.status == jas.JAS_ENOMEM and "refused" in e.message, str(e)
+        refused.append((k, e.message, lib.model_pending()))
         lib.model_drain()  # (what is still enqueued uses freed buffers, if any were given back too early)
         continue
     lib.model_fail_at(-1)
@@ -87,6 +89,7 @@ assert k > 15
 lib.model_drain()
 assert lib.model_live() == 0
 """
+NOTHING_LEFT = "assert not [r for r in refused if r[2]], refused"
 
 
 @pytest.mark.parametrize("dmin", [5, 1000])
@@ -100,3 +103,9 @@ def test_query_keys_of_a_refused_encode(library):
     """The same with a query index: its keys are still being written when a later
     allocation is refused, so they are not idle when they go back."""
     run(library, REFUSED, 64, 16000, 30, 0.5, 0, 1000, 2, 64)
+
+
+def test_nothing_runs_after_a_refused_encode(library):
+    """Once an encode is back with an error, no kernel of it is left to read the
+    caller's IDs."""
+    run(library, REFUSED + NOTHING_LEFT, 64, 16000, 30, 0.5, 24, 6, 2, 32)
