@@ -354,7 +354,8 @@ jas_status jas_relabel(const uint64_t *ids, uint64_t n_ids, uint32_t universe_bi
         if (universe_bits < 1 || universe_bits > 64) fail(JAS_EINVAL, "jas_relabel: universe_bits must be in 1..64");
         if (n_ids > 0 && (!ids || !out)) fail(JAS_EINVAL, "jas_relabel: ids or out is NULL");
         JAS_HOST_TIMED("jas_relabel");
-        const uint64_t D = relabel(ids, n_ids, universe_bits, (hipStream_t)hip_stream, out);
+        uint64_t D = 0;
+        waited((hipStream_t)hip_stream, [&] { D = relabel(ids, n_ids, universe_bits, (hipStream_t)hip_stream, out); });
         if (n_distinct) *n_distinct = D;
         if (new_universe_bits) *new_universe_bits = std::max<uint32_t>(1, ceil_log2_u64(D));
     });
@@ -418,28 +419,30 @@ jas_status jas_query(const jas_db *db, const uint64_t *q_ids, const uint64_t *q_
         if (NQ > 0 && !q_ids) fail(JAS_EINVAL, "jas_query: q_ids is NULL");
         const uint64_t n = (uint64_t)db->n;
         const uint64_t len = (uint64_t)nq * n;
-        if (!host) {
-            query(db, q_ids, q_offsets, nq, hoff, s, B, q_card, den, J);
-            return;
-        }
-        DevBuf<uint64_t> di, doff;
-        DevBuf<int32_t> dB;
-        DevBuf<int64_t> dC, dD;
-        DevBuf<double> dJ;
-        doff.alloc(nq + 1, s, nullptr, true, "query offsets staging");
-        JAS_HIP(hipMemcpyAsync(doff.p, hoff.data(), 8 * (nq + 1), hipMemcpyHostToDevice, s));
-        di.alloc(std::max<uint64_t>(NQ, 1), s, nullptr, true, "query ids staging");
-        if (NQ) JAS_HIP(hipMemcpyAsync(di.p, q_ids, 8 * NQ, hipMemcpyHostToDevice, s));
-        dB.alloc(std::max<uint64_t>(len, 1), s, nullptr, true, "B staging");
-        if (q_card) dC.alloc(nq, s, nullptr, true, "q_card staging");
-        if (den) dD.alloc(std::max<uint64_t>(len, 1), s, nullptr, true, "den staging");
-        if (J) dJ.alloc(std::max<uint64_t>(len, 1), s, nullptr, true, "J staging");
-        query(db, di.p, doff.p, nq, hoff, s, dB.p, q_card ? dC.p : nullptr, den ? dD.p : nullptr, J ? dJ.p : nullptr);
-        if (len) JAS_HIP(hipMemcpyAsync(B, dB.p, len * 4, hipMemcpyDeviceToHost, s));
-        if (q_card) JAS_HIP(hipMemcpyAsync(q_card, dC.p, 8 * (uint64_t)nq, hipMemcpyDeviceToHost, s));
-        if (den && len) JAS_HIP(hipMemcpyAsync(den, dD.p, len * 8, hipMemcpyDeviceToHost, s));
-        if (J && len) JAS_HIP(hipMemcpyAsync(J, dJ.p, len * 8, hipMemcpyDeviceToHost, s));
-        JAS_HIP(hipStreamSynchronize(s));
+        waited(s, [&] {
+            if (!host) {
+                query(db, q_ids, q_offsets, nq, hoff, s, B, q_card, den, J);
+                return;
+            }
+            DevBuf<uint64_t> di, doff;
+            DevBuf<int32_t> dB;
+            DevBuf<int64_t> dC, dD;
+            DevBuf<double> dJ;
+            doff.alloc(nq + 1, s, nullptr, true, "query offsets staging");
+            JAS_HIP(hipMemcpyAsync(doff.p, hoff.data(), 8 * (nq + 1), hipMemcpyHostToDevice, s));
+            di.alloc(std::max<uint64_t>(NQ, 1), s, nullptr, true, "query ids staging");
+            if (NQ) JAS_HIP(hipMemcpyAsync(di.p, q_ids, 8 * NQ, hipMemcpyHostToDevice, s));
+            dB.alloc(std::max<uint64_t>(len, 1), s, nullptr, true, "B staging");
+            if (q_card) dC.alloc(nq, s, nullptr, true, "q_card staging");
+            if (den) dD.alloc(std::max<uint64_t>(len, 1), s, nullptr, true, "den staging");
+            if (J) dJ.alloc(std::max<uint64_t>(len, 1), s, nullptr, true, "J staging");
+            query(db, di.p, doff.p, nq, hoff, s, dB.p, q_card ? dC.p : nullptr, den ? dD.p : nullptr, J ? dJ.p : nullptr);
+            if (len) JAS_HIP(hipMemcpyAsync(B, dB.p, len * 4, hipMemcpyDeviceToHost, s));
+            if (q_card) JAS_HIP(hipMemcpyAsync(q_card, dC.p, 8 * (uint64_t)nq, hipMemcpyDeviceToHost, s));
+            if (den && len) JAS_HIP(hipMemcpyAsync(den, dD.p, len * 8, hipMemcpyDeviceToHost, s));
+            if (J && len) JAS_HIP(hipMemcpyAsync(J, dJ.p, len * 8, hipMemcpyDeviceToHost, s));
+            JAS_HIP(hipStreamSynchronize(s));
+        });
     });
 }
 
@@ -470,12 +473,8 @@ jas_status jas_query_noalloc(const jas_db *db, const uint64_t *q_ids, const uint
             fail(JAS_ENOMEM, "jas_query_noalloc: " + std::to_string(NQ) + " query IDs exceed the fixed workspace (at most " +
                                  std::to_string(noalloc_max_ids()) + ")");
         if (NQ > 0 && !q_ids) fail(JAS_EINVAL, "jas_query_noalloc: q_ids is NULL");
-        try {
-            query(db, q_ids, q_offsets, nq, hoff, s, B, q_card, den, J, &ar);
-        } catch (...) {
-            (void)hipStreamSynchronize(s);  // the workspace is free again only when its kernels are done
-            throw;
-        }
+        // (the workspace, too, is free again only when its kernels are done)
+        waited(s, [&] { query(db, q_ids, q_offsets, nq, hoff, s, B, q_card, den, J, &ar); });
         JAS_HIP(hipStreamSynchronize(s));
     });
 }

@@ -109,3 +109,42 @@ def test_nothing_runs_after_a_refused_encode(library):
     """Once an encode is back with an error, no kernel of it is left to read the
     caller's IDs."""
     run(library, REFUSED + NOTHING_LEFT, 64, 16000, 30, 0.5, 24, 6, 2, 32)
+
+
+CALLS_REFUSED = r"""
+rng = np.random.default_rng(5)
+ids, off = collection(40, 20000, 30, 0.5)
+db, _ = jas.jas_encode(ids, off, 40, jas.jas_encode_opts(30, 0, 0, jas.JAS_KEEP_IDS | jas.JAS_QUERY_ONLY, 0, 64))
+lib.model_drain()
+q = np.concatenate([rng.choice(ids, 40000), rng.integers(0, 1 << 30, 1000).astype(np.uint64)])  # one set, sorted
+qoff = np.array([0, q.size], np.uint64)
+long_ids = rng.integers(0, 1 << 62, 30000).astype(np.uint64)
+crowded = rng.integers(0, 1 << 14, 30000).astype(np.uint64)
+
+def query(flags):
+    B, card = np.zeros(40, np.int32), np.zeros(1, np.int64)
+    jas.jas_query(db, q, qoff, 1, flags, None, B, card)
+    return card[0] == np.unique(q).size and B[7] == np.intersect1d(q, ids[int(off[7]):int(off[8])]).size
+
+def relabel(x):
+    out = np.zeros(x.size, np.uint64)
+    u, inv = np.unique(x, return_inverse=True)
+    return jas.jas_relabel(x, x.size, 62, None, out)[0] == u.size and np.array_equal(out, inv)
+
+lib.model_lazy(1)
+for call in (lambda: query(0), lambda: query(jas.JAS_HOST_PTRS), lambda: relabel(long_ids), lambda: relabel(crowded)):
+    for k in range(1000):
+        lib.model_fail_at(k)
+        try:
+            ok = call()
+        except jas.JasError as e:
+            assert e.status == jas.JAS_ENOMEM and lib.model_pending() == 0, (k, str(e), lib.model_pending())
+            continue
+        assert ok and k > 5
+        break
+"""
+
+
+def test_nothing_runs_after_a_refused_query_or_relabelling(library):
+    """Nor of a query (which writes the caller's B first) or a relabelling."""
+    run(library, CALLS_REFUSED)
