@@ -88,6 +88,9 @@ __device__ __forceinline__ void build_keys_chunk(const uint64_t *__restrict__ id
     int32_t lo = kWrite ? s_lo : 0;
     const auto take = [&](uint64_t t, uint64_t id) {
         bad |= (id & hi_mask) != 0;
+        // the last pass sorts only the digit bits below U: with the others counted, an ID >= 2^U (refused later)
+        // would be counted by another digit than it is sorted by, and places would be left unwritten
+        id &= ~hi_mask;
         if constexpr (kWrite) {
             lo = find_sample(off, lo, s_hi, t);  // t only grows, so the search range only shrinks
             keys[t] = (id << sbits) | (uint64_t)lo;

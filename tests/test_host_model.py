@@ -148,3 +148,30 @@ for call in (lambda: query(0), lambda: query(jas.JAS_HOST_PTRS), lambda: relabel
 def test_nothing_runs_after_a_refused_query_or_relabelling(library):
     """Nor of a query (which writes the caller's B first) or a relabelling."""
     run(library, CALLS_REFUSED)
+
+
+OUTSIDE = r"""
+# 11 sorted bits in passes of 6 and 5: bit 40 of an ID lies in the last pass's 6-bit digit, not in the 5 bits it sorts
+n, ubits = 50, 40
+ids, off = collection(n, 580000, ubits, 0.3)
+assert 1 << 19 < ids.size <= 1 << 20
+opts = jas.jas_encode_opts(ubits, 0, 4, 0, 0, 64)
+plan = jas.jas_plan_create(ids, off, n, opts, 0.1)
+bad = ids.copy()
+bad[::ids.size // 200] |= np.uint64(1 << ubits)
+for call in (lambda: jas.jas_encode(bad, off, n, opts), lambda: (jas.jas_plan_encode(plan, bad, off), jas.jas_plan_check(plan))):
+    try:
+        call()
+        raise SystemExit("an ID outside the universe was accepted")
+    except jas.JasError as e:
+        assert e.status == jas.JAS_EINVAL, str(e)
+jas.jas_plan_encode(plan, ids, off)
+jas.jas_plan_check(plan)
+"""
+
+
+def test_ids_outside_the_universe_are_sorted_by_the_digits_they_are_counted_by(library):
+    """IDs >= 2^U are refused after the sort: until then every place of the sorted
+    keys is written, also where the last pass is narrower than the others (a plan
+    classifies them before the host sees the flag)."""
+    run(library, OUTSIDE)
