@@ -376,7 +376,10 @@ __device__ __forceinline__ uint32_t dev_ceil_log2(uint64_t v) { return v <= 1 ? 
 
 // rs[c] = first bucket edge at or after c*stride, c in [0, nlc]; positions
 // 0 and N are edges.  One wave per c, 256 keys per step.  An edge more than
-// cap keys away is not looked for: rs[c] = ~0 and err |= 8.
+// cap keys away is not looked for: rs[c] = ~0 and err |= 8.  Planned: nor is any
+// edge when the ID check or the sort has failed (err bits 1, 2, 4, set by earlier
+// launches): places of the keys may then be unwritten, and a range without a
+// start is not classified.
 __global__ __launch_bounds__(256) void k_range_starts(const uint64_t *__restrict__ K, uint64_t N, uint32_t bsh,
                                                        uint64_t stride, uint64_t nlc, uint64_t *__restrict__ rs,
                                                        uint32_t *err, const uint64_t *__restrict__ dsz,
@@ -389,6 +392,10 @@ __global__ __launch_bounds__(256) void k_range_starts(const uint64_t *__restrict
     const uint64_t c = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const uint32_t lane = lane_id();
     if (c > nlc) return;  // whole waves
+    if (dsz && (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 7u)) {
+        if (lane == 0) rs[c] = ~0ull;
+        return;
+    }
     const uint64_t x = c * stride;
     if (x == 0 || x >= N) {
         if (lane == 0) rs[c] = min(x, N);

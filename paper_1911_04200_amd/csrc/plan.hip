@@ -289,11 +289,12 @@ jas_status jas_plan_check(jas_plan *plan, void *hip_stream, jas_encode_stats *st
                        std::to_string(caps[k - 1]) + ")";
             fail(JAS_ENOMEM, "jas_plan_encode: " + what + " exceeded the plan (plan with more headroom)");
         }
+        // (a failed sort leaves the ranges without starts, which sets bit 8 too)
+        if (e & 4u) fail(JAS_EUNSUPPORTED, "jas_plan_encode: a digit total is too large for the single-pass sort");
+        if (e & 2u) fail(JAS_EDEVICE, "jas_plan_encode: the radix sort's look-back waited too long");
         if (e & 8u) fail(JAS_EUNSUPPORTED, "jas_plan_encode: a range of buckets exceeds the LDS capacity at the "
                                            "planned stride (plan on this collection)");
         if (e & 16u) fail(JAS_EUNSUPPORTED, "jas_plan_encode: keys need 64 bits in LDS (plan on this collection)");
-        if (e & 4u) fail(JAS_EUNSUPPORTED, "jas_plan_encode: a digit total is too large for the single-pass sort");
-        if (e & 2u) fail(JAS_EDEVICE, "jas_plan_encode: the radix sort's look-back waited too long");
         if (e & 64u) fail(JAS_EOVERFLOW, "jas_plan_encode: a set has " + std::to_string(card_limit()) +
                                              " or more distinct IDs");
     });

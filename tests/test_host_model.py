@@ -175,3 +175,32 @@ def test_ids_outside_the_universe_are_sorted_by_the_digits_they_are_counted_by(l
     keys is written, also where the last pass is narrower than the others (a plan
     classifies them before the host sees the flag)."""
     run(library, OUTSIDE)
+
+
+REFUSED_BY_A_PLAN = r"""
+n, ubits = 40, 30
+ids, off = collection(n, 16000, ubits, 0.5)
+plan = jas.jas_plan_create(ids, off, n, jas.jas_encode_opts(ubits, 0, 4, 0, 0, 64), 0.1)
+want = intersections(ids, off)
+for bad in (False, True, False):
+    x = ids.copy()
+    if bad:
+        x[100] |= np.uint64(1 << ubits)
+    jas.jas_plan_encode(plan, x, off)
+    B = gram(plan.db, n)
+    assert np.array_equal(B, want) != bad
+    if bad:
+        assert not B[~np.eye(n, dtype=bool)].any()
+    try:
+        jas.jas_plan_check(plan)
+        assert not bad
+    except jas.JasError as e:
+        assert bad and e.status == jas.JAS_EINVAL, str(e)
+"""
+
+
+def test_a_plan_classifies_nothing_after_a_failed_sort(library):
+    """Keys that were not all placed (an ID >= 2^U, or a look-back that gave up)
+    are not classified: no rows, the error as before, and the next collection is
+    encoded as ever."""
+    run(library, REFUSED_BY_A_PLAN)
