@@ -572,8 +572,13 @@ __global__ void k_list_pairs(const uint64_t *__restrict__ lp, const uint32_t *__
 // to row a of B once (one atomic per touched pair and chunk instead of one per
 // row and pair).  A shorter run touches few counters twice, and finding its end,
 // waiting and looking through the counters take longer than its own atomics on
-// B; a chunk whose runs are that short on average is counted so as a whole.
-// Chunks of at least kPairChunk words, at most kPairBlocks of them:
+// B; a chunk whose runs are that short on average, and none of which is twice as
+// long as that, is counted so as a whole.  Equal words that are neighbours are
+// added together: atomics on one word of B take 11 ns each, one after another
+// (two samples of 10000 that share 3 M rows of their own: 34 ms without, 0.04 ms
+// so; 1 M words on 500 pairs 0.12 and 0.013 ms).
+// Chunks of at least kPairChunk words (and n/8, so that a run that fills its
+// chunk is counted in LDS), at most kPairBlocks of them:
 // longer chunks split a sample's run fewer times, so fewer atomics, but a block
 // takes its runs one after another.  778 K words of 8192 samples: 0.83 ms as 48 blocks of 16384 words with LDS
 // counters for every run, 0.19 ms as 760, 0.028 ms directly; 1.7 G words of
@@ -588,14 +593,35 @@ __global__ __launch_bounds__(kPairCountNT) void k_pair_count(const uint32_t *__r
     extern __shared__ uint32_t lds[];
     uint32_t *cnt = lds;  // n counters
     __shared__ uint64_t seg_end;
+    __shared__ uint32_t long_run;
     if (dsz) P = min(P, dsz[PZ_P]);  // a plan's db: P is the capacity, the count is on the device
     const uint64_t lo = (uint64_t)blockIdx.x * chunk, hi = min(P, lo + chunk);
     if (lo >= hi) return;
-    const auto add = [&](uint32_t w) { atomicAdd(B + out_index(w >> 16, w & 0xFFFFu, n, upper), 1); };
+    // words [p0, p1) straight to B, the first of equal neighbours in a wave for all of them
+    const auto add = [&](uint64_t p0, uint64_t p1) {
+        for (uint64_t p = p0 + threadIdx.x; p - threadIdx.x < p1; p += blockDim.x) {  // uniform
+            const bool have = p < p1;
+            const uint32_t w = have ? pairs[p] : ~0u;  // (no word: a < b)
+            const uint32_t before = wave_shift_up(w);
+            const bool first = lane_id() == 0 || before != w;
+            const uint64_t after = __ballot(first) & ~(lanemask_lt() | (uint64_t(1) << lane_id()));
+            const uint32_t c = (after ? (uint32_t)__builtin_ctzll(after) : (uint32_t)kWave) - lane_id();
+            if (first && have) atomicAdd(B + out_index(w >> 16, w & 0xFFFFu, n, upper), (int32_t)c);
+        }
+    };
     const uint64_t samples = (pairs[hi - 1] >> 16) - (pairs[lo] >> 16) + 1;
     if ((hi - lo) * 8 < samples * n) {  // block-uniform
-        for (uint64_t p = lo + threadIdx.x; p < hi; p += blockDim.x) add(pairs[p]);
-        return;
+        // a run of n/4 words holds two places that are n/8 words apart
+        if (threadIdx.x == 0) long_run = 0;
+        __syncthreads();
+        const uint64_t far = (n + 7) / 8;
+        for (uint64_t p = lo + threadIdx.x * far; p + far < hi; p += blockDim.x * far)
+            if ((pairs[p] >> 16) == (pairs[p + far] >> 16)) long_run = 1;
+        __syncthreads();
+        if (!long_run) {
+            add(lo, hi);
+            return;
+        }
     }
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) cnt[i] = 0;
     __syncthreads();
@@ -626,7 +652,7 @@ __global__ __launch_bounds__(kPairCountNT) void k_pair_count(const uint32_t *__r
         __syncthreads();
         const uint64_t s1 = seg_end;
         if ((s1 - s0) * 8 < n) {  // block-uniform
-            for (uint64_t p = s0 + threadIdx.x; p < s1; p += blockDim.x) add(pairs[p]);
+            add(s0, s1);
             s0 = s1;
             __syncthreads();  // seg_end is read
             continue;
@@ -999,7 +1025,7 @@ void gram(const jas_db *db, uint32_t flags, hipStream_t s, int32_t *B, int64_t *
         check_launch("gram");
     }
     if (db->n_list > 0 && db->n_lpairs > 0) {
-        const uint64_t chunk = std::max<uint64_t>(kPairChunk, div_up(db->n_lpairs, kPairBlocks));
+        const uint64_t chunk = std::max<uint64_t>({kPairChunk, div_up(n, 8), div_up(db->n_lpairs, kPairBlocks)});
         const uint64_t blocks = div_up(db->n_lpairs, chunk);
         if (blocks > 0xFFFFFFFFull) fail(JAS_EUNSUPPORTED, "row lists too long");
         const size_t lds = (size_t)n * sizeof(uint32_t);

@@ -92,6 +92,7 @@ struct Index {
 extern Index tid, bid;
 extern dim3 bdim, gdim;
 extern char *dynamic_lds;
+extern long atomic_adds;  // calls of atomicAdd so far
 
 void enqueue(const char *name, hipStream_t s, std::function<void()> f);
 void check_launch(const char *name, dim3 grid, dim3 block, size_t lds);
@@ -238,12 +239,17 @@ MODEL_INLINE unsigned long long __umul64hi(unsigned long long a, unsigned long l
 #define MODEL_STEP(scope) ((scope) == __HIP_MEMORY_SCOPE_WORKGROUP ? (void)model::exchange(0, 0) : (void)0)
 #define __hip_atomic_load(p, o, scope) (MODEL_STEP(scope), *(p))
 #define __hip_atomic_store(p, v, o, scope) (MODEL_STEP(scope), (void)(*(p) = (v)), MODEL_STEP(scope))
-#define __hip_atomic_fetch_add(p, v, o, scope) (MODEL_STEP(scope), atomicAdd((p), (v)))
+#define __hip_atomic_fetch_add(p, v, o, scope) (MODEL_STEP(scope), model_fetch_add((p), (v)))
 template <class T, class V>
-MODEL_INLINE T atomicAdd(T *p, V v) {
+MODEL_INLINE T model_fetch_add(T *p, V v) {
     const T old = *p;
     *p = (T)(old + v);
     return old;
+}
+template <class T, class V>
+MODEL_INLINE T atomicAdd(T *p, V v) {
+    ++model::atomic_adds;
+    return model_fetch_add(p, v);
 }
 template <class T, class V>
 MODEL_INLINE T atomicOr(T *p, V v) {

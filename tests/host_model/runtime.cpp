@@ -20,6 +20,7 @@ namespace model {
 Index tid, bid;
 dim3 bdim, gdim;
 char *dynamic_lds;
+long atomic_adds;
 
 namespace {
 constexpr uint32_t kMaxThreads = 1024;
@@ -328,5 +329,6 @@ void model_fail_at(long k) {
     jas::fail_at = k;
 }
 long model_allocations() { return (long)jas::asked.size(); }
+long model_atomic_adds() { return model::atomic_adds; }
 long model_live() { return (long)jas::live.size(); }
 }

@@ -204,3 +204,49 @@ def test_a_plan_classifies_nothing_after_a_failed_sort(library):
     are not classified: no rows, the error as before, and the next collection is
     encoded as ever."""
     run(library, REFUSED_BY_A_PLAN)
+
+
+SAME_PAIRS = r"""
+n, upper = int(sys.argv[2]), int(sys.argv[3])
+rng = np.random.default_rng(n)
+# two samples share nearly all list rows, a few others some
+sets = [rng.integers(1 << 20, 1 << 21, 3) for _ in range(n)]
+a, b = n // 3, n // 2
+rows = rng.choice(1 << 20, 6000, replace=False)
+for s in (a, b):
+    sets[s] = np.concatenate([sets[s], rows])
+for s in rng.choice(n, 40, replace=False):
+    sets[s] = np.concatenate([sets[s], rows[:2]])
+off = np.zeros(n + 1, np.uint64)
+off[1:] = np.cumsum([s.size for s in sets])
+ids = np.concatenate(sets).astype(np.uint64)
+db, st = jas.jas_encode(ids, off, n, jas.jas_encode_opts(21, 0, 1000, 0, 0, 64))
+B = np.zeros(n * (n + 1) // 2 if upper else n * n, np.int32)
+before = lib.model_atomic_adds()
+jas.jas_gram(db, jas.JAS_ACCUMULATE | (jas.JAS_UPPER if upper else 0), None, B, np.zeros(n, np.int64))
+lib.model_drain()
+adds = lib.model_atomic_adds() - before
+at = np.flatnonzero(B)
+i = at // n if not upper else np.searchsorted(np.cumsum(np.arange(n, 0, -1)), at, side="right")
+j = at % n if not upper else at - (i * n - i * (i - 1) // 2) + i
+want = {}
+smp = np.repeat(np.arange(n), np.diff(off).astype(np.int64))
+order = np.lexsort((smp, ids))
+rows_of = np.split(smp[order], np.flatnonzero(np.diff(ids[order])) + 1)
+for r in rows_of:
+    r = np.unique(r)
+    for x in range(r.size):
+        for y in r[x + 1:]:
+            want[(int(r[x]), int(y))] = want.get((int(r[x]), int(y)), 0) + 1
+assert {(int(p), int(q)): int(v) for p, q, v in zip(i, j, B[at])} == want
+assert st["n_list_pairs"] > 7000 and want[(a, b)] >= 6000
+print(adds, "additions for", st["n_list_pairs"], "pairs;", len(want), "different")
+assert adds < 2 * len(want) + st["n_list_pairs"] // 16
+"""
+
+
+@pytest.mark.parametrize("n, upper", [(3000, 0), (8192, 1), (8193, 0), (10240, 1)])
+def test_pairs_of_the_same_two_samples(library, n, upper):
+    """Samples with many rows of their own: their pair words are equal, and B gets
+    few additions for them (each would wait for the one before it)."""
+    print(run(library, SAME_PAIRS, n, upper))
