@@ -95,7 +95,7 @@ extern char *dynamic_lds;
 extern long atomic_adds;  // calls of atomicAdd so far
 
 void enqueue(const char *name, hipStream_t s, std::function<void()> f);
-void check_launch(const char *name, dim3 grid, dim3 block, size_t lds);
+bool check_launch(const char *name, dim3 grid, dim3 block, size_t lds);
 void run_grid(dim3 grid, dim3 block, size_t lds, const std::function<void()> &thread);
 
 struct Launch {
@@ -107,8 +107,8 @@ struct Launch {
     template <class... P, class... A>
     void operator()(void (*kernel)(P...), A &&...args) {
         std::tuple<std::decay_t<P>...> a{static_cast<std::decay_t<P>>(args)...};
-        check_launch(name, grid, block, lds);
-        enqueue(name, s, [kernel, a, g = grid, b = block, l = lds] { run_grid(g, b, l, [&] { std::apply(kernel, a); }); });
+        if (check_launch(name, grid, block, lds))
+            enqueue(name, s, [kernel, a, g = grid, b = block, l = lds] { run_grid(g, b, l, [&] { std::apply(kernel, a); }); });
     }
 };
 

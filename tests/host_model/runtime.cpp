@@ -181,10 +181,12 @@ void enqueue(const char *name, hipStream_t s, std::function<void()> f) {
     if (!lazy) drain(stream(s));
 }
 // The limits of a launch: 2^32 threads along x, 1024 per block, 160 KB of LDS.
-void check_launch(const char *name, dim3 g, dim3 b, size_t lds) {
-    if (g.x && g.y && b.x && (uint64_t)g.x * b.x < (1ull << 32) && b.x * b.y <= kMaxThreads && lds <= 163840) return;
+bool check_launch(const char *name, dim3 g, dim3 b, size_t lds) {
+    if (g.x && g.y && b.x && (uint64_t)g.x * b.x < (1ull << 32) && b.x * b.y <= kMaxThreads && lds <= 163840)
+        return true;
     fprintf(stderr, "launch of %s refused: grid %u x %u, block %u, %zu bytes of LDS\n", name, g.x, g.y, b.x, lds);
     last_error = hipErrorInvalidConfiguration;
+    return false;
 }
 }  // namespace model
 using namespace model;

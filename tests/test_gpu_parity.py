@@ -945,6 +945,40 @@ def test_query_set_sizes_on_both_paths(sizes):
     db.close()
 
 
+@pytest.mark.parametrize("sizes", [[32768] + [1] * 4000, [0] * 3 + [20000] + [0] * 3000 + [17, 16, 15],
+                                   [0] * 50 + [40000] + [3, 0] * 1000])
+def test_query_sets_of_unequal_sizes(sizes):
+    """One large set among many small or empty ones, through the tables and through the sort."""
+    rng = np.random.default_rng(len(sizes))
+    pool = rng.integers(0, 1 << 30, 30000, dtype=np.uint64)
+    ids, off = csr([rng.choice(pool, 2000) for _ in range(20)])
+    db, _ = jas.encode(dev(ids), dev(off), universe_bits=30, keep_ids=True)
+    check_query(db, [rng.choice(pool, z) for z in sizes], ids, off)
+    db.close()
+
+
+@pytest.mark.parametrize("set_ids", [100, 40000])
+def test_query_of_more_sets_than_a_launch_has_blocks(set_ids):
+    """2^22 + 5 sets, all but two empty: slices and sets past the grid's size are taken in turn."""
+    rng = np.random.default_rng(set_ids)
+    pool = rng.integers(0, 1 << 30, 30000, dtype=np.uint64)
+    ids, off = csr([rng.choice(pool, 2000) for _ in range(3)])
+    db, _ = jas.encode(dev(ids), dev(off), universe_bits=30, keep_ids=True)
+    nq, at = (1 << 22) + 5, (12345, (1 << 22) + 3)
+    sizes = np.zeros(nq, np.int64)
+    sizes[list(at)] = set_ids, 7
+    qo = np.zeros(nq + 1, np.uint64)
+    qo[1:] = np.cumsum(sizes)
+    qi = rng.choice(pool, int(qo[-1]))
+    out = jas.query(db, dev(qi), dev(qo))
+    torch.cuda.synchronize()
+    B, card = out["B"].cpu().numpy(), out["q_card"].cpu().numpy()
+    db.close()
+    ref = oracle.cross(qi, np.array([0, set_ids, set_ids + 7], np.uint64), ids, off)
+    assert np.array_equal(B[list(at)], ref["inter"]) and np.array_equal(card[list(at)], ref["q_card"])
+    assert B.any(axis=1).sum() <= 2 and np.count_nonzero(card) == 2
+
+
 @pytest.mark.parametrize("n", [513, 3000, 20000])
 def test_query_ids_most_samples_hold(n):
     """A database ID in every one of n samples: beyond the 512 entries a thread

@@ -250,3 +250,29 @@ def test_pairs_of_the_same_two_samples(library, n, upper):
     """Samples with many rows of their own: their pair words are equal, and B gets
     few additions for them (each would wait for the one before it)."""
     print(run(library, SAME_PAIRS, n, upper))
+
+
+UNEQUAL_SETS = r"""
+rng = np.random.default_rng(11)
+ids, off = collection(4, 3000, 20, 0.5)
+db, _ = jas.jas_encode(ids, off, 4, jas.jas_encode_opts(20, 0, 0, jas.JAS_KEEP_IDS | jas.JAS_QUERY_ONLY, 0, 64))
+members = [np.unique(ids[int(off[j]):int(off[j + 1])]) for j in range(4)]
+for sizes in ([0] * 16500 + [32768] + [0] * 16500, [32768] + [0] * 9, [0, 31, 0, 0, 16, 1, 15, 17, 0]):
+    nq = len(sizes)
+    qoff = np.zeros(nq + 1, np.uint64)
+    qoff[1:] = np.cumsum(sizes)
+    q = rng.choice(ids, int(qoff[-1]))
+    B, card = np.full((nq, 4), -1, np.int32), np.full(nq, -1, np.int64)
+    jas.jas_query(db, q, qoff, nq, 0, None, B, card)
+    assert not card[np.diff(qoff) == 0].any() and not B[np.diff(qoff) == 0].any()
+    for k in np.flatnonzero(np.diff(qoff)):
+        s = np.unique(q[int(qoff[k]):int(qoff[k + 1])])
+        assert card[k] == s.size and all(B[k, j] == np.intersect1d(s, members[j]).size for j in range(4)), k
+"""
+
+
+def test_query_sets_of_unequal_sizes(library):
+    """A request of one large set and many small or empty ones takes as many blocks
+    as there are sets and shares of IDs (the largest set's number for every set is
+    more than a launch may have)."""
+    run(library, UNEQUAL_SETS)
