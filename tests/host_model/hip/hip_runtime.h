@@ -92,7 +92,7 @@ struct Index {
 extern Index tid, bid;
 extern dim3 bdim, gdim;
 extern char *dynamic_lds;
-extern long atomic_adds;  // calls of atomicAdd so far
+extern long atomic_adds, atomic_swaps;  // calls of atomicAdd and atomicCAS so far
 
 void enqueue(const char *name, hipStream_t s, std::function<void()> f);
 bool check_launch(const char *name, dim3 grid, dim3 block, size_t lds);
@@ -259,6 +259,7 @@ MODEL_INLINE T atomicOr(T *p, V v) {
 }
 template <class T, class U, class V>
 MODEL_INLINE T atomicCAS(T *p, U expected, V v) {
+    ++model::atomic_swaps;
     const T old = *p;
     if (old == (T)expected) *p = (T)v;
     return old;

@@ -20,7 +20,7 @@ namespace model {
 Index tid, bid;
 dim3 bdim, gdim;
 char *dynamic_lds;
-long atomic_adds;
+long atomic_adds, atomic_swaps;
 
 namespace {
 constexpr uint32_t kMaxThreads = 1024;
@@ -332,5 +332,6 @@ void model_fail_at(long k) {
 }
 long model_allocations() { return (long)jas::asked.size(); }
 long model_atomic_adds() { return model::atomic_adds; }
+long model_atomic_swaps() { return model::atomic_swaps; }
 long model_live() { return (long)jas::live.size(); }
 }

@@ -979,6 +979,19 @@ def test_query_of_more_sets_than_a_launch_has_blocks(set_ids):
     assert B.any(axis=1).sum() <= 2 and np.count_nonzero(card) == 2
 
 
+@pytest.mark.parametrize("n", [10300, 16384, 16385])
+def test_query_rows_of_more_than_64_kb_of_lds(n):
+    """From about 10300 samples on a block's row of counters and its table pass 64 KB
+    of LDS; past 16384 samples the counters are in memory."""
+    rng = np.random.default_rng(n)
+    pool = rng.integers(0, 1 << 24, 4000, dtype=np.uint64)
+    ids, off = csr([rng.choice(pool, 5) for _ in range(n)])
+    db, _ = jas.encode(dev(ids), dev(off), universe_bits=24, keep_ids=True, query_only=True)
+    check_query(db, [rng.choice(pool, 700), pool, pool[:0], pool[-1:]], ids, off)
+    check_query(db, [rng.choice(pool, 33000), pool[:9]], ids, off)
+    db.close()
+
+
 @pytest.mark.parametrize("n", [513, 3000, 20000])
 def test_query_ids_most_samples_hold(n):
     """A database ID in every one of n samples: beyond the 512 entries a thread

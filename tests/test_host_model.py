@@ -276,3 +276,26 @@ def test_query_sets_of_unequal_sizes(library):
     as there are sets and shares of IDs (the largest set's number for every set is
     more than a launch may have)."""
     run(library, UNEQUAL_SETS)
+
+
+ONE_SHARE = r"""
+# 5000 IDs the hash deals to the first of their 313 blocks
+x = np.arange(1 << 22, dtype=np.uint64)
+h = ((x ^ (x >> np.uint64(32))) * np.uint64(0x9E3779B97F4A7C15)) >> np.uint64(32)
+q = x[(h * np.uint64(313)) >> np.uint64(32) == 0][:5000]
+assert q.size == 5000
+ids = np.concatenate([q[::3], q[:10], x[:2000]])
+off = np.array([0, q[::3].size, ids.size], np.uint64)
+db, _ = jas.jas_encode(ids, off, 2, jas.jas_encode_opts(22, 0, 0, jas.JAS_KEEP_IDS | jas.JAS_QUERY_ONLY, 0, 64))
+B, card = np.zeros(2, np.int32), np.zeros(1, np.int64)
+jas.jas_query(db, q, np.array([0, q.size], np.uint64), 1, 0, None, B, card)
+assert card[0] == q.size and B[0] == q[::3].size and B[1] == np.intersect1d(q, ids[int(off[1]):]).size
+print(lib.model_atomic_swaps(), "slots looked at")
+assert lib.model_atomic_swaps() < 1 << 20
+"""
+
+
+def test_query_ids_that_fill_one_table(library):
+    """A block whose table is full leaves the request to the sort without looking at
+    every slot for each ID that is left (256 threads do so once)."""
+    print(run(library, ONE_SHARE))
