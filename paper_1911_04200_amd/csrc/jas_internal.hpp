@@ -342,6 +342,10 @@ struct KeySource {
     uint32_t *tinfo = nullptr;
     uint64_t tinfo_words = 0;
 };
+// Per pass of `width` bits: where each digit's keys start in the output (starts:
+// kMaxPasses * 256 entries) and the largest digit total (maxima: kMaxPasses entries).
+void digit_starts(const unsigned long long *ghist, uint32_t npass, uint32_t width, uint64_t *starts, uint64_t *maxima,
+                  hipStream_t s);
 uint64_t onesweep_tile_keys_from_ids(uint64_t N);  // entries per tile of the pass that forms N keys
 // With src, keys.p is not read: the first pass forms the keys from src.  With
 // first, the first pass reads the keys there (they are not changed).

@@ -663,11 +663,7 @@ bool onesweep_sort(DevBuf<K> &keys, DevBuf<K> &alt, uint64_t N, uint32_t lo_bit,
     DevBuf<uint64_t> gstart, maxima;
     temp_buf(gstart, (uint64_t)kMaxPasses * kRadix, s, b, ar, "digit starts");
     temp_buf(maxima, kMaxPasses, s, b, ar, "digit maxima");
-    {
-        JAS_TIMED("digit_starts", s);
-        k_digit_starts<<<npass, kOsNT, 0, s>>>(ghist, radix, gstart.p, maxima.p, nullptr);
-    }
-    check_launch("digit starts");
+    digit_starts(ghist, npass, width, gstart.p, maxima.p, s);
     // no digit total is as large as the look-back counts' limit unless N is: only then they are read back
     const uint64_t limit = std::min<uint64_t>(kValMask, scatter_count_limit());
     if (N >= limit) {
@@ -747,6 +743,16 @@ void onesweep_sort_planned(K *&keys, K *&alt, const uint64_t *dN, uint64_t Ncap,
 }
 
 }  // namespace
+
+void digit_starts(const unsigned long long *ghist, uint32_t npass, uint32_t width, uint64_t *starts, uint64_t *maxima,
+                  hipStream_t s) {
+    if (npass == 0) return;
+    {
+        JAS_TIMED("digit_starts", s);
+        k_digit_starts<<<npass, kOsNT, 0, s>>>(ghist, onesweep::radix_of(width), starts, maxima, nullptr);
+    }
+    check_launch("digit starts");
+}
 
 uint64_t onesweep_tile_keys_from_ids(uint64_t N) { return (uint64_t)kOsNT * tile_rounds(N, true); }
 

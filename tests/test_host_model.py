@@ -299,3 +299,35 @@ def test_query_ids_that_fill_one_table(library):
     """A block whose table is full leaves the request to the sort without looking at
     every slot for each ID that is left (256 threads do so once)."""
     print(run(library, ONE_SHARE))
+
+
+CROWDED_IDS = r"""
+rng = np.random.default_rng(2)
+N = 30000
+low = rng.integers(0, 1 << 30, N).astype(np.uint64)
+few = rng.choice(low[:500], N)
+groups = rng.choice(rng.integers(0, 1 << 62, 300), N).astype(np.uint64) + rng.integers(0, 100, N).astype(np.uint64)
+two = np.where(np.arange(N) % 2 == 0, low, low + np.uint64(1 << 61))
+prefix = np.uint64(5 << 40)
+
+def passes(ids, ubits):
+    out, before = np.zeros(N, np.uint64), lib.model_launches(b"k_radix_onesweep")
+    u, inv = np.unique(ids, return_inverse=True)
+    d, bits = jas.jas_relabel(ids, N, ubits, None, out)
+    assert d == u.size and bits == max(1, int(u.size - 1).bit_length()) and np.array_equal(out, inv.astype(np.uint64))
+    return lib.model_launches(b"k_radix_onesweep") - before
+
+alone = passes(low, 30)
+assert passes(low, 62) == alone and passes(low + prefix, 62) == alone and passes(low + np.uint64(1 << 63), 64) == alone
+one = passes(np.full(N, 77, np.uint64), 62)
+assert one == 1, one  # sorted on the one bit that is left
+assert passes(two, 62) == 8, passes(two, 62)  # every bit, and nothing before
+for ids in (few, few + prefix, groups):
+    passes(ids, 63)
+"""
+
+
+def test_relabelling_of_ids_that_share_their_top_bits(library):
+    """Crowded IDs are sorted as if the universe ended at the highest bit in which
+    two of them differ, or, where that does not help, on every bit at once."""
+    run(library, CROWDED_IDS)
