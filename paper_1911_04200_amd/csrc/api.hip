@@ -260,8 +260,8 @@ jas_status jas_encode(const uint64_t *ids, const uint64_t *offsets, int32_t n, c
                 alt.alloc(N + 2, s, &tb, true, "sort keys (second buffer)");
                 err.alloc(2, s, &tb, true, "error flag");
                 DevBuf<unsigned long long> ghist;
-                ghist.alloc((uint64_t)kGhistReplicas * kMaxPasses * 256, s, &tb, true, "digit totals");
-                clear_words(Clear().add(err.p, 1).add(ghist.p, (uint64_t)kGhistReplicas * kMaxPasses * 256), s);
+                ghist.alloc(digit_words(plan.npass, plan.width), s, &tb, true, "digit totals");
+                clear_words(Clear().add(err.p, 1).add(ghist.p, ghist.n), s);
                 // with a global sort its first pass forms the keys from the IDs
                 const bool from_ids = plan.top_bits > 0 && N > 1;
                 build_keys(dids, doff, n, N, sbits, U, plan, from_ids ? nullptr : keys.p, err.p, ghist.p, s);

@@ -496,7 +496,8 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(local_cls_
     uint64_t *__restrict__ K, uint32_t sbits, uint64_t smask, uint32_t bsh, uint32_t lowbits,
     const uint64_t *__restrict__ rs, uint32_t nlc, uint32_t *__restrict__ cnt, int keep, uint32_t *__restrict__ Sg,
     uint64_t *__restrict__ rid_g, uint64_t *__restrict__ rptr_g, unsigned long long *__restrict__ dupc,
-    unsigned long long *__restrict__ rows_rep, const uint64_t *__restrict__ dsz, uint64_t stride, uint32_t *err) {
+    unsigned long long *__restrict__ row_slots, uint32_t slots, const uint64_t *__restrict__ dsz, uint64_t stride,
+    uint32_t *err) {
     static_assert(Cap <= kLocalCapKeys && Cap % kLNT == 0 && kLDigits == kLNT, "range cap");
     constexpr uint32_t kLRounds = Cap / kLNT;  // keys per thread
     __shared__ KT A[Cap];
@@ -653,7 +654,7 @@ __global__ __launch_bounds__(kLNT) __attribute__((amdgpu_waves_per_eu(local_cls_
         cnt[c] = tD;
         cnt[nlc + c] = tS;
         cnt[2 * (uint64_t)nlc + c] = tR;
-        if (all_rows) atomicAdd(&rows_rep[c % kStatReplicas], (unsigned long long)all_rows);
+        if (all_rows) atomicAdd(&row_slots[c % slots], (unsigned long long)all_rows);
     }
 
     // --- ordered writes at the range's own position (every read of the range is done)
@@ -791,8 +792,8 @@ __device__ __forceinline__ void load_degrees(const uint32_t *__restrict__ row_de
 }
 
 __global__ __launch_bounds__(kNT) void k_row_count(const uint32_t *__restrict__ row_deg, uint64_t R, uint32_t dmin,
-                                                    uint32_t *__restrict__ tcnt, unsigned long long *lp_rep,
-                                                    const uint64_t *__restrict__ dsz) {
+                                                    uint32_t *__restrict__ tcnt, unsigned long long *pair_slots,
+                                                    uint32_t slots, const uint64_t *__restrict__ dsz) {
     __shared__ uint64_t sh[kWaves], sh2[kWaves];
     if (plan_aborted(dsz)) return;
     if (dsz) R = dsz[PZ_R];  // tiles past R count nothing
@@ -823,7 +824,7 @@ __global__ __launch_bounds__(kNT) void k_row_count(const uint32_t *__restrict__ 
             tot_p += sh2[k];
         }
         tcnt[blockIdx.x] = (uint32_t)tot_d;
-        if (tot_p) atomicAdd(&lp_rep[blockIdx.x % kStatReplicas], (unsigned long long)tot_p);
+        if (tot_p) atomicAdd(&pair_slots[blockIdx.x % slots], (unsigned long long)tot_p);
     }
 }
 
@@ -946,7 +947,7 @@ __global__ __launch_bounds__(G < 4 ? 256 : G * kWave) void k_pack(
     uint64_t *__restrict__ W, uint64_t ldw, uint64_t H, uint64_t Hw, uint32_t wb, const uint64_t *__restrict__ wq0,
     const uint64_t *__restrict__ wq1, uint64_t QD, const uint64_t *__restrict__ Drow,
     const uint64_t *__restrict__ row_ptr, const uint32_t *__restrict__ row_deg, const uint32_t *__restrict__ S,
-    uint32_t cols, unsigned long long *st, const uint64_t *__restrict__ dsz) {
+    uint32_t cols, unsigned long long *word_slots, uint32_t slots, const uint64_t *__restrict__ dsz) {
     constexpr uint32_t kTeam = G * kWave, kTeams = kTeam < 256 ? 256 / kTeam : 1;
     extern __shared__ __attribute__((aligned(16))) unsigned long long lds[];
     if (plan_aborted(dsz)) return;
@@ -1090,9 +1091,9 @@ __global__ __launch_bounds__(G < 4 ? 256 : G * kWave) void k_pack(
         }
     }
     if (tid == 0 && nnz_acc) {
-        const uint32_t rep = (blockIdx.x * kTeams + team) % kStatReplicas;
-        atomicAdd(&st[kStatNnzw + rep], nnz_acc);
-        atomicAdd(&st[kStatF + rep], f_acc);
+        const uint32_t slot = (blockIdx.x * kTeams + team) % slots;
+        atomicAdd(&word_slots[slot], nnz_acc);
+        atomicAdd(&word_slots[slots + slot], f_acc);
     }
 }
 
@@ -1432,25 +1433,26 @@ __global__ void k_plan_pairs(const uint64_t *npo, uint64_t gcap, uint64_t Pcap, 
 template <int G>
 void launch_pack_waves(uint64_t H, uint32_t cols, hipStream_t s, uint64_t *W, uint64_t ldw, uint64_t Hw, uint32_t wb,
                        const uint64_t *wq0, const uint64_t *wq1, uint64_t QD, const uint64_t *Drow,
-                       const uint64_t *row_ptr, const uint32_t *row_deg, const uint32_t *S, unsigned long long *st,
-                       const uint64_t *dsz) {
+                       const uint64_t *row_ptr, const uint32_t *row_deg, const uint32_t *S, unsigned long long *word_slots,
+                       uint32_t slots, const uint64_t *dsz) {
     constexpr uint32_t threads = std::max(256, G * kWave), teams = threads / (G * kWave);
     const size_t lds = teams * ((size_t)cols + kPackFlat / 64 + 1) * sizeof(uint64_t);
     const uint32_t blocks = (uint32_t)std::min<uint64_t>(div_up(H, (uint64_t)teams), G == 1 ? 2048 : 4096);
     if (lds > 65536)
         JAS_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_pack<G>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    k_pack<G><<<blocks, threads, lds, s>>>(W, ldw, H, Hw, wb, wq0, wq1, QD, Drow, row_ptr, row_deg, S, cols, st, dsz);
+    k_pack<G><<<blocks, threads, lds, s>>>(W, ldw, H, Hw, wb, wq0, wq1, QD, Drow, row_ptr, row_deg, S, cols, word_slots,
+                                           slots, dsz);
 }
 
 void launch_pack(uint64_t *W, uint64_t ldw, uint64_t H, uint64_t Hw, uint32_t wb, const uint64_t *wq0,
                  const uint64_t *wq1, uint64_t QD, const uint64_t *Drow, const uint64_t *row_ptr,
-                 const uint32_t *row_deg, const uint32_t *S, unsigned long long *st, const uint64_t *dsz,
-                 hipStream_t s) {
+                 const uint32_t *row_deg, const uint32_t *S, unsigned long long *word_slots, uint32_t slots,
+                 const uint64_t *dsz, hipStream_t s) {
     const uint64_t nchunk = div_up(ldw, (uint64_t)kPackCols);
     const uint32_t cols = (uint32_t)(div_up(div_up(ldw, nchunk), 128) * 128);
     const auto go = [&](auto launch) {
-        launch(H, cols, s, W, ldw, Hw, wb, wq0, wq1, QD, Drow, row_ptr, row_deg, S, st, dsz);
+        launch(H, cols, s, W, ldw, Hw, wb, wq0, wq1, QD, Drow, row_ptr, row_deg, S, word_slots, slots, dsz);
     };
     if (ldw <= 1024 && H >= 4096) go(launch_pack_waves<1>);
     else if (ldw <= 1024) go(launch_pack_waves<4>);
@@ -1562,7 +1564,7 @@ uint64_t distinct_sorted(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t
     DevBuf<unsigned long long> rows;
     DevBuf<uint32_t> cnt;
     DevBuf<uint64_t> off, zero, tmp;
-    rows.alloc(kStatReplicas, s, nullptr, true, "row counters");
+    rows.alloc(kStatSlots, s, nullptr, true, "row counters");
     cnt.alloc(3 * rg.nlc, s, nullptr, true, "range counts");
     off.alloc(rg.nlc + 1, s, nullptr, true, "range offsets");
     zero.alloc(rg.nlc + 1, s, nullptr, true, "range offsets");
@@ -1572,7 +1574,7 @@ uint64_t distinct_sorted(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t
         JAS_TIMED(rg.err & 16u ? "local_cls_wide" : "local_cls", s);
         launch_local_cls((rg.err & 16u) != 0, rg.cap, (uint32_t)rg.nlc, s, keys.p, 0u, (uint64_t)0, lowbits, lowbits,
                          (const uint64_t *)rs.p, (uint32_t)rg.nlc, cnt.p, 1, (uint32_t *)nullptr, (uint64_t *)nullptr,
-                         (uint64_t *)nullptr, (unsigned long long *)nullptr, rows.p, (const uint64_t *)nullptr,
+                         (uint64_t *)nullptr, (unsigned long long *)nullptr, rows.p, kStatSlots, (const uint64_t *)nullptr,
                          (uint64_t)0, reinterpret_cast<uint32_t *>(flags.p));
     }
     check_launch("local distinct");
@@ -1587,6 +1589,19 @@ uint64_t distinct_sorted(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t
     return to_host_u64(off.p + rg.nlc, s);
 }
 
+namespace {
+// Scans of the three counts of len ranges or chunks: one launch or two, or, within
+// a memory limit, one after another in a third of the scratch.
+void scan_counts(const DevBuf<uint32_t> &cnt, uint64_t len, DevBuf<uint64_t> &offD, DevBuf<uint64_t> &offS,
+                 DevBuf<uint64_t> &offR, DevBuf<uint64_t> &tmp, hipStream_t s, Budget *tb) {
+    const bool limited = tb && tb->limit;
+    tmp.alloc(scan_tmp_elems(len, limited ? 1 : kScanRows), s, tb, true, "scan scratch");
+    uint64_t *const out[kScanRows] = {offD.p, offS.p, offR.p};
+    if (!limited) return scan_excl_u32_rows(cnt.p, len, out, len, tmp.p, s);
+    for (uint32_t y = 0; y < kScanRows; ++y) scan_excl_u32(cnt.p + y * len, out[y], len, tmp.p, s);
+}
+}  // namespace
+
 void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, const SortPlan &plan,
                    const uint64_t *offsets, const uint32_t *sort_err, hipStream_t s, Budget *tb) {
     const int32_t n = db->n;
@@ -1596,9 +1611,10 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
     const bool query_only = db->flags & JAS_QUERY_ONLY;  // no packed words or row lists
 
     DevBuf<unsigned long long> st;
-    st.alloc(kStatWords, s, tb, true, "encode counters");
+    const uint32_t slots = stat_slots(N, tb && tb->limit);
+    st.alloc(stat_words(slots), s, tb, true, "encode counters");
     Clear clear;  // by the first launch below
-    clear.add(st.p, kStatWords);
+    clear.add(st.p, st.n);
     const auto check_sort = [](uint32_t e) {
         if (e & 1u) fail(JAS_EINVAL, "jas_encode: an ID is >= 2^universe_bits");
         if (e) fail(JAS_EDEVICE, "jas_encode: the radix sort's look-back waited too long (result discarded)");
@@ -1663,7 +1679,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
                 JAS_TIMED(herr & 16u ? "local_cls_wide" : "local_cls", s);
                 launch_local_cls((herr & 16u) != 0, cap, (uint32_t)nlc, s, keys.p, sbits, smask, bsh, lowbits,
                                  (const uint64_t *)rs.p, (uint32_t)nlc, cnt.p, keep ? 1 : 0, Sg, rid_g.p, rptr_g,
-                                 dupc.p, st.p + kStatRows, (const uint64_t *)nullptr, (uint64_t)0, errL);
+                                 dupc.p, st.p + stat_rows(slots), slots, (const uint64_t *)nullptr, (uint64_t)0, errL);
             }
             check_launch("local classify");
             if (n > 0) {
@@ -1675,8 +1691,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
             offD.alloc(nlc + 1, s, tb, true, "range offsets");
             offS.alloc(nlc + 1, s, tb, true, "range offsets");
             offR.alloc(nlc + 1, s, tb, true, "range offsets");
-            stmp.alloc(scan_tmp_elems(nlc, kScanRows), s, tb, true, "scan scratch");
-            scan_excl_u32_rows(cnt.p, nlc, {offD.p, offS.p, offR.p}, nlc, stmp.p, s);
+            scan_counts(cnt, nlc, offD, offS, offR, stmp, s, tb);
             uint64_t t3[4];
             read_back(ReadBack().add(offD.p + nlc).add(offS.p + nlc).add(offR.p + nlc).add(flags.p), t3, s);
             herr = t3[3];
@@ -1685,6 +1700,11 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
             NDk = t3[0];
             NS = t3[1];
             R = t3[2];
+            cnt.release();
+            stmp.release();
+            dupc.release();
+            flags.release();
+            if (!keep) keys.release();
             db->trace.local = true;
             db->trace.wide = (herr & 16u) != 0;
             db->trace.nlc = nlc;
@@ -1703,6 +1723,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
                     rdegp, nullptr, 0);
             }
             check_launch("local move");
+            keys.release();
             done = true;
         }
     }
@@ -1737,8 +1758,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         offD.alloc(nch + 1, s, tb, true, "classify offsets");
         offS.alloc(nch + 1, s, tb, true, "classify offsets");
         offR.alloc(nch + 1, s, tb, true, "classify offsets");
-        stmp.alloc(scan_tmp_elems(nch, kScanRows), s, tb, true, "scan scratch");
-        scan_excl_u32_rows(cnt.p, nch, {offD.p, offS.p, offR.p}, nch, stmp.p, s);
+        scan_counts(cnt, nch, offD, offS, offR, stmp, s, tb);
         uint64_t t3[3];
         read_back(ReadBack().add(offD.p + nch).add(offS.p + nch).add(offR.p + nch), t3, s);
         check_card(true);  // (looks at every sum)
@@ -1825,7 +1845,7 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         {
             JAS_TIMED("row_count", s);
             k_row_count<<<(uint32_t)nt, kNT, 0, s>>>(rdegp, R, db->dmin, tcnt.p,
-                                                      st.p + kStatLists, nullptr);
+                                                      st.p + stat_lists(slots), slots, nullptr);
         }
         check_launch("row count");
         scan_excl_u32(tcnt.p, toff.p, nt, tmp.p, s);
@@ -1890,14 +1910,14 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         if (npass > kPairPasses) fail(JAS_EUNSUPPORTED, "row-list pairs: too many sample bits");
         pk.alloc(P + 2, s, &db->budget, true, "row-list pairs");
         palt.alloc(P + 2, s, tb, true, "row-list pairs (second buffer)");
-        pgh.alloc((uint64_t)kGhistReplicas * kMaxPasses * 256, s, tb, true, "pair digit totals");
+        pgh.alloc(digit_words(npass, pwidth), s, tb, true, "pair digit totals");
         perr.alloc(2, s, tb, true, "pair sort flag");
         s2 = side_stream();
         stream_after(s2, s);  // everything the pair path reads is on s so far
         join.waiter = s;
         join.on = s2;
         join.armed = true;
-        clear_words(Clear().add(pgh.p, (uint64_t)kGhistReplicas * kMaxPasses * 256).add(perr.p, 1), s2);
+        clear_words(Clear().add(pgh.p, pgh.n).add(perr.p, 1), s2);
         {
             JAS_TIMED("pair_emit", s2);
             k_pair_emit<<<pair_emit_grid(QL), 256, 0, s2>>>(
@@ -1956,12 +1976,19 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
                 }
             });
             check_launch("word rows");
+            bs.release();
+            bpos.release();
+            bq.release();
+            nw.release();
+            wbase.release();
+            tmp.release();
         }
         H = wb == 64 ? Hw : div_up(Hw, 2);
         db->W.alloc(H * ldw, s, &db->budget, false, "packed words");
         {
             JAS_TIMED("pack", s);
-            launch_pack(db->W.p, ldw, H, Hw, wb, wq0.p, wq1.p, QD, Drow.p, rptrp, rdegp, Sp, st.p, nullptr, s);
+            launch_pack(db->W.p, ldw, H, Hw, wb, wq0.p, wq1.p, QD, Drow.p, rptrp, rdegp, Sp, st.p + stat_words_of(slots),
+                        slots, nullptr, s);
         }
         check_launch("pack");
     }
@@ -1976,8 +2003,8 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
         stream_after(s, s2);
         join.armed = false;
         uint64_t got[1 + kStatWords];
-        read_back(ReadBack().add(perr.p).add(st.p, kStatWords), got, s);
-        std::copy(got + 1, got + 1 + kStatWords, hst);
+        read_back(ReadBack().add(perr.p).add(st.p, (uint32_t)st.n), got, s);
+        std::copy(got + 1, got + 1 + st.n, hst);
         have_st = true;
         if (ok && (uint32_t)got[0] == 0) {
             db->n_lpairs = P;
@@ -2043,8 +2070,8 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
     }
 
     // --- stats -----------------------------------------------------------------
-    if (!have_st) read_back(ReadBack().add(st.p, kStatWords), hst, s);
-    add_replicas(hst);
+    if (!have_st) read_back(ReadBack().add(st.p, (uint32_t)st.n), hst, s);
+    add_slots(hst, slots);
     if (sized) hst[ST_LISTPAIRS] = list_pairs;
     jas_encode_stats &o = db->stats;
     db->trace.N = N;
@@ -2092,10 +2119,10 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
     {
         JAS_TIMED("plan_sizes", s);
         Clear c;
-        c.add(p.ghist.p, (uint64_t)kGhistReplicas * kMaxPasses * 256);
-        c.add(p.st.p, kStatWords);
+        c.add(p.ghist.p, p.ghist.n);
+        c.add(p.st.p, p.st.n);
         c.add(p.dupc.p, (uint64_t)std::max<int32_t>(n, 1));
-        if (p.QLcap > 0) c.add(p.gh.p, (uint64_t)kGhistReplicas * kMaxPasses * 256);
+        if (p.QLcap > 0) c.add(p.gh.p, p.gh.n);
         k_plan_begin<<<256, 256, 0, s>>>(offsets, n, Ncap, dsz, err, c);
     }
     check_launch("plan begin");
@@ -2148,8 +2175,8 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
     {
         JAS_TIMED(p.wide ? "local_cls_wide" : "local_cls", s);
         launch_local_cls(p.wide, p.lcap, (uint32_t)nlc, s, K, sbits, smask, bsh, lowbits, (const uint64_t *)p.rs.p,
-                         (uint32_t)nlc, p.cnt.p, 0, Sg, p.rid_g.p, rptr_g, p.dupc.p, p.st.p + kStatRows, dsz, p.stride,
-                         err);
+                         (uint32_t)nlc, p.cnt.p, 0, Sg, p.rid_g.p, rptr_g, p.dupc.p, p.st.p + stat_rows(p.slots), p.slots, dsz,
+                         p.stride, err);
     }
     check_launch("local classify (planned)");
     scan_excl_u32_rows(p.cnt.p, nlc, {p.offD.p, p.offS.p, p.offR.p}, nlc, p.stmp.p, s);
@@ -2172,7 +2199,8 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
     // rows by degree
     {
         JAS_TIMED("row_count", s);
-        k_row_count<<<(uint32_t)p.tile_cap, kNT, 0, s>>>(p.rdeg.p, p.Rcap, p.dmin, p.tcnt.p, p.st.p + kStatLists, dsz);
+        k_row_count<<<(uint32_t)p.tile_cap, kNT, 0, s>>>(p.rdeg.p, p.Rcap, p.dmin, p.tcnt.p,
+                                                            p.st.p + stat_lists(p.slots), p.slots, dsz);
     }
     scan_excl_u32(p.tcnt.p, p.toff.p, p.tile_cap, p.stmp.p, s);
     {
@@ -2213,7 +2241,7 @@ void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, 
         {
             JAS_TIMED("pack", s);
             launch_pack(p.W.p, p.ldw, p.Hcap, p.Hwcap, p.word_bits, p.wq0.p, p.wq1.p, p.QDcap, p.Drow.p, p.rptr.p,
-                        p.rdeg.p, reinterpret_cast<const uint32_t *>(F), p.st.p, dsz, s);
+                        p.rdeg.p, reinterpret_cast<const uint32_t *>(F), p.st.p + stat_words_of(p.slots), p.slots, dsz, s);
         }
         check_launch("pack (planned)");
     }

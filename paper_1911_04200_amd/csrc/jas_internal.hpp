@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <mutex>
 #include <string>
@@ -324,12 +325,17 @@ void radix_sort_u64(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, u
 
 // Single-pass-per-digit sort (decoupled look-back) of keys whose digit totals
 // are known: ghist = kGhistReplicas copies of kMaxPasses * 256 totals, a row of
-// 256 per pass (512 when width is 9); pass q sorts on bits
-// [lo_bit + width*q, min(lo_bit + width*(q+1), hi_bit)), width <= 9.  Returns false (and does nothing) when a digit total reaches
-// 2^30, where the caller uses radix_sort_u64.  A look-back that waits too long
+// 256 per pass (512 when width is 9), see digit_words; pass q sorts on bits
+// [lo_bit + width*q, min(lo_bit + width*(q+1), hi_bit)), width <= 9.  Returns
+// false (and does nothing) when a digit total reaches 2^30, where the caller uses radix_sort_u64.  A look-back that waits too long
 // sets bit 1 of err[0] (the result is then invalid).
 constexpr uint32_t kMaxPasses = 8;
 constexpr uint32_t kGhistReplicas = 32;
+// Words of ghist for npass passes: whole copies but for the unused end of the last.
+inline uint64_t digit_words(uint32_t npass, uint32_t width) {
+    const uint64_t used = (uint64_t)npass * (width > 8 ? 512 : 256);
+    return (uint64_t)(kGhistReplicas - 1) * kMaxPasses * 256 + std::max<uint64_t>(used, 1);
+}
 // Where a sort's first pass takes its keys from when it forms them from CSR
 // sets itself (key = id << sbits | sample): the IDs and offsets of the n >= 1
 // sets, and a device buffer of 2 words per tile (the samples holding
@@ -364,7 +370,9 @@ struct OnesweepBufs {
     uint32_t *status = nullptr;
     uint64_t status_words = 0;
 };
-uint64_t onesweep_look_back_words(uint64_t N, uint32_t width);
+// The status words are of two passes, or of one (cleared before each pass) where
+// memory is limited; the sort takes the form its buffer has room for.
+uint64_t onesweep_look_back_words(uint64_t N, uint32_t width, bool two = true);
 // Planned sorts: the key count is *dN (at most Ncap); keys/alt are swapped
 // as the passes go; no readback, no allocation.  err |= 4 when a digit total
 // is too large, err |= 2 when a look-back gave up.
@@ -400,7 +408,7 @@ constexpr uint32_t kLocalShortCap = 4096;  // ranges no longer than this run fou
 // kLocalCapKeys; shorter ones leave room for larger buckets.
 constexpr uint64_t kLocalStrides[2] = {3072, 2048};
 constexpr uint64_t kLocalWideStride = 4096;  // tried first when the ranges need no LDS sort passes
-SortPlan sort_plan(uint64_t N, uint32_t U, uint32_t sbits);
+SortPlan sort_plan(uint64_t N, uint32_t U, uint32_t sbits, uint32_t max_width = 9);
 
 // Keys (id << sbits) | sample from CSR sets; err[0] |= 1 for an ID >= 2^U;
 // ghist: totals of every digit of the plan's passes (kGhistReplicas copies).
@@ -424,6 +432,29 @@ void encode_sorted(jas_db *db, DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, ui
 uint64_t distinct_sorted(DevBuf<uint64_t> &keys, DevBuf<uint64_t> &alt, uint64_t N, uint32_t U, const SortPlan &plan,
                          hipStream_t s);
 
+// Encode counters (encode.hip): the totals, then `slots` words each for those
+// that many blocks add to (one counter would serialise an atomic from every
+// block): rows, list pairs, nonzero words, F; add_slots sums them once they are
+// on the host.  Within a memory limit a slot per 65536 entries, up to 16.
+enum { ST_PAIRS = 0, ST_ROWS, ST_NNZW, ST_F, ST_LISTPAIRS, ST_N };
+constexpr uint32_t kStatSlots = 64;  // at most
+constexpr uint32_t kStatWords = ST_N + 4 * kStatSlots;
+inline uint32_t stat_slots(uint64_t N, bool limited) {
+    return limited ? (uint32_t)std::min<uint64_t>(std::max<uint64_t>(N >> 16, 1), 16) : kStatSlots;
+}
+constexpr uint32_t stat_words(uint32_t slots) { return ST_N + 4 * slots; }
+constexpr uint32_t stat_rows(uint32_t) { return ST_N; }
+constexpr uint32_t stat_lists(uint32_t slots) { return ST_N + slots; }
+constexpr uint32_t stat_words_of(uint32_t slots) { return ST_N + 2 * slots; }  // nonzero words, then F
+inline void add_slots(uint64_t (&st)[kStatWords], uint32_t slots) {
+    for (uint32_t k = 0; k < slots; ++k) {
+        st[ST_ROWS] += st[ST_N + k];
+        st[ST_LISTPAIRS] += st[ST_N + slots + k];
+        st[ST_NNZW] += st[ST_N + 2 * slots + k];
+        st[ST_F] += st[ST_N + 3 * slots + k];
+    }
+}
+
 // A planned encode (plan.hip creates it, encode.hip runs it): the decisions
 // of one eager encode and buffers sized for them with headroom, so a like
 // collection encodes with no host synchronisation and no allocation.
@@ -438,6 +469,7 @@ struct PlanState {
     uint64_t Ncap = 0, nlc_cap = 0, Rcap = 0, QDcap = 0, QLcap = 0, Hwcap = 0, Hcap = 0, Pcap = 0, tile_cap = 0,
              gcap = 0, ldw = 0;
     uint32_t pair_npass = 0, pair_width = 8, pair_bits = 0;
+    uint32_t slots = kStatSlots;
     // device buffers (owned by the plan)
     DevBuf<uint64_t> keys, alt, rs, offD, offS, offR, stmp, rid_g, rid, rptr, toff, Drow, Lrow, bpos, bq, nw, wbase,
         wq0, wq1, npo, np, dsz;
@@ -450,21 +482,6 @@ struct PlanState {
     uint32_t *pairs_final = nullptr;  // the buffer holding the sorted pair words after the pair sort
 };
 void encode_planned(PlanState &p, const uint64_t *ids, const uint64_t *offsets, hipStream_t s);
-// Encode counters (encode.hip): the totals, then kStatReplicas slots each for
-// those that many blocks add to (one counter would serialise an atomic from
-// every block); add_replicas sums them once they are on the host.
-enum { ST_PAIRS = 0, ST_ROWS, ST_NNZW, ST_F, ST_LISTPAIRS, ST_N };
-constexpr uint32_t kStatReplicas = 64;
-constexpr uint32_t kStatRows = ST_N, kStatLists = kStatRows + kStatReplicas, kStatNnzw = kStatLists + kStatReplicas,
-                   kStatF = kStatNnzw + kStatReplicas, kStatWords = kStatF + kStatReplicas;
-inline void add_replicas(uint64_t (&st)[kStatWords]) {
-    for (uint32_t k = 0; k < kStatReplicas; ++k) {
-        st[ST_ROWS] += st[kStatRows + k];
-        st[ST_LISTPAIRS] += st[kStatLists + k];
-        st[ST_NNZW] += st[kStatNnzw + k];
-        st[ST_F] += st[kStatF + k];
-    }
-}
 constexpr uint64_t kSplitTilePub = 256 * 8;  // rows per row-split tile
 
 // Degree threshold: rows of degree >= the result are bit-packed, 2..result-1

@@ -130,7 +130,10 @@ jas_status jas_plan_create(const uint64_t *ids, const uint64_t *offsets, int32_t
         p.batch_bits = bb;
         p.word_bits = wb;
         p.dmin = dmin;
-        p.sort = sort_plan(tr.N, U, sbits);
+        // within a memory limit the sorts keep to 256 digits and one pass's look-back
+        // words (as an encode's do), half and a quarter of the bytes
+        const bool limited = opts->hbm_budget_bytes != 0;
+        p.sort = sort_plan(tr.N, U, sbits, limited ? 8 : 9);
         p.stride = tr.stride ? tr.stride : kLocalStrides[0];
         p.lcap = tr.lcap ? tr.lcap : kLocalShortCap;
         p.wide = tr.wide;
@@ -160,11 +163,12 @@ jas_status jas_plan_create(const uint64_t *ids, const uint64_t *offsets, int32_t
         plan_buf(p.alt, p.Ncap + 2, s, &bud, "plan keys (second buffer)");
         plan_buf(p.dsz, PZ_COUNT, s, &bud, "plan sizes");
         plan_buf(p.err, 4, s, &bud, "plan flags");
-        plan_buf(p.st, kStatWords, s, &bud, "plan counters");
-        plan_buf(p.ghist, (uint64_t)kGhistReplicas * kMaxPasses * 256, s, &bud, "plan digit totals");
+        p.slots = stat_slots(tr.N, limited);
+        plan_buf(p.st, stat_words(p.slots), s, &bud, "plan counters");
+        plan_buf(p.ghist, digit_words(p.sort.npass, p.sort.width), s, &bud, "plan digit totals");
         plan_buf(p.os_gstart, (uint64_t)kMaxPasses * 256, s, &bud, "plan digit starts");
         plan_buf(p.os_maxima, kMaxPasses, s, &bud, "plan digit maxima");
-        plan_buf(p.os_status, onesweep_look_back_words(p.Ncap, p.sort.width), s, &bud, "plan look-back status");
+        plan_buf(p.os_status, onesweep_look_back_words(p.Ncap, p.sort.width, !limited), s, &bud, "plan look-back status");
         if (p.sort.top_bits > 0)
             plan_buf(p.os_tinfo, 2 * div_up(p.Ncap, onesweep_tile_keys_from_ids(p.Ncap)), s, &bud, "plan tile samples");
         plan_buf(p.rs, p.nlc_cap + 1, s, &bud, "plan range starts");
@@ -199,10 +203,11 @@ jas_status jas_plan_create(const uint64_t *ids, const uint64_t *offsets, int32_t
             plan_buf(p.npo, p.gcap + 1, s, &bud, "plan row group pair offsets");
             plan_buf(p.pk, p.Pcap + 2, s, &bud, "plan row-list pairs");
             plan_buf(p.palt, p.Pcap + 2, s, &bud, "plan row-list pairs (second buffer)");
-            plan_buf(p.gh, (uint64_t)kGhistReplicas * kMaxPasses * 256, s, &bud, "plan pair digit totals");
+            plan_buf(p.gh, digit_words(p.pair_npass, p.pair_width), s, &bud, "plan pair digit totals");
             plan_buf(p.os2_gstart, (uint64_t)kMaxPasses * 256, s, &bud, "plan pair digit starts");
             plan_buf(p.os2_maxima, kMaxPasses, s, &bud, "plan pair digit maxima");
-            plan_buf(p.os2_status, onesweep_look_back_words(p.Pcap, p.pair_width), s, &bud, "plan pair look-back status");
+            plan_buf(p.os2_status, onesweep_look_back_words(p.Pcap, p.pair_width, !limited), s, &bud,
+                     "plan pair look-back status");
             p.pairs_final = (p.pair_npass % 2) ? p.palt.p : p.pk.p;
         }
         // the plan's db: views of the plan's buffers
@@ -258,9 +263,9 @@ jas_status jas_plan_check(jas_plan *plan, void *hip_stream, jas_encode_stats *st
         uint64_t cnt[kStatWords];
         JAS_HIP(hipMemcpyAsync(err, p.err.p, sizeof(err), hipMemcpyDeviceToHost, s));
         JAS_HIP(hipMemcpyAsync(sz, p.dsz.p, sizeof(sz), hipMemcpyDeviceToHost, s));
-        JAS_HIP(hipMemcpyAsync(cnt, p.st.p, sizeof(cnt), hipMemcpyDeviceToHost, s));
+        JAS_HIP(hipMemcpyAsync(cnt, p.st.p, p.st.n * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
         JAS_HIP(hipStreamSynchronize(s));
-        add_replicas(cnt);
+        add_slots(cnt, p.slots);
         jas_encode_stats &o = plan->db.stats;
         o.n_ids = sz[PZ_N];
         o.n_rows = cnt[ST_ROWS];

@@ -481,15 +481,15 @@ __global__ void k_tile_samples(const uint64_t *__restrict__ off, int32_t n, uint
 
 }  // namespace
 
-SortPlan sort_plan(uint64_t N, uint32_t U, uint32_t sbits) {
+SortPlan sort_plan(uint64_t N, uint32_t U, uint32_t sbits, uint32_t max_width) {
     SortPlan p;
     if (N <= kLocalCapKeys) return p;  // one LDS range holds everything
     p.top_bits = std::min<uint32_t>(U, ceil_log2_u64(div_up(N, kBucketKeys)));
     const uint32_t fewer = std::min<uint32_t>(U, ceil_log2_u64(div_up(N, 2 * kBucketKeys)));
     if (fewer > 0 && (U - fewer) + kSpanBits + sbits <= 32) p.top_bits = fewer;
-    // the fewest passes of at most 9 bits, of equal width: a pass over 18 bits'
+    // the fewest passes of at most 9 (max_width) bits, of equal width: a pass over 18 bits'
     // halves takes 1.4 times one over 6 (1.78 G keys: 9.0, 6.3 ms), so two beat three
-    p.npass = (p.top_bits + 8) / 9;
+    p.npass = (p.top_bits + max_width - 1) / max_width;
     p.width = p.npass ? (p.top_bits + p.npass - 1) / p.npass : 8;
     return p;
 }
@@ -722,7 +722,7 @@ void onesweep_sort_planned(K *&keys, K *&alt, const uint64_t *dN, uint64_t Ncap,
     if (npass * radix > kMaxPasses * kRadix || width < 1 || width > (sizeof(K) == 8 ? 9 : 8))
         fail(JAS_EUNSUPPORTED, "planned sort: bad digit plan");
     const uint64_t ntiles = most_tiles(Ncap);
-    if (b.status_words < look_back_words(ntiles, radix) || ntiles > 0xFFFFFFFFull)
+    if (b.status_words < look_back_words(ntiles, radix, false) || ntiles > 0xFFFFFFFFull)
         fail(JAS_EDEVICE, "planned sort: status buffer too small");
     {
         JAS_TIMED("digit_starts", s);
@@ -732,6 +732,7 @@ void onesweep_sort_planned(K *&keys, K *&alt, const uint64_t *dN, uint64_t Ncap,
     if (src) tile_samples(*src, Ncap, (uint32_t)kOsNT * tile_rounds(Ncap, true), dN, s);
     PassArgs a;
     a.N = Ncap;
+    a.two = npass > 1 && b.status_words >= look_back_words(ntiles, radix);
     a.look_back = b.status;
     a.err = err;
     a.radix = radix;
@@ -756,8 +757,8 @@ void digit_starts(const unsigned long long *ghist, uint32_t npass, uint32_t widt
 
 uint64_t onesweep_tile_keys_from_ids(uint64_t N) { return (uint64_t)kOsNT * tile_rounds(N, true); }
 
-uint64_t onesweep_look_back_words(uint64_t N, uint32_t width) {
-    return look_back_words(most_tiles(N), onesweep::radix_of(width));
+uint64_t onesweep_look_back_words(uint64_t N, uint32_t width, bool two) {
+    return look_back_words(most_tiles(N), onesweep::radix_of(width), two);
 }
 
 void radix_sort_onesweep_planned(uint64_t *&keys, uint64_t *&alt, const uint64_t *dN, uint64_t Ncap,

@@ -765,6 +765,33 @@ def test_id_outside_universe_is_rejected():
     assert e.value.status == cabi.JAS_EINVAL
 
 
+@pytest.mark.parametrize("dmin", [4, 1000])
+def test_budgets_around_the_smallest_that_is_enough(dmin):
+    """Budgets from enough down to far too small, on the null stream: refused ones
+    leave nothing behind that the encode after them could meet."""
+    rng = np.random.default_rng(dmin)
+    pool = rng.integers(0, 1 << 30, 10000, dtype=np.uint64)
+    sets = [np.concatenate([rng.choice(pool, 1500), rng.integers(0, 1 << 30, 1500, dtype=np.uint64)]) for _ in range(64)]
+    ids, off = csr(sets)
+    d, o = dev(ids), dev(off)
+    ref = oracle.all_pairs(ids, off)
+    enough, refused = 1 << 25, 0
+    for budget in [int((1 << 25) * 0.93 ** k) for k in range(60)]:
+        try:
+            db, _ = jas.encode(d, o, universe_bits=30, dense_min_degree=dmin, hbm_budget_bytes=budget)
+            db.close()
+            assert not refused, "a smaller budget was enough"
+            enough = budget
+        except jas.JasError as e:
+            assert e.status == cabi.JAS_ENOMEM
+            refused += 1
+            if refused % 8 == 1:
+                db, _ = jas.encode(d, o, universe_bits=30, dense_min_degree=dmin, hbm_budget_bytes=enough)
+                assert np.array_equal(jas.gram(db)["B"].cpu().numpy(), ref["inter"])
+                db.close()
+    assert refused > 20
+
+
 def test_budget_is_enforced():
     spec = synth.workload("tiny")
     ids, off = synth.generate(spec)

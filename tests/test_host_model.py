@@ -331,3 +331,29 @@ def test_relabelling_of_ids_that_share_their_top_bits(library):
     """Crowded IDs are sorted as if the universe ended at the highest bit in which
     two of them differ, or, where that does not help, on every bit at once."""
     run(library, CROWDED_IDS)
+
+
+BUDGET = r"""
+plan, n, total, ubits, share, batch, dmin, flags, wb, budget = [float(a) if "." in a else int(a) for a in sys.argv[2:12]]
+ids, off = collection(n, total, ubits, share)
+opts = jas.jas_encode_opts(ubits, batch, dmin, flags, budget, wb)
+if plan:
+    p = jas.jas_plan_create(ids, off, n, opts, 0.25)
+    jas.jas_plan_encode(p, ids, off)
+    jas.jas_plan_check(p)
+    db = p.db
+else:
+    db, _ = jas.jas_encode(ids, off, n, opts)
+assert np.array_equal(gram(db, n), intersections(ids, off))
+"""
+
+
+@pytest.mark.parametrize("call", [
+    "0 10 2000 20 0.5 0 3 0 64 560244", "0 10 2000 20 0.5 0 50 2 64 609668", "0 64 8000 30 0.5 0 2 0 64 670468",
+    "0 300 60000 36 0.7 26 7 0 64 4572944", "0 64 200000 30 0.01 0 2 0 64 4028696", "0 64 200000 36 0.01 0 2 2 64 5543584",
+    "1 40 20000 30 0.5 22 2 0 32 1319600", "1 40 20000 30 0.5 0 4 0 64 1757740", "1 300 60000 36 0.7 0 1000 0 64 5379348"])
+def test_memory_budgets_that_were_enough_are(library, call):
+    """The smallest budgets that an encode or a plan took with 8-bit sort passes,
+    one pass's look-back words and counters without slots of their own (bytes, for
+    collections of few and many sets, rows of both forms, batches, a query index)."""
+    run(library, BUDGET, *call.split())
