@@ -42,13 +42,19 @@ def rewrite(text):
                   lambda m: 'model::Launch("%s", %s)(%s, ' % (m.group(1), m.group(2), m.group(1)), text, flags=re.S)
 
 
-def build(folder, csrc=CSRC):
-    """Compiles the library into folder; returns (its path, the sanitizer's runtime)."""
+def build(folder, csrc=CSRC, changes=()):
+    """Compiles the library into folder; returns (its path, the sanitizer's runtime).
+    changes: (file, text, text in its place), each found once."""
     cxx, rt = compiler()
     sources = []
     for f in sorted(os.listdir(csrc)):
         with open(os.path.join(csrc, f)) as fh:
-            text = rewrite(fh.read())
+            text = fh.read()
+        for name, old, new in changes:
+            if name == f:
+                assert text.count(old) == 1, (f, old)
+                text = text.replace(old, new)
+        text = rewrite(text)
         if f == "memory.hip":  # runtime.cpp has the buffers
             text = text.replace("*cache_alloc(", "*unused_cache_alloc(").replace("void cache_free(", "void unused_cache_free(")
         name = f[:-4] + ".cpp" if f.endswith(".hip") else f

@@ -150,33 +150,6 @@ def test_nothing_runs_after_a_refused_query_or_relabelling(library):
     run(library, CALLS_REFUSED)
 
 
-OUTSIDE = r"""
-# 11 sorted bits in passes of 6 and 5: bit 40 of an ID lies in the last pass's 6-bit digit, not in the 5 bits it sorts
-n, ubits = 50, 40
-ids, off = collection(n, 580000, ubits, 0.3)
-assert 1 << 19 < ids.size <= 1 << 20
-opts = jas.jas_encode_opts(ubits, 0, 4, 0, 0, 64)
-plan = jas.jas_plan_create(ids, off, n, opts, 0.1)
-bad = ids.copy()
-bad[::ids.size // 200] |= np.uint64(1 << ubits)
-for call in (lambda: jas.jas_encode(bad, off, n, opts), lambda: (jas.jas_plan_encode(plan, bad, off), jas.jas_plan_check(plan))):
-    try:
-        call()
-        raise SystemExit("an ID outside the universe was accepted")
-    except jas.JasError as e:
-        assert e.status == jas.JAS_EINVAL, str(e)
-jas.jas_plan_encode(plan, ids, off)
-jas.jas_plan_check(plan)
-"""
-
-
-def test_ids_outside_the_universe_are_sorted_by_the_digits_they_are_counted_by(library):
-    """IDs >= 2^U are refused after the sort: until then every place of the sorted
-    keys is written, also where the last pass is narrower than the others (a plan
-    classifies them before the host sees the flag)."""
-    run(library, OUTSIDE)
-
-
 REFUSED_BY_A_PLAN = r"""
 n, ubits = 40, 30
 ids, off = collection(n, 16000, ubits, 0.5)
@@ -357,3 +330,87 @@ def test_memory_budgets_that_were_enough_are(library, call):
     one pass's look-back words and counters without slots of their own (bytes, for
     collections of few and many sets, rows of both forms, batches, a query index)."""
     run(library, BUDGET, *call.split())
+
+
+@pytest.fixture(scope="module")
+def library_of_many_passes(tmp_path_factory):
+    """The library with one key per bucket instead of 512, and the large tiles from
+    32 K keys on: 100,000 keys are then sorted as 50 M are, in passes of 9 bits and
+    tiles of 24, 32 and 64 keys per thread.  A tile's look-back words have to be
+    clear when it publishes its own."""
+    if model.compiler() is None:
+        pytest.skip("clang's AddressSanitizer runtime is not installed")
+    publish = "            status_store(status + onesweep::status_index(tile, tid, kDigits), (tile == 0 ? kFlagP : kFlagA) | tc);"
+    return model.build(str(tmp_path_factory.mktemp("many_passes")), changes=[
+        ("jas_internal.hpp", "constexpr uint64_t kBucketKeys = 512;", "constexpr uint64_t kBucketKeys = 1;"),
+        ("radix.hip", "const uint64_t two_tiles = (uint64_t)4 * 256 * kOsNT;", "const uint64_t two_tiles = 1024;"),
+        # (a plan classifies the keys of a refused collection too: see the IDs outside the universe)
+        ("encode.hip", "    if (dsz && (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 7u)) {", "    if (false) {"),
+        ("radix.hip", publish, "            if (status_load(status + onesweep::status_index(tile, tid, kDigits))) abort();\n" + publish)])
+
+
+MANY_PASSES = r"""
+total, ubits, dmin, passes = [int(a) for a in sys.argv[2:6]]
+n = 60
+ids, off = collection(n, total, ubits, 0.5)
+want = intersections(ids, off)
+def count(f):
+    before = lib.model_launches(b"k_radix_onesweep")
+    B = f()
+    assert np.array_equal(B, want)
+    return lib.model_launches(b"k_radix_onesweep") - before
+def encode(budget):
+    db, st = jas.jas_encode(ids, off, n, jas.jas_encode_opts(ubits, 0, dmin, 0, budget, 64))
+    assert dmin == 2 or st["n_list_pairs"] > 1 << 16  # pairs in the largest tiles
+    B = gram(db, n)
+    db.close()
+    return B
+pair_passes = 1 if dmin > 2 else 0
+assert count(lambda: encode(0)) == passes + pair_passes
+assert total > 200000 or count(lambda: encode(1 << 40)) == passes + pair_passes
+for budget in (0, 1 << 40) if total <= 100000 else ():
+    plan = jas.jas_plan_create(ids, off, n, jas.jas_encode_opts(ubits, 0, dmin, 0, budget, 64), 0.1)
+    for _ in range(2 if total < 10000 else 1):
+        jas.jas_plan_encode(plan, ids, off)
+        assert np.array_equal(gram(plan.db, n), want)
+        jas.jas_plan_check(plan)
+    plan.close()
+out = np.zeros(ids.size, np.uint64)
+u, inv = np.unique(ids, return_inverse=True)
+assert jas.jas_relabel(ids, ids.size, ubits, None, out)[0] == u.size and np.array_equal(out, inv.astype(np.uint64))
+"""
+
+
+@pytest.mark.parametrize("total, dmin, passes", [(9000, 2, 2), (75000, 1000, 2), (150000, 2, 2), (300000, 2, 3)])
+def test_sorts_of_many_passes(library_of_many_passes, total, dmin, passes):
+    """Sorts on 14 to 19 top bits (7 + 7, 9 + 8, 9 + 9, 7 + 7 + 5) with the look-back words
+    of two passes cleared in turn, or of one where memory is limited; tiles of 16
+    keys per thread, or 24 in the first pass and 32 in the next (64 for pair words)."""
+    run(library_of_many_passes, MANY_PASSES, total, 50, dmin, passes)
+
+
+OUTSIDE = r"""
+# 13 sorted bits in passes of 7 and 6: bit 40 of an ID lies in the last pass's 7-bit digit, not in the 6 bits it sorts
+n, ubits = 50, 40
+ids, off = collection(n, 7600, ubits, 0.3)
+assert 6144 < ids.size <= 1 << 13
+opts = jas.jas_encode_opts(ubits, 0, 4, 0, 0, 64)
+plan = jas.jas_plan_create(ids, off, n, opts, 0.1)
+bad = ids.copy()
+bad[::ids.size // 200] |= np.uint64(1 << ubits)
+for call in (lambda: jas.jas_encode(bad, off, n, opts), lambda: (jas.jas_plan_encode(plan, bad, off), jas.jas_plan_check(plan))):
+    try:
+        call()
+        raise SystemExit("an ID outside the universe was accepted")
+    except jas.JasError as e:
+        assert e.status == jas.JAS_EINVAL, str(e)
+jas.jas_plan_encode(plan, ids, off)
+jas.jas_plan_check(plan)
+"""
+
+
+def test_ids_outside_the_universe_are_sorted_by_the_digits_they_are_counted_by(library_of_many_passes):
+    """IDs >= 2^U are refused after the sort: until then every place of the sorted
+    keys is written, also where the last pass is narrower than the others (a plan
+    classifies them before the host sees the flag)."""
+    run(library_of_many_passes, OUTSIDE)
