@@ -496,21 +496,37 @@ __device__ __forceinline__ void fp4_block(const uint64_t *__restrict__ W, uint64
 
 // Adds a wave's tiles at (I0, J0) into the strict upper part of B:
 // accumulator r of lane (lg, lm) holds row 8*(r/4) + 4*lg + r%4, column lm of
-// each 32 x 32 tile.
-template <int TA, int TB>
+// each 32 x 32 tile, and a pair of tiles holds every other column each.  With
+// kTrade the lanes trade values so that an addition of 32 lanes covers 32 columns
+// in a row instead of every other one of 64: 0.19 ms for 0.30 where 3160 tile pairs
+// of 16 word rows are hardly more than additions, 0.23 for 0.34 with 94 rows.
+// Blocks of kTradeRows word rows or more go without (65 K rows: 57.6 ms, 57.9 with).
+constexpr uint64_t kTradeRows = 1024;
+template <bool kTrade, int TA, int TB>
 __device__ __forceinline__ void fp4_add(const v16f (&acc)[TA][TB], uint32_t I0, uint32_t J0, uint32_t lm, uint32_t lg,
                                         uint32_t n, int32_t *__restrict__ B, int upper) {
+    const int from = (int)(32 * lg + lm / 2);  // the lane with columns lm & ~1 and lm | 1 of the pair's first half
 #pragma unroll
     for (int x = 0; x < TA; ++x)
 #pragma unroll
-        for (int y = 0; y < TB; ++y)
+        for (int y = 0; y < TB; y += 2)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const uint32_t m = 8 * (r >> 2) + 4 * lg + (r & 3);
                 const uint32_t i = I0 + 64 * (x >> 1) + 2 * m + (x & 1);
-                const uint32_t j = J0 + 64 * (y >> 1) + 2 * lm + (y & 1);
-                const int32_t v = (int32_t)acc[x][y][r];  // an exact integer below 2^24
-                if (v && i < j && j < n) atomicAdd(B + out_index(i, j, n, upper), v);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    uint32_t j = J0 + 32 * y + 2 * lm + h;
+                    float c = acc[x][y + h][r];
+                    if constexpr (kTrade) {  // columns 0..31, then 32..63 of the pair
+                        j = J0 + 32 * (y + h) + lm;
+                        const float even = __shfl(acc[x][y][r], from + 16 * h, kWave);
+                        const float odd = __shfl(acc[x][y + 1][r], from + 16 * h, kWave);
+                        c = lm & 1 ? odd : even;
+                    }
+                    const int32_t v = (int32_t)c;  // an exact integer below 2^24
+                    if (v && i < j && j < n) atomicAdd(B + out_index(i, j, n, upper), v);
+                }
             }
 }
 
@@ -522,6 +538,7 @@ __device__ __forceinline__ void fp4_add(const v16f (&acc)[TA][TB], uint32_t I0, 
 // 16.9 -> 9.9; n = 10000, 65 K: 96 -> 57).  256 x 256 tiles of four 128 x 128
 // waves, one per SIMD, reach 6.5: nothing runs beside a wave that waits.
 constexpr int kFp4Pairs = 4;  // row pairs in flight (3, 4 and 6 measured alike)
+template <bool kTrade>
 __global__ __launch_bounds__(kMfmaNT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gram_fp4(
     const uint64_t *__restrict__ W, uint64_t ldw, uint64_t H, uint64_t kper, uint32_t nt, uint32_t n,
     int32_t *__restrict__ B, int upper) {
@@ -546,12 +563,12 @@ __global__ __launch_bounds__(kMfmaNT) __attribute__((amdgpu_waves_per_eu(2, 2)))
         const uint32_t oh[1] = {oa[0]};
         v16f acc[2][2];
         fp4_block<2, 2, kFp4Pairs>(W, ldw, k0, k1, oh, ob, acc);
-        fp4_add<2, 2>(acc, I0, J0, lm, lg, n, B, upper);
+        fp4_add<kTrade, 2, 2>(acc, I0, J0, lm, lg, n, B, upper);
         return;
     }
     v16f acc[4][2];
     fp4_block<4, 2, kFp4Pairs>(W, ldw, k0, k1, oa, ob, acc);
-    fp4_add<4, 2>(acc, I0, J0, lm, lg, n, B, upper);
+    fp4_add<kTrade, 4, 2>(acc, I0, J0, lm, lg, n, B, upper);
 }
 
 // Row lists: one thread per row, every pair of its (ascending) samples.
@@ -903,7 +920,8 @@ void launch_mfma(const jas_db *db, int v, hipStream_t s, int32_t *B, bool upper)
         fp4_split(db->H, np, kVariants[v].want_blocks, kper, splits);
         if (splits <= 65535) {
             dim3 grid((uint32_t)np, (uint32_t)splits);
-            k_gram_fp4<<<grid, kMfmaNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);
+            if (kper < kTradeRows) k_gram_fp4<true><<<grid, kMfmaNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);
+            else k_gram_fp4<false><<<grid, kMfmaNT, 0, s>>>(db->W.p, ldw, db->H, kper, nt, n, B, upper);
             return;
         }
     }

@@ -887,6 +887,34 @@ def test_fp4_row_pairs_and_diagonal_tiles(n, rows):
     db.close()
 
 
+@pytest.mark.parametrize("word_rows", [1008, 1024, 1041])
+def test_fp4_blocks_of_few_and_many_word_rows(word_rows):
+    """Blocks of fewer than 1024 word rows add 32 columns in a row, longer ones
+    every other column.  With 276 tile pairs, the last tile ragged, the fixed
+    splits give blocks of all the rows, of half of them and shorter ones."""
+    n, degree, rows = 2900, 6, 64 * word_rows
+    rng = np.random.default_rng(word_rows)
+    cols = np.sort(rng.integers(0, n - degree, (rows, degree)), axis=1) + np.arange(degree)  # distinct
+    every = rng.choice(1 << 20, rows, replace=False).astype(np.uint64)
+    order = np.lexsort((np.repeat(every, degree), cols.ravel()))
+    ids = np.repeat(every, degree)[order]
+    off = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(cols.ravel(), minlength=n), out=off[1:])
+    want = np.zeros(n * n, np.int64)
+    for a in range(degree):
+        for b in range(a + 1, degree):
+            want += np.bincount(cols[:, a] * n + cols[:, b], minlength=n * n)
+    upper = np.triu_indices(n)
+    want = want.reshape(n, n)
+    np.fill_diagonal(want, np.diff(off))
+    db, st = jas.encode(dev(ids), dev(off), universe_bits=20, dense_min_degree=2)
+    assert st["n_word_rows"] == word_rows
+    for flags in [cabi.JAS_FORCE_MFMA] + [cabi.JAS_GRAM_VARIANT(v) for v in range(cabi.jas_gram_variants())]:
+        B = jas.gram(db, upper=True, flags=flags)["B"].cpu().numpy()
+        assert np.array_equal(B, want[upper]), flags
+    db.close()
+
+
 def test_repeat_runs_are_identical():
     spec = synth.scaled(synth.workload("precision"), n=300, size_scale=0.01, pool_scale=0.01)
     ids, off = synth.generate(spec)
