@@ -832,7 +832,10 @@ __global__ __launch_bounds__(kFinNT) void k_finalize_upper(int32_t *__restrict__
 // Tile variants of the MFMA Gram: word rows per step of the int8 K loops, and
 // how many blocks the K split aims for (int8: at least that many; fp4: at most,
 // or 0: the split fp4_split chooses).  The autotuner (JAS_TUNE) times each on
-// the caller's db and keeps the fastest for dbs of the same shape.
+// the caller's db and keeps the fastest for dbs of the same shape: the fixed
+// numbers of blocks are there for shapes on which the fitted rule is off (n = 60
+// with 65 K word rows: 0.064 ms, 0.051 with 512 blocks; most shapes by less than
+// the noise), for a program that multiplies many of one shape.
 enum GramKind { kInt8 = 0, kInt8Wide = 1, kFp4 = 2 };
 struct GramVariant {
     int step;
@@ -868,17 +871,27 @@ void k_split(uint64_t H, uint64_t np, uint64_t want, uint64_t &kper, uint64_t &s
 
 // The K split of the fp4 kernel over np tile pairs and H word rows: word rows
 // per block (a multiple of kKC) and blocks per tile pair.  kFp4Slots blocks run
-// at once, so the grid takes ceil(blocks / kFp4Slots) rounds of (rows per block
-// + kFp4Add) word rows' time, where kFp4Add is what a block's start and its
-// atomics cost, and the blocks drift apart by up to one block's time.  Fewer
-// rounds save additions, but a last round that is nearly empty costs a whole
-// one (n = 1024: 36 x 114 = 4104 blocks take 13.6 ms, 36 x 113 12.8), and long
-// blocks drift out of step and share less of their XCD's L2 (1 round 13.4 ms,
-// 8 rounds 12.4, 24 rounds 11.4; n = 300, 65 K rows: 1 round 0.177 ms, 2 rounds
-// 0.224, 8 rounds 0.51).  The split with the least such time is taken.
+// at once, so the grid takes ceil(blocks / kFp4Slots) rounds, each of the time a
+// block takes for its rows, and the blocks drift apart by up to one block's time.
+// Fewer rounds are fewer additions to B, but a last round that is nearly empty
+// costs a whole one (n = 1024: 36 x 114 = 4104 blocks take 13.6 ms, 36 x 113
+// 12.8), and long blocks drift out of step and share less of their XCD's L2 (1
+// round 13.4 ms, 8 rounds 12.4, 24 rounds 11.4; less so where more tile pairs than
+// slots share a range of rows).  A block's additions take kBlockUs of the chip's
+// time whatever its length, more where all blocks add to one tile.  Over long
+// grids they hide behind the multiplications (the two times add up like the sides
+// of a right angle, nearly enough), but with few rows they are nearly all there
+// is: blocks of 16 rows that fill the slots took 0.171 ms (n = 128, 16 K word
+// rows), 0.040 as 128 blocks now, and 0.076 (n = 1024, 313), now 0.026.
+// The split with the least modelled time is taken, of those that fill 1/64 to 7/8
+// of the slots or a whole number of rounds.  The constants are fitted to 82
+// products of n = 10 to 10000 and 13 to 65 K word rows at up to 18 splits each:
+// the split taken is at most 1.3 times the best of them, 1.07 on average.
 constexpr uint64_t kFp4Slots = 256 * 4;  // blocks resident: two waves of 232 VGPRs each, eight waves per CU
-constexpr uint64_t kFp4Add = 96;
-constexpr uint64_t kFp4Rounds = 64;  // most rounds considered
+constexpr uint64_t kFp4Rounds = 64;      // most rounds considered
+constexpr uint64_t kFp4Part[] = {16, 21, 32, 42, 64, 85, 128, 170, 256, 341, 384, 512, 640, 768, 896};  // of a round
+constexpr double kRowUs = 0.20, kRowFullUs = 0.08;      // a word row of a block; more with every slot in use
+constexpr double kBlockUs = 0.07, kBlockTileUs = 0.02;  // a block's additions; more, per tile pair, with few of them
 
 void fp4_split(uint64_t H, uint64_t np, uint64_t want, uint64_t &kper, uint64_t &splits) {
     const auto rows = [&](uint64_t sp) { return std::min(div_up(div_up(H, sp), kKC) * kKC, kFp4MaxK / kKC * kKC); };
@@ -886,16 +899,22 @@ void fp4_split(uint64_t H, uint64_t np, uint64_t want, uint64_t &kper, uint64_t 
     if (want) {
         best = std::max<uint64_t>(1, want / np);
     } else {
-        uint64_t best_t = ~0ull;
-        for (uint64_t r = 1; r <= kFp4Rounds; ++r) {
-            const uint64_t sp = std::max<uint64_t>(1, std::min(r * kFp4Slots / np, div_up(H, kKC)));
-            const uint64_t k = rows(sp), drift = std::min(k, H * np / kFp4Slots / 8);
-            const uint64_t t = div_up(div_up(H, k) * np, kFp4Slots) * (k + kFp4Add) + drift;
-            if (t < best_t) {
-                best_t = t;
+        double best_t = INFINITY;
+        const auto consider = [&](uint64_t grid) {
+            const uint64_t sp = std::max<uint64_t>(1, std::min(grid / np, div_up(H, kKC)));
+            const uint64_t k = rows(sp), blocks = div_up(H, k) * np;
+            const double drift = (double)std::min(k, H * np / kFp4Slots / 8) * std::min(1.0, (double)kFp4Slots / np);
+            const double row = kRowUs + kRowFullUs * std::min(1.0, (double)blocks / kFp4Slots);
+            const double multiply = ((double)(div_up(blocks, kFp4Slots) * k) + drift) * row;
+            const double add = (double)blocks * (kBlockUs + kBlockTileUs / (double)np);
+            const double time = std::hypot(multiply, add);
+            if (time < best_t) {
+                best_t = time;
                 best = sp;
             }
-        }
+        };
+        for (const uint64_t grid : kFp4Part) consider(grid);
+        for (uint64_t r = 1; r <= kFp4Rounds; ++r) consider(r * kFp4Slots);
     }
     kper = rows(best);
     splits = div_up(H, kper);

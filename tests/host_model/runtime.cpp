@@ -164,7 +164,7 @@ model_stream null_stream;
 std::set<model_stream *> streams{&null_stream};
 hipError_t last_error = hipSuccess;
 bool lazy = false;
-std::map<std::string, long> launches;
+std::map<std::string, long> launches, blocks;
 
 model_stream *stream(hipStream_t s) { return s ? s : &null_stream; }
 void step(model_stream *s) {
@@ -183,7 +183,9 @@ void enqueue(const char *name, hipStream_t s, std::function<void()> f) {
 }
 // The limits of a launch: 2^32 threads along x, 1024 per block, 160 KB of LDS.
 bool check_launch(const char *name, dim3 g, dim3 b, size_t lds) {
-    ++launches[std::string(name).substr(0, std::string(name).find('<'))];
+    const std::string kernel = std::string(name).substr(0, std::string(name).find('<'));
+    ++launches[kernel];
+    blocks[kernel] += (long)g.x * g.y;
     if (g.x && g.y && b.x && (uint64_t)g.x * b.x < (1ull << 32) && b.x * b.y <= kMaxThreads && lds <= 163840)
         return true;
     fprintf(stderr, "launch of %s refused: grid %u x %u, block %u, %zu bytes of LDS\n", name, g.x, g.y, b.x, lds);
@@ -335,7 +337,8 @@ void model_fail_at(long k) {
 long model_allocations() { return (long)jas::asked.size(); }
 long model_atomic_adds() { return model::atomic_adds; }
 long model_atomic_swaps() { return model::atomic_swaps; }
-// Launches of a kernel (of all of a template's) so far.
+// Launches of a kernel (of all of a template's) so far, and their blocks.
 long model_launches(const char *kernel) { return model::launches[kernel]; }
+long model_blocks(const char *kernel) { return model::blocks[kernel]; }
 long model_live() { return (long)jas::live.size(); }
 }

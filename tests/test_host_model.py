@@ -332,6 +332,25 @@ def test_memory_budgets_that_were_enough_are(library, call):
     run(library, BUDGET, *call.split())
 
 
+SMALL_PRODUCT = r"""
+# two sets of the same IDs and 298 empty ones: 1024 word rows, 6 tile pairs
+x = np.arange(65536, dtype=np.uint64)
+off = np.full(301, 2 * x.size, np.uint64)
+off[:2] = [0, x.size]
+db, st = jas.jas_encode(np.concatenate([x, x]), off, 300, jas.jas_encode_opts(16, 0, 2, 0, 0, 64))
+assert st["w_rows"] == 1024, st
+jas.jas_gram(db, jas.JAS_FORCE_MFMA, None, np.zeros((300, 300), np.int32))
+print(lib.model_blocks(b"k_gram_fp4"), "blocks")
+assert lib.model_launches(b"k_gram_fp4") == 1 and lib.model_blocks(b"k_gram_fp4") < 192
+"""
+
+
+def test_small_products_take_few_blocks(library):
+    """Each block adds whole tiles to B: 1024 word rows of 300 samples are not cut
+    into as many blocks as run at once (16 rows each, 0.035 ms for 0.023)."""
+    run(library, SMALL_PRODUCT)
+
+
 @pytest.fixture(scope="module")
 def library_of_many_passes(tmp_path_factory):
     """The library with one key per bucket instead of 512, and the large tiles from
