@@ -28,12 +28,12 @@ constexpr int32_t kHistMax = 16384;
 constexpr uint64_t kMaxBlocks = uint64_t(1) << 22;  // of a launch (2^32 threads are too many)
 constexpr uint32_t kWalk = 512;  // database entries of one ID a thread reads before it leaves the rest to its block
 
-// Small sets: IDs per block on average (kMinShare to kShare, for about
-// kSmallBlocks blocks), slots of a block's table (at least four times as many: a
+// Small sets: IDs per block on average (16 to 512, for about kSmallBlocks
+// blocks), slots of a block's table (at least four times as many: a
 // share is binomial, so at most a few dozen slots in a row are taken unless IDs are
 // chosen against the hash; an ID that finds kProbes taken leaves the request to
 // the sorted path), and the largest set and request taken.
-constexpr uint32_t kMinShare = 16, kShare = 512, kSlots = 2048, kProbes = 128, kSmallBlocks = 512;
+constexpr uint32_t kMinShareLog = 4, kShareLog = 9, kSlots = 2048, kProbes = 128, kSmallBlocks = 512;
 constexpr uint64_t kSmallSet = 32768, kSmallIds = uint64_t(1) << 20;
 
 // Keys (q << U) | id of 4096 entries per block, and the totals of every
@@ -220,10 +220,12 @@ __global__ __launch_bounds__(kNT) void k_qlookup(const uint64_t *__restrict__ K,
 // queries plus that of shares however unequal the sets are.  As many blocks for
 // each as the longest has, 20,000 sets of which one has 32,768 IDs took 3.5 ms,
 // and with more sets the grid passed a launch's 2^32 threads.)
-__device__ __host__ __forceinline__ uint64_t small_block(uint64_t q, uint64_t start, uint32_t share) { return q + start / share; }
+__device__ __host__ __forceinline__ uint64_t small_block(uint64_t q, uint64_t start, uint32_t log_share) {
+    return q + (start >> log_share);
+}
 
 __global__ __launch_bounds__(kNT) void k_query_small(const uint64_t *__restrict__ ids,
-                                                      const uint64_t *__restrict__ qoff, int32_t nq, uint32_t share,
+                                                      const uint64_t *__restrict__ qoff, int32_t nq, uint32_t log_share,
                                                       Index ix, int lds, int32_t *__restrict__ B, unsigned long long *__restrict__ qcard,
                                                       uint32_t *err) {
     extern __shared__ uint32_t hist[];
@@ -232,15 +234,21 @@ __global__ __launch_bounds__(kNT) void k_query_small(const uint64_t *__restrict_
     __shared__ uint32_t nfound;
     __shared__ LongRuns lr;
     const uint32_t tid = threadIdx.x;
-    int32_t q = 0;
-    for (int32_t hi = nq - 1; q < hi;) {
-        const int32_t mid = q + (hi - q + 1) / 2;
-        if (small_block(mid, qoff[mid], share) <= blockIdx.x) q = mid;
-        else hi = mid - 1;
+    // the last query whose blocks start here or before; as many blocks as the grid has
+    // more than there are queries are in front of it at most.  Each wave looks at 64
+    // of the rest at once (one after the other, six loads for 64 queries, took 2 of
+    // 113 us)
+    int32_t q = max((int32_t)(blockIdx.x - (gridDim.x - (uint32_t)nq)), 0);
+    for (int32_t left = min(nq, (int32_t)blockIdx.x + 1) - q; left > 1;) {
+        const int32_t step = (left + kWave - 1) / kWave, o = step * (int32_t)(tid % kWave);
+        const uint64_t before = __ballot(o < left && small_block(q + o, qoff[o < left ? q + o : q], log_share) <= blockIdx.x);
+        const int32_t first = step * (__popcll(before) - 1);
+        q += first;
+        left = min(step, left - first);
     }
     const uint64_t qs = qoff[q];
-    const uint32_t len = (uint32_t)(qoff[q + 1] - qs), p = blockIdx.x - (uint32_t)small_block(q, qs, share);
-    const uint32_t parts = (len + share - 1) / share;
+    const uint32_t len = (uint32_t)(qoff[q + 1] - qs), p = blockIdx.x - (uint32_t)small_block(q, qs, log_share);
+    const uint32_t parts = (len + (1u << log_share) - 1) >> log_share;
     if (p >= parts) return;
     constexpr unsigned long long kEmpty = ~0ull;  // no ID: U <= 63
     for (uint32_t i = tid; i < kSlots; i += kNT) slot[i] = kEmpty;
@@ -379,13 +387,13 @@ void query(const jas_db *db, const uint64_t *q_ids, const uint64_t *q_offsets, i
     if (longest <= kSmallSet && NQ <= kSmallIds) {
         zero((uint64_t)nq + 1);
         if (NQ > 0) {
-            uint32_t share = kMinShare;
-            while (share < kShare && (uint64_t)share * kSmallBlocks < NQ) share *= 2;
-            const uint64_t blocks = small_block((uint64_t)nq - 1, NQ, share) + 1;
+            uint32_t log_share = kMinShareLog;
+            while (log_share < kShareLog && (uint64_t)kSmallBlocks << log_share < NQ) ++log_share;
+            const uint64_t blocks = small_block((uint64_t)nq - 1, NQ, log_share) + 1;
             if (blocks <= kMaxBlocks) {
                 {
                     JAS_TIMED("query_small", s);
-                    k_query_small<<<(uint32_t)blocks, kNT, row, s>>>(q_ids, q_offsets, nq, share, ix, lds, B, qc.p, err);
+                    k_query_small<<<(uint32_t)blocks, kNT, row, s>>>(q_ids, q_offsets, nq, log_share, ix, lds, B, qc.p, err);
                 }
                 check_launch("small queries");
                 if (!(finish() & 8u)) return;
