@@ -584,24 +584,25 @@ __global__ void k_list_pairs(const uint64_t *__restrict__ lp, const uint32_t *__
 }
 
 // Row-list pairs sorted by their smaller sample a: block g takes pairs
-// [g*chunk, ...); for each run of one a in it of at least n/8 words, an LDS row
-// cnt[b] counts the rows holding both a and b, and each touched counter is added
-// to row a of B once (one atomic per touched pair and chunk instead of one per
-// row and pair).  A shorter run touches few counters twice, and finding its end,
-// waiting and looking through the counters take longer than its own atomics on
-// B; a chunk whose runs are that short on average, and none of which is twice as
-// long as that, is counted so as a whole.  Equal words that are neighbours are
-// added together: atomics on one word of B take 11 ns each, one after another
-// (two samples of 10000 that share 3 M rows of their own: 34 ms without, 0.04 ms
-// so; 1 M words on 500 pairs 0.12 and 0.013 ms).
+// [g*chunk, ...).  For each run of one a in it of at least n/8 words (and
+// kPairRun), an LDS row cnt[b] counts the rows holding both a and b, and each
+// touched counter is added to row a of B once (one atomic per touched pair and
+// chunk instead of one per row and pair).  A shorter run touches few counters
+// twice, and finding its end, waiting and looking through the counters take longer
+// than its own atomics on B (0.5 us a run: 778 K words of 8192 samples 0.19 ms, and
+// 0.028 directly), so the words up to the next long run go to B all at once.
+// Neighbours that are equal are added together: atomics on one word of B take 11 ns
+// each, one after another (two samples of 10000 that share 3 M rows of their own:
+// 34 ms with every word by itself, 0.04 ms so; 1 M words on 500 pairs 0.12 and
+// 0.013 ms).
 // Chunks of at least kPairChunk words (and n/8, so that a run that fills its
-// chunk is counted in LDS), at most kPairBlocks of them:
-// longer chunks split a sample's run fewer times, so fewer atomics, but a block
-// takes its runs one after another.  778 K words of 8192 samples: 0.83 ms as 48 blocks of 16384 words with LDS
-// counters for every run, 0.19 ms as 760, 0.028 ms directly; 1.7 G words of
-// 10000: 1.9 ms.
+// chunk is counted in LDS), at most kPairBlocks of them: longer chunks split a
+// sample's run fewer times, so fewer atomics, but a block takes its long runs one
+// after another.  1.7 G words of 10000 samples: 1.9 ms.
 constexpr uint64_t kPairChunk = 1024;
 constexpr uint64_t kPairBlocks = 4096;
+constexpr uint64_t kPairRun = 512;
+static_assert(kPairRun <= kPairChunk, "a chunk of one run is counted in LDS");
 
 constexpr int kPairCountNT = 512;  // threads per pair-count block (one LDS row of counters each)
 __global__ __launch_bounds__(kPairCountNT) void k_pair_count(const uint32_t *__restrict__ pairs, uint64_t P, uint64_t chunk,
@@ -610,7 +611,7 @@ __global__ __launch_bounds__(kPairCountNT) void k_pair_count(const uint32_t *__r
     extern __shared__ uint32_t lds[];
     uint32_t *cnt = lds;  // n counters
     __shared__ uint64_t seg_end;
-    __shared__ uint32_t long_run;
+    __shared__ uint32_t next_run;
     if (dsz) P = min(P, dsz[PZ_P]);  // a plan's db: P is the capacity, the count is on the device
     const uint64_t lo = (uint64_t)blockIdx.x * chunk, hi = min(P, lo + chunk);
     if (lo >= hi) return;
@@ -626,24 +627,28 @@ __global__ __launch_bounds__(kPairCountNT) void k_pair_count(const uint32_t *__r
             if (first && have) atomicAdd(B + out_index(w >> 16, w & 0xFFFFu, n, upper), (int32_t)c);
         }
     };
-    const uint64_t samples = (pairs[hi - 1] >> 16) - (pairs[lo] >> 16) + 1;
-    if ((hi - lo) * 8 < samples * n) {  // block-uniform
-        // a run of n/4 words holds two places that are n/8 words apart
-        if (threadIdx.x == 0) long_run = 0;
-        __syncthreads();
-        const uint64_t far = (n + 7) / 8;
-        for (uint64_t p = lo + threadIdx.x * far; p + far < hi; p += blockDim.x * far)
-            if ((pairs[p] >> 16) == (pairs[p + far] >> 16)) long_run = 1;
-        __syncthreads();
-        if (!long_run) {
-            add(lo, hi);
-            return;
-        }
-    }
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) cnt[i] = 0;
-    __syncthreads();
+    const uint64_t far = max((uint64_t)(n + 7) / 8, kPairRun);  // <= chunk
+    bool cleared = false;
     for (uint64_t s0 = lo; s0 < hi;) {
         const uint32_t a = pairs[s0] >> 16;
+        if (hi - s0 < far || (pairs[s0 + far - 1] >> 16) != a) {  // block-uniform
+            // a short run: on to the first of the places far words apart from which a
+            // sample goes on for as long (twice as long a run holds such a place)
+            if (threadIdx.x == 0) next_run = (uint32_t)(hi - lo);
+            __syncthreads();
+            for (uint64_t p = s0 + (threadIdx.x + 1) * far; p + far <= hi; p += blockDim.x * far)
+                if ((pairs[p] >> 16) == (pairs[p + far - 1] >> 16)) atomicMin(&next_run, (uint32_t)(p - lo));
+            __syncthreads();
+            const uint64_t s1 = lo + next_run;
+            add(s0, s1);
+            s0 = s1;
+            __syncthreads();  // next_run is read
+            continue;
+        }
+        if (!cleared) {
+            for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) cnt[i] = 0;  // (the barrier below)
+            cleared = true;
+        }
         // end of the run of a inside the chunk (the chunk is sorted by a): the
         // first wave narrows [l, h] by 64 probes per step; positions before l
         // hold samples <= a, positions from h on samples > a
@@ -668,12 +673,6 @@ __global__ __launch_bounds__(kPairCountNT) void k_pair_count(const uint32_t *__r
         }
         __syncthreads();
         const uint64_t s1 = seg_end;
-        if ((s1 - s0) * 8 < n) {  // block-uniform
-            add(s0, s1);
-            s0 = s1;
-            __syncthreads();  // seg_end is read
-            continue;
-        }
         // Words are read 16 bytes at a time (four per thread in flight); the
         // buffer is 16-byte aligned, the unaligned ends by word.
         const auto count = [&](uint32_t w) {

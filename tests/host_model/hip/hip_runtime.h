@@ -257,6 +257,12 @@ MODEL_INLINE T atomicOr(T *p, V v) {
     *p = (T)(old | v);
     return old;
 }
+template <class T, class V>
+MODEL_INLINE T atomicMin(T *p, V v) {
+    const T old = *p;
+    if ((T)v < old) *p = (T)v;
+    return old;
+}
 template <class T, class U, class V>
 MODEL_INLINE T atomicCAS(T *p, U expected, V v) {
     ++model::atomic_swaps;

@@ -92,7 +92,7 @@ def attach(path):
                             ("model_pending", ctypes.c_long, []), ("model_fail_at", None, [ctypes.c_long]),
                             ("model_allocations", ctypes.c_long, []), ("model_live", ctypes.c_long, []),
                             ("model_atomic_adds", ctypes.c_long, []), ("model_atomic_swaps", ctypes.c_long, []),
-                            ("model_launches", ctypes.c_long, [ctypes.c_char_p]),
+                            ("model_barriers", ctypes.c_long, []), ("model_launches", ctypes.c_long, [ctypes.c_char_p]),
                             ("model_blocks", ctypes.c_long, [ctypes.c_char_p])):
         f = getattr(lib, name)
         f.restype, f.argtypes = ret, args

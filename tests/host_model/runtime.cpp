@@ -20,7 +20,7 @@ namespace model {
 Index tid, bid;
 dim3 bdim, gdim;
 char *dynamic_lds;
-long atomic_adds, atomic_swaps;
+long atomic_adds, atomic_swaps, barriers;
 
 namespace {
 constexpr uint32_t kMaxThreads = 1024;
@@ -113,6 +113,7 @@ void run_block() {
             fibers[t].state = kRun;
             live = true;
         }
+        barriers += live;
     }
 }
 }  // namespace
@@ -336,6 +337,7 @@ void model_fail_at(long k) {
 }
 long model_allocations() { return (long)jas::asked.size(); }
 long model_atomic_adds() { return model::atomic_adds; }
+long model_barriers() { return model::barriers; }  // of blocks
 long model_atomic_swaps() { return model::atomic_swaps; }
 // Launches of a kernel (of all of a template's) so far, and their blocks.
 long model_launches(const char *kernel) { return model::launches[kernel]; }

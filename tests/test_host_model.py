@@ -225,6 +225,48 @@ def test_pairs_of_the_same_two_samples(library, n, upper):
     print(run(library, SAME_PAIRS, n, upper))
 
 
+RUNS = r"""
+n, long_runs = 1024, [int(x) for x in sys.argv[2:]]
+rng = np.random.default_rng(len(long_runs))
+# a row for every pair word: runs of 0 to 5 words with the long ones among them
+words = rng.integers(0, 6, n)
+words[n - 1] = 0
+words[np.linspace(5, n - 30, len(long_runs)).astype(int)] = long_runs
+x = np.repeat(np.arange(n), words)
+y = rng.integers(x + 1, np.minimum(x + 8, n))
+row = rng.permutation(x.size)
+smp, ids = np.concatenate([x, y]), np.concatenate([row, row])
+order = np.lexsort((ids, smp))
+off = np.zeros(n + 1, np.uint64)
+np.cumsum(np.bincount(smp, minlength=n), out=off[1:])
+db, st = jas.jas_encode(ids[order].astype(np.uint64), off, n, jas.jas_encode_opts(20, 0, 1000, 0, 0, 64))
+assert st["n_list_pairs"] == x.size
+B = np.zeros((n, n), np.int32)
+before = lib.model_barriers()
+jas.jas_gram(db, jas.JAS_ACCUMULATE, None, B, np.zeros(n, np.int64))
+lib.model_drain()
+print(lib.model_barriers() - before, "waits for", x.size, "words in", (words > 0).sum(), "runs")
+want = np.zeros((n, n), np.int32)
+np.add.at(want, (x, y), 1)
+assert np.array_equal(B, want)
+"""
+
+
+def test_short_runs_of_pairs_are_not_counted_one_by_one(library):
+    """A run of a quarter of n words among hundreds of short ones: none is worth the
+    waits that counting it by itself takes (0.106 ms for 0.006)."""
+    waits = int(run(library, RUNS, 300).split()[0])
+    assert waits < 40
+
+
+@pytest.mark.parametrize("long_runs", [(511, 512, 513), (1023, 1024, 1025, 2047), (5000, 700, 3000, 1500), (9000,)])
+@pytest.mark.parametrize("blocks", ["library", "library_of_many_passes"])
+def test_runs_of_pairs_of_every_length(request, blocks, long_runs):
+    """Runs around the shortest that is counted in LDS and around a chunk's length,
+    between short ones, in chunks of 1024 words and in a few long ones."""
+    run(request.getfixturevalue(blocks), RUNS, *long_runs)
+
+
 UNEQUAL_SETS = r"""
 rng = np.random.default_rng(11)
 ids, off = collection(4, 3000, 20, 0.5)
@@ -356,12 +398,13 @@ def library_of_many_passes(tmp_path_factory):
     """The library with one key per bucket instead of 512, and the large tiles from
     32 K keys on: 100,000 keys are then sorted as 50 M are, in passes of 9 bits and
     tiles of 24, 32 and 64 keys per thread.  A tile's look-back words have to be
-    clear when it publishes its own."""
+    clear when it publishes its own.  Pair words are counted in few, long chunks."""
     if model.compiler() is None:
         pytest.skip("clang's AddressSanitizer runtime is not installed")
     publish = "            status_store(status + onesweep::status_index(tile, tid, kDigits), (tile == 0 ? kFlagP : kFlagA) | tc);"
     return model.build(str(tmp_path_factory.mktemp("many_passes")), changes=[
         ("jas_internal.hpp", "constexpr uint64_t kBucketKeys = 512;", "constexpr uint64_t kBucketKeys = 1;"),
+        ("gram.hip", "constexpr uint64_t kPairBlocks = 4096;", "constexpr uint64_t kPairBlocks = 3;"),
         ("radix.hip", "const uint64_t two_tiles = (uint64_t)4 * 256 * kOsNT;", "const uint64_t two_tiles = 1024;"),
         # (a plan classifies the keys of a refused collection too: see the IDs outside the universe)
         ("encode.hip", "    if (dsz && (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 7u)) {", "    if (false) {"),
