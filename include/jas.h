@@ -239,7 +239,8 @@ jas_status jas_kmers(const uint64_t *seq, const uint64_t *seq_off, int64_t n_seq
  *  n_distinct, new_universe_bits  host outputs (may be NULL): D, and
  *          max(1, ceil(log2 D)), the universe_bits to encode the result with.
  * Sorts a copy of the IDs on hip_stream (two arrays of 8 bytes per ID, and
- * tables of up to 2 bytes per ID, as temporaries) and synchronises it.
+ * tables of up to 2 bytes per ID, as temporaries; 12 bytes per ID more where many
+ * distinct IDs share their top bits) and synchronises it.
  */
 jas_status jas_relabel(const uint64_t *ids, uint64_t n_ids, uint32_t universe_bits, void *hip_stream, uint64_t *out,
                        uint64_t *n_distinct, uint32_t *new_universe_bits);

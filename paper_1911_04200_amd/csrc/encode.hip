@@ -1425,7 +1425,6 @@ __global__ void k_plan_pairs(const uint64_t *npo, uint64_t gcap, uint64_t Pcap, 
     dsz[PZ_P] = P;
 }
 
-// err bit 64: a set reaches the int32 bound (|X_i| >= limit)
 // k_pack with a wave, 4 or 8 waves per row of W: a wave where the row is short
 // and there are rows enough to fill the chip (16 waves per CU), 8 where its
 // words leave room for few blocks per CU (16 measured the same).  Column chunks

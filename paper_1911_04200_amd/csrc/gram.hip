@@ -511,31 +511,38 @@ __device__ __forceinline__ void fp4_add(const v16f (&acc)[TA][TB], uint32_t I0, 
 #pragma unroll
         for (int y = 0; y < TB; y += 2)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t m = 8 * (r >> 2) + 4 * lg + (r & 3);
-                const uint32_t i = I0 + 64 * (x >> 1) + 2 * m + (x & 1);
+            for (int r0 = 0; r0 < 16; r0 += 4) {
+                const uint32_t i0 = I0 + 64 * (x >> 1) + 4 * r0 + (x & 1);  // the first of these rows
+                float c[4][2];
+                if constexpr (kTrade) {  // columns 0..31, then 32..63 of the pair; eight trades in flight
+                    if (i0 >= n || J0 + 32 * y >= n) continue;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    uint32_t j = J0 + 32 * y + 2 * lm + h;
-                    float c = acc[x][y + h][r];
-                    if constexpr (kTrade) {  // columns 0..31, then 32..63 of the pair
-                        j = J0 + 32 * (y + h) + lm;
-                        const float even = __shfl(acc[x][y][r], from + 16 * h, kWave);
-                        const float odd = __shfl(acc[x][y + 1][r], from + 16 * h, kWave);
-                        c = lm & 1 ? odd : even;
-                    }
-                    const int32_t v = (int32_t)c;  // an exact integer below 2^24
-                    if (v && i < j && j < n) atomicAdd(B + out_index(i, j, n, upper), v);
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            const float even = __shfl(acc[x][y][r0 + r], from + 16 * h, kWave);
+                            const float odd = __shfl(acc[x][y + 1][r0 + r], from + 16 * h, kWave);
+                            c[r][h] = lm & 1 ? odd : even;
+                        }
                 }
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const uint32_t i = i0 + 8 * lg + 2 * r;
+                        const uint32_t j = kTrade ? J0 + 32 * (y + h) + lm : J0 + 32 * y + 2 * lm + h;
+                        const int32_t v = (int32_t)(kTrade ? c[r][h] : acc[x][y + h][r0 + r]);  // an exact integer below 2^24
+                        if (v && i < j && j < n) atomicAdd(B + out_index(i, j, n, upper), v);
+                    }
             }
 }
 
 // 128 x 128 tiles, two waves of 128 x 64 each, two waves per SIMD (232 VGPRs),
 // so one wave's loads and masks run beside the other's MFMAs.  On a diagonal
 // tile the first wave's lower half lies below the diagonal and is not
-// computed.  Bound by the matrix unit: 7.3 to 7.9 PF/s of 10.1 (n = 1024,
-// 1.25 M word rows: 20.9 -> 12.0 ms against the LDS-table form; n = 4096, 65 K:
-// 16.9 -> 9.9; n = 10000, 65 K: 96 -> 57).  256 x 256 tiles of four 128 x 128
+// computed.  Bound by the matrix unit: 7.1 to 7.9 PF/s of 10.1 (n = 1024,
+// 1.25 M word rows: 20.9 -> 11.4 ms against the LDS-table form; n = 4096, 65 K:
+// 16.9 -> 10.0; n = 10000, 65 K: 96 -> 57.6).  256 x 256 tiles of four 128 x 128
 // waves, one per SIMD, reach 6.5: nothing runs beside a wave that waits.
 constexpr int kFp4Pairs = 4;  // row pairs in flight (3, 4 and 6 measured alike)
 template <bool kTrade>
@@ -881,7 +888,7 @@ void k_split(uint64_t H, uint64_t np, uint64_t want, uint64_t &kper, uint64_t &s
 // grids they hide behind the multiplications (the two times add up like the sides
 // of a right angle, nearly enough), but with few rows they are nearly all there
 // is: blocks of 16 rows that fill the slots took 0.171 ms (n = 128, 16 K word
-// rows), 0.040 as 128 blocks now, and 0.076 (n = 1024, 313), now 0.026.
+// rows), 0.040 as 128 blocks now, and 0.076 (n = 1024, 313), now 0.027.
 // The split with the least modelled time is taken, of those that fill 1/64 to 7/8
 // of the slots or a whole number of rounds.  The constants are fitted to 82
 // products of n = 10 to 10000 and 13 to 65 K word rows at up to 18 splits each:
