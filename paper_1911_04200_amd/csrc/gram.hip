@@ -509,13 +509,20 @@ __device__ __forceinline__ void fp4_add(const v16f (&acc)[TA][TB], uint32_t I0, 
 #pragma unroll
     for (int x = 0; x < TA; ++x)
 #pragma unroll
-        for (int y = 0; y < TB; y += 2)
+        for (int y = 0; y < TB; y += 2) {
+            bool some = true;
+            if constexpr (kTrade) {  // a plan's word rows may be empty
+                uint32_t bits = 0;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) bits |= __float_as_uint(acc[x][y][r]) | __float_as_uint(acc[x][y + 1][r]);
+                some = __ballot(bits != 0) != 0;
+            }
 #pragma unroll
             for (int r0 = 0; r0 < 16; r0 += 4) {
                 const uint32_t i0 = I0 + 64 * (x >> 1) + 4 * r0 + (x & 1);  // the first of these rows
                 float c[4][2];
                 if constexpr (kTrade) {  // columns 0..31, then 32..63 of the pair; eight trades in flight
-                    if (i0 >= n || J0 + 32 * y >= n) continue;
+                    if (!some || i0 >= n || J0 + 32 * y >= n) continue;
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -535,6 +542,7 @@ __device__ __forceinline__ void fp4_add(const v16f (&acc)[TA][TB], uint32_t I0, 
                         if (v && i < j && j < n) atomicAdd(B + out_index(i, j, n, upper), v);
                     }
             }
+        }
 }
 
 // 128 x 128 tiles, two waves of 128 x 64 each, two waves per SIMD (232 VGPRs),
@@ -840,7 +848,7 @@ __global__ __launch_bounds__(kFinNT) void k_finalize_upper(int32_t *__restrict__
 // or 0: the split fp4_split chooses).  The autotuner (JAS_TUNE) times each on
 // the caller's db and keeps the fastest for dbs of the same shape: the fixed
 // numbers of blocks are there for shapes on which the fitted rule is off (n = 60
-// with 65 K word rows: 0.064 ms, 0.051 with 512 blocks; most shapes by less than
+// with 65 K word rows: 0.056 ms, 0.051 with 512 blocks; most shapes by less than
 // the noise), for a program that multiplies many of one shape.
 enum GramKind { kInt8 = 0, kInt8Wide = 1, kFp4 = 2 };
 struct GramVariant {
@@ -891,8 +899,9 @@ void k_split(uint64_t H, uint64_t np, uint64_t want, uint64_t &kper, uint64_t &s
 // rows), 0.040 as 128 blocks now, and 0.076 (n = 1024, 313), now 0.027.
 // The split with the least modelled time is taken, of those that fill 1/64 to 7/8
 // of the slots or a whole number of rounds.  The constants are fitted to 82
-// products of n = 10 to 10000 and 13 to 65 K word rows at up to 18 splits each:
-// the split taken is at most 1.3 times the best of them, 1.07 on average.
+// products of n = 10 to 10000 and 13 to 65 K word rows at up to 18 splits each;
+// over 198 of n = 3 to 10000 the split taken is at most 1.4 times the best, 1.04 on
+// average.
 constexpr uint64_t kFp4Slots = 256 * 4;  // blocks resident: two waves of 232 VGPRs each, eight waves per CU
 constexpr uint64_t kFp4Rounds = 64;      // most rounds considered
 constexpr uint64_t kFp4Part[] = {16, 21, 32, 42, 64, 85, 128, 170, 256, 341, 384, 512, 640, 768, 896};  // of a round

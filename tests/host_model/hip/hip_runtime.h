@@ -257,6 +257,11 @@ MODEL_INLINE T atomicOr(T *p, V v) {
     *p = (T)(old | v);
     return old;
 }
+MODEL_INLINE uint32_t __float_as_uint(float v) {
+    uint32_t u;
+    memcpy(&u, &v, 4);
+    return u;
+}
 template <class T, class V>
 MODEL_INLINE T atomicMin(T *p, V v) {
     const T old = *p;
