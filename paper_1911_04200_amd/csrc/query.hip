@@ -34,6 +34,7 @@ constexpr uint32_t kWalk = 512;  // database entries of one ID a thread reads be
 // chosen against the hash; an ID that finds kProbes taken leaves the request to
 // the sorted path), and the largest set and request taken.
 constexpr uint32_t kMinShareLog = 4, kShareLog = 9, kSlots = 2048, kProbes = 128, kSmallBlocks = 512;
+constexpr uint64_t kSpareBlocks = 1024;  // blocks without a share that may be launched: half of what runs at once
 constexpr uint64_t kSmallSet = 32768, kSmallIds = uint64_t(1) << 20;
 
 // Keys (q << U) | id of 4096 entries per block, and the totals of every
@@ -210,8 +211,8 @@ __global__ __launch_bounds__(kNT) void k_qlookup(const uint64_t *__restrict__ K,
     }
 }
 
-// Small sets: query q has the blocks from small_block(q) on, one for each share
-// of its IDs; block p takes the IDs whose hash falls in share p, drops repeats
+// Small sets: query q has P blocks, or with P = 0 those from small_block(q) on, one
+// for each share of its IDs; block p takes the IDs whose hash falls in share p, drops repeats
 // through a hash table in LDS and looks the others up.
 // err |= 1 for an ID >= 2^U, |= 8 when a table is too full (the sorted path then
 // runs instead).
@@ -225,7 +226,7 @@ __device__ __host__ __forceinline__ uint64_t small_block(uint64_t q, uint64_t st
 }
 
 __global__ __launch_bounds__(kNT) void k_query_small(const uint64_t *__restrict__ ids,
-                                                      const uint64_t *__restrict__ qoff, int32_t nq, uint32_t log_share,
+                                                      const uint64_t *__restrict__ qoff, int32_t nq, uint32_t P, uint32_t log_share,
                                                       Index ix, int lds, int32_t *__restrict__ B, unsigned long long *__restrict__ qcard,
                                                       uint32_t *err) {
     extern __shared__ uint32_t hist[];
@@ -234,20 +235,27 @@ __global__ __launch_bounds__(kNT) void k_query_small(const uint64_t *__restrict_
     __shared__ uint32_t nfound;
     __shared__ LongRuns lr;
     const uint32_t tid = threadIdx.x;
-    // the last query whose blocks start here or before; as many blocks as the grid has
-    // more than there are queries are in front of it at most.  Each wave looks at 64
-    // of the rest at once (one after the other, six loads for 64 queries, took 2 of
-    // 113 us)
-    int32_t q = max((int32_t)(blockIdx.x - (gridDim.x - (uint32_t)nq)), 0);
-    for (int32_t left = min(nq, (int32_t)blockIdx.x + 1) - q; left > 1;) {
-        const int32_t step = (left + kWave - 1) / kWave, o = step * (int32_t)(tid % kWave);
-        const uint64_t before = __ballot(o < left && small_block(q + o, qoff[o < left ? q + o : q], log_share) <= blockIdx.x);
-        const int32_t first = step * (__popcll(before) - 1);
-        q += first;
-        left = min(step, left - first);
+    int32_t q = 0;
+    uint32_t p = 0;
+    if (P) {
+        q = (int32_t)(blockIdx.x / P);
+        p = blockIdx.x % P;
+    } else {
+        // the last query whose blocks start here or before; as many blocks as the grid has
+        // more than there are queries are in front of it at most.  Each wave looks at 64
+        // of the rest at once
+        q = max((int32_t)(blockIdx.x - (gridDim.x - (uint32_t)nq)), 0);
+        for (int32_t left = min(nq, (int32_t)blockIdx.x + 1) - q; left > 1;) {
+            const int32_t step = (left + kWave - 1) / kWave, o = step * (int32_t)(tid % kWave);
+            const uint64_t before = __ballot(o < left && small_block(q + o, qoff[o < left ? q + o : q], log_share) <= blockIdx.x);
+            const int32_t first = step * (__popcll(before) - 1);
+            q += first;
+            left = min(step, left - first);
+        }
+        p = blockIdx.x - (uint32_t)small_block(q, qoff[q], log_share);
     }
     const uint64_t qs = qoff[q];
-    const uint32_t len = (uint32_t)(qoff[q + 1] - qs), p = blockIdx.x - (uint32_t)small_block(q, qs, log_share);
+    const uint32_t len = (uint32_t)(qoff[q + 1] - qs);
     const uint32_t parts = (len + (1u << log_share) - 1) >> log_share;
     if (p >= parts) return;
     constexpr unsigned long long kEmpty = ~0ull;  // no ID: U <= 63
@@ -262,7 +270,7 @@ __global__ __launch_bounds__(kNT) void k_query_small(const uint64_t *__restrict_
     uint32_t bad = 0;
     // (a thread that found the table too full stops: the sorted path takes the
     // request.  8194 IDs chosen for one share: 7.4 ms with every slot looked at for
-    // each ID, 0.32 ms so, the sorted path and all)
+    // each ID, 0.44 ms so, the sorted path and all)
     for (uint32_t i0 = tid; i0 < len && !(bad & 8u); i0 += 8 * kNT) {
         uint64_t v[8];
 #pragma unroll
@@ -276,7 +284,7 @@ __global__ __launch_bounds__(kNT) void k_query_small(const uint64_t *__restrict_
             }
             // a multiplicative hash (Knuth): its high half picks the block, both halves the slot
             const uint64_t h = (id ^ (id >> 32)) * 0x9E3779B97F4A7C15ull;
-            if (i0 + u * kNT >= len || (uint32_t)(((h >> 32) * parts) >> 32) != p || (bad & 8u)) continue;
+            if (i0 + u * kNT >= len || (uint32_t)(((h >> 32) * parts) >> 32) != p) continue;
             uint32_t s = ((uint32_t)h ^ (uint32_t)(h >> 32)) % kSlots, probes = 0;
             for (;;) {
                 const unsigned long long old = atomicCAS(&slot[s], kEmpty, (unsigned long long)id);
@@ -389,11 +397,16 @@ void query(const jas_db *db, const uint64_t *q_ids, const uint64_t *q_offsets, i
         if (NQ > 0) {
             uint32_t log_share = kMinShareLog;
             while (log_share < kShareLog && (uint64_t)kSmallBlocks << log_share < NQ) ++log_share;
-            const uint64_t blocks = small_block((uint64_t)nq - 1, NQ, log_share) + 1;
+            // a number for every set where that is hardly more blocks: no search (16 sets,
+            // hubs among them: 414 us for 424)
+            const uint64_t packed = small_block((uint64_t)nq - 1, NQ, log_share) + 1;
+            const uint64_t per = (longest + (uint64_t(1) << log_share) - 1) >> log_share;
+            const uint32_t P = (uint64_t)nq * per <= packed + kSpareBlocks ? (uint32_t)per : 0;
+            const uint64_t blocks = P ? (uint64_t)nq * P : packed;
             if (blocks <= kMaxBlocks) {
                 {
                     JAS_TIMED("query_small", s);
-                    k_query_small<<<(uint32_t)blocks, kNT, row, s>>>(q_ids, q_offsets, nq, log_share, ix, lds, B, qc.p, err);
+                    k_query_small<<<(uint32_t)blocks, kNT, row, s>>>(q_ids, q_offsets, nq, P, log_share, ix, lds, B, qc.p, err);
                 }
                 check_launch("small queries");
                 if (!(finish() & 8u)) return;
